@@ -95,11 +95,10 @@ int asci_ctx_destroy(asci_ctx *ctx);
 
 /*
  * Tuning parameters of a context (they change speed, never results):
- *   "finish_cap": records per LDS bucket in the sort-and-accumulate finish,
- *                 1024, 2048 or 4096 (default 4096, any key width).  A
- *                 workgroup of cap / 8 threads takes a bucket; smaller
- *                 buckets let more workgroups share a CU but need more split
- *                 passes.
+ *   "finish_cap": records a workgroup of the sort-and-accumulate finish holds
+ *                 in LDS, 1024, 2048 or 4096 (default 4096, any key width).
+ *                 Each of its eight wavefronts takes a final segment of up
+ *                 to an eighth of them; smaller segments need more splitting.
  *   "batch_slots": concurrent searches of asci_search_batch, 1..8 (default 4).
  *   "spin_tables": 1 (default) tabulates E(s) of every alpha and beta string
  *                 (at most 2^27 strings per spin, and only when the search
@@ -125,8 +124,8 @@ int asci_ctx_destroy(asci_ctx *ctx);
  *                 faults, such as a record slot past its buffer, are reported
  *                 the same way); 0 (default) turns it off.
  * Read-only diagnostics of the last search on ctx (asci_ctx_get_param):
- *   "last_batches" (class batches), "last_finals" (LDS buckets),
- *   "last_levels" (deepest bucket split), "last_candidates" (candidates).
+ *   "last_batches" (class batches), "last_finals" (final segments),
+ *   "last_levels" (split levels), "last_candidates" (candidates).
  * Unknown names or values: ASCI_EINVAL.
  */
 int asci_ctx_set_param(asci_ctx *ctx, const char *name, int64_t value);

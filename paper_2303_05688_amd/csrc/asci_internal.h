@@ -139,7 +139,7 @@ struct ProfScope {
 
 struct asci_ctx {
     int device = 0;
-    int finish_cap = 4096;  // tunable: records per LDS bucket (see asci_ctx_set_param)
+    int finish_cap = 4096;  // tunable: records a finish workgroup holds in LDS (see asci_ctx_set_param)
     int batch_slots = 4;    // tunable: concurrent searches of a batch
     int spin_tables = 1;    // tunable: 1 = spin-string energy tables when they pay, 0 = never
     int fault_test = 0;     // 1: the next search raises a forced fault (tests of the error path)
@@ -333,12 +333,17 @@ __device__ __forceinline__ uint32_t psi_hash(uint64_t lo, uint64_t hi, uint32_t 
 // against) four bits of one 64-bit word, both drawn from a hash independent of
 // psi_hash's slot.  At 32 filter bits per key about one absent key in a
 // thousand reaches the table.
+// (32-bit multiplies: a 64-bit one is several of them)
 __device__ __forceinline__ uint64_t psi_filter_hash(uint64_t lo, uint64_t hi)
 {
-    uint64_t h = (lo ^ 0xA0761D6478BD642Full) * 0xE7037ED1A0B428DBull + hi * 0x8EBC6AF09C88C6E3ull;
-    h ^= h >> 29;
-    h *= 0xBF58476D1CE4E5B9ull;
-    return h ^ (h >> 32);
+    uint32_t a = ((uint32_t)lo * 0x9E3779B1u) ^ ((uint32_t)(lo >> 32) * 0x85EBCA77u);
+    a ^= ((uint32_t)hi * 0xC2B2AE3Du) ^ ((uint32_t)(hi >> 32) * 0x27D4EB2Fu);
+    a ^= a >> 15;
+    a *= 0x2C1B3C6Du;
+    a ^= a >> 12;
+    uint32_t b = a * 0x297A2D39u;
+    b ^= b >> 15;
+    return ((uint64_t)a << 32) | b;
 }
 __device__ __forceinline__ uint32_t psi_filter_word(uint64_t h, uint32_t fmask) { return (uint32_t)(h >> 32) & fmask; }
 __device__ __forceinline__ uint64_t psi_filter_bits(uint64_t h)
@@ -372,7 +377,8 @@ __device__ __forceinline__ bool psi_contains(const PsiSet &t, uint64_t lo, uint6
 // strings, e[1] the beta strings (null: no table, evaluate directly).
 struct SpinTables {
     const double *e[2] = {nullptr, nullptr};
-    const uint32_t *binom = nullptr;  // (kmax + 4) rows of n + 1: C(p, k) for k <= kmax, then zeros
+    uint32_t last[2] = {0, 0};        // largest rank of each table
+    const uint32_t *binom = nullptr;  // kmax + 1 rows of n + 1: C(p, k)
     int kmax = 0;
 };
 
@@ -390,19 +396,18 @@ SpinTablePlan spin_table_plan(int n, int na, int nb, uint64_t pairs, bool enable
 // ---------------------------------------------------------------- buckets (bucket.hip)
 struct BucketArgs {
     size_t P;                       // records of the batch
-    uint32_t c0, nc, nq;            // classes [c0, c0 + nc), core count
-    int n;
-    const uint64_t *cls;            // class masks (all classes)
+    uint32_t nc, nq;                // classes of the batch, core count
+    int n, na, nb;
     const uint32_t *offsets;        // [nc][nq] item starts
     const uint32_t *total;          // device: records of the batch
     uint64_t *klo[2], *khi[2];      // record buffers (ping-pong)
     double *val[2];
     PsiSet psi;                     // the same keys as a hash set
-    const double *jk, *h;
+    const double *jk;
     SpinTables st;                  // tabulated E(alpha), E(beta) (optional)
     const uint64_t *thr = nullptr;  // device: drop candidates whose |A| order bits are below (optional)
     double ecore, E0, eps;
-    int finish_cap = 4096;          // LDS capacity of a final segment (tunable)
+    int finish_cap = 4096;          // records a finish workgroup holds in LDS (tunable)
     uint64_t *clo, *chi;            // candidate slots (P)
     double *cnum, *cscore;
     // results of bucket_accumulate.  With defer_v the candidate count V is
@@ -413,10 +418,12 @@ struct BucketArgs {
     uint32_t nfinal = 0, V = 0, levels = 0;
     Profiler *prof = nullptr;       // the finish launch's profiler token, for its byte count
     int finish_tok = -1;
-    // the device-driven variant: nfinal and V are then bounds, the counts are on the device
-    const uint32_t *dn_final = nullptr, *dn_V = nullptr;
-    const uint32_t *order = nullptr, *cnt_sorted = nullptr, *off = nullptr;
-    const void *finals = nullptr;
+    // the device-driven variant: nfinal and V are then bounds, the count is on the device
+    const uint32_t *dn_V = nullptr;
+    // where the candidates lie: a bit per slot, a count and an output offset per tile of slots
+    unsigned long long *mask = nullptr;
+    uint32_t *tcnt = nullptr, ntile = 0;
+    const uint32_t *off = nullptr;
     // destination of bucket_collect
     uint64_t *pool_lo = nullptr, *pool_hi = nullptr;
     double *pool_num = nullptr, *pool_score = nullptr;
@@ -431,8 +438,8 @@ void bucket_read_v(BucketArgs &b, hipStream_t s);
 // sum over the batch's candidates of N_a * A_a (deterministic order)
 double bucket_pt2(BucketArgs &b, Arena &ar, hipStream_t s, HostStage &hs);
 // The same sort-and-accumulate with no count read back (asynchronous search):
-// launches sized for host bounds, a fixed number of split levels, counts in
-// b.dn_final and b.dn_V.  A failure sets bits of *d_stat (kStat*).
+// launches sized for host bounds, a fixed number of split levels, the count in
+// b.dn_V.  A failure sets bits of *d_stat (kStat*).
 template <int W>
 void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s, uint32_t *d_stat);
 template <int W>

@@ -1,35 +1,37 @@
 // Sort-and-accumulate of one class batch by buckets (Alg. 2, the sort on
 // the target bitstring and the sum per unique target), built for LDS:
 //
-//   segments: contiguous record ranges whose keys agree on every bit at or
-//             above `top`; the classes of the batch are the first segments
-//             (the generator lays records out class by class).
-//   split   : a segment larger than the LDS capacity is split, stably, into
-//             up to 256 key ranges bounded by splitters sampled from it
-//             (sample sort: the ranges are balanced however skewed the keys
-//             are, and they keep key order), with per-tile histograms laid out
-//             segment by segment, one global exclusive scan and a ranked
-//             scatter into the other buffer.  A segment the splitters cannot
-//             divide (its keys lie in one range) is split at the next level
-//             on the 8 key bits just below `top` instead, which always lowers
-//             `top`.  Repeat level by level.
-//   finish  : one workgroup per final segment sorts the segment's record
-//             indices in LDS (stable LSD on a 32-bit window of each key that
-//             holds the bits varying inside the segment), gathers the values
-//             in sorted order, sums every run of equal keys in record order
-//             (record order is ascending core index), drops input
-//             determinants (and, after an earlier class batch, candidates
-//             below the pool's k-th |A|), forms H_aa and A_a, and writes the
-//             surviving candidates, compacted, at the segment's start in slot
-//             arrays.
-//   collect : final segments ordered by start (= key order), their candidate
-//             counts scanned, and the candidates copied to the pool.
+//   segments: contiguous record ranges in key order; the classes of the batch
+//             are the first segments (the generator lays records out class by
+//             class).
+//   split   : a segment larger than the capacity of one wavefront's LDS share
+//             is split, stably, into up to 256 key ranges bounded by splitters
+//             sampled from it (sample sort: the ranges are balanced however
+//             skewed the keys are, and they keep key order), with per-tile
+//             histograms laid out segment by segment, one global exclusive
+//             scan and a ranked scatter into the other buffer.  Repeat level
+//             by level.  A sampled key that fills several quantiles gets a
+//             range of its own, so a range that stays too large either divides
+//             at the next level or holds a single key.  Ranges of at most one
+//             tile that a wavefront cannot hold yet are split last, each by one
+//             workgroup in one read and one write of its records.
+//   finish  : one wavefront per final segment, with no barrier: it sorts the
+//             segment's record indices in its LDS share (stable LSD on a 32-bit
+//             window of each key that holds the bits varying inside the
+//             segment), puts the values in sorted order, sums every run of
+//             equal keys in record order (record order is ascending core
+//             index), drops input determinants (and, after an earlier class
+//             batch, candidates below the pool's k-th |A|), forms H_aa and
+//             A_a, and writes the surviving candidates, compacted, at the
+//             segment's start in slot arrays; a bit per slot marks them.
+//   collect : the marked slots, in slot (= key) order, are copied to the pool.
 //
 // Keys are handled as the 2n-bit value (alpha << n) | beta: one word for
 // n <= 32, two words (hi = alpha, lo = beta) above.
 #include "hamiltonian.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace asci {
 
@@ -40,38 +42,21 @@ constexpr int kTileItems = 4;
 constexpr int kHistT = 256;           // threads of the histogram pass
 constexpr int kTileN = kTileT * kTileItems;  // 4096 records per tile
 
+// Records one wavefront finishes: an eighth of the workgroup capacity that
+// finish_cap names (eight wavefronts share a workgroup and its tables).
+constexpr int kFinishWaves = 8;
+inline int wave_cap(int finish_cap) { return (finish_cap >= 4096 ? 4096 : (finish_cap >= 2048 ? 2048 : 1024)) / kFinishWaves; }
+
 struct Seg {
-    // meta: top (bits 0-7) | buf (bit 8) | single key (bit 9) | split on key bits (bit 10)
-    uint32_t start, size, meta;
+    uint32_t start, size, meta;  // meta: buf (bit 0) | single key (bit 1)
 };
 
-__host__ __device__ __forceinline__ uint32_t seg_top(const Seg &s) { return s.meta & 0xFFu; }
-__host__ __device__ __forceinline__ uint32_t seg_buf(const Seg &s) { return (s.meta >> 8) & 1u; }
-__host__ __device__ __forceinline__ bool seg_single(const Seg &s) { return (s.meta >> 9) & 1u; }
-__host__ __device__ __forceinline__ bool seg_bits(const Seg &s) { return (s.meta >> 10) & 1u; }
-__host__ __device__ __forceinline__ uint32_t make_meta(uint32_t top, uint32_t buf, bool single, bool bits = false)
-{
-    return top | (buf << 8) | (single ? 512u : 0u) | (bits ? 1024u : 0u);
-}
+__host__ __device__ __forceinline__ uint32_t seg_buf(const Seg &s) { return s.meta & 1u; }
+__host__ __device__ __forceinline__ bool seg_single(const Seg &s) { return (s.meta >> 1) & 1u; }
+__host__ __device__ __forceinline__ uint32_t make_meta(uint32_t buf, bool single) { return buf | (single ? 2u : 0u); }
 
 constexpr int kMaxSplit = 256;       // ranges per split
-constexpr int kSplitSample = 16;     // samples per range
-
-// bits [sh, sh + w) of the 2n-bit key, w <= 8
-template <int W>
-__device__ __forceinline__ uint32_t vdigit(uint64_t lo, uint64_t hi, int n, int sh, int w)
-{
-    uint64_t x;
-    if (W == 1) {
-        x = lo >> sh;
-    } else if (sh >= n) {
-        x = hi >> (sh - n);
-    } else {
-        x = lo >> sh;
-        if (sh + w > n) x |= hi << (n - sh);
-    }
-    return (uint32_t)x & ((1u << w) - 1u);
-}
+constexpr int kSplitSample = 8;      // samples per range
 
 template <int W>
 __device__ __forceinline__ bool key_less(uint64_t alo, uint64_t ahi, uint64_t blo, uint64_t bhi)
@@ -80,22 +65,64 @@ __device__ __forceinline__ bool key_less(uint64_t alo, uint64_t ahi, uint64_t bl
 }
 
 // a value every lane of the wavefront holds, moved to a scalar register
+__device__ __forceinline__ uint32_t uniform32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 __device__ __forceinline__ uint64_t uniform64(uint64_t x)
 {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
-    return (uint64_t)lo | ((uint64_t)hi << 32);
+    return (uint64_t)uniform32((uint32_t)x) | ((uint64_t)uniform32((uint32_t)(x >> 32)) << 32);
 }
 
+// One data-parallel-primitive step: x of another lane (row_shr:n within a row
+// of 16 lanes, row_bcast:15 / row_bcast:31 across rows), 0 where there is none.
+// Every lane of the wavefront must be active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+
+// x of the lane before, `first` in lane 0
+__device__ __forceinline__ uint32_t lane_before(uint32_t x, uint32_t first)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)x, 0x138, 0xF, 0xF, false);
+}
+
+// inclusive sum over the lanes: six register moves, where a shuffle would make
+// six round trips through the LDS unit
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
 {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
+    x += dpp_from<0x111, 0xF>(x);
+    x += dpp_from<0x112, 0xF>(x);
+    x += dpp_from<0x114, 0xF>(x);
+    x += dpp_from<0x118, 0xF>(x);
+    x += dpp_from<0x142, 0xA>(x);
+    x += dpp_from<0x143, 0xC>(x);
     return x;
+}
+
+// OR over the lanes, in a scalar register
+__device__ __forceinline__ uint32_t wave_or(uint32_t x)
+{
+    x |= dpp_from<0x111, 0xF>(x);
+    x |= dpp_from<0x112, 0xF>(x);
+    x |= dpp_from<0x114, 0xF>(x);
+    x |= dpp_from<0x118, 0xF>(x);
+    x |= dpp_from<0x142, 0xA>(x);
+    x |= dpp_from<0x143, 0xC>(x);
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+__device__ __forceinline__ uint64_t wave_or64(uint64_t x)
+{
+    return (uint64_t)wave_or((uint32_t)x) | ((uint64_t)wave_or((uint32_t)(x >> 32)) << 32);
+}
+
+// Orders the LDS accesses of one wavefront around it (its lanes run in
+// lockstep and the LDS unit takes a wavefront's accesses in order, so only the
+// compiler has to be held back).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // exclusive scan over the block (NW waves); every thread must call it
@@ -118,165 +145,96 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *s_tmp, uint
     return base + x - v;
 }
 
-// The same scan with one barrier: consecutive calls alternate between the two
-// halves of s_tmp (2 * NW entries), so a call's totals are never overwritten
-// before every thread has passed the next call's barrier.  `parity` flips per
-// call and must be uniform across the workgroup.
-template <int NW>
-__device__ __forceinline__ uint32_t block_scan1(uint32_t v, uint32_t *s_tmp, uint32_t &parity, uint32_t &total)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t *buf = s_tmp + parity * NW;
-    parity ^= 1u;
-    const uint32_t x = wave_incl_scan(v);
-    if (lane == 63) buf[w] = x;
-    __syncthreads();
-    uint32_t base = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        const uint32_t t = buf[i];
-        base += (i < w) ? t : 0u;
-        tot += t;
-    }
-    total = tot;
-    return base + x - v;
-}
-
-// ---------------------------------------------------------------- split level
-struct SplitArgs {
-    const Seg *segs;          // large segments of this level
-    uint32_t nseg;
-    const uint32_t *tile_base;  // per segment: first tile (exclusive scan of tile counts)
-    const uint32_t *tile_seg;   // per tile: its segment
-    uint32_t ntiles;
-    uint32_t *hist;             // [tiles * 256], segment-major, digit-major inside a segment
-    uint64_t *klo[2], *khi[2];
-    double *val[2];
-    int n;
-    uint32_t cap;
-    const uint64_t *spl_lo, *spl_hi;  // splitters: kMaxSplit - 1 per segment
-    unsigned long long *kvar;         // per segment: the key bits that vary in it (2 words each)
-    uint8_t *dig;                     // per record: its digit, from the histogram pass
-    const uint32_t *dn_seg = nullptr;    // device: segments of the level (nseg is then a bound)
-    const uint32_t *dn_tiles = nullptr;  // device: tiles of the level (ntiles is then a bound)
-};
-
 __device__ __forceinline__ uint32_t dev_count(uint32_t n, const uint32_t *dn) { return dn ? min(n, *dn) : n; }
 
-// ranges of a splitter split: about half the LDS capacity each, 2 to 256
+// ---------------------------------------------------------------- split level
+// ranges of a split: about half the capacity each, 3 to 256 (three ranges have
+// the two splitters that can isolate one key)
 __host__ __device__ __forceinline__ uint32_t split_ranges(uint32_t size, uint32_t cap)
 {
     const uint64_t want = ((uint64_t)size * 2 + cap - 1) / cap;
-    return (uint32_t)(want < 2 ? 2 : (want > (uint64_t)kMaxSplit ? (uint64_t)kMaxSplit : want));
+    return (uint32_t)(want < 3 ? 3 : (want > (uint64_t)kMaxSplit ? (uint64_t)kMaxSplit : want));
+}
+__host__ __device__ __forceinline__ uint32_t seg_tiles(uint32_t size) { return (size + kTileN - 1) / kTileN; }
+// where a segment's splitters start: a segment larger than cap has at most
+// 2 size / cap of them, so the disjoint segments' ranges do not overlap
+__host__ __device__ __forceinline__ size_t split_at(uint32_t start, uint32_t cap)
+{
+    return (size_t)((uint64_t)start * 2 / cap);
+}
+// bounds of one level's tiles and histogram entries, for nseg segments of more
+// than cap records out of P
+inline size_t level_tiles(size_t P, size_t nseg) { return P / kTileN + nseg; }
+inline size_t level_hist(size_t P, size_t nseg, size_t cap)
+{
+    return P / (kTileN / kMaxSplit) + std::min<size_t>((size_t)kMaxSplit * nseg, 2 * P / cap + 3 * nseg);
 }
 
-// How one split level divides a segment: by splitters (nb ranges, the
-// splitters of segment s staged in LDS by the caller) or by key bits.
-struct SplitRule {
-    bool bits;
-    int sh, w;
-    uint32_t nb;  // digits in use
+struct SplitArgs {
+    const Seg *segs;            // large segments of this level
+    uint32_t nseg;
+    const uint32_t *tile_base;  // per segment: first tile
+    const uint32_t *hist_base;  // per segment: first histogram entry
+    const uint32_t *tile_seg;   // per tile: its segment
+    uint32_t ntiles;            // bound; the count is lev[0]
+    const uint32_t *lev;        // tiles, histogram entries of the level
+    uint32_t *hist;             // segment-major, range-major inside a segment, then tile
+    uint64_t *klo[2], *khi[2];
+    double *val[2];
+    uint32_t cap;
+    const uint64_t *spl_lo, *spl_hi;  // splitters, at split_at of each segment
+    uint8_t *dig;                     // per record: its range, from the histogram pass
 };
 
-__device__ __forceinline__ SplitRule split_rule(const Seg &sg, uint32_t cap)
-{
-    SplitRule r;
-    r.bits = seg_bits(sg);
-    if (r.bits) {
-        // the fallback: the 8 bits below top (top is the highest varying bit + 1)
-        const int top = (int)seg_top(sg);
-        r.w = top < 8 ? top : 8;
-        r.sh = top - r.w;
-        r.nb = 1u << r.w;
-    } else {
-        r.sh = r.w = 0;
-        r.nb = split_ranges(sg.size, cap);
-    }
-    return r;
-}
-
-// the digit of a key: its range (number of splitters <= key) or its key bits
-template <int W>
-__device__ __forceinline__ uint32_t split_key_digit(const SplitRule &r, const uint64_t *spl_lo,
-                                                   const uint64_t *spl_hi, uint64_t lo, uint64_t hi, int n)
-{
-    if (r.bits) return vdigit<W>(lo, hi, n, r.sh, r.w);
-    // count of splitters <= key by binary lifting over the 255 staged entries
-    // (the unused ones hold the largest key): eight steps, no branches, so
-    // the searches of several keys overlap
-    uint32_t pos = 0;
-#pragma unroll
-    for (uint32_t step = 128; step >= 1; step >>= 1) {
-        const uint32_t m = pos + step - 1u;
-        const bool le = W == 1 ? spl_lo[m] <= lo : (spl_hi[m] < hi || (spl_hi[m] == hi && spl_lo[m] <= lo));
-        pos += le ? step : 0u;
-    }
-    return min(pos, r.nb - 1u);
-}
-
-// stage the splitters of segment s in LDS (every thread of the block calls it)
-template <int W>
-__device__ __forceinline__ void load_splitters(const SplitRule &r, const uint64_t *__restrict__ g_lo,
-                                               const uint64_t *__restrict__ g_hi, uint32_t s, uint64_t *spl_lo,
-                                               uint64_t *spl_hi)
-{
-    static_assert(kMaxSplit == 256, "binary lifting over 255 splitters");
-    if (!r.bits)
-        for (uint32_t j = threadIdx.x; j < kMaxSplit - 1; j += blockDim.x) {
-            const bool used = j + 1u < r.nb;
-            spl_lo[j] = used ? g_lo[(size_t)s * (kMaxSplit - 1) + j] : ~0ull;
-            if (W == 2) spl_hi[j] = used ? g_hi[(size_t)s * (kMaxSplit - 1) + j] : ~0ull;
-        }
-    __syncthreads();
-}
-
-// Splitters of every large segment that splits by ranges: kSplitSample
-// records per range, taken at even strides (the records are in generation
-// order, not key order, so a strided pick is a fair sample), sorted in LDS by
-// a bitonic network; the splitters are the sample's quantiles.
 struct KeyBufs {
     const uint64_t *lo[2], *hi[2];
 };
 
+// Splitters of every large segment: kSplitSample records per range, taken at
+// even strides (the records are in generation order, not key order, so a
+// strided pick is a fair sample), sorted in LDS by a bitonic network; the
+// splitters are the sample's quantiles.  A quantile equal to the one before it
+// becomes the next larger key, so that a key which fills more than one quantile
+// has a range of its own.
 template <int W, int T>
 __global__ __launch_bounds__(T) void k_seg_splitters(const Seg *__restrict__ segs, uint32_t cap, KeyBufs kb,
                                                        uint64_t *__restrict__ g_lo, uint64_t *__restrict__ g_hi,
                                                        uint32_t nseg, const uint32_t *dn_seg)
 {
-    constexpr int kMaxSample = kMaxSplit * kSplitSample;  // 4096
+    constexpr int kMaxSample = kMaxSplit * kSplitSample;
     __shared__ uint64_t x_lo[kMaxSample];
     __shared__ uint64_t x_hi[W == 2 ? kMaxSample : 1];
     const uint32_t ns = dev_count(nseg, dn_seg);
     for (uint32_t s = blockIdx.x; s < ns; s += gridDim.x) {
-    const Seg sg = segs[s];
-    if (seg_bits(sg)) continue;  // uniform per block
-    const uint32_t nb = split_ranges(sg.size, cap);
-    const uint32_t m = min(sg.size, nb * (uint32_t)kSplitSample);
-    uint32_t p = 1;
-    while (p < m) p <<= 1;
-    const uint64_t *klo = kb.lo[seg_buf(sg)], *khi = kb.hi[seg_buf(sg)];
-    __syncthreads();  // the previous segment's samples are read
-    for (uint32_t i = threadIdx.x; i < p; i += T) {
-        if (i < m) {
-            const size_t j = (size_t)sg.start + (size_t)(((uint64_t)2 * i + 1) * sg.size / (2 * (uint64_t)m));
-            x_lo[i] = klo[j];
-            if (W == 2) x_hi[i] = khi[j];
-        } else {
-            x_lo[i] = ~0ull;
-            if (W == 2) x_hi[i] = ~0ull;
+        const Seg sg = segs[s];
+        const uint32_t nb = split_ranges(sg.size, cap);
+        const uint32_t m = min(sg.size, nb * (uint32_t)kSplitSample);
+        uint32_t p = 1;
+        while (p < m) p <<= 1;
+        const uint64_t *klo = kb.lo[seg_buf(sg)], *khi = kb.hi[seg_buf(sg)];
+        __syncthreads();  // the previous segment's samples are read
+        for (uint32_t i = threadIdx.x; i < p; i += T) {
+            if (i < m) {
+                const size_t j = (size_t)sg.start + (size_t)(((uint64_t)2 * i + 1) * sg.size / (2 * (uint64_t)m));
+                x_lo[i] = klo[j];
+                if (W == 2) x_hi[i] = khi[j];
+            } else {
+                x_lo[i] = ~0ull;
+                if (W == 2) x_hi[i] = ~0ull;
+            }
         }
-    }
-    __syncthreads();
-    for (uint32_t k = 2; k <= p; k <<= 1) {
-        for (uint32_t jj = k >> 1; jj > 0; jj >>= 1) {
-            for (uint32_t i = threadIdx.x; i < p; i += T) {
-                const uint32_t o = i ^ jj;
-                if (o > i) {
+        __syncthreads();
+        // pair t of a stage is (i, i + jj) with i = t with a zero bit inserted at
+        // jj: every lane works, and up to jj = 64 a wavefront's 64 pairs lie in
+        // its own 128 elements, so those stages need no barrier between them
+        for (uint32_t k = 2; k <= p; k <<= 1) {
+            for (uint32_t jj = k >> 1; jj > 0; jj >>= 1) {
+                for (uint32_t t = threadIdx.x; t < p / 2; t += T) {
+                    const uint32_t i = 2u * (t & ~(jj - 1u)) + (t & (jj - 1u)), o = i + jj;
                     const bool up = (i & k) == 0;
                     const uint64_t al = x_lo[i], bl = x_lo[o];
                     const uint64_t ah = W == 2 ? x_hi[i] : 0ull, bh = W == 2 ? x_hi[o] : 0ull;
-                    const bool gt = key_less<W>(bl, bh, al, ah);
-                    if (gt == up) {
+                    if (key_less<W>(bl, bh, al, ah) == up) {
                         x_lo[i] = bl;
                         x_lo[o] = al;
                         if (W == 2) {
@@ -285,44 +243,87 @@ __global__ __launch_bounds__(T) void k_seg_splitters(const Seg *__restrict__ seg
                         }
                     }
                 }
+                if (jj > 64u || (jj == 1u && k >= 128u)) __syncthreads();
+                else wave_sync();
             }
-            __syncthreads();
+        }
+        __syncthreads();
+        const size_t at = split_at(sg.start, cap);
+        for (uint32_t j = threadIdx.x; j + 1u < nb; j += T) {
+            const uint32_t q = (uint32_t)(((uint64_t)(j + 1) * m) / nb);
+            const uint32_t q0 = (uint32_t)(((uint64_t)j * m) / nb);
+            uint64_t lo = x_lo[q], hi = W == 2 ? x_hi[q] : 0ull;
+            if (j > 0 && lo == x_lo[q0] && (W == 1 || hi == x_hi[q0])) {
+                ++lo;  // the next larger key (no stored key is all ones)
+                if (W == 2 && lo == 0ull) ++hi;
+            }
+            g_lo[at + j] = lo;
+            if (W == 2) g_hi[at + j] = hi;
         }
     }
-    for (uint32_t j = threadIdx.x; j + 1u < nb; j += T) {
-        const uint32_t q = (uint32_t)(((uint64_t)(j + 1) * m) / nb);
-        g_lo[(size_t)s * (kMaxSplit - 1) + j] = x_lo[q];
-        if (W == 2) g_hi[(size_t)s * (kMaxSplit - 1) + j] = x_hi[q];
+}
+
+// One workgroup lays a level out: first tile and first histogram entry of
+// every large segment, the totals, cleared skip flags and next-level count.
+__global__ __launch_bounds__(1024) void k_level_plan(const Seg *__restrict__ segs, uint32_t nseg, uint32_t cap,
+                                                     uint32_t *__restrict__ tile_base,
+                                                     uint32_t *__restrict__ hist_base, uint32_t *__restrict__ skip,
+                                                     uint32_t *__restrict__ lev, uint32_t *__restrict__ nnext,
+                                                     const uint32_t *dn_seg)
+{
+    __shared__ uint32_t s_tmp[16];
+    const uint32_t ns = dev_count(nseg, dn_seg);
+    uint32_t tiles = 0, entries = 0;
+    for (uint32_t b = 0; b < ns; b += 4096) {
+        const uint32_t s0 = b + threadIdx.x * 4u;
+        uint32_t t[4], e[4], st = 0, se = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            t[k] = e[k] = 0u;
+            if (s0 + k < ns) {
+                const uint32_t size = segs[s0 + k].size;
+                t[k] = seg_tiles(size);
+                e[k] = t[k] * split_ranges(size, cap);
+            }
+            st += t[k];
+            se += e[k];
+        }
+        uint32_t tt, et;
+        uint32_t at = tiles + block_scan<16>(st, s_tmp, tt), ae = entries + block_scan<16>(se, s_tmp, et);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (s0 + k < ns) {
+                tile_base[s0 + k] = at;
+                hist_base[s0 + k] = ae;
+                skip[s0 + k] = 0u;
+            }
+            at += t[k];
+            ae += e[k];
+        }
+        tiles += tt;
+        entries += et;
     }
+    if (threadIdx.x == 0) {
+        lev[0] = tiles;
+        lev[1] = entries;
+        *nnext = 0u;
     }
 }
 
-// tiles per large segment; also clears the level's skip flags and the count of
-// next-level segments (instead of separate fill launches)
-__global__ __launch_bounds__(256) void k_seg_tiles(const Seg *__restrict__ segs, uint32_t nseg,
-                                                   uint32_t *__restrict__ ntile, uint32_t *__restrict__ skip,
-                                                   uint32_t *__restrict__ nnext, const uint32_t *dn_seg)
+// the segment of every tile: the last one that starts at or before it
+__global__ __launch_bounds__(256) void k_tile_seg(const uint32_t *__restrict__ tile_base, uint32_t nseg,
+                                                  const uint32_t *__restrict__ lev, uint32_t *__restrict__ tile_seg,
+                                                  const uint32_t *dn_seg)
 {
-    const uint32_t ns = dev_count(nseg, dn_seg);
-    for (uint32_t s = blockIdx.x * 256 + threadIdx.x; s <= ns; s += gridDim.x * 256) {
-        if (s < ns) ntile[s] = (segs[s].size + kTileN - 1) / kTileN;
-        skip[s] = 0u;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *nnext = 0u;
-}
-
-// the segment of every tile; also clears the varying-bit words of every segment
-__global__ __launch_bounds__(256) void k_seg_expand(const Seg *__restrict__ segs, uint32_t nseg,
-                                                    const uint32_t *__restrict__ tile_base,
-                                                    uint32_t *__restrict__ tile_seg, unsigned long long *__restrict__ kvar,
-                                                    const uint32_t *dn_seg)
-{
-    const uint32_t ns = dev_count(nseg, dn_seg);
-    for (uint32_t s = blockIdx.x * 256 + threadIdx.x; s < ns; s += gridDim.x * 256) {
-        kvar[2 * s] = 0ull;
-        kvar[2 * s + 1] = 0ull;
-        const uint32_t nt = (segs[s].size + kTileN - 1) / kTileN, tb = tile_base[s];
-        for (uint32_t t = 0; t < nt; ++t) tile_seg[tb + t] = s;
+    const uint32_t ns = dev_count(nseg, dn_seg), nt = lev[0];
+    for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < nt; t += gridDim.x * 256) {
+        uint32_t l = 0, r = ns;  // tile_base[l] <= t
+        while (r - l > 1u) {
+            const uint32_t m = (l + r) >> 1;
+            if (tile_base[m] <= t) l = m;
+            else r = m;
+        }
+        tile_seg[t] = l;
     }
 }
 
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(256) void k_seg_expand(const Seg *__restrict__ segs
 // XCD x (workgroups are handed to the 8 XCDs in turn), taken by that XCD's
 // workgroups in turn.  With a grid of 8 * per workgroups each takes one tile.
 #define FOR_LEVEL_TILES(a, t)                                                          \
-    const uint32_t nt_all_ = dev_count((a).ntiles, (a).dn_tiles);                     \
+    const uint32_t nt_all_ = min((a).ntiles, (a).lev[0]);                             \
     const uint32_t per_ = (nt_all_ + 7u) / 8u, slots_ = max(gridDim.x >> 3, 1u);      \
     for (uint32_t i_ = blockIdx.x >> 3, t = (blockIdx.x & 7u) * per_ + i_;            \
          i_ < per_ && t < nt_all_; i_ += slots_, t = (blockIdx.x & 7u) * per_ + i_)
@@ -342,189 +343,214 @@ __global__ __launch_bounds__(kHistT) void k_split_hist(SplitArgs a)
     __shared__ uint64_t spl_lo[kMaxSplit - 1];
     __shared__ uint64_t spl_hi[W == 2 ? kMaxSplit - 1 : 1];
     FOR_LEVEL_TILES(a, t) {
-    const uint32_t s = a.tile_seg[t];
-    const Seg sg = a.segs[s];
-    const uint32_t tb = a.tile_base[s], nt = (sg.size + kTileN - 1) / kTileN, tl = t - tb;
-    const SplitRule rule = split_rule(sg, a.cap);
-    const uint32_t buf = seg_buf(sg);
-    __syncthreads();  // the previous tile's counts are written out
-    for (int i = threadIdx.x; i < (kHistT / 64) * 256; i += kHistT) (&h[0][0])[i] = 0u;
-    load_splitters<W>(rule, a.spl_lo, a.spl_hi, s, spl_lo, spl_hi);
-    const uint32_t r0 = tl * kTileN, r1 = min(sg.size, r0 + kTileN);
-    const int wv = threadIdx.x >> 6;
-    // the bits in which some key differs from the segment's first key vary in
-    // the segment (one OR per word instead of an OR and an AND)
-    const uint64_t ref_lo = a.klo[buf][sg.start], ref_hi = W == 2 ? a.khi[buf][sg.start] : 0ull;
-    uint64_t d0 = 0ull, d1 = 0ull;
-    // four records per step, their searches interleaved
-    for (uint32_t rb = r0 + threadIdx.x; rb < r1; rb += 4 * kHistT) {
-        uint64_t lo[4], hi[4];
-        uint32_t dg[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t r = rb + (uint32_t)k * kHistT;
-            const size_t j = (size_t)sg.start + (r < r1 ? r : r0);
-            lo[k] = a.klo[buf][j];
-            hi[k] = W == 2 ? a.khi[buf][j] : 0ull;
+        const uint32_t s = a.tile_seg[t];
+        const Seg sg = a.segs[s];
+        const uint32_t nt = seg_tiles(sg.size), tl = t - a.tile_base[s];
+        const uint32_t nb = split_ranges(sg.size, a.cap);
+        const uint32_t buf = seg_buf(sg);
+        const size_t at = split_at(sg.start, a.cap);
+        __syncthreads();  // the previous tile's counts are written out
+        for (int i = threadIdx.x; i < (kHistT / 64) * 256; i += kHistT) (&h[0][0])[i] = 0u;
+        // unused splitters hold the largest key
+        for (uint32_t j = threadIdx.x; j < kMaxSplit - 1; j += kHistT) {
+            const bool used = j + 1u < nb;
+            spl_lo[j] = used ? a.spl_lo[at + j] : ~0ull;
+            if (W == 2) spl_hi[j] = used ? a.spl_hi[at + j] : ~0ull;
         }
+        __syncthreads();
+        const uint32_t r0 = tl * kTileN, r1 = min(sg.size, r0 + kTileN);
+        const int wv = threadIdx.x >> 6;
+        // four records per step, their searches interleaved
+        for (uint32_t rb = r0 + threadIdx.x; rb < r1; rb += 4 * kHistT) {
+            uint64_t lo[4], hi[4];
+            uint32_t dg[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) dg[k] = split_key_digit<W>(rule, spl_lo, spl_hi, lo[k], hi[k], a.n);
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t r = rb + (uint32_t)k * kHistT;
+                const size_t j = (size_t)sg.start + (r < r1 ? r : r0);
+                lo[k] = a.klo[buf][j];
+                hi[k] = W == 2 ? a.khi[buf][j] : 0ull;
+                dg[k] = 0u;
+            }
+            // the range of a key is the number of splitters <= it, by binary
+            // lifting over the 255 entries: no branches
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t r = rb + (uint32_t)k * kHistT;
-            if (r < r1) {
-                d0 |= lo[k] ^ ref_lo;
-                d1 |= hi[k] ^ ref_hi;
-                a.dig[(size_t)sg.start + r] = (uint8_t)dg[k];
-                atomicAdd(&h[wv][dg[k]], 1u);
+            for (uint32_t step = 128; step >= 1; step >>= 1) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t m = dg[k] + step - 1u;
+                    const bool le = W == 1 ? spl_lo[m] <= lo[k]
+                                           : (spl_hi[m] < hi[k] || (spl_hi[m] == hi[k] && spl_lo[m] <= lo[k]));
+                    dg[k] += le ? step : 0u;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t r = rb + (uint32_t)k * kHistT;
+                if (r < r1) {
+                    const uint32_t d = min(dg[k], nb - 1u);
+                    a.dig[(size_t)sg.start + r] = (uint8_t)d;
+                    atomicAdd(&h[wv][d], 1u);
+                }
             }
         }
-    }
-    // which key bits vary inside the segment (for segments the split cannot divide)
-    for (int dd = 32; dd >= 1; dd >>= 1) {
-        d0 |= __shfl_xor(d0, dd, 64);
-        if (W == 2) d1 |= __shfl_xor(d1, dd, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        atomicOr(&a.kvar[2 * s], (unsigned long long)d0);
-        if (W == 2) atomicOr(&a.kvar[2 * s + 1], (unsigned long long)d1);
-    }
-    __syncthreads();
-    const int d = threadIdx.x;
-    if (d < 256) {
-        uint32_t c = 0;
+        __syncthreads();
+        const uint32_t d = threadIdx.x;
+        if (d < nb) {
+            uint32_t c = 0;
 #pragma unroll
-        for (int i = 0; i < kHistT / 64; ++i) c += h[i][d];
-        a.hist[(size_t)tb * 256 + (size_t)d * nt + tl] = c;
-    }
+            for (int i = 0; i < kHistT / 64; ++i) c += h[i][d];
+            a.hist[(size_t)a.hist_base[s] + (size_t)d * nt + tl] = c;
+        }
     }
 }
 
-// children of every large segment (one block of 256 threads per segment).
-// Digits larger than the LDS capacity become large segments of the next level
-// (or single-key finals once no bits are left); runs of consecutive smaller
-// digits are coalesced into final segments of at most `cap` records, so the
-// finish never sees fragments.  A segment whose records all share the digit
-// is not moved: skip[s] = 1 and its child keeps its buffer.
+// Greedy grouping of consecutive parts of sizes pre[i + 1] - pre[i], i < m,
+// into groups of at most cap records (a larger part is a group of its own):
+// next[i] is the end of the group that would start at part i, mark[i] tells
+// whether one does.  Pointer doubling: after round r every start within 2^r
+// groups of the first is marked.  pre, next, jump (m + 1 entries each) and mark
+// lie in LDS; the T threads tid of a block (or of a wavefront, with sync to
+// match) share the work, at most P parts each.
+template <int P, typename Sync>
+__device__ __forceinline__ void greedy_groups(const uint32_t *pre, uint32_t m, uint32_t cap, uint16_t *next,
+                                              uint16_t *jump, uint8_t *mark, uint32_t tid, uint32_t T, Sync sync)
+{
+    uint32_t bits = 1;
+    while ((1u << bits) <= m) ++bits;
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+        const uint32_t i = tid + (uint32_t)c * T;
+        if (i > m) continue;
+        uint32_t l = i;  // largest l <= m with pre[l] - pre[i] <= cap
+        for (uint32_t step = 1u << (bits - 1u); step; step >>= 1)
+            if (l + step <= m && pre[l + step] - pre[i] <= cap) l += step;
+        const uint32_t nx = i >= m ? m : max(l, i + 1u);
+        next[i] = (uint16_t)nx;
+        jump[i] = (uint16_t)nx;
+        mark[i] = i == 0u ? 1 : 0;
+    }
+    sync();
+    for (uint32_t r = 0; r < bits; ++r) {
+        uint32_t j2[P];
+#pragma unroll
+        for (int c = 0; c < P; ++c) {
+            const uint32_t i = tid + (uint32_t)c * T;
+            const uint32_t j = i <= m ? jump[i] : m;
+            if (i <= m && mark[i]) mark[j] = 1;
+            j2[c] = jump[j];
+        }
+        sync();
+#pragma unroll
+        for (int c = 0; c < P; ++c) {
+            const uint32_t i = tid + (uint32_t)c * T;
+            if (i <= m) jump[i] = (uint16_t)j2[c];
+        }
+        sync();
+    }
+}
+
+// where new segments go: finals, segments of one tile at most, larger ones
+struct SegLists {
+    Seg *finals, *small, *next;
+    uint32_t *nfinal, *nsmall, *nnext, *overflow;
+    uint32_t finals_cap, small_cap, next_cap;
+};
+__device__ __forceinline__ void put_seg(Seg *list, uint32_t cap, uint32_t i, const Seg &c, uint32_t *overflow)
+{
+    if (i < cap) list[i] = c;
+    else atomicOr(overflow, 1u);
+}
+// appends the wavefront's segments (kind 0 none, 1 final, 2 small, 3 next): one
+// atomic per list
+__device__ __forceinline__ void append_segs(const SegLists &l, uint32_t kind, const Seg &c)
+{
+    const int lane = threadIdx.x & 63;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const uint64_t f = __ballot(kind == 1u), m = __ballot(kind == 2u), x = __ballot(kind == 3u);
+    uint32_t at = 0;
+    if (lane == 0 && f) at = atomicAdd(l.nfinal, (uint32_t)__popcll(f));
+    if (lane == 1 && m) at = atomicAdd(l.nsmall, (uint32_t)__popcll(m));
+    if (lane == 2 && x) at = atomicAdd(l.nnext, (uint32_t)__popcll(x));
+    const uint32_t bf = (uint32_t)__builtin_amdgcn_readlane((int)at, 0);
+    const uint32_t bm = (uint32_t)__builtin_amdgcn_readlane((int)at, 1);
+    const uint32_t bx = (uint32_t)__builtin_amdgcn_readlane((int)at, 2);
+    if (kind == 1u) put_seg(l.finals, l.finals_cap, bf + (uint32_t)__popcll(f & lt), c, l.overflow);
+    if (kind == 2u) put_seg(l.small, l.small_cap, bm + (uint32_t)__popcll(m & lt), c, l.overflow);
+    if (kind == 3u) put_seg(l.next, l.next_cap, bx + (uint32_t)__popcll(x & lt), c, l.overflow);
+}
+
+// Children of every large segment, one wavefront per segment (no barrier).
+// Ranges larger than the capacity become small or large segments, or
+// single-key finals; runs of consecutive smaller ranges are coalesced into
+// final segments of at most `cap` records.  A segment whose records all fall in
+// one range has one key (its splitters would otherwise divide it): it is not
+// moved (skip[s] = 1) and becomes a single-key final in its buffer.
+constexpr int kChildWaves = 4;
 template <int W>
-__global__ __launch_bounds__(256) void k_split_children(const Seg *__restrict__ segs, uint32_t nseg,
-                                                        const uint32_t *__restrict__ tile_base,
+__global__ __launch_bounds__(64 * kChildWaves) void k_split_children(const Seg *__restrict__ segs, uint32_t nseg,
+                                                        const uint32_t *__restrict__ hist_base,
                                                         const uint32_t *__restrict__ scan, uint32_t cap,
-                                                        uint32_t *__restrict__ skip, Seg *__restrict__ finals,
-                                                        uint32_t *__restrict__ nfinal, uint32_t finals_cap,
-                                                        Seg *__restrict__ next, uint32_t *__restrict__ nnext,
-                                                        uint32_t next_cap, uint32_t *__restrict__ overflow,
-                                                        const unsigned long long *__restrict__ kvar, int n,
+                                                        const uint64_t *__restrict__ spl_lo,
+                                                        const uint64_t *__restrict__ spl_hi,
+                                                        uint32_t *__restrict__ skip, SegLists lists,
                                                         const uint32_t *dn_seg)
 {
-    __shared__ uint32_t s_cnt[256], s_off[256];
-    __shared__ Seg s_fin[256], s_nxt[256];
-    __shared__ uint32_t s_nf, s_nn, s_bf, s_bn;
+    __shared__ uint32_t s_pre[kChildWaves][kMaxSplit + 1];
+    __shared__ uint16_t s_next[kChildWaves][kMaxSplit + 2], s_jump[kChildWaves][kMaxSplit + 2];
+    __shared__ uint8_t s_mark[kChildWaves][kMaxSplit + 2];
     const uint32_t ns = dev_count(nseg, dn_seg);
-    for (uint32_t s = blockIdx.x; s < ns; s += gridDim.x) {
-    __syncthreads();  // the previous segment's children are copied out
-    const Seg sg = segs[s];
-    const uint32_t tb = tile_base[s], nt = (sg.size + kTileN - 1) / kTileN;
-    const SplitRule rule = split_rule(sg, cap);
-    const uint32_t d = threadIdx.x;
-    const size_t b0 = (size_t)tb * 256;
-    const uint32_t base = scan[b0];
-    const uint32_t off = scan[b0 + (size_t)d * nt] - base;
-    const uint32_t end = (d + 1 < 256u) ? scan[b0 + (size_t)(d + 1) * nt] - base : sg.size;
-    s_cnt[d] = (d < rule.nb) ? end - off : 0u;
-    s_off[d] = off;
-    __syncthreads();
-    // thread 0 lays out the children in LDS (no global atomics in the loop)
-    if (d == 0) {
-    uint32_t nf = 0, nn = 0;
-    auto push_fin = [&](const Seg &c) { s_fin[nf++] = c; };
-    auto push_nxt = [&](const Seg &c) { s_nxt[nn++] = c; };
-    // the children of a range split keep the parent's top (their keys share at
-    // least its prefix); those of a bit split share bits down to sh
-    const uint32_t ptop = seg_top(sg), top = rule.bits ? (uint32_t)rule.sh : ptop;
-    bool whole = false;
-    for (uint32_t x = 0; x < rule.nb; ++x) {
-        if (s_cnt[x] == sg.size) {  // one digit holds everything: relabel, do not move
-            whole = true;
-            skip[s] = 1u;
-            Seg c{sg.start, sg.size, 0u};
-            // highest key bit that varies inside the segment, + 1 (0: one key)
-            const uint64_t v0 = kvar[2 * s], v1 = W == 2 ? kvar[2 * s + 1] : 0ull;
-            const uint32_t vtop = W == 1 ? (v0 ? 64u - (uint32_t)__clzll((long long)v0) : 0u)
-                                         : (v1 ? (uint32_t)n + 64u - (uint32_t)__clzll((long long)v1)
-                                               : (v0 ? 64u - (uint32_t)__clzll((long long)v0) : 0u));
-            if (vtop == 0) {
-                // a single key: one final segment, summed in record order
-                c.meta = make_meta(0u, seg_buf(sg), sg.size > cap);
-                push_fin(c);
-            } else if (!rule.bits) {
-                // the splitters cannot divide it: split on its top varying bits next
-                c.meta = make_meta(vtop, seg_buf(sg), false, true);
-                push_nxt(c);
-            } else if (sg.size <= cap || top == 0) {
-                c.meta = make_meta(top, seg_buf(sg), sg.size > cap);
-                push_fin(c);
-            } else {
-                c.meta = make_meta(top, seg_buf(sg), false);
-                push_nxt(c);
+    const uint32_t wv = uniform32(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    uint32_t *pre = s_pre[wv];
+    for (uint32_t s = blockIdx.x * kChildWaves + wv; s < ns; s += gridDim.x * kChildWaves) {
+        const Seg sg = segs[s];
+        const uint32_t nt = seg_tiles(sg.size), nb = split_ranges(sg.size, cap);
+        const size_t b0 = (size_t)hist_base[s], sp = split_at(sg.start, cap);
+        const uint32_t base = scan[b0];
+        wave_sync();
+        bool one_key[kMaxSplit / 64];
+#pragma unroll
+        for (int c = 0; c < kMaxSplit / 64; ++c) {
+            const uint32_t d = (uint32_t)c * 64 + lane;
+            one_key[c] = false;
+            if (d < nb) pre[d] = scan[b0 + (size_t)d * nt] - base;
+            // range d holds one key when its bounds are consecutive keys
+            if (d > 0 && d + 1u < nb) {
+                const size_t at = sp + d;
+                const uint64_t lo = spl_lo[at - 1] + 1ull;
+                one_key[c] = W == 1 ? spl_lo[at] == lo
+                                    : (spl_lo[at] == lo && spl_hi[at] == spl_hi[at - 1] + (lo == 0ull ? 1ull : 0ull));
             }
-            break;
         }
-    }
-    const uint32_t buf = seg_buf(sg) ^ 1u;
-    uint32_t g_start = 0, g_size = 0, g_digits = 0;
-    auto flush = [&]() {
-        if (g_size) {
-            Seg c{sg.start + g_start, g_size, make_meta(g_digits == 1 ? top : ptop, buf, false)};
-            push_fin(c);
-        }
-        g_size = 0;
-        g_digits = 0;
-    };
-    for (uint32_t x = 0; x < (whole ? 0u : rule.nb); ++x) {
-        const uint32_t c = s_cnt[x];
-        if (c == 0) continue;
-        if (c > cap) {
-            flush();
-            Seg L{sg.start + s_off[x], c, 0u};
-            if (top == 0) {
-                L.meta = make_meta(0u, buf, true);
-                push_fin(L);
-            } else {
-                L.meta = make_meta(top, buf, false);
-                push_nxt(L);
+        if (lane == 0) pre[nb] = sg.size;
+        wave_sync();
+        greedy_groups<kMaxSplit / 64 + 1>(pre, nb, cap, s_next[wv], s_jump[wv], s_mark[wv], lane, 64u, [] { wave_sync(); });
+#pragma unroll
+        for (int c = 0; c < kMaxSplit / 64; ++c) {
+            const uint32_t d = (uint32_t)c * 64 + lane;
+            if ((uint32_t)c * 64 >= nb) break;  // uniform
+            uint32_t kind = 0;
+            Seg ch{0u, 0u, 0u};
+            if (d < nb && s_mark[wv][d]) {
+                const uint32_t size = pre[s_next[wv][d]] - pre[d];
+                const bool whole = size == sg.size;  // more than cap records: a single range
+                if (size > 0u) kind = size <= cap || one_key[c] ? 1u : (size <= kTileN ? 2u : 3u);
+                if (whole) {
+                    skip[s] = 1u;
+                    if (!one_key[c]) raise_fault(kFaultSlot);
+                    kind = 1u;
+                }
+                ch = Seg{sg.start + pre[d], size, make_meta(seg_buf(sg) ^ (whole ? 0u : 1u), size > cap)};
             }
-            continue;
+            append_segs(lists, kind, ch);
         }
-        if (g_size + c > cap) flush();
-        if (g_size == 0) g_start = s_off[x];
-        g_size += c;
-        ++g_digits;
-    }
-    flush();
-    s_nf = nf;
-    s_nn = nn;
-    s_bf = nf ? atomicAdd(nfinal, nf) : 0u;
-    s_bn = nn ? atomicAdd(nnext, nn) : 0u;
-    }
-    __syncthreads();
-    // every thread copies its share of the children out
-    const uint32_t nf = s_nf, nn = s_nn, bf = s_bf, bn = s_bn;
-    for (uint32_t i = d; i < nf; i += 256) {
-        if (bf + i < finals_cap) finals[bf + i] = s_fin[i];
-        else atomicOr(overflow, 1u);
-    }
-    for (uint32_t i = d; i < nn; i += 256) {
-        if (bn + i < next_cap) next[bn + i] = s_nxt[i];
-        else atomicOr(overflow, 1u);
-    }
     }
 }
 
 template <int W>
 // eight waves per SIMD (64 VGPRs): the load, rank and write phases of four
 // workgroups' worth of waves overlap on each CU
-__global__ __launch_bounds__(kTileT) __attribute__((amdgpu_waves_per_eu(8))) void k_split_scatter(SplitArgs a, const uint32_t *__restrict__ scan,
+__global__ __launch_bounds__(kTileT) __attribute__((amdgpu_waves_per_eu(8))) void k_split_scatter(SplitArgs a,
                                                           const uint32_t *__restrict__ skip)
 {
     constexpr int NW = kTileT / 64;
@@ -541,7 +567,7 @@ __global__ __launch_bounds__(kTileT) __attribute__((amdgpu_waves_per_eu(8))) voi
     const uint32_t s = a.tile_seg[t];
     if (skip[s]) continue;  // uniform per block
     const Seg sg = a.segs[s];
-    const uint32_t tb = a.tile_base[s], nt = (sg.size + kTileN - 1) / kTileN, tl = t - tb;
+    const uint32_t nt = seg_tiles(sg.size), tl = t - a.tile_base[s], nb = split_ranges(sg.size, a.cap);
     const uint32_t ib = seg_buf(sg), ob = ib ^ 1u;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     __syncthreads();  // the previous tile's records are written out
@@ -581,9 +607,9 @@ __global__ __launch_bounds__(kTileT) __attribute__((amdgpu_waves_per_eu(8))) voi
         }
         uint32_t tot;
         const uint32_t e = block_scan<NW>(d < 256 ? run : 0u, s_tmp, tot);
-        if (d < 256) {
+        if ((uint32_t)d < nb) {
             s_dbase[d] = e;
-            const size_t b0 = (size_t)tb * 256;
+            const size_t b0 = (size_t)a.hist_base[s];
             s_gbase[d] = sg.start + (a.hist[b0 + (size_t)d * nt + tl] - a.hist[b0]);
         }
     }
@@ -614,41 +640,321 @@ __global__ __launch_bounds__(kTileT) __attribute__((amdgpu_waves_per_eu(8))) voi
         }
     }
     }
-    (void)scan;
+}
+
+// Splits a segment of at most one tile (and more than cap records) into finals,
+// in place, one workgroup per segment: the records are read once into
+// registers, 16 samples a range are ranked against each other in LDS, and the
+// records are written back range by range, each range in record order.  The
+// separate splitter, histogram, scan and scatter launches of a level would read
+// the records twice more and leave most of every tile empty.  A range that
+// still exceeds cap and holds several keys (the sample misled) goes to the next
+// list; one of a single key is a single-key final.
+constexpr int kSmallT = 512;
+constexpr int kSmallItems = kTileN / kSmallT;
+constexpr int kSmallMax = 64;      // ranges: half of cap each
+constexpr int kSmallSample = 512;  // samples at most
+template <int W>
+__global__ __launch_bounds__(kSmallT) __attribute__((amdgpu_waves_per_eu(4))) void k_small_split(
+    const Seg *__restrict__ segs, uint32_t nseg, const uint32_t *dn_seg, uint32_t cap, uint64_t *__restrict__ klo0,
+    uint64_t *__restrict__ klo1, uint64_t *__restrict__ khi0, uint64_t *__restrict__ khi1, double *__restrict__ val0,
+    double *__restrict__ val1, SegLists lists)
+{
+    constexpr int NW = kSmallT / 64;
+    __shared__ uint64_t s_lo[kTileN];
+    __shared__ uint64_t s_hi[W == 2 ? kTileN : 1];
+    // the values of two-word keys take the array of the low words after these are written
+    __shared__ double s_val[W == 1 ? kTileN : 1];
+    __shared__ uint64_t q_lo[kSmallMax], q_hi[W == 2 ? kSmallMax : 1];
+    __shared__ uint16_t s_wcnt[NW][kSmallMax];
+    __shared__ uint32_t s_pre[kSmallMax + 1];
+    __shared__ uint16_t s_next[kSmallMax + 2], s_jump[kSmallMax + 2];
+    __shared__ uint8_t s_mark[kSmallMax + 2];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const uint32_t ns = dev_count(nseg, dn_seg);
+    for (uint32_t s = blockIdx.x; s < ns; s += gridDim.x) {
+        const Seg sg = segs[s];
+        const uint32_t size = sg.size, buf = seg_buf(sg);
+        uint64_t *klo = (buf ? klo1 : klo0) + sg.start, *khi = W == 2 ? (buf ? khi1 : khi0) + sg.start : nullptr;
+        double *val = (buf ? val1 : val0) + sg.start;
+        // every wavefront takes the same whole number of rows of 64 records
+        const uint32_t rows = (size + 64u * NW - 1u) / (64u * NW), r0 = (uint32_t)wv * rows * 64u + (uint32_t)lane;
+        uint64_t lo[kSmallItems], hi[W == 2 ? kSmallItems : 1];
+        double v[kSmallItems];
+#pragma unroll
+        for (int q = 0; q < kSmallItems; ++q) {
+            const uint32_t r = r0 + (uint32_t)q * 64;
+            const bool in = (uint32_t)q < rows && r < size;
+            lo[q] = in ? klo[r] : 0ull;
+            if (W == 2) hi[q] = in ? khi[r] : 0ull;
+            v[q] = in ? val[r] : 0.0;
+        }
+        const uint32_t nb = min(max((2u * size + cap - 1u) / cap, 3u), (uint32_t)kSmallMax);
+        const uint32_t m = min(min(size, 16u * nb), (uint32_t)kSmallSample);
+        __syncthreads();  // the previous segment's LDS is read
+        for (uint32_t i = tid; i < m; i += kSmallT) {
+            const uint32_t j = (uint32_t)(((uint64_t)(2u * i + 1u) * size) / (2u * m));
+            s_lo[i] = klo[j];
+            if (W == 2) s_hi[i] = khi[j];
+        }
+        for (int i = tid; i < NW * kSmallMax; i += kSmallT) (&s_wcnt[0][0])[i] = 0u;
+        __syncthreads();
+        // splitter j is the sample of rank q_j = j m / nb (ties by index): every
+        // sample counts the ones below it and takes the splitters of its rank;
+        // one equal to the splitter before it becomes the next larger key below
+        for (uint32_t i = tid; i < m; i += kSmallT) {
+            const uint64_t xl = s_lo[i], xh = W == 2 ? s_hi[i] : 0ull;
+            uint32_t rank = 0;
+            for (uint32_t j = 0; j < m; ++j) {
+                const uint64_t yl = s_lo[j], yh = W == 2 ? s_hi[j] : 0ull;
+                const bool eq = yl == xl && (W == 1 || yh == xh);
+                rank += (key_less<W>(yl, yh, xl, xh) || (eq && j < i)) ? 1u : 0u;
+            }
+            const uint32_t j = (rank * nb + m - 1u) / m;  // smallest j with j m / nb >= rank
+            if (j > 0u && j < nb && (j * m) / nb == rank) {
+                q_lo[j] = xl;
+                if (W == 2) q_hi[j] = xh;
+            }
+        }
+        __syncthreads();
+        uint64_t ql = 0ull, qh = 0ull;
+        bool one_key = false;
+        if (tid > 0 && (uint32_t)tid < nb) {
+            ql = q_lo[tid];
+            qh = W == 2 ? q_hi[tid] : 0ull;
+            if (tid > 1 && ql == q_lo[tid - 1] && (W == 1 || qh == q_hi[tid - 1])) {
+                ++ql;
+                if (W == 2 && ql == 0ull) ++qh;
+            }
+        }
+        __syncthreads();
+        if (tid < kSmallMax) {
+            const bool used = tid > 0 && (uint32_t)tid < nb;
+            q_lo[tid] = used ? ql : ~0ull;
+            if (W == 2) q_hi[tid] = used ? qh : ~0ull;
+        }
+        __syncthreads();
+        if (tid > 0 && (uint32_t)tid + 1u < nb) {
+            const uint64_t nl = q_lo[tid] + 1ull;
+            one_key = W == 1 ? q_lo[tid + 1] == nl
+                             : (q_lo[tid + 1] == nl && q_hi[tid + 1] == q_hi[tid] + (nl == 0ull ? 1ull : 0ull));
+        }
+        // the range of a key is the number of splitters <= it; stable ranks by
+        // wavefront, row and lane
+        uint32_t dr[kSmallItems];  // range | rank << 8
+        uint32_t nbits = 1;
+        while ((1u << nbits) < nb) ++nbits;
+#pragma unroll
+        for (int q = 0; q < kSmallItems; ++q) {
+            dr[q] = 0;
+            if ((uint32_t)q >= rows) continue;  // uniform
+            uint32_t d = 0;
+            for (uint32_t step = 1u << (nbits - 1u); step; step >>= 1) {
+                const uint32_t k = min(d + step, (uint32_t)kSmallMax - 1u);
+                const bool le = W == 1 ? q_lo[k] <= lo[q] : (q_hi[k] < hi[q] || (q_hi[k] == hi[q] && q_lo[k] <= lo[q]));
+                d += le ? step : 0u;
+            }
+            d = min(d, nb - 1u);
+            const bool valid = r0 + (uint32_t)q * 64 < size;
+            const uint64_t peers = wave_match(d, valid, (int)nbits);
+            const uint32_t before = s_wcnt[wv][d];
+            wave_sync();
+            dr[q] = d | ((before + (uint32_t)__popcll(peers & lt)) << 8);
+            if (valid && (peers & lt) == 0ull) s_wcnt[wv][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+            wave_sync();
+        }
+        __syncthreads();
+        if (wv == 0) {
+            // lane d: the bases of range d
+            uint32_t run = 0;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                const uint32_t c = s_wcnt[i][lane];
+                s_wcnt[i][lane] = (uint16_t)run;
+                run += c;
+            }
+            const uint32_t e = wave_incl_scan(run) - run;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) s_wcnt[i][lane] = (uint16_t)(s_wcnt[i][lane] + e);
+            if ((uint32_t)lane < nb) s_pre[lane] = e;
+            if (lane == 0) s_pre[nb] = size;
+        }
+        __syncthreads();
+        // records to LDS in range order
+#pragma unroll
+        for (int q = 0; q < kSmallItems; ++q) {
+            const uint32_t r = r0 + (uint32_t)q * 64;
+            if ((uint32_t)q < rows && r < size) {
+                const uint32_t p = min((uint32_t)s_wcnt[wv][dr[q] & 0xFFu] + (dr[q] >> 8), (uint32_t)kTileN - 1u);
+                dr[q] = p;
+                s_lo[p] = lo[q];
+                if (W == 2) s_hi[p] = hi[q];
+                else s_val[p] = v[q];
+            }
+        }
+        if (wv == 0) {
+            // the finals: greedy groups of the ranges
+            greedy_groups<2>(s_pre, nb, cap, s_next, s_jump, s_mark, (uint32_t)lane, 64u, [] { wave_sync(); });
+            uint32_t kind = 0;
+            Seg c{0u, 0u, 0u};
+            if ((uint32_t)lane < nb && s_mark[lane]) {
+                const uint32_t gs = s_pre[s_next[lane]] - s_pre[lane];
+                if (gs > 0u) kind = gs <= cap || one_key ? 1u : 3u;
+                c = Seg{sg.start + s_pre[lane], gs, make_meta(buf, gs > cap && one_key)};
+            }
+            append_segs(lists, kind, c);
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < size; i += kSmallT) {
+            klo[i] = s_lo[i];
+            if (W == 2) khi[i] = s_hi[i];
+            else val[i] = s_val[i];
+        }
+        if (W == 2) {
+            __syncthreads();
+            double *sv = reinterpret_cast<double *>(s_lo);
+#pragma unroll
+            for (int q = 0; q < kSmallItems; ++q)
+                if ((uint32_t)q < rows && r0 + (uint32_t)q * 64 < size) sv[dr[q]] = v[q];
+            __syncthreads();
+            for (uint32_t i = tid; i < size; i += kSmallT) val[i] = sv[i];
+        }
+    }
 }
 
 // ---------------------------------------------------------------- finish
 struct FinishArgs {
     const Seg *finals;
-    uint64_t *klo[2], *khi[2];
-    double *val[2];
+    const uint64_t *klo[2], *khi[2];
+    const double *val[2];
     int n;
-    const double *jk, *h;       // J, J-K (n^2 each), h_pp (n); h (n^2)
+    const double *jk;           // J, J-K (n^2 each), h_pp (n)
     SpinTables st;              // E(alpha), E(beta) by string rank (optional)
     const uint64_t *thr;        // candidates with abs_order(A) below *thr cannot enter the top k (optional)
     double ecore, E0, eps;      // eps > 0: keep a pair only if |H_ai C_i / (E0 - H_aa)| > eps
     uint64_t *clo, *chi;        // slot arrays (batch positions)
     double *cnum, *cscore;
-    uint32_t *cnt;              // per final segment: candidates written
+    unsigned long long *mask;   // a bit per slot: holds a candidate (cleared by the caller)
+    uint32_t *tcnt;             // candidates per tile of kSlotTile slots (cleared by the caller)
     uint32_t nfinal;
     const uint32_t *dn_final;   // device: final segments (nfinal is then a bound; optional)
     PsiSet psi;                 // input determinants (exclusion)
-    int tab_in_lds;             // staged in LDS: 1 J, J-K, h_pp; 2 J and the binomials; 3 the binomials; 0 none
+    int na, nb;
+    int stage_x;                // some strings have no table: J-K (triangle) and h_pp are staged in LDS
+    uint32_t tab_bytes;         // LDS of the staged tables
+    uint32_t wave_bytes;        // LDS of one wavefront
+    uint32_t amax;              // alpha strings one wavefront caches (a power of two)
 };
 
-// E(s) of one spin string (0 = alpha, 1 = beta): looked up when tabulated
-__device__ __forceinline__ double spin_e(const SpinTables &st, int spin, const double *X, const double *hd, int n,
-                                         uint64_t str)
+constexpr uint32_t kSlotTile = 4096;  // slots per collect tile
+
+// The tables a finish reads and the electron counts.  The counts are the same
+// for every string of a search, so that the walks over a string's set bits
+// below run a uniform number of steps.  Each table lies in one known memory (a
+// pointer that may be either makes every access a flat one): X, h_pp and the
+// binomials in LDS, J there too when JL.
+template <bool JL>
+struct Diag {
+    // J (JL: its lower triangle row by row, else n^2), X = J - K (its strict
+    // upper triangle row by row), h_pp
+    const double *J, *X, *hd;
+    const double *e[2];        // E(alpha), E(beta) by string rank, or null
+    uint32_t last[2];          // the largest rank
+    const uint32_t *binom;
+    int n, ne[2];
+};
+
+// index of the lowest set bit; n - 1 for an empty word (a string with fewer
+// electrons than it should have, from inputs that fail validation, must not
+// send an access out of its table)
+template <typename M>
+__device__ __forceinline__ uint32_t low_orb(M m, int n)
 {
-    const double *t = st.e[spin];
-    return t ? t[spin_rank(st.binom, n, str)] : spin_energy(X, hd, n, str);
+    return min((uint32_t)__builtin_ctzg(m, (int)(8 * sizeof(M))), (uint32_t)n - 1u);
+}
+
+// load(i, orbital) for the ne lowest set bits of m, ascending, then add of what
+// it returned, in the same order; the loads of four are in flight at a time
+template <typename M, typename L, typename A>
+__device__ __forceinline__ void for_bits(M m, int n, int ne, L load, A add)
+{
+    int i = 0;
+    for (; i + 4 <= ne; i += 4) {
+        decltype(load(0, 0u)) x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x[k] = load(i + k, low_orb(m, n));
+            m &= m - 1;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) add(x[k]);
+    }
+    if (i < ne) {  // one to three more
+        decltype(load(0, 0u)) x[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (k == 0 || i + k < ne) {
+                x[k] = load(i + k, low_orb(m, n));
+                m &= m - 1;
+            }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (k == 0 || i + k < ne) add(x[k]);
+    }
+}
+
+// c_q(alpha) = sum over p in alpha of J_pq, p ascending; alpha is uniform
+template <bool JL, typename M>
+__device__ __forceinline__ double column_sum(const Diag<JL> &D, M alpha, uint32_t q)
+{
+    const uint32_t n = (uint32_t)D.n, qb = q * (q + 1u) / 2u;
+    double c = 0.0;
+    for_bits(alpha, D.n, D.ne[0],
+             [&](int, uint32_t p) { return D.J[JL ? (q >= p ? qb + p : p * (p + 1u) / 2u + q) : p * n + q]; },
+             [&](double x) { c = c + x; });
+    return c;
+}
+
+// E(s) in the order of spin_energy: h_pp ascending, then the pairs p < q row by row
+template <bool JL, typename M>
+__device__ __forceinline__ double spin_energy_u(const Diag<JL> &D, int ne, M s)
+{
+    double e = 0.0;
+    for_bits(s, D.n, ne, [&](int, uint32_t q) { return D.hd[q]; }, [&](double x) { e = e + x; });
+    for (int i = 0; i + 1 < ne; ++i) {
+        const uint32_t p = low_orb(s, D.n);
+        s &= s - 1;
+        // the strict upper triangle's row p starts at p n - p (p + 3) / 2 - 1 for column 0
+        const int row = (int)(p * (uint32_t)D.n) - (int)(p * (p + 3u) / 2u + 1u);
+        for_bits(s, D.n, ne - 1 - i, [&](int, uint32_t q) { return D.X[max(row + (int)q, 0)]; }, [&](double x) { e = e + x; });
+    }
+    return e;
+}
+
+// rank of the string in the combinatorial number system
+template <bool JL, typename M>
+__device__ __forceinline__ uint32_t spin_rank_u(const Diag<JL> &D, int ne, M s)
+{
+    uint32_t r = 0;
+    for_bits(s, D.n, ne, [&](int i, uint32_t q) { return D.binom[(i + 1) * (D.n + 1) + (int)q]; }, [&](uint32_t x) { r += x; });
+    return r;
+}
+
+// E of one spin string (0 = alpha, 1 = beta): looked up when tabulated
+template <bool JL, typename M>
+__device__ __forceinline__ double spin_e(const Diag<JL> &D, int spin, M s)
+{
+    return D.e[spin] ? D.e[spin][min(spin_rank_u(D, D.ne[spin], s), D.last[spin])] : spin_energy_u(D, D.ne[spin], s);
 }
 
 // H_aa = ((ecore + E(alpha)) + E(beta)) + E(alpha, beta)
-__device__ __forceinline__ double diag_tab(const SpinTables &st, const double *J, const double *X, const double *hd,
-                                           int n, double ecore, uint64_t a, uint64_t b)
+template <bool JL, typename M>
+__device__ __forceinline__ double diag_tab(const Diag<JL> &D, double ecore, M a, M b)
 {
-    return ((ecore + spin_e(st, 0, X, hd, n, a)) + spin_e(st, 1, X, hd, n, b)) + cross_energy(J, n, a, b);
+    double cross = 0.0;
+    for (M m = b; m; m &= m - 1) cross = cross + column_sum(D, a, low_orb(m, D.n));
+    return ((ecore + spin_e(D, 0, a)) + spin_e(D, 1, b)) + cross;
 }
 
 // The key as one 2n-bit value (alpha << n) | beta.  Bits [o, o + 32) of it:
@@ -679,6 +985,24 @@ __device__ __forceinline__ void key_put(uint32_t c, int o, int n, uint64_t &lo, 
     if (n - o < 32) hi |= (uint64_t)c >> (n - o);
 }
 
+// f(source shift, width mask, destination shift) for every run of set bits of
+// m, lowest first; returns the number of set bits.  m is uniform, so the walk
+// is scalar work.
+template <typename F>
+__device__ __forceinline__ int for_bit_runs(uint64_t m, int at, F f)
+{
+    while (m) {
+        const int s = __builtin_ctzll(m);
+        const uint64_t t = ~(m >> s);
+        const int len = t ? __builtin_ctzll(t) : 64 - s;
+        const uint64_t wm = len >= 64 ? ~0ull : (1ull << len) - 1ull;
+        f(s, wm, at);
+        at += len;
+        m &= ~(wm << s);
+    }
+    return at;
+}
+
 // lowest varying key bit (-1: none) and one past the highest
 template <int W>
 __device__ __forceinline__ int key_low(uint64_t vlo, uint64_t vhi, int n)
@@ -695,449 +1019,484 @@ __device__ __forceinline__ int key_top(uint64_t vlo, uint64_t vhi, int n)
     return 0;
 }
 
-// LDS of one workgroup.  The sort permutes 16-bit record indices, ranking
-// them by a 32-bit window of each key that holds its varying bits (a key is
-// rebuilt from its window and the segment's constant bits); the values are
-// then gathered from the segment in sorted order.  After the sort ix[cur ^ 1] holds the run
-// heads, `aidx` (over the digit counters) each run's alpha slot, and `acache`
-// E(alpha) and c_q(alpha) of the segment's alpha strings when they fit: a
-// segment whose keys need two or more windows reads its keys from memory
-// after the sort, so the window array `ck` just before `acache` extends it.
-template <int W, int CAP, int NT>
-struct FinishLds {
-    static constexpr int NW = NT / 64;
-    static constexpr uint32_t kAcacheBytes = CAP;
+// LDS share of one wavefront: 64 * IT records.  The sort permutes 16-bit
+// record indices (ix), ranking them by a 32-bit window of each key that holds
+// its varying bits (ck); the values stay in registers meanwhile, so that their
+// array holds the digit counters (two 16-bit counters a word).  After the sort
+// ix holds the run heads (position, and bit 15 where the alpha string
+// changes) and ck each run's window, or its record where the keys have to be
+// read back.  Behind it lies the alpha cache: c_q(alpha) of amax strings.
+template <int IT>
+struct WaveLds {
+    static constexpr int CAP = 64 * IT;
+    static constexpr int DIGITS = 256 * IT;  // counters that fit over the values
     uint32_t ck[CAP];
-    uint64_t acache[kAcacheBytes / 8];
-    uint16_t ix[2][CAP + 8];
-    double val[CAP];
+    uint16_t ix[CAP + 8];
     union {
-        uint16_t wcnt[NW][256];
-        uint8_t aidx[CAP];
+        double val[CAP];
+        uint32_t cnt[DIGITS / 2];
     };
-    uint32_t dbase[256];
-    uint32_t tmp[2 * NW];
-    uint32_t nruns, nalpha;
-    uint64_t red[2][NW];  // per wave: OR of the key words' differences from the first key
+    double zero[2];  // val[CAP]: what a lane past the end of its run adds
 };
-
-// one final segment, processed by the whole workgroup
-template <int W, int CAP, int NT>
-__device__ __forceinline__ void finish_segment(const FinishArgs &f, const SpinTables &st, FinishLds<W, CAP, NT> &S,
-                                               const double *J, const double *X, const double *hd, uint32_t sidx)
+template <int IT>
+constexpr int digit_bits()
 {
-    using L = FinishLds<W, CAP, NT>;
-    constexpr int NW = L::NW;
-    constexpr int IT = CAP / NT;
-    static_assert(CAP % NT == 0 && NW * 256 * 2 >= CAP, "aidx must fit over the digit counters");
-    const int n = f.n;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const uint64_t lt = (1ull << lane) - 1ull;
+    return IT == 8 ? 11 : (IT == 4 ? 10 : 9);
+}
 
-    const Seg sg = f.finals[sidx];
-    const uint32_t buf = seg_buf(sg);
+// exclusive scan of N counter words per lane, in place: a word's two 16-bit
+// counters become the bases of their digits
+template <int N>
+__device__ __forceinline__ void scan_counters(uint32_t *cnt)
+{
+    uint32_t *c = cnt + (threadIdx.x & 63) * N;
+    uint32_t x[N], mine = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = c[i];
+#pragma unroll
+    for (int i = 0; i < N; ++i) mine += (x[i] & 0xFFFFu) + (x[i] >> 16);
+    uint32_t base = wave_incl_scan(mine) - mine;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t lo = base + (x[i] & 0xFFFFu);
+        c[i] = base | (lo << 16);
+        base = lo + (x[i] >> 16);
+    }
+}
+
+// marks the slots [start, start + written) and counts them in their tiles
+__device__ __forceinline__ void mark_slots(const FinishArgs &f, uint32_t start, uint32_t written)
+{
+    if (written == 0) return;
+    const int lane = threadIdx.x & 63;
+    const uint32_t end = start + written, w0 = start >> 6, w1 = (end - 1u) >> 6;
+    for (uint32_t w = w0 + (uint32_t)lane; w <= w1; w += 64) {
+        unsigned long long m = ~0ull;
+        if (w == w0) m &= ~0ull << (start & 63u);
+        if (w == w1) m &= ~0ull >> (63u - ((end - 1u) & 63u));
+        atomicOr(&f.mask[w], m);
+    }
+    const uint32_t t0 = start / kSlotTile, t1 = (end - 1u) / kSlotTile;
+    if (lane == 0) {
+        const uint32_t first = min(end, (t0 + 1u) * kSlotTile) - start;
+        atomicAdd(&f.tcnt[t0], first);
+        if (t1 != t0) atomicAdd(&f.tcnt[t1], written - first);  // a segment holds at most 512 candidates
+    }
+}
+
+// a segment of one key with more records than a wavefront's share: summed in
+// record order, 64 * IT values at a time staged in LDS
+template <int W, int IT, bool JL>
+__device__ __forceinline__ void finish_single(const FinishArgs &f, const Diag<JL> &D, WaveLds<IT> &S, const Seg &sg)
+{
+    constexpr int CAP = WaveLds<IT>::CAP;
+    const int n = f.n, lane = threadIdx.x & 63;
     const uint64_t nmask = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
-    uint32_t parity = 0;  // half of S.tmp for the next block scan
-    const uint64_t *gk = f.klo[buf] + sg.start;
-    const uint64_t *gh = f.khi[buf] + sg.start;
-    const double *gv = f.val[buf] + sg.start;
-
-    if (seg_single(sg)) {
-        // more records than fit in LDS, all with one key: sum in record order
-        __syncthreads();
-        if (tid == 0) {
-            const uint64_t lo = gk[0], hi = W == 2 ? gh[0] : 0ull;
-            const bool ex = psi_contains(f.psi, lo, hi);
-            uint32_t c = 0;
-            if (!ex) {
-                const uint64_t a = W == 1 ? (lo >> n) : hi, b = W == 1 ? (lo & nmask) : lo;
-                const double den = f.E0 - diag_tab(st, J, X, hd, n, f.ecore, a, b);
-                double sum = 0.0;
-                uint32_t kept = 0;
-                for (uint32_t r = 0; r < sg.size; ++r) {
-                    const double v = gv[r];
-                    if (f.eps > 0.0 && !(fabs(v / den) > f.eps)) continue;
-                    sum = sum + v;
-                    ++kept;
-                }
-                if (kept && (!f.thr || abs_order(sum / den) >= *f.thr)) {
-                    const size_t j0 = sg.start;
-                    f.clo[j0] = lo;
-                    if (W == 2) f.chi[j0] = hi;
-                    if (f.cnum) f.cnum[j0] = sum;
-                    f.cscore[j0] = sum / den;
-                    c = 1;
-                }
-            }
-            f.cnt[sidx] = c;
+    const uint64_t lo = f.klo[seg_buf(sg)][sg.start], hi = W == 2 ? f.khi[seg_buf(sg)][sg.start] : 0ull;
+    if (psi_contains(f.psi, lo, hi)) return;
+    const double *gv = f.val[seg_buf(sg)] + sg.start;
+    const uint64_t a = W == 1 ? (lo >> n) : hi, b = W == 1 ? (lo & nmask) : lo;
+    const double den = f.E0 - (n <= 32 ? diag_tab<JL, uint32_t>(D, f.ecore, (uint32_t)a, (uint32_t)b)
+                                       : diag_tab<JL, uint64_t>(D, f.ecore, a, b));
+    double sum = 0.0;
+    bool kept = false;
+    for (uint32_t r0 = 0; r0 < sg.size; r0 += CAP) {
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < IT; ++k) {
+            const uint32_t r = r0 + (uint32_t)(k * 64 + lane);
+            double v = r < sg.size ? gv[r] : 0.0;
+            bool in = r < sg.size;
+            if (f.eps > 0.0) in = in && fabs(v / den) > f.eps;
+            // a dropped value adds +0.0, which leaves the sum's bits alone (it
+            // starts at +0.0 and so never is -0.0)
+            S.val[k * 64 + lane] = in ? v : 0.0;
+            kept |= __ballot(in) != 0ull;
         }
-        return;
+        wave_sync();
+        const uint32_t m = min(sg.size - r0, (uint32_t)CAP);
+        for (uint32_t j = 0; j < m; j += 16) {
+            double v[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[k] = S.val[j + k];  // past the end: zeros
+#pragma unroll
+            for (int k = 0; k < 16; ++k) sum = sum + v[k];
+        }
     }
+    const double score = sum / den;
+    if (!kept || (f.thr && abs_order(score) < *f.thr)) return;
+    if (lane == 0) {
+        f.clo[sg.start] = lo;
+        if (W == 2) f.chi[sg.start] = hi;
+        if (f.cnum) f.cnum[sg.start] = sum;
+        f.cscore[sg.start] = score;
+    }
+    mark_slots(f, sg.start, 1u);
+}
 
+// one final segment of at most 64 * IT records, by one wavefront
+template <int W, int IT, bool JL>
+__device__ __forceinline__ void finish_segment(const FinishArgs &f, const Diag<JL> &D, WaveLds<IT> &S, double *acache,
+                                               const Seg &sg)
+{
+    using M = std::conditional_t<W == 1, uint32_t, uint64_t>;  // a spin string
+    constexpr int CAP = WaveLds<IT>::CAP;
+    constexpr int DB = digit_bits<IT>();
+    static_assert(1 << DB == WaveLds<IT>::DIGITS, "the digit counters lie over the values");
+    const int n = f.n;
+    const int lane = threadIdx.x & 63;
+    const uint64_t lt = (1ull << lane) - 1ull;
     const uint32_t size = sg.size;
-    // identity order; the values in record order (permuted in LDS once the
-    // sort is done, instead of gathered from memory in sorted order).  One-word
-    // keys stay in registers for their windows; two-word keys are read again,
-    // from cache.
-    uint64_t rk[IT];
-    // the bits that vary inside the segment: those in which some key differs
-    // from the first (one OR reduction; the constant bits are the first key's)
-    const uint64_t k0lo = size ? gk[0] : 0ull, k0hi = (W == 2 && size) ? gh[0] : 0ull;
-    {
-        uint64_t d0 = 0ull, d1 = 0ull;
-        double rv[IT];
-        // record r = wv * 64 * IT + k * 64 + lane: the layout of the radix
-        // passes' items, so the first pass ranks straight from these registers
+    const uint64_t nmask = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
+    const uint64_t *gk = f.klo[seg_buf(sg)] + sg.start;
+    const uint64_t *gh = f.khi[seg_buf(sg)] + sg.start;
+    const double *gv = f.val[seg_buf(sg)] + sg.start;
+
+    // record r = k * 64 + lane in registers; the bits that vary inside the
+    // segment are those in which some key differs from the first
+    uint64_t rk[IT], rh[W == 2 ? IT : 1];
+    double rv[IT];
 #pragma unroll
-        for (int k = 0; k < IT; ++k) {
-            const uint32_t r = (uint32_t)wv * 64 * IT + (uint32_t)k * 64 + (uint32_t)lane;
-            rk[k] = r < size ? gk[r] : 0ull;
-            rv[k] = r < size ? gv[r] : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < IT; ++k) {
-            const uint32_t r = (uint32_t)wv * 64 * IT + (uint32_t)k * 64 + (uint32_t)lane;
-            if (r < size) {
-                S.val[r] = rv[k];
-                d0 |= rk[k] ^ k0lo;
-                if (W == 2) d1 |= gh[r] ^ k0hi;
-            }
-        }
-        for (int d = 32; d >= 1; d >>= 1) {
-            d0 |= __shfl_xor(d0, d, 64);
-            if (W == 2) d1 |= __shfl_xor(d1, d, 64);
-        }
-        if (lane == 0) {
-            S.red[0][wv] = d0;
-            S.red[1][wv] = d1;
-        }
+    for (int k = 0; k < IT; ++k) {
+        const uint32_t r = (uint32_t)(k * 64 + lane);
+        rk[k] = r < size ? gk[r] : 0ull;
+        if (W == 2) rh[k] = r < size ? gh[r] : 0ull;
+        rv[k] = r < size ? gv[r] : 0.0;
     }
-    __syncthreads();
+    const uint64_t k0lo = uniform64(rk[0]), k0hi = W == 2 ? uniform64(rh[0]) : 0ull;
     uint64_t var_lo = 0ull, var_hi = 0ull;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        var_lo |= S.red[0][i];
-        if (W == 2) var_hi |= S.red[1][i];
+    for (int k = 0; k < IT; ++k) {
+        const uint32_t r = (uint32_t)(k * 64 + lane);
+        var_lo |= r < size ? rk[k] ^ k0lo : 0ull;
+        if (W == 2) var_hi |= r < size ? rh[k] ^ k0hi : 0ull;
     }
-    // the same for every lane: kept in scalar registers
-    var_lo = uniform64(var_lo);
-    var_hi = uniform64(var_hi);
+    var_lo = wave_or64(var_lo);
+    if (W == 2) var_hi = wave_or64(var_hi);
     const uint64_t and_lo = k0lo & ~var_lo, and_hi = k0hi & ~var_hi;
     const int low = key_low<W>(var_lo, var_hi, n);
     const int span = low < 0 ? 0 : key_top<W>(var_lo, var_hi, n) - low;
-    const int nwin = (span + 31) / 32;  // 32-bit windows holding the varying bits
+    const int nvar = __popcll(var_lo) + (W == 2 ? __popcll(var_hi) : 0);
+    // The window: the key's bits [low, low + 32) where the span fits, else its
+    // varying bits packed together; more than 32 varying bits take several
+    // windows of the span, and the keys are read back from memory (cache).
+    const bool packed = span > 32 && nvar <= 32;
+    const bool multi = nvar > 32;
+    const int bits = packed ? nvar : span;
+    // digits of equal width, at most DB bits: as few passes as that allows
+    const int npass = (bits + DB - 1) / DB;
+    const int dw = npass ? (bits + npass - 1) / npass : 1;
+    const int per_win = multi ? 32 / dw : max(npass, 1);
+    // window bits at or above this one belong to the alpha string
+    const int aw = packed ? __popcll(W == 1 ? (var_lo & nmask) : var_lo) : n - low;
 
-    // stable LSD radix sort of the record indices, one window at a time.  The
-    // first pass of one-word keys takes its items (the identity order) and
-    // windows from registers and stores the windows for the later passes.
-    int cur = 0;
-    if (nwin == 0) {
-        // one key: no pass runs, the order stays the identity
-        for (uint32_t r = tid; r < size; r += NT) S.ix[0][r] = (uint16_t)r;
-        __syncthreads();
+    if (packed) {
+        uint32_t w[IT];
+#pragma unroll
+        for (int k = 0; k < IT; ++k) w[k] = 0u;
+        const int d = for_bit_runs(var_lo, 0, [&](int s, uint64_t m, int to) {
+#pragma unroll
+            for (int k = 0; k < IT; ++k) w[k] |= (uint32_t)((rk[k] >> s) & m) << to;
+        });
+        if (W == 2)
+            (void)for_bit_runs(var_hi, d, [&](int s, uint64_t m, int to) {
+#pragma unroll
+                for (int k = 0; k < IT; ++k) w[k] |= (uint32_t)((rh[k] >> s) & m) << to;
+            });
+#pragma unroll
+        for (int k = 0; k < IT; ++k) S.ck[k * 64 + lane] = w[k];
+    } else if (!multi && npass) {
+#pragma unroll
+        for (int k = 0; k < IT; ++k) S.ck[k * 64 + lane] = key_window<W>(rk[k], W == 2 ? rh[k] : 0ull, n, low);
     }
-    for (int win = 0; win < nwin; ++win) {
-        const int o = low + 32 * win;
-        const uint32_t vwin = key_window<W>(var_lo, var_hi, n, o);
-        // the first window comes from the low key words held in registers when
-        // it lies inside them (always for one-word keys; for two-word keys when
-        // it ends at or below bit n, i.e. inside the beta word)
-        const bool regs = win == 0 && (W == 1 || low + 32 <= n);
-        if (W == 1 && !regs) {
+    uint32_t c[IT], rec[IT];  // after the sort: window and record at position q * 64 + lane
+    uint32_t hd = 0;          // bit q: run head there, bit 16 + q: alpha head
+    // Stable LSD radix sort of the record indices.  A record's rank among equal
+    // digits is the counter value that its LDS atomic returns: one instruction
+    // a row of 64 records, where a ballot match takes four a digit bit (which
+    // made 8-bit digits the widest that paid).  The order in which one
+    // instruction's lanes reach a counter is not specified, so nothing is taken
+    // on trust: the run-head pass compares every neighbouring pair, and a
+    // segment found out of (key, record) order is sorted again from the start
+    // with ballot ranks, whose order is defined.
+    for (int attempt = 0;; ++attempt) {
+        const bool ballots = attempt > 0;  // uniform
+        bool first = true;
+        wave_sync();
+        if (npass == 0) {
+            // one key: no pass runs, the order is the identity
 #pragma unroll
-            for (int k = 0; k < IT; ++k) {
-                const uint32_t r = (uint32_t)wv * 64 * IT + (uint32_t)k * 64 + (uint32_t)lane;
-                if (r < size) S.ck[r] = key_window<W>(rk[k], 0ull, n, o);
-            }
-        } else if (W == 2 && !regs) {
-            for (uint32_t r = tid; r < size; r += NT) S.ck[r] = key_window<W>(gk[r], gh[r], n, o);
-            // a first pass of two-word keys not taken from registers reads the
-            // identity order from LDS
-            if (win == 0)
-                for (uint32_t r = tid; r < size; r += NT) S.ix[0][r] = (uint16_t)r;
+            for (int k = 0; k < IT; ++k) S.ix[k * 64 + lane] = (uint16_t)(k * 64 + lane);
         }
-        if (!regs) __syncthreads();
-        for (int sh = 0; sh < 32; sh += 8) {
-            const uint32_t dv = (vwin >> sh) & 0xFFu;
-            if (dv == 0u) continue;  // no record differs in these bits
-            const int w = 32 - __builtin_clz(dv);  // up to the highest varying bit
-            const uint32_t dmask = (1u << w) - 1u;
-            for (int i = lane; i < (1 << w); i += 64) S.wcnt[wv][i] = 0;
-            static_assert(CAP <= 4096, "rank and record index take 12 bits each");
-            uint32_t item[IT];  // rank | record << 12 | digit << 24
-            // records and digits of all items first, so their loads overlap (the
-            // loads are unconditional and in bounds; past the segment's end the
-            // values are ignored)
-            static_assert((CAP & (CAP - 1)) == 0, "CAP must be a power of two");
-            uint32_t cw[IT];
-            if (regs && sh == 0) {
-                // window 0 always varies in its lowest bit, so this is the first pass
+        for (int p0 = 0; p0 < npass; p0 += per_win) {
+            if (multi) {
+                wave_sync();
 #pragma unroll
-                for (int q = 0; q < IT; ++q) {
-                    const uint32_t li = (uint32_t)wv * 64 * IT + (uint32_t)q * 64 + lane;
-                    item[q] = li;
-                    cw[q] = key_window<W>(rk[q], 0ull, n, o);
-                    if (li < size) S.ck[li] = cw[q];
+                for (int k = 0; k < IT; ++k) {
+                    const uint32_t r = (uint32_t)(k * 64 + lane);
+                    if (r < size) S.ck[r] = key_window<W>(gk[r], W == 2 ? gh[r] : 0ull, n, low + p0 * dw);
                 }
-            } else {
-#pragma unroll
-                for (int q = 0; q < IT; ++q) {
-                    const uint32_t li = (uint32_t)wv * 64 * IT + (uint32_t)q * 64 + lane;
-                    item[q] = (uint32_t)S.ix[cur][li] & (uint32_t)(CAP - 1);
-                }
-#pragma unroll
-                for (int q = 0; q < IT; ++q) cw[q] = S.ck[item[q]];
+                wave_sync();
             }
+            for (int p = p0; p < min(p0 + per_win, npass); ++p) {
+                const int sh = (p - p0) * dw;
+                const uint32_t dmask = (1u << dw) - 1u;
+                const uint32_t words = max(1u << (dw - 1), 64u);
+                for (uint32_t i = (uint32_t)lane; i < words; i += 64) S.cnt[i] = 0u;
+                uint32_t item[IT], dg[IT];  // record | rank << 16, digit
 #pragma unroll
-            for (int q = 0; q < IT; ++q) {
-                const uint32_t li = (uint32_t)wv * 64 * IT + (uint32_t)q * 64 + lane;
-                const uint32_t v = (item[q] << 12) | (((cw[q] >> sh) & dmask) << 24);
-                item[q] = li < size ? v : 0u;
-            }
+                for (int q = 0; q < IT; ++q)
+                    item[q] = first ? (uint32_t)(q * 64 + lane) : (uint32_t)S.ix[q * 64 + lane] & (uint32_t)(CAP - 1);
 #pragma unroll
-            for (int q = 0; q < IT; ++q) {
-                if ((uint32_t)wv * 64 * IT + (uint32_t)q * 64 >= size) break;  // whole wave past the end
-                const uint32_t li = (uint32_t)wv * 64 * IT + (uint32_t)q * 64 + lane;
-                const bool valid = li < size;
-                const uint32_t d = item[q] >> 24;
-                const uint64_t peers = wave_match(d, valid, w);
-                const uint32_t before = S.wcnt[wv][d];
-                item[q] |= before + (uint32_t)__popcll(peers & lt);
-                if (valid && (peers & lt) == 0ull) S.wcnt[wv][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
-            }
-            __syncthreads();
-            if (wv == 0) {
-                // one wavefront scans the (digit, wave) counts: each lane takes up
-                // to four consecutive digits, then one scan across the lanes
-                const int nd = 1 << w, dpl = (nd + 63) >> 6;
-                uint32_t dsum[4], lane_tot = 0;
+                for (int q = 0; q < IT; ++q) dg[q] = (S.ck[item[q]] >> sh) & dmask;
+                first = false;
+                wave_sync();
+                if (!ballots) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    dsum[k] = 0;
-                    const int dg = lane * dpl + k;
-                    if (k < dpl && dg < nd) {
-                        uint32_t run = 0;
+                    for (int q = 0; q < IT; ++q) {
+                        const uint32_t hs = (dg[q] & 1u) * 16u;
+                        if ((uint32_t)(q * 64 + lane) < size)
+                            item[q] |= ((atomicAdd(&S.cnt[dg[q] >> 1], 1u << hs) >> hs) & 0xFFFFu) << 16;
+                        wave_sync();
+                    }
+                } else {
+                    uint16_t *c16 = reinterpret_cast<uint16_t *>(&S.cnt[0]);
 #pragma unroll
-                        for (int i = 0; i < NW; ++i) {
-                            const uint32_t c = S.wcnt[i][dg];
-                            S.wcnt[i][dg] = (uint16_t)run;
-                            run += c;
+                    for (int q = 0; q < IT; ++q) {
+                        const bool valid = (uint32_t)(q * 64 + lane) < size;
+                        const uint64_t peers = wave_match(dg[q], valid, dw);
+                        const uint32_t before = c16[dg[q]];
+                        wave_sync();
+                        if (valid) {
+                            item[q] |= (before + (uint32_t)__popcll(peers & lt)) << 16;
+                            if ((peers & lt) == 0ull) c16[dg[q]] = (uint16_t)(before + (uint32_t)__popcll(peers));
                         }
-                        dsum[k] = run;
-                        lane_tot += run;
+                        wave_sync();
                     }
                 }
-                uint32_t base = wave_incl_scan(lane_tot) - lane_tot;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int dg = lane * dpl + k;
-                    if (k < dpl && dg < nd) {
-                        S.dbase[dg] = base;
-                        base += dsum[k];
-                    }
+                wave_sync();
+                switch (words) {  // uniform
+                case 64: scan_counters<1>(S.cnt); break;
+                case 128: scan_counters<2>(S.cnt); break;
+                case 256: scan_counters<4>(S.cnt); break;
+                case 512: if (IT >= 4) scan_counters<IT >= 4 ? 8 : 1>(S.cnt); break;
+                default: if (IT >= 8) scan_counters<IT >= 8 ? 16 : 1>(S.cnt); break;
                 }
-            }
-            __syncthreads();
+                wave_sync();
+                {
+                    const uint16_t *c16 = reinterpret_cast<const uint16_t *>(&S.cnt[0]);
 #pragma unroll
-            for (int q = 0; q < IT; ++q) {
-                const uint32_t li = (uint32_t)wv * 64 * IT + (uint32_t)q * 64 + lane;
-                if (li < size) {
-                    const uint32_t d = item[q] >> 24;
-                    const uint32_t p = min(S.dbase[d] + (uint32_t)S.wcnt[wv][d] + (item[q] & 0xFFFu), (uint32_t)CAP - 1u);
-                    S.ix[cur ^ 1][p] = (uint16_t)((item[q] >> 12) & 0xFFFu);
+                    for (int q = 0; q < IT; ++q)
+                        if ((uint32_t)(q * 64 + lane) < size) {
+                            const uint32_t d = min((uint32_t)c16[dg[q]] + (item[q] >> 16), (uint32_t)CAP - 1u);
+                            S.ix[d] = (uint16_t)(item[q] & 0xFFFFu);
+                        }
                 }
+                wave_sync();
             }
-            __syncthreads();
-            cur ^= 1;
         }
-    }
-    // runs of equal keys and the alpha strings among them.  Each thread owns IT
-    // consecutive sorted records; one scan of packed counts (runs low, alpha
-    // heads high) places both.  With one window the window decides equality,
-    // else the keys are read back from the segment.
-    uint16_t *head = &S.ix[cur ^ 1][0];
-    const uint16_t *perm = &S.ix[cur][0];
-    // values in sorted order: each thread gathers the IT consecutive positions
-    // it owns below from the record-order copy in LDS and stores them back in
-    // sorted order after the scan of the run-head pass (whose barriers order
-    // every read before any write)
-    double gval[IT];
-    {
-        const uint32_t j0 = (uint32_t)tid * IT;
+        // values to LDS in record order; then runs of equal keys and the alpha
+        // strings among them, row by row of the sorted positions: the position
+        // before a lane's is the lane before's, or the last of the row before
 #pragma unroll
-        for (int i = 0; i < IT; ++i) gval[i] = j0 + i < size ? S.val[perm[j0 + i]] : 0.0;
-    }
-    const int aw = n - low;  // window bits at or above this one are alpha bits (one-word keys: also two-word)
-    const uint32_t cache_bytes = L::kAcacheBytes + (nwin >= 2 ? (uint32_t)sizeof(S.ck) : 0u);
-    const uint32_t amax = min(255u, cache_bytes / (8u * (uint32_t)(n + 2)));
-    static_assert(offsetof(L, acache) == sizeof(S.ck), "the window array must end where the cache starts");
-    double *ealpha = reinterpret_cast<double *>(nwin >= 2 ? (void *)&S.ck[0] : (void *)&S.acache[0]);
-    double *colsum = ealpha + amax;
-    uint32_t nalpha, nruns;
-    {
-        const uint32_t j0 = (uint32_t)tid * IT;
-        uint32_t flags = 0;  // bit i: run head, bit 16 + i: alpha head
-        uint64_t prev_lo = 0ull, prev_hi = 0ull;
-        uint32_t prev_c = 0;
-        if (j0 > 0 && j0 < size) {
-            const uint32_t r = perm[j0 - 1];
-            if (nwin >= 2) {
-                prev_lo = gk[r];
-                prev_hi = W == 2 ? gh[r] : 0ull;
+        for (int k = 0; k < IT; ++k) S.val[k * 64 + lane] = rv[k];
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < IT; ++q) rec[q] = (uint32_t)S.ix[q * 64 + lane] & (uint32_t)(CAP - 1);
+        if (!multi) {
+#pragma unroll
+            for (int q = 0; q < IT; ++q) c[q] = npass ? S.ck[rec[q]] : 0u;
+        } else {
+#pragma unroll
+            for (int q = 0; q < IT; ++q) c[q] = rec[q];  // a run's key is read back through its record
+        }
+        hd = 0;
+        bool bad = false;
+        uint32_t pc = 0, pr = 0;  // last lane of the row before
+#pragma unroll
+        for (int q = 0; q < IT; ++q) {
+            if ((uint32_t)q * 64 >= size) break;  // uniform
+            const uint32_t j = (uint32_t)(q * 64 + lane);
+            const uint32_t bc = lane_before(c[q], pc), br = lane_before(rec[q], pr);
+            pc = (uint32_t)__builtin_amdgcn_readlane((int)c[q], 63);
+            pr = (uint32_t)__builtin_amdgcn_readlane((int)rec[q], 63);
+            bool head, ahead, order;  // order: out of (key, record) order
+            if (!multi) {
+                const uint32_t x = c[q] ^ bc;
+                head = x != 0u;
+                ahead = aw < 32 && (x >> max(aw, 0)) != 0u;
+                order = head ? c[q] < bc : rec[q] <= br;
             } else {
-                prev_c = nwin ? S.ck[r] : 0u;
+                const bool in = j > 0u && j < size;
+                const uint64_t klo = in ? gk[rec[q]] : 0ull, khi = W == 2 && in ? gh[rec[q]] : 0ull;
+                const uint64_t plo = in ? gk[br] : 0ull, phi = W == 2 && in ? gh[br] : 0ull;
+                head = klo != plo || khi != phi;
+                ahead = W == 1 ? (klo >> n) != (plo >> n) : khi != phi;
+                order = head ? key_less<W>(klo, khi, plo, phi) : rec[q] <= br;
+            }
+            if (j < size) {
+                bad |= j != 0u && order;
+                hd |= (j == 0u || head ? 1u : 0u) << q;
+                hd |= (j == 0u || ahead ? 1u : 0u) << (16 + q);
             }
         }
-#pragma unroll
-        for (int i = 0; i < IT; ++i) {
-            const uint32_t j = j0 + i;
-            if (j >= size) continue;
-            const uint32_t r = perm[j];
-            bool rh, ah;
-            if (nwin >= 2) {
-                const uint64_t klo = gk[r], khi = W == 2 ? gh[r] : 0ull;
-                rh = j == 0 || klo != prev_lo || khi != prev_hi;
-                ah = j == 0 || (W == 1 ? (klo >> n) != (prev_lo >> n) : khi != prev_hi);
-                prev_lo = klo;
-                prev_hi = khi;
-            } else {
-                const uint32_t c = nwin ? S.ck[r] : 0u;
-                const uint32_t x = c ^ prev_c;
-                rh = j == 0 || x != 0u;
-                ah = j == 0 || (aw < 32 && (x >> max(aw, 0)) != 0u);
-                prev_c = c;
-            }
-            flags |= (rh ? 1u : 0u) << i;
-            flags |= (ah ? 1u : 0u) << (16 + i);
-        }
-        const uint32_t cnt = (uint32_t)__popc(flags & 0xFFFFu) | ((uint32_t)__popc(flags >> 16) << 16);
-        uint32_t tot;
-        const uint32_t at = block_scan1<NW>(cnt, S.tmp, parity, tot);
-        nruns = tot & 0xFFFFu;
-        nalpha = tot >> 16;
-        // counts are below 2^16 (size <= CAP <= 4096), so the packed scan is exact
-        uint32_t rb = at & 0xFFFFu, ab = at >> 16;
-#pragma unroll
-        for (int i = 0; i < IT; ++i) {
-            if ((flags >> (16 + i)) & 1u) ++ab;
-            if ((flags >> i) & 1u) {
-                head[rb] = (uint16_t)(j0 + i);
-                S.aidx[rb] = (uint8_t)min(ab - 1u, 255u);
-                ++rb;
-            }
-        }
-        if (tid == 0) head[nruns] = (uint16_t)size;
-        // the alpha strings, in order: E(alpha) by the thread that owns the
-        // alpha head, the column sums c_q(alpha) by the lanes of its wavefront
-        // (one alpha head of the wavefront at a time)
-        if (nalpha <= amax) {
-            uint32_t ai_next = at >> 16;
-            uint32_t pend = (flags >> 16) & ((1u << IT) - 1u);
-            for (uint64_t owners = __ballot(pend != 0u); owners; owners = __ballot(pend != 0u)) {
-                const int src = __ffsll((long long)owners) - 1;
-                uint32_t a_lo = 0u, a_hi = 0u, ai = 0u;
-                if (lane == src) {
-                    const int i = __ffs(pend) - 1;
-                    const uint32_t r = perm[j0 + (uint32_t)i];
-                    uint64_t klo = and_lo, khi = and_hi;
-                    if (nwin >= 2) {
-                        klo = gk[r];
-                        khi = W == 2 ? gh[r] : 0ull;
-                    } else if (nwin == 1) {
-                        key_put<W>(S.ck[r], low, n, klo, khi);
-                    }
-                    const uint64_t alpha = W == 1 ? (klo >> n) : khi;
-                    ai = ai_next++;
-                    ealpha[ai] = spin_e(st, 0, X, hd, n, alpha);
-                    a_lo = (uint32_t)alpha;
-                    a_hi = (uint32_t)(alpha >> 32);
-                    pend &= pend - 1u;
-                }
-                a_lo = __shfl(a_lo, src, 64);
-                a_hi = __shfl(a_hi, src, 64);
-                ai = __shfl(ai, src, 64);
-                const uint64_t alpha = (uint64_t)a_lo | ((uint64_t)a_hi << 32);
-                for (int q = lane; q < n; q += 64) colsum[(size_t)ai * n + q] = cross_col(J, n, alpha, q);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < IT; ++i)
-            if (j0 + i < size) S.val[j0 + i] = gval[i];
-        __syncthreads();
+        if (ballots || __ballot(bad) == 0ull) break;
     }
-    const bool cached = nalpha <= amax;
-    // runs, NT at a time: key (read back from the segment), exclusion,
-    // diagonal, sum in record order, score; one scan per round places the
-    // surviving candidates, compacted, in run order
-    // a lower bound of the final k-th |A| from earlier class batches, if any
+    uint32_t nruns = 0;
+    {
+        double gval[IT];
+#pragma unroll
+        for (int q = 0; q < IT; ++q) gval[q] = S.val[rec[q]];
+        wave_sync();  // every lane holds its values, windows and records
+#pragma unroll
+        for (int q = 0; q < IT; ++q) {
+            if ((uint32_t)q * 64 >= size) break;  // uniform
+            S.val[q * 64 + lane] = gval[q];
+            const bool head = (hd >> q) & 1u;
+            const uint64_t m = __ballot(head);
+            if (head) {
+                const uint32_t at = nruns + (uint32_t)__popcll(m & lt);
+                S.ix[at] = (uint16_t)((uint32_t)(q * 64 + lane) | (((hd >> (16 + q)) & 1u) << 15));
+                S.ck[at] = c[q];
+            }
+            nruns += (uint32_t)__popcll(m);
+        }
+        if (lane == 0) S.ix[nruns] = (uint16_t)size;
+        wave_sync();
+    }
+    // Runs, 64 at a time: key, diagonal, sum in record order, score, exclusion;
+    // a ballot places the surviving candidates, compacted, in run order.
+    // thr: a lower bound of the final k-th |A| from earlier class batches, if any
     const uint64_t thr = f.thr ? *f.thr : 0ull;
-    uint32_t written = 0;
-    for (uint32_t base = 0; base < nruns; base += NT) {
-        const uint32_t u = base + (uint32_t)tid;
+    // a score is below thr for certain where |N| < tlow |E0 - H_aa| (the margin
+    // covers the roundings of both sides; no test for a bound that is not finite)
+    const double tlow = thr < 0x7FE0000000000000ull ? __longlong_as_double((long long)thr) * (1.0 - 0x1p-40) : 0.0;
+    const uint32_t amask = f.amax - 1u;
+    uint32_t written = 0, nalpha = 0;
+    double ea_last = 0.0;  // E(alpha) of the last string so far
+    for (uint32_t base = 0; base < nruns; base += 64) {
+        const uint32_t u = base + (uint32_t)lane;
+        const bool act = u < nruns;
         bool keep = false;
-        uint64_t lo = 0ull, hi = 0ull;
-        double sum = 0.0, score = 0.0;
-        if (u < nruns) {
-            const uint32_t j0 = head[u], j1 = head[u + 1];
-            const uint32_t r0 = perm[j0];
-            lo = and_lo;
-            hi = and_hi;
-            if (nwin >= 2) {
-                lo = gk[r0];
-                hi = W == 2 ? gh[r0] : 0ull;
-            } else if (nwin == 1) {
-                key_put<W>(S.ck[r0], low, n, lo, hi);
+        uint64_t lo = and_lo, hi = and_hi;
+        double sum = 0.0, score = 0.0, eb = 0.0, cross = 0.0, ea = 0.0;
+        uint32_t p0 = 0, p1 = 0;
+        bool ahead = false;
+        if (act) {
+            const uint32_t h0 = S.ix[u];
+            p0 = h0 & 0x7FFFu;
+            p1 = (uint32_t)S.ix[u + 1] & 0x7FFFu;
+            ahead = (h0 >> 15) != 0u;
+            const uint32_t w = S.ck[u];
+            if (multi) {
+                lo = gk[w];
+                hi = W == 2 ? gh[w] : 0ull;
+            } else if (packed) {
+                const int d = for_bit_runs(var_lo, 0, [&](int s, uint64_t m, int to) { lo |= ((uint64_t)(w >> to) & m) << s; });
+                if (W == 2)
+                    (void)for_bit_runs(var_hi, d, [&](int s, uint64_t m, int to) { hi |= ((uint64_t)(w >> to) & m) << s; });
+            } else if (npass) {
+                key_put<W>(w, low, n, lo, hi);
             }
-            // the exclusion filter is read before H_aa and the sum are formed,
-            // so its latency overlaps theirs; the table is probed only when the
-            // filter bit is set
-            const bool maybe = psi_maybe(f.psi, lo, hi);
+        }
+        const M a = (M)(W == 1 ? (lo >> n) : hi), b = (M)(W == 1 ? (lo & nmask) : lo);
+        // without a threshold every candidate asks the exclusion filter: its
+        // word is read first, so that the latency overlaps the work below
+        const uint64_t fh = psi_filter_hash(lo, hi), fb = psi_filter_bits(fh);
+        uint64_t fw = 0ull;
+        if (act && !thr) fw = f.psi.filter[psi_filter_word(fh, f.psi.fmask)];
+        // Alpha strings: the n-th string of the segment takes slot n mod amax
+        // of the cache.  The lanes are taken in turns of at most amax strings;
+        // a turn's new strings are the alpha heads among its lanes.
+        const uint64_t heads = __ballot(ahead);
+        const uint32_t ai = nalpha + (uint32_t)__popcll(heads & (lt | (1ull << lane))) - 1u;
+        nalpha += (uint32_t)__popcll(heads);
+        // E(alpha) by the lane of its head; its table entry, like E(beta)'s
+        // below, is a read at random from memory that is waited for at the end
+        double ea_head = 0.0;
+        if (ahead) ea_head = spin_e(D, 0, a);
+        for (uint64_t pend = __ballot(act); pend;) {
+            const int l0 = __ffsll((long long)pend) - 1;
+            const uint32_t a0 = (uint32_t)__builtin_amdgcn_readlane((int)ai, l0);
+            const bool turn = ((pend >> lane) & 1ull) && ai - a0 < f.amax;
+            const uint64_t tm = __ballot(turn);
+            for (uint64_t fresh = tm & heads; fresh; fresh &= fresh - 1ull) {
+                // c_q(alpha) of the head's string, q by lane
+                const int hl = __ffsll((long long)fresh) - 1;
+                const uint32_t sl = (uint32_t)__builtin_amdgcn_readlane((int)ai, hl) & amask;
+                M as = (M)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)a, hl);
+                if (W == 2) as |= (M)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)a >> 32), hl) << 32);
+                if (lane < n) acache[sl * (uint32_t)n + (uint32_t)lane] = column_sum(D, as, (uint32_t)lane);
+            }
+            wave_sync();
+            if (turn) {
+                // E(alpha, beta), and the rank of beta in the same walk over its orbitals
+                const double *cs = acache + (ai & amask) * (uint32_t)n;
+                if (D.e[1]) {
+                    struct Two {
+                        double x;
+                        uint32_t r;
+                    };
+                    uint32_t r = 0;
+                    for_bits(b, n, D.ne[1], [&](int i, uint32_t q) { return Two{cs[q], D.binom[(i + 1) * (n + 1) + (int)q]}; },
+                             [&](const Two &t) {
+                                 cross = cross + t.x;
+                                 r += t.r;
+                             });
+                    eb = D.e[1][min(r, D.last[1])];
+                } else {
+                    for_bits(b, n, D.ne[1], [&](int, uint32_t q) { return cs[q]; }, [&](double x) { cross = cross + x; });
+                }
+            }
+            pend &= ~tm;
+            if (pend) wave_sync();  // the next turn reuses slots this one reads
+        }
+        if (!D.e[1] && act) eb = spin_energy_u(D, D.ne[1], b);
+        if (act) {
+            if (f.eps <= 0.0) {
+                // the run's values, in sorted (= record, ascending core) order,
+                // eight in flight at a time, added in order (past the end +0.0,
+                // which leaves the sum's bits alone: it starts at +0.0 and so
+                // never is -0.0)
+                for (uint32_t j = p0; j < p1; j += 8) {
+                    double v[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[k] = S.val[j + (uint32_t)k < p1 ? j + (uint32_t)k : (uint32_t)CAP];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) sum = sum + v[k];
+                }
+                keep = true;
+            }
             {
-                const uint64_t a = W == 1 ? (lo >> n) : hi, b = W == 1 ? (lo & nmask) : lo;
-                double haa;
-                const uint32_t ai = S.aidx[u];
-                // E(beta) first: a table entry read at random from HBM, whose
-                // latency then overlaps the LDS work below (the sums keep their order)
-                const double eb = cached ? spin_e(st, 1, X, hd, n, b) : 0.0;
-                double cross = 0.0;
-                if (cached) {
-                    const double *cs = colsum + (size_t)ai * n;
-                    cross = n <= 32 ? bit_sum<uint32_t>((uint32_t)b, [&](int q) { return cs[q]; })
-                                    : bit_sum<uint64_t>(b, [&](int q) { return cs[q]; });
-                }
-                if (f.eps <= 0.0) {
-                    // the run's values, in sorted (= record, ascending core)
-                    // order, four in flight at a time, added in order
-                    for (uint32_t j = j0; j < j1; j += 4) {
-                        double v[4];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) v[k] = S.val[min(j + (uint32_t)k, j1 - 1u)];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) sum = j + (uint32_t)k < j1 ? sum + v[k] : sum;
-                    }
-                    keep = true;
-                }
-                if (cached) haa = ((f.ecore + ealpha[ai]) + eb) + cross;
-                else haa = diag_tab(st, J, X, hd, n, f.ecore, a, b);
-                const double den = f.E0 - haa;
-                if (f.eps > 0.0) {
-                    // Alg. 2's threshold, per pair
-                    for (uint32_t j = j0; j < j1; ++j) {
-                        const double v = S.val[j];
-                        if (fabs(v / den) > f.eps) {
-                            sum = sum + v;
-                            keep = true;
-                        }
-                    }
-                }
-                score = sum / den;
-                keep = keep && abs_order(score) >= thr;
+                // of the alpha head at or before this lane, or of the last batch
+                const uint64_t hm = heads & (lt | (1ull << lane));
+                const double x = __shfl(ea_head, hm ? 63 - __clzll((long long)hm) : 0, 64);
+                ea = hm ? x : ea_last;
             }
-            // an input determinant is not a candidate
-            if (maybe && keep) {
+            const double den = f.E0 - (((f.ecore + ea) + eb) + cross);
+            if (f.eps > 0.0) {
+                // Alg. 2's threshold, per pair
+                for (uint32_t j = p0; j < p1; ++j) {
+                    const double v = S.val[j];
+                    if (fabs(v / den) > f.eps) {
+                        sum = sum + v;
+                        keep = true;
+                    }
+                }
+            }
+            const double least = tlow * fabs(den);
+            keep = keep && !(least > 1e-280 && fabs(sum) < least);
+            if (keep) {
+                score = sum / den;
+                keep = abs_order(score) >= thr;
+            }
+            // an input determinant is not a candidate: the table is probed only
+            // when the filter bits are set
+            if (thr && keep) fw = f.psi.filter[psi_filter_word(fh, f.psi.fmask)];
+            if (keep && (fw & fb) == fb) {
                 uint32_t sl = psi_hash(lo, hi, f.psi.mask);
                 bool found = false;
-                for (uint32_t st = f.psi.state[sl]; st != 0u; st = f.psi.state[sl]) {
+                for (uint32_t t = f.psi.state[sl]; t != 0u; t = f.psi.state[sl]) {
                     if (f.psi.lo[sl] == lo && f.psi.hi[sl] == hi) {
                         found = true;
                         break;
@@ -1147,96 +1506,107 @@ __device__ __forceinline__ void finish_segment(const FinishArgs &f, const SpinTa
                 keep = !found;
             }
         }
-        uint32_t tot;
-        const uint32_t at = block_scan1<NW>(keep ? 1u : 0u, S.tmp, parity, tot);
+        if (heads) {
+            const int hl = 63 - __clzll((long long)heads);
+            const uint64_t x = (uint64_t)__double_as_longlong(ea_head);
+            ea_last = __longlong_as_double((long long)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, hl) |
+                                                       ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), hl) << 32)));
+        }
+        const uint64_t kb = __ballot(keep);
         if (keep) {
-            const size_t d = (size_t)sg.start + written + at;
+            const size_t d = (size_t)sg.start + written + (uint32_t)__popcll(kb & lt);
             f.clo[d] = lo;
             if (W == 2) f.chi[d] = hi;
             if (f.cnum) f.cnum[d] = sum;
             f.cscore[d] = score;
         }
-        written += tot;
+        written += (uint32_t)__popcll(kb);
     }
-    if (tid == 0) f.cnt[sidx] = written;
+    mark_slots(f, sg.start, written);
 }
 
-// persistent workgroups loop over the final segments (a grid of one
-// workgroup per segment could exceed the 2^32 work-item limit of a dispatch)
-template <int W, int CAP, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_finish(FinishArgs f)
+// A resident grid: every wavefront strides over the final segments on its own
+// (no barrier after the tables are staged), so that the load, sort and run
+// phases of the sixteen wavefronts of a CU overlap.  Bound by VALU issue (about
+// 60 % of the SIMD cycles) and, behind it, LDS.  One workgroup per segment of
+// 4096 records, with a barrier between phases, issued VALU work 35 % of the time
+// and waited 72 %; per launch, then and now: 9.6e8 records of 24e30o 24.3 and
+// 14.4 ms, 1.3e8 of 16e20o 2.98 and 1.68 ms, 9.7e7 two-word ones of 20e36o 7.5
+// and 5.45 ms.
+template <int W, int IT, bool JL>
+__global__ __launch_bounds__(64 * kFinishWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_finish(FinishArgs f)
 {
-    using L = FinishLds<W, CAP, NT>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    L &S = *reinterpret_cast<L *>(smem_raw);
-    double *tab = reinterpret_cast<double *>(smem_raw + ((sizeof(L) + 15) & ~size_t(15)));
+    constexpr int NT = 64 * kFinishWaves;
     const int n = f.n;
     const int tid = threadIdx.x;
-    const double *J = f.jk, *X = f.jk + n * n, *hd = f.jk + 2 * n * n;
-    SpinTables st = f.st;
-    if (f.tab_in_lds == 1) {
-        for (int t = tid; t < 2 * n * n; t += NT) tab[t] = f.jk[t];
-        for (int t = tid; t < n; t += NT) tab[2 * n * n + t] = f.h[(size_t)t * n + t];
-        J = tab;
-        X = tab + n * n;
-        hd = tab + 2 * n * n;
-    } else if (f.tab_in_lds >= 2) {
-        // with both spin tables only J and the binomials of the string ranks are read
-        const int nj = f.tab_in_lds == 2 ? n * n : 0;
-        for (int t = tid; t < nj; t += NT) tab[t] = f.jk[t];
-        uint32_t *bt = reinterpret_cast<uint32_t *>(tab + nj);
-        for (int t = tid; t < (st.kmax + 4) * (n + 1); t += NT) bt[t] = f.st.binom[t];
-        if (nj) J = tab;
-        st.binom = bt;
+    double *lx = reinterpret_cast<double *>(smem_raw);        // X, h_pp: where a string has no table
+    double *lj = lx + (f.stage_x ? n * (n - 1) / 2 + n : 0);  // J
+    uint32_t *lb = reinterpret_cast<uint32_t *>(lj + (JL ? n * (n + 1) / 2 : 0));  // binomials
+    if (f.stage_x) {
+        for (int t = tid; t < n * n; t += NT) {
+            const int p = t / n, q = t % n;
+            if (q > p) lx[p * n - (p * (p + 3) / 2 + 1) + q] = f.jk[n * n + t];
+        }
+        for (int t = tid; t < n; t += NT) lx[n * (n - 1) / 2 + t] = f.jk[2 * n * n + t];
     }
+    if (JL)  // J_pq = J_qp bit for bit (the integrals are checked symmetric)
+        for (int t = tid; t < n * n; t += NT) {
+            const int p = t / n, q = t % n;
+            if (q <= p) lj[p * (p + 1) / 2 + q] = f.jk[t];
+        }
+    if (f.st.binom)
+        for (int t = tid; t < (f.st.kmax + 1) * (n + 1); t += NT) lb[t] = f.st.binom[t];
+    const Diag<JL> D{JL ? lj : f.jk,  lx, lx + n * (n - 1) / 2, {f.st.e[0], f.st.e[1]}, {f.st.last[0], f.st.last[1]},
+                     lb, n, {f.na, f.nb}};
+    const uint32_t wv = uniform32((uint32_t)tid >> 6);
+    unsigned char *mine = smem_raw + f.tab_bytes + wv * f.wave_bytes;
+    WaveLds<IT> &S = *reinterpret_cast<WaveLds<IT> *>(mine);
+    double *acache = reinterpret_cast<double *>(mine + ((sizeof(WaveLds<IT>) + 15) & ~size_t(15)));
+    if ((tid & 63) < 2) S.zero[tid & 63] = 0.0;
+    __syncthreads();
     const uint32_t nf = dev_count(f.nfinal, f.dn_final);
-    for (uint32_t sidx = blockIdx.x; sidx < nf; sidx += gridDim.x) {
-        __syncthreads();
-        finish_segment<W, CAP, NT>(f, st, S, J, X, hd, sidx);
+    for (uint32_t sidx = blockIdx.x + gridDim.x * wv; sidx < nf; sidx += gridDim.x * kFinishWaves) {
+        const Seg sg = f.finals[sidx];
+        if (seg_single(sg)) finish_single<W, IT, JL>(f, D, S, sg);
+        else finish_segment<W, IT, JL>(f, D, S, acache, sg);
     }
 }
 
 // ---------------------------------------------------------------- collect
-__global__ __launch_bounds__(256) void k_final_keys_start(const Seg *__restrict__ finals, uint32_t nf,
-                                                          uint64_t *__restrict__ key, uint32_t *__restrict__ idx,
-                                                          const uint32_t *dn)
-{
-    const uint32_t j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= dev_count(nf, dn)) return;
-    key[j] = finals[j].start;
-    idx[j] = j;
-}
-
-__global__ __launch_bounds__(256) void k_gather_counts(const uint32_t *__restrict__ order,
-                                                       const uint32_t *__restrict__ cnt, uint32_t nf,
-                                                       uint32_t *__restrict__ out, const uint32_t *dn)
-{
-    const uint32_t j = blockIdx.x * 256 + threadIdx.x;
-    if (j < dev_count(nf, dn)) out[j] = cnt[order[j]];
-}
-
-// one block per final segment (in key order): copy its candidates to the pool
+// one block per tile of slots: copies the marked ones, in order, to the pool
 template <int W>
-__global__ __launch_bounds__(256) void k_collect(const Seg *__restrict__ finals, uint32_t nf,
-                                                 const uint32_t *__restrict__ order,
-                                                 const uint32_t *__restrict__ cnt_sorted,
+__global__ __launch_bounds__(256) void k_collect(const unsigned long long *__restrict__ mask, size_t P,
+                                                 uint32_t ntile, const uint32_t *__restrict__ tcnt,
                                                  const uint32_t *__restrict__ off, const uint64_t *__restrict__ clo,
                                                  const uint64_t *__restrict__ chi, const double *__restrict__ cnum,
                                                  const double *__restrict__ cscore, uint64_t *__restrict__ plo,
                                                  uint64_t *__restrict__ phi, double *__restrict__ pnum,
-                                                 double *__restrict__ pscore, size_t base, size_t cap,
-                                                 const uint32_t *dn)
+                                                 double *__restrict__ pscore, size_t base, size_t cap)
 {
-    nf = dev_count(nf, dn);
-    for (uint32_t j = blockIdx.x; j < nf; j += gridDim.x) {
-        const Seg sg = finals[order[j]];
-        const uint32_t c = cnt_sorted[j];
-        const size_t dst0 = base + off[j];
-        for (uint32_t t = threadIdx.x; t < c; t += 256) {
-            const size_t s = (size_t)sg.start + t, d = dst0 + t;
+    static_assert(kSlotTile == 64 * 64, "one mask word a lane");
+    __shared__ unsigned long long s_m[64];
+    __shared__ uint32_t s_at[64];
+    const int lane = threadIdx.x & 63;
+    for (uint32_t t = blockIdx.x; t < ntile; t += gridDim.x) {
+        if (tcnt[t] == 0u) continue;  // uniform per block
+        const size_t s0 = (size_t)t * kSlotTile;
+        __syncthreads();  // the previous tile's words are read
+        if (threadIdx.x < 64) {
+            const unsigned long long m = s0 + (size_t)lane * 64 < P ? mask[s0 / 64 + lane] : 0ull;
+            const uint32_t c = (uint32_t)__popcll(m);
+            s_m[lane] = m;
+            s_at[lane] = off[t] + wave_incl_scan(c) - c;
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x >> 6; i < 64; i += 4) {
+            const unsigned long long m = s_m[i];
+            if (!((m >> lane) & 1ull)) continue;
+            const size_t s = s0 + i * 64 + (uint32_t)lane;
+            const size_t d = base + s_at[i] + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
             if (d >= cap) {
                 raise_fault(kFaultSlot);
-                break;
+                continue;
             }
             plo[d] = clo[s];
             if (W == 2) phi[d] = chi[s];
@@ -1248,90 +1618,39 @@ __global__ __launch_bounds__(256) void k_collect(const Seg *__restrict__ finals,
 
 constexpr uint32_t kMaxClassSegs = 2048;  // classes of one batch
 
-__global__ __launch_bounds__(256) void k_class_segs(const uint64_t *__restrict__ cls, uint32_t c0, uint32_t nc,
-                                                    uint32_t nq, const uint32_t *__restrict__ offsets,
-                                                    const uint32_t *__restrict__ total, int n, uint32_t cap,
-                                                    Seg *__restrict__ large, uint32_t *__restrict__ nlarge,
-                                                    Seg *__restrict__ finals, uint32_t *__restrict__ nfinal,
-                                                    uint32_t nrec)
+// the first segments: classes larger than the capacity, and runs of
+// consecutive smaller ones coalesced into finals of at most `cap` records
+__global__ __launch_bounds__(1024) void k_class_segs(uint32_t nc, uint32_t nq, const uint32_t *__restrict__ offsets,
+                                                     const uint32_t *__restrict__ total, uint32_t cap, SegLists lists,
+                                                     uint32_t *__restrict__ ctr, uint32_t nrec)
 {
-    // class bounds and masks staged in LDS in parallel; one thread then walks
-    // the classes (the counters start at zero and this kernel is their only
-    // writer).  Bounds are clamped to the record buffer (nrec records): counts
-    // that overrun it (inputs that fail validation) cannot send a segment past it.
+    // Bounds are clamped to the record buffer (nrec records): counts that
+    // overrun it (inputs that fail validation) cannot send a segment past it.
     __shared__ uint32_t s_start[kMaxClassSegs + 1];
-    __shared__ uint64_t s_cls[kMaxClassSegs];
-    for (uint32_t c = threadIdx.x; c < nc; c += 256) {
-        s_start[c] = min(offsets[(size_t)c * nq], nrec);
-        s_cls[c] = cls[c0 + c];
-    }
+    __shared__ uint16_t s_next[kMaxClassSegs + 2], s_jump[kMaxClassSegs + 2];
+    __shared__ uint8_t s_mark[kMaxClassSegs + 2];
+    if (threadIdx.x < 8) ctr[threadIdx.x] = 0u;
+    for (uint32_t c = threadIdx.x; c < nc; c += 1024) s_start[c] = min(offsets[(size_t)c * nq], nrec);
     if (threadIdx.x == 0) s_start[nc] = min(*total, nrec);
+    __threadfence();  // the counters are zero before any wavefront adds to them
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    uint32_t nf = 0, nl = 0;
-    // a class's keys share every bit at or above n + (lowest bit of its mask);
-    // a run of classes shares the bits above the highest bit where its first
-    // lower bound and last upper bound differ
-    uint32_t g_start = 0, g_size = 0;
-    uint64_t g_first = 0, g_last = 0;  // masks of the run's first and last class
-    bool g_one = true;                 // the run holds one class
-    auto top_of = [&](uint64_t Tf, uint64_t Tl, bool one) -> uint32_t {
-        const int of = Tf ? __ffsll((unsigned long long)Tf) - 1 : 0;
-        const int ol = Tl ? __ffsll((unsigned long long)Tl) - 1 : 0;
-        if (one) return (uint32_t)(n + of);
-        // alpha range [Tf, Tl | (2^ol - 1)]
-        const uint64_t lo = Tf, hi = Tl | ((1ull << ol) - 1ull);
-        const uint64_t diff = lo ^ hi;
-        return (uint32_t)n + (diff ? (uint32_t)(64 - __clzll((long long)diff)) : 0u);
-    };
-    auto flush = [&]() {
-        if (g_size) finals[nf++] = Seg{g_start, g_size, make_meta(top_of(g_first, g_last, g_one), 0u, false)};
-        g_size = 0;
-    };
-    // eight classes' bounds and masks are read at a time, so the walk waits on
-    // LDS once per eight classes
-    uint32_t prev = s_start[0];
-    for (uint32_t cb = 0; cb < nc; cb += 8) {
-        uint32_t e8[8];
-        uint64_t t8[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const uint32_t c = min(cb + (uint32_t)k, nc - 1u);
-            e8[k] = s_start[c + 1];
-            t8[k] = s_cls[c];
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (cb + (uint32_t)k >= nc) break;
-            const uint32_t start = prev, end = e8[k];
-            prev = end;
-            if (end <= start) continue;
-            const uint32_t size = end - start;
-            if (size > cap) {
-                flush();
-                large[nl++] = Seg{start, size, make_meta(top_of(t8[k], t8[k], true), 0u, false)};
-                continue;
-            }
-            if (g_size + size > cap) flush();
-            if (g_size == 0) {
-                g_start = start;
-                g_first = t8[k];
-                g_one = true;
-            } else {
-                g_one = false;
-            }
-            g_size += size;
-            g_last = t8[k];
-        }
+    greedy_groups<3>(s_start, nc, cap, s_next, s_jump, s_mark, threadIdx.x, 1024u, [] { __syncthreads(); });
+    for (uint32_t b = 0; b < nc; b += 1024) {
+        const uint32_t c = b + threadIdx.x;
+        uint32_t size = 0;
+        if (c < nc && s_mark[c]) size = s_start[s_next[c]] - s_start[c];
+        // offsets that wrapped round (inputs that fail validation) give no segment
+        if (size > nrec || (size && (uint64_t)s_start[c] + size > nrec)) size = 0;
+        const uint32_t kind = size == 0u ? 0u : (size <= cap ? 1u : (size <= (uint32_t)kTileN ? 2u : 3u));
+        append_segs(lists, kind, size ? Seg{s_start[c], size, make_meta(0u, false)} : Seg{0u, 0u, 0u});
     }
-    flush();
-    *nfinal = nf;
-    *nlarge = nl;
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------- host side
+// A bound: the split, finish and collect of P records in nc classes take less
+// (see level_tiles, level_hist) for every finish capacity.
 size_t bucket_workspace_bytes(size_t P, size_t nc, int W, int finish_cap)
 {
     const size_t cap = finish_cap >= 4096 ? 4096 : (finish_cap >= 2048 ? 2048 : 1024);
@@ -1342,44 +1661,43 @@ size_t bucket_workspace_bytes(size_t P, size_t nc, int W, int finish_cap)
            (4 << 20);
 }
 
-// LDS per workgroup: the table of J, J-K and h_pp is staged when the whole
-// still lets two workgroups share a CU (their barriers then overlap)
+// LDS per workgroup: two workgroups share a CU
 constexpr size_t kFinishLdsBudget = 80 * 1024;
 
-template <int W, int CAP, int NT>
+template <int W, int IT>
 static int launch_finish(FinishArgs &fa, const BucketArgs &b, uint32_t nf, hipStream_t s, Profiler *prof)
 {
-    const size_t base_lds = (sizeof(FinishLds<W, CAP, NT>) + 15) & ~size_t(15);
-    const size_t n = (size_t)b.n;
-    size_t tab_lds = 0;
-    fa.tab_in_lds = 0;
-    if (b.st.e[0] && b.st.e[1]) {
-        // E(alpha), E(beta) are looked up: stage J and the binomials, else the binomials
-        const size_t bin = (size_t)(b.st.kmax + 4) * (n + 1) * 4;
-        if (base_lds + n * n * 8 + bin <= kFinishLdsBudget) {
-            fa.tab_in_lds = 2;
-            tab_lds = n * n * 8 + bin;
-        } else if (base_lds + bin <= kFinishLdsBudget) {
-            fa.tab_in_lds = 3;
-            tab_lds = bin;
-        }
-    } else if (base_lds + (2 * n * n + n) * 8 <= kFinishLdsBudget) {
-        fa.tab_in_lds = 1;
-        tab_lds = (2 * n * n + n) * 8;
-    }
-    const size_t lds = base_lds + ((tab_lds + 15) & ~size_t(15));
-    const void *fn = (const void *)k_finish<W, CAP, NT>;
+    const size_t base = (sizeof(WaveLds<IT>) + 15) & ~size_t(15);
+    const size_t n = (size_t)b.n, entry = n * 8;  // of the alpha cache
+    // strings without a table are evaluated from X and h_pp, those with one are
+    // ranked; J is staged where every wavefront keeps room for two alpha strings
+    fa.stage_x = !b.st.e[0] || !b.st.e[1] ? 1 : 0;
+    size_t tab = (fa.stage_x ? (n * (n - 1) / 2 + n) * 8 : 0) + (b.st.binom ? (size_t)(b.st.kmax + 1) * (n + 1) * 4 : 0);
+    auto total = [&](size_t tables, size_t strings) {
+        return ((tables + 15) & ~size_t(15)) + kFinishWaves * ((base + strings * entry + 15) & ~size_t(15));
+    };
+    const bool jl = total(tab + n * (n + 1) / 2 * 8, 2) <= kFinishLdsBudget;
+    if (jl) tab += n * (n + 1) / 2 * 8;
+    tab = (tab + 15) & ~size_t(15);
+    fa.amax = 1;
+    while (fa.amax < 32 && total(tab, 2 * fa.amax) <= kFinishLdsBudget) fa.amax *= 2;
+    fa.tab_bytes = (uint32_t)tab;
+    fa.wave_bytes = (uint32_t)((base + fa.amax * entry + 15) & ~size_t(15));
+    const size_t lds = tab + (size_t)kFinishWaves * fa.wave_bytes;
+    void (*kernel)(FinishArgs) = jl ? k_finish<W, IT, true> : k_finish<W, IT, false>;
+    const void *fn = (const void *)kernel;
+    constexpr int NT = 64 * kFinishWaves;
     ASCI_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     int dev = 0, ncu = 0, per_cu = 0;
     ASCI_HIP(hipGetDevice(&dev));
     ASCI_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     ASCI_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, NT, lds));
-    // one resident grid: every workgroup strides over the segments
+    // one resident grid; few segments are spread one wavefront to a workgroup
     const uint32_t grid = std::min<uint32_t>(nf, (uint32_t)std::max(1, ncu * std::max(per_cu, 1)));
     // bytes: every record read once; the candidates it writes are added once
     // their number is known (finish_bytes)
     ProfScope ps(prof, "finish", (8.0 * W + 8.0) * (double)b.P, s);
-    k_finish<W, CAP, NT><<<grid, NT, lds, s>>>(fa);
+    kernel<<<grid, NT, lds, s>>>(fa);
     ASCI_LAUNCH_CHECK();
     return ps.tok;
 }
@@ -1393,68 +1711,98 @@ static void finish_bytes(const BucketArgs &b, int W)
                                             (8.0 * W + 8.0 + (b.cnum ? 8.0 : 0.0)) * (double)b.V);
 }
 
-template <int W>
-void bucket_accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, HostStage &hs)
+// Split levels run when no count is read back: three take the largest batch
+// (below 2^31 records) to ranges of one tile, one more isolates single keys,
+// one is spare; the last one takes what the small split could not divide.
+constexpr int kDevLevels = 5;
+
+// device counters of one batch
+enum { kCtrFinal = 0, kCtrLarge = 1 /* and 2: per level parity */, kCtrOverflow = 3, kCtrSmall = 4 /* and 5: per round */ };
+
+// after the last level: segments still too large for the finish, or a list
+// that overflowed its capacity, fail the call
+__global__ __launch_bounds__(64) void k_levels_done(const uint32_t *__restrict__ ctr, int last_parity,
+                                                    uint32_t *__restrict__ stat)
 {
-    // LDS capacity of a final segment: 4096, 2048 or 1024 records
-    const int CAP = b.finish_cap >= 4096 ? 4096 : (b.finish_cap >= 2048 ? 2048 : 1024);
+    if (threadIdx.x != 0) return;
+    if (ctr[kCtrLarge + last_parity] != 0u || ctr[kCtrOverflow] != 0u) atomicOr(stat, kStatSplit);
+}
+
+// Split levels, finish, and the scan that places the candidates.  With d_stat
+// nothing is read back: a fixed number of levels runs on launch shapes sized
+// for bounds, and a failure sets bits of *d_stat; else the host reads the
+// number of large segments once per level and stops when none is left.
+template <int W>
+static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, HostStage *hs, uint32_t *d_stat)
+{
+    const bool dev = d_stat != nullptr;
+    const uint32_t cap = (uint32_t)wave_cap(b.finish_cap);
     const size_t P = b.P;
     const uint32_t finals_cap = (uint32_t)std::min<size_t>(b.nc + P / 8 + 65536, 0xFFFFFFF0u);
-    const uint32_t level_cap = (uint32_t)(P / CAP + b.nc + 16);
+    const uint32_t level_cap = (uint32_t)(P / cap + 16);  // disjoint segments of more than cap records
     Seg *finals = ar.take<Seg>(finals_cap);
     Seg *lv[2] = {ar.take<Seg>(level_cap), ar.take<Seg>(level_cap)};
-    uint32_t *ctr = ar.take<uint32_t>(8);  // 0: finals, 1/2: large segments per level parity, 3: overflow
-    uint32_t *hcnt = (uint32_t *)hs.ptr;
-    ASCI_HIP(hipMemsetAsync(ctr, 0, 8 * sizeof(uint32_t), s));
+    Seg *small = ar.take<Seg>(level_cap);
+    uint32_t *ctr = ar.take<uint32_t>(8);
+    uint32_t *hcnt = hs ? (uint32_t *)hs->ptr : nullptr;
+    SegLists lists{finals, small, lv[0], ctr + kCtrFinal, ctr + kCtrSmall, ctr + kCtrLarge, ctr + kCtrOverflow,
+                   finals_cap, level_cap, level_cap};
     require(b.nc <= kMaxClassSegs, ASCI_EINVAL, "too many classes in one batch");
-    k_class_segs<<<1, 256, 0, s>>>(b.cls, b.c0, b.nc, b.nq, b.offsets, b.total, b.n, (uint32_t)CAP, lv[0], ctr + 1,
-                                   finals, ctr, (uint32_t)std::min<size_t>(P, 0xFFFFFFFFu));
+    k_class_segs<<<1, 1024, 0, s>>>(b.nc, b.nq, b.offsets, b.total, cap, lists, ctr,
+                                    (uint32_t)std::min<size_t>(P, 0xFFFFFFFFu));
     ASCI_LAUNCH_CHECK();
-    ASCI_HIP(hipMemcpyAsync(hcnt, ctr, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    ASCI_HIP(hipStreamSynchronize(s));
-    uint32_t nlarge = hcnt[1];
-    int lev = 0;
+    auto read_counts = [&]() {
+        ASCI_HIP(hipMemcpyAsync(hcnt, ctr, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+        ASCI_HIP(hipStreamSynchronize(s));
+        require(hcnt[kCtrOverflow] == 0, ASCI_EDEVICE, "bucket segment list overflow");
+    };
     uint8_t *dig = ar.take<uint8_t>(P + 1);
+    uint64_t *spl_lo = ar.take<uint64_t>(2 * P / cap + 1);
+    uint64_t *spl_hi = W == 2 ? ar.take<uint64_t>(2 * P / cap + 1) : nullptr;
+    uint32_t *lev_tot = ar.take<uint32_t>(4);
     const size_t mark = ar.used();
-    while (nlarge > 0) {
+    const KeyBufs kb{{b.klo[0], b.klo[1]}, {b.khi[0], b.khi[1]}};
+    int lev = 0;
+    // one split level of the (at most nlarge) large segments of list lev & 1
+    auto split_level = [&](uint32_t nlarge) {
         ar.reset();
         (void)ar.take<char>(mark);
         require(lev < 64, ASCI_EDEVICE, "bucket split did not converge");
-        Seg *segs = lv[lev & 1], *next = lv[(lev & 1) ^ 1];
-        uint32_t *nnext = ctr + 1 + ((lev & 1) ^ 1);
-        uint32_t *ntile = ar.take<uint32_t>(nlarge + 1);
-        uint32_t *tbase = ar.take<uint32_t>(nlarge + 1);
-        uint32_t *skip = ar.take<uint32_t>(nlarge + 1);
-        uint32_t *d_ntiles = ar.take<uint32_t>(4);
-        k_seg_tiles<<<(nlarge + 256) / 256, 256, 0, s>>>(segs, nlarge, ntile, skip, nnext, nullptr);
+        Seg *segs = lv[lev & 1];
+        const uint32_t *dn_seg = dev ? ctr + kCtrLarge + (lev & 1) : nullptr;
+        lists.next = lv[(lev & 1) ^ 1];
+        lists.nnext = ctr + kCtrLarge + ((lev & 1) ^ 1);
+        const uint32_t ntiles = (uint32_t)level_tiles(P, nlarge);
+        const size_t nhist = level_hist(P, nlarge, cap);
+        uint32_t *tbase = ar.take<uint32_t>((size_t)nlarge + 1);
+        uint32_t *hbase = ar.take<uint32_t>((size_t)nlarge + 1);
+        uint32_t *skip = ar.take<uint32_t>((size_t)nlarge + 1);
+        uint32_t *tseg = ar.take<uint32_t>((size_t)ntiles + 1);
+        uint32_t *hist = ar.take<uint32_t>(nhist + 1);
+        // launch shapes: per-segment kernels stride over the level's segments,
+        // tile kernels over its tiles (eight XCD groups of workgroups)
+        const unsigned g_seg = dev ? std::min(nlarge, 2048u) : nlarge;
+        const unsigned g_tiles = 8u * (dev ? std::min((ntiles + 7) / 8, 256u) : (ntiles + 7) / 8);
+        k_level_plan<<<1, 1024, 0, s>>>(segs, nlarge, cap, tbase, hbase, skip, lev_tot, lists.nnext, dn_seg);
         ASCI_LAUNCH_CHECK();
-        scan_u32(ntile, tbase, nlarge, d_ntiles, ar, s, prof);
-        ASCI_HIP(hipMemcpyAsync(hcnt + 4, d_ntiles, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-        ASCI_HIP(hipStreamSynchronize(s));
-        const uint32_t ntiles = hcnt[4];
-        uint32_t *tseg = ar.take<uint32_t>(ntiles + 1);
-        uint32_t *hist = ar.take<uint32_t>((size_t)ntiles * 256 + 1);
-        uint32_t *hscan = ar.take<uint32_t>((size_t)ntiles * 256 + 1);
-        uint64_t *spl_lo = ar.take<uint64_t>((size_t)nlarge * (kMaxSplit - 1));
-        uint64_t *spl_hi = W == 2 ? ar.take<uint64_t>((size_t)nlarge * (kMaxSplit - 1)) : nullptr;
-        unsigned long long *kvar = ar.take<unsigned long long>(2 * (size_t)nlarge);
-        k_seg_expand<<<(nlarge + 255) / 256, 256, 0, s>>>(segs, nlarge, tbase, tseg, kvar, nullptr);
+        k_tile_seg<<<std::min((ntiles + 255) / 256, 1024u), 256, 0, s>>>(tbase, nlarge, lev_tot, tseg, dn_seg);
         ASCI_LAUNCH_CHECK();
         {
             ProfScope ps(prof, "split_sample", 0.0, s);
-            const KeyBufs kb{{b.klo[0], b.klo[1]}, {b.khi[0], b.khi[1]}};
-            // class-sized segments of the first level sort up to 4096 samples:
+            // class-sized segments of the first level sort up to 2048 samples:
             // more threads per sort; later levels sort a few hundred
-            if (lev == 0) k_seg_splitters<W, 1024><<<nlarge, 1024, 0, s>>>(segs, (uint32_t)CAP, kb, spl_lo, spl_hi, nlarge, nullptr);
-            else k_seg_splitters<W, 256><<<nlarge, 256, 0, s>>>(segs, (uint32_t)CAP, kb, spl_lo, spl_hi, nlarge, nullptr);
+            if (lev == 0) k_seg_splitters<W, 1024><<<g_seg, 1024, 0, s>>>(segs, cap, kb, spl_lo, spl_hi, nlarge, dn_seg);
+            else k_seg_splitters<W, 256><<<g_seg, 256, 0, s>>>(segs, cap, kb, spl_lo, spl_hi, nlarge, dn_seg);
             ASCI_LAUNCH_CHECK();
         }
         SplitArgs sa;
         sa.segs = segs;
         sa.nseg = nlarge;
         sa.tile_base = tbase;
+        sa.hist_base = hbase;
         sa.tile_seg = tseg;
         sa.ntiles = ntiles;
+        sa.lev = lev_tot;
         sa.hist = hist;
         sa.klo[0] = b.klo[0];
         sa.klo[1] = b.klo[1];
@@ -1462,51 +1810,88 @@ void bucket_accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         sa.khi[1] = b.khi[1];
         sa.val[0] = b.val[0];
         sa.val[1] = b.val[1];
-        sa.n = b.n;
-        sa.cap = (uint32_t)CAP;
+        sa.cap = cap;
         sa.spl_lo = spl_lo;
         sa.spl_hi = spl_hi;
-        sa.kvar = kvar;
         sa.dig = dig;
         {
             ProfScope ps(prof, "split_hist", (8.0 * W) * (double)ntiles * kTileN, s);
-            k_split_hist<W><<<8 * ((ntiles + 7) / 8), kHistT, 0, s>>>(sa);
+            k_split_hist<W><<<g_tiles, kHistT, 0, s>>>(sa);
             ASCI_LAUNCH_CHECK();
         }
-        scan_u32(hist, hscan, (size_t)ntiles * 256, nullptr, ar, s, prof);
-        k_split_children<W><<<nlarge, 256, 0, s>>>(segs, nlarge, tbase, hscan, (uint32_t)CAP, skip, finals, ctr,
-                                                   finals_cap, next, nnext, level_cap, ctr + 3, kvar, b.n, nullptr);
+        scan_u32(hist, hist, nhist, nullptr, ar, s, prof, lev_tot + 1);
+        k_split_children<W><<<(g_seg + kChildWaves - 1) / kChildWaves, 64 * kChildWaves, 0, s>>>(
+            segs, nlarge, hbase, hist, cap, spl_lo, spl_hi, skip, lists, dn_seg);
         ASCI_LAUNCH_CHECK();
-        sa.hist = hscan;
         {
             ProfScope ps(prof, "split_scatter", 2.0 * (8.0 * W + 8.0) * (double)ntiles * kTileN, s);
-            k_split_scatter<W><<<8 * ((ntiles + 7) / 8), kTileT, 0, s>>>(sa, hscan, skip);
+            k_split_scatter<W><<<g_tiles, kTileT, 0, s>>>(sa, skip);
             ASCI_LAUNCH_CHECK();
         }
-        ASCI_HIP(hipMemcpyAsync(hcnt, ctr, 8 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-        ASCI_HIP(hipStreamSynchronize(s));
-        require(hcnt[3] == 0, ASCI_EDEVICE, "bucket segment list overflow");
-        nlarge = hcnt[1 + ((lev & 1) ^ 1)];
         ++lev;
+    };
+    // the segments of one tile at most, each by one workgroup
+    auto small_split = [&](uint32_t nsmall, uint32_t *nsm) {
+        if (nsmall == 0) return;
+        ProfScope ps(prof, "small_split", 0.0, s);
+        k_small_split<W><<<dev ? std::min(nsmall, 4096u) : nsmall, kSmallT, 0, s>>>(
+            small, nsmall, dev ? nsm : nullptr, cap, b.klo[0], b.klo[1], b.khi[0], b.khi[1], b.val[0], b.val[1], lists);
+        ASCI_LAUNCH_CHECK();
+    };
+    if (dev) {
+        for (int l = 0; l < kDevLevels; ++l) split_level(level_cap);
+        for (int round = 0; round < 2; ++round) {
+            // round 1 takes what the small split of round 0 left, from list lev & 1
+            lists.nsmall = ctr + kCtrSmall + (round ^ 1);
+            small_split(level_cap, ctr + kCtrSmall + round);
+            if (round == 0) split_level(level_cap);
+        }
+        k_levels_done<<<1, 64, 0, s>>>(ctr, lev & 1, d_stat);
+        ASCI_LAUNCH_CHECK();
+    } else {
+        read_counts();
+        for (int round = 0;; ++round) {
+            while (hcnt[kCtrLarge + (lev & 1)] > 0) {
+                split_level(hcnt[kCtrLarge + (lev & 1)]);
+                read_counts();
+            }
+            const uint32_t nsmall = hcnt[kCtrSmall + (round & 1)];
+            if (nsmall == 0) break;
+            // leftovers go to list lev & 1, whose count is zero here, and the
+            // small ones among their children to the other round's count
+            if (round > 0) ASCI_HIP(hipMemsetAsync(ctr + kCtrSmall + ((round & 1) ^ 1), 0, sizeof(uint32_t), s));
+            lists.nsmall = ctr + kCtrSmall + ((round & 1) ^ 1);
+            lists.next = lv[lev & 1];
+            lists.nnext = ctr + kCtrLarge + (lev & 1);
+            small_split(nsmall, nullptr);
+            read_counts();
+        }
     }
     ar.reset();
     (void)ar.take<char>(mark);
-    const uint32_t nf = hcnt[0];
+    const uint32_t nf = dev ? finals_cap : hcnt[kCtrFinal];
     b.nfinal = nf;
     b.levels = (uint32_t)lev;
-    uint32_t *cnt = ar.take<uint32_t>(nf + 1);
+    // candidate marks: a bit per slot, a count per tile of slots, cleared together
+    const uint32_t ntile = (uint32_t)((P + kSlotTile - 1) / kSlotTile);
+    const size_t mwords = 2 * (size_t)ntile * (kSlotTile / 64);
+    uint32_t *marks = ar.take<uint32_t>(mwords + ntile + 1);
+    fill_u32(marks, mwords + ntile, 0u, s);
+    b.mask = reinterpret_cast<unsigned long long *>(marks);
+    b.tcnt = marks + mwords;
+    b.ntile = ntile;
     if (nf) {
         FinishArgs fa;
         fa.finals = finals;
-        fa.klo[0] = b.klo[0];
-        fa.klo[1] = b.klo[1];
-        fa.khi[0] = b.khi[0];
-        fa.khi[1] = b.khi[1];
-        fa.val[0] = b.val[0];
-        fa.val[1] = b.val[1];
+        for (int i = 0; i < 2; ++i) {
+            fa.klo[i] = b.klo[i];
+            fa.khi[i] = b.khi[i];
+            fa.val[i] = b.val[i];
+        }
         fa.n = b.n;
+        fa.na = b.na;
+        fa.nb = b.nb;
         fa.jk = b.jk;
-        fa.h = b.h;
         fa.st = b.st;
         fa.thr = b.thr;
         fa.ecore = b.ecore;
@@ -1516,35 +1901,29 @@ void bucket_accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         fa.chi = b.chi;
         fa.cnum = b.cnum;
         fa.cscore = b.cscore;
-        fa.cnt = cnt;
+        fa.mask = b.mask;
+        fa.tcnt = b.tcnt;
         fa.nfinal = nf;
-        fa.dn_final = nullptr;
+        fa.dn_final = dev ? ctr + kCtrFinal : nullptr;
         fa.psi = b.psi;
-        // eight records per thread
         b.prof = prof;
-        if (CAP == 4096) b.finish_tok = launch_finish<W, 4096, 512>(fa, b, nf, s, prof);
-        else if (CAP == 2048) b.finish_tok = launch_finish<W, 2048, 256>(fa, b, nf, s, prof);
-        else b.finish_tok = launch_finish<W, 1024, 128>(fa, b, nf, s, prof);
+        if (cap == 512) b.finish_tok = launch_finish<W, 8>(fa, b, nf, s, prof);
+        else if (cap == 256) b.finish_tok = launch_finish<W, 4>(fa, b, nf, s, prof);
+        else b.finish_tok = launch_finish<W, 2>(fa, b, nf, s, prof);
     }
-    // candidates in key order: final segments by start, counts scanned
-    uint64_t *sk[2] = {ar.take<uint64_t>(nf + 1), ar.take<uint64_t>(nf + 1)};
-    uint32_t *si[2] = {ar.take<uint32_t>(nf + 1), ar.take<uint32_t>(nf + 1)};
-    uint32_t *cs = ar.take<uint32_t>(nf + 1);
-    uint32_t *co = ar.take<uint32_t>(nf + 1);
+    uint32_t *off = ar.take<uint32_t>((size_t)ntile + 1);
     uint32_t *d_v = ar.take<uint32_t>(4);
-    uint64_t *nohi[2] = {nullptr, nullptr};
-    int r = 0;
-    if (nf) {
-        k_final_keys_start<<<(nf + 255) / 256, 256, 0, s>>>(finals, nf, sk[0], si[0], nullptr);
-        ASCI_LAUNCH_CHECK();
-        std::vector<Digit> dg;
-        for (int sh = 0; sh < 32; sh += 8) dg.push_back({0, sh});
-        r = radix_sort<uint32_t>(sk, nohi, si, nf, 1, dg, ar, s, nullptr);
-        k_gather_counts<<<(nf + 255) / 256, 256, 0, s>>>(si[r], cnt, nf, cs, nullptr);
-        ASCI_LAUNCH_CHECK();
-    }
-    scan_u32(cs, co, nf, d_v, ar, s, nullptr);
-    ASCI_HIP(hipMemcpyAsync(hcnt + 6, d_v, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    scan_u32(b.tcnt, off, ntile, d_v, ar, s, nullptr);
+    b.off = off;
+    b.dn_V = d_v;
+}
+
+template <int W>
+void bucket_accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, HostStage &hs)
+{
+    accumulate<W>(b, ar, s, prof, &hs, nullptr);
+    uint32_t *hcnt = (uint32_t *)hs.ptr;
+    ASCI_HIP(hipMemcpyAsync(hcnt + 6, b.dn_V, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     b.h_v = hcnt + 6;
     if (b.defer_v) {
         b.V = ~0u;  // unknown until bucket_read_v
@@ -1553,10 +1932,13 @@ void bucket_accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         b.V = hcnt[6];
         finish_bytes(b, W);
     }
-    b.order = si[r];
-    b.cnt_sorted = cs;
-    b.off = co;
-    b.finals = finals;
+}
+
+template <int W>
+void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s, uint32_t *d_stat)
+{
+    accumulate<W>(b, ar, s, nullptr, nullptr, d_stat);
+    b.V = (uint32_t)std::min<size_t>(b.P, 0xFFFFFFFFu);  // a bound: the count is *dn_V
 }
 
 template <int W>
@@ -1565,9 +1947,9 @@ int bucket_collect(BucketArgs &b, hipStream_t s, Profiler *prof)
     if (b.nfinal == 0 || b.V == 0) return -1;
     // with the count still in flight the bytes are set once it is known
     ProfScope ps(prof, "collect", b.defer_v ? 0.0 : (8.0 * W + 8.0) * 2.0 * b.V, s);
-    k_collect<W><<<std::min<uint32_t>(b.nfinal, 65536u), 256, 0, s>>>((const Seg *)b.finals, b.nfinal, b.order, b.cnt_sorted, b.off, b.clo, b.chi, b.cnum,
-                                         b.cscore, b.pool_lo, b.pool_hi, b.pool_num, b.pool_score, b.pool_base,
-                                         b.pool_cap, nullptr);
+    k_collect<W><<<std::min<uint32_t>(b.ntile, 65536u), 256, 0, s>>>(b.mask, b.P, b.ntile, b.tcnt, b.off, b.clo, b.chi,
+                                                                     b.cnum, b.cscore, b.pool_lo, b.pool_hi,
+                                                                     b.pool_num, b.pool_score, b.pool_base, b.pool_cap);
     ASCI_LAUNCH_CHECK();
     return ps.tok;
 }
@@ -1581,20 +1963,36 @@ void bucket_read_v(BucketArgs &b, hipStream_t s)
     finish_bytes(b, b.n <= 32 ? 1 : 2);
 }
 
-// sum of N_a * A_a over the batch's candidates: per final segment in key
-// order (sequential inside a segment), then a fixed-order tree over segments
-__global__ __launch_bounds__(256) void k_pt2_segments(const Seg *__restrict__ finals, uint32_t nf,
-                                                      const uint32_t *__restrict__ order,
-                                                      const uint32_t *__restrict__ cnt_sorted,
-                                                      const double *__restrict__ cnum,
-                                                      const double *__restrict__ cscore, double *__restrict__ part)
+// sum of N_a * A_a over the batch's candidates: per tile of slots (each lane
+// its marked slots in order, then a fixed tree), then a fixed-order tree over
+// the tiles
+__global__ __launch_bounds__(256) void k_pt2_tiles(const unsigned long long *__restrict__ mask, size_t P,
+                                                   uint32_t ntile, const uint32_t *__restrict__ tcnt,
+                                                   const double *__restrict__ cnum,
+                                                   const double *__restrict__ cscore, double *__restrict__ part)
 {
-    const uint32_t j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= nf) return;
-    const Seg sg = finals[order[j]];
-    double e = 0.0;
-    for (uint32_t t = 0; t < cnt_sorted[j]; ++t) e = e + cnum[sg.start + t] * cscore[sg.start + t];
-    part[j] = e;
+    __shared__ double sh[256];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (uint32_t t = blockIdx.x; t < ntile; t += gridDim.x) {
+        double e = 0.0;
+        if (tcnt[t]) {
+            const size_t s0 = (size_t)t * kSlotTile;
+            for (uint32_t i = (uint32_t)wv; i < kSlotTile / 64; i += 4) {
+                if (s0 + (size_t)i * 64 >= P) break;
+                const unsigned long long m = mask[s0 / 64 + i];
+                const size_t s = s0 + (size_t)i * 64 + (uint32_t)lane;
+                if ((m >> lane) & 1ull) e = e + cnum[s] * cscore[s];
+            }
+        }
+        __syncthreads();
+        sh[threadIdx.x] = e;
+        __syncthreads();
+        for (int w = 128; w >= 1; w >>= 1) {
+            if ((int)threadIdx.x < w) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) part[t] = sh[0];
+    }
 }
 
 __global__ __launch_bounds__(1024) void k_sum_fixed(const double *__restrict__ x, uint32_t n, double *__restrict__ out)
@@ -1614,12 +2012,11 @@ __global__ __launch_bounds__(1024) void k_sum_fixed(const double *__restrict__ x
 double bucket_pt2(BucketArgs &b, Arena &ar, hipStream_t s, HostStage &hs)
 {
     if (b.nfinal == 0) return 0.0;
-    double *part = ar.take<double>(b.nfinal);
+    double *part = ar.take<double>(b.ntile);
     double *tot = ar.take<double>(1);
-    k_pt2_segments<<<(b.nfinal + 255) / 256, 256, 0, s>>>((const Seg *)b.finals, b.nfinal, b.order, b.cnt_sorted,
-                                                          b.cnum, b.cscore, part);
+    k_pt2_tiles<<<std::min<uint32_t>(b.ntile, 65536u), 256, 0, s>>>(b.mask, b.P, b.ntile, b.tcnt, b.cnum, b.cscore, part);
     ASCI_LAUNCH_CHECK();
-    k_sum_fixed<<<1, 1024, 0, s>>>(part, b.nfinal, tot);
+    k_sum_fixed<<<1, 1024, 0, s>>>(part, b.ntile, tot);
     ASCI_LAUNCH_CHECK();
     double *h = (double *)((char *)hs.ptr + 128);
     ASCI_HIP(hipMemcpyAsync(h, tot, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1627,170 +2024,13 @@ double bucket_pt2(BucketArgs &b, Arena &ar, hipStream_t s, HostStage &hs)
     return *h;
 }
 
-// ---------------------------------------------------------------- device-driven variant
-constexpr int kDevLevels = 8;  // split levels run when no count is read back
-
-__global__ __launch_bounds__(64) void k_times256(const uint32_t *__restrict__ n, uint32_t *__restrict__ out)
-{
-    if (threadIdx.x == 0) *out = *n * 256u;
-}
-
-// after the last level: segments still too large for the finish, or a list
-// that overflowed its capacity, fail the call
-__global__ __launch_bounds__(64) void k_levels_done(const uint32_t *__restrict__ ctr, int last_parity,
-                                                    uint32_t *__restrict__ stat)
-{
-    if (threadIdx.x != 0) return;
-    if (ctr[1 + last_parity] != 0u || ctr[3] != 0u) atomicOr(stat, kStatSplit);
-}
-
-template <int W>
-void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s, uint32_t *d_stat)
-{
-    const int CAP = b.finish_cap >= 4096 ? 4096 : (b.finish_cap >= 2048 ? 2048 : 1024);
-    const size_t P = b.P;
-    const uint32_t finals_cap = (uint32_t)std::min<size_t>(b.nc + P / 8 + 65536, 0xFFFFFFF0u);
-    const uint32_t level_cap = (uint32_t)(P / CAP + b.nc + 16);
-    const uint32_t max_tiles = (uint32_t)((P + kTileN - 1) / kTileN + level_cap);
-    Seg *finals = ar.take<Seg>(finals_cap);
-    Seg *lv[2] = {ar.take<Seg>(level_cap), ar.take<Seg>(level_cap)};
-    uint32_t *ctr = ar.take<uint32_t>(8);  // 0: finals, 1/2: large segments per level parity, 3: overflow
-    require(b.nc <= kMaxClassSegs, ASCI_EINVAL, "too many classes in one batch");
-    fill_u32(ctr, 8, 0u, s);
-    k_class_segs<<<1, 256, 0, s>>>(b.cls, b.c0, b.nc, b.nq, b.offsets, b.total, b.n, (uint32_t)CAP, lv[0], ctr + 1,
-                                   finals, ctr, (uint32_t)std::min<size_t>(P, 0xFFFFFFFFu));
-    ASCI_LAUNCH_CHECK();
-    uint8_t *dig = ar.take<uint8_t>(P + 1);
-    uint32_t *ntile = ar.take<uint32_t>((size_t)level_cap + 1);
-    uint32_t *tbase = ar.take<uint32_t>((size_t)level_cap + 1);
-    uint32_t *skip = ar.take<uint32_t>((size_t)level_cap + 1);
-    uint32_t *d_ntiles = ar.take<uint32_t>(4);
-    uint32_t *tseg = ar.take<uint32_t>((size_t)max_tiles + 1);
-    uint32_t *hist = ar.take<uint32_t>((size_t)max_tiles * 256 + 1);
-    uint32_t *hscan = ar.take<uint32_t>((size_t)max_tiles * 256 + 1);
-    uint64_t *spl_lo = ar.take<uint64_t>((size_t)level_cap * (kMaxSplit - 1));
-    uint64_t *spl_hi = W == 2 ? ar.take<uint64_t>((size_t)level_cap * (kMaxSplit - 1)) : nullptr;
-    unsigned long long *kvar = ar.take<unsigned long long>(2 * (size_t)level_cap);
-    // launch shapes: per-segment kernels stride over the level's segments, tile
-    // kernels over its tiles (eight XCD groups of workgroups)
-    const unsigned g_seg = std::min<uint32_t>(level_cap, 2048u);
-    const unsigned g_seg256 = std::min<uint32_t>((level_cap + 256) / 256, 1024u);
-    const unsigned g_tiles = 8u * std::min<uint32_t>((max_tiles + 7) / 8, 256u);
-    const size_t mark = ar.used();
-    const KeyBufs kb{{b.klo[0], b.klo[1]}, {b.khi[0], b.khi[1]}};
-    for (int lev = 0; lev < kDevLevels; ++lev) {
-        ar.reset();
-        (void)ar.take<char>(mark);
-        Seg *segs = lv[lev & 1], *next = lv[(lev & 1) ^ 1];
-        const uint32_t *dn_seg = ctr + 1 + (lev & 1);
-        uint32_t *nnext = ctr + 1 + ((lev & 1) ^ 1);
-        k_seg_tiles<<<g_seg256, 256, 0, s>>>(segs, level_cap, ntile, skip, nnext, dn_seg);
-        ASCI_LAUNCH_CHECK();
-        scan_u32(ntile, tbase, level_cap, d_ntiles, ar, s, nullptr, dn_seg);
-        k_seg_expand<<<g_seg256, 256, 0, s>>>(segs, level_cap, tbase, tseg, kvar, dn_seg);
-        ASCI_LAUNCH_CHECK();
-        if (lev == 0) k_seg_splitters<W, 1024><<<g_seg, 1024, 0, s>>>(segs, (uint32_t)CAP, kb, spl_lo, spl_hi, level_cap, dn_seg);
-        else k_seg_splitters<W, 256><<<g_seg, 256, 0, s>>>(segs, (uint32_t)CAP, kb, spl_lo, spl_hi, level_cap, dn_seg);
-        ASCI_LAUNCH_CHECK();
-        SplitArgs sa;
-        sa.segs = segs;
-        sa.nseg = level_cap;
-        sa.tile_base = tbase;
-        sa.tile_seg = tseg;
-        sa.ntiles = max_tiles;
-        sa.hist = hist;
-        sa.klo[0] = b.klo[0];
-        sa.klo[1] = b.klo[1];
-        sa.khi[0] = b.khi[0];
-        sa.khi[1] = b.khi[1];
-        sa.val[0] = b.val[0];
-        sa.val[1] = b.val[1];
-        sa.n = b.n;
-        sa.cap = (uint32_t)CAP;
-        sa.spl_lo = spl_lo;
-        sa.spl_hi = spl_hi;
-        sa.kvar = kvar;
-        sa.dig = dig;
-        sa.dn_seg = dn_seg;
-        sa.dn_tiles = d_ntiles;
-        k_split_hist<W><<<g_tiles, kHistT, 0, s>>>(sa);
-        ASCI_LAUNCH_CHECK();
-        k_times256<<<1, 64, 0, s>>>(d_ntiles, d_ntiles + 1);
-        ASCI_LAUNCH_CHECK();
-        scan_u32(hist, hscan, (size_t)max_tiles * 256, nullptr, ar, s, nullptr, d_ntiles + 1);
-        k_split_children<W><<<g_seg, 256, 0, s>>>(segs, level_cap, tbase, hscan, (uint32_t)CAP, skip, finals, ctr,
-                                                  finals_cap, next, nnext, level_cap, ctr + 3, kvar, b.n, dn_seg);
-        ASCI_LAUNCH_CHECK();
-        sa.hist = hscan;
-        k_split_scatter<W><<<g_tiles, kTileT, 0, s>>>(sa, hscan, skip);
-        ASCI_LAUNCH_CHECK();
-    }
-    k_levels_done<<<1, 64, 0, s>>>(ctr, kDevLevels & 1, d_stat);
-    ASCI_LAUNCH_CHECK();
-    ar.reset();
-    (void)ar.take<char>(mark);
-    uint32_t *cnt = ar.take<uint32_t>((size_t)finals_cap + 1);
-    FinishArgs fa;
-    fa.finals = finals;
-    fa.klo[0] = b.klo[0];
-    fa.klo[1] = b.klo[1];
-    fa.khi[0] = b.khi[0];
-    fa.khi[1] = b.khi[1];
-    fa.val[0] = b.val[0];
-    fa.val[1] = b.val[1];
-    fa.n = b.n;
-    fa.jk = b.jk;
-    fa.h = b.h;
-    fa.st = b.st;
-    fa.thr = nullptr;
-    fa.ecore = b.ecore;
-    fa.E0 = b.E0;
-    fa.eps = b.eps;
-    fa.clo = b.clo;
-    fa.chi = b.chi;
-    fa.cnum = b.cnum;
-    fa.cscore = b.cscore;
-    fa.cnt = cnt;
-    fa.nfinal = finals_cap;
-    fa.dn_final = ctr;
-    fa.psi = b.psi;
-    if (CAP == 4096) (void)launch_finish<W, 4096, 512>(fa, b, finals_cap, s, nullptr);
-    else if (CAP == 2048) (void)launch_finish<W, 2048, 256>(fa, b, finals_cap, s, nullptr);
-    else (void)launch_finish<W, 1024, 128>(fa, b, finals_cap, s, nullptr);
-    // candidates in key order: final segments by start, counts scanned
-    uint64_t *sk[2] = {ar.take<uint64_t>((size_t)finals_cap + 1), ar.take<uint64_t>((size_t)finals_cap + 1)};
-    uint32_t *si[2] = {ar.take<uint32_t>((size_t)finals_cap + 1), ar.take<uint32_t>((size_t)finals_cap + 1)};
-    uint32_t *cs = ar.take<uint32_t>((size_t)finals_cap + 1);
-    uint32_t *co = ar.take<uint32_t>((size_t)finals_cap + 1);
-    uint32_t *d_v = ar.take<uint32_t>(4);
-    uint64_t *nohi[2] = {nullptr, nullptr};
-    const unsigned gf = std::min<uint32_t>((finals_cap + 255) / 256, 65535u);
-    k_final_keys_start<<<(finals_cap + 255) / 256, 256, 0, s>>>(finals, finals_cap, sk[0], si[0], ctr);
-    ASCI_LAUNCH_CHECK();
-    std::vector<Digit> dg;
-    for (int sh = 0; sh < 32; sh += 8) dg.push_back({0, sh});
-    const int r = radix_sort<uint32_t>(sk, nohi, si, finals_cap, 1, dg, ar, s, nullptr, ctr);
-    k_gather_counts<<<(finals_cap + 255) / 256, 256, 0, s>>>(si[r], cnt, finals_cap, cs, ctr);
-    ASCI_LAUNCH_CHECK();
-    scan_u32(cs, co, finals_cap, d_v, ar, s, nullptr, ctr);
-    (void)gf;
-    b.nfinal = finals_cap;  // a bound: the count is *dn_final
-    b.dn_final = ctr;
-    b.dn_V = d_v;
-    b.V = (uint32_t)std::min<size_t>(P, 0xFFFFFFFFu);  // a bound: the count is *dn_V
-    b.order = si[r];
-    b.cnt_sorted = cs;
-    b.off = co;
-    b.finals = finals;
-}
-
 // the collect of the device-driven variant: counts read on the device
 template <int W>
 void bucket_collect_dev(BucketArgs &b, hipStream_t s)
 {
-    k_collect<W><<<std::min<uint32_t>(b.nfinal, 65536u), 256, 0, s>>>(
-        (const Seg *)b.finals, b.nfinal, b.order, b.cnt_sorted, b.off, b.clo, b.chi, b.cnum, b.cscore, b.pool_lo,
-        b.pool_hi, b.pool_num, b.pool_score, b.pool_base, b.pool_cap, b.dn_final);
+    k_collect<W><<<std::min<uint32_t>(b.ntile, 65536u), 256, 0, s>>>(b.mask, b.P, b.ntile, b.tcnt, b.off, b.clo, b.chi,
+                                                                     b.cnum, b.cscore, b.pool_lo, b.pool_hi,
+                                                                     b.pool_num, b.pool_score, b.pool_base, b.pool_cap);
     ASCI_LAUNCH_CHECK();
 }
 

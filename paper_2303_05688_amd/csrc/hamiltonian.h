@@ -279,52 +279,4 @@ __device__ __forceinline__ double spin_energy(const double *X, const double *hd,
     return spin_energy_m<uint64_t>(X, hd, n, s);
 }
 
-// E(alpha, beta) of the diagonal element: sum over q in beta of c_q(alpha)
-__device__ __forceinline__ double cross_energy(const double *J, int n, uint64_t a, uint64_t b)
-{
-    if (n <= 32) {
-        double cross = 0.0;
-        for (uint32_t m = (uint32_t)b; m; m &= m - 1) cross = cross + cross_col_m<uint32_t>(J, n, (uint32_t)a, tz(m));
-        return cross;
-    }
-    double cross = 0.0;
-    for (uint64_t m = b; m; m &= m - 1) cross = cross + cross_col_m<uint64_t>(J, n, a, tz(m));
-    return cross;
-}
-
-// combinatorial rank of a spin string: sum over its set bits p_1 < p_2 < ...
-// of C(p_j, j), with binom[k * (n + 1) + p] = C(p, k)
-// (four table loads in flight at a time; integer sums need no order)
-template <typename M>
-__device__ __forceinline__ uint32_t spin_rank_m(const uint32_t *binom, int n, M m)
-{
-    uint32_t r = 0;
-    const uint32_t *row = binom + (n + 1);
-    while (m) {
-        // unconditional loads (a spare slot reads C(0, k) and adds nothing)
-        uint32_t v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool ok = m != 0;
-            v[k] = row[k * (n + 1) + (ok ? tz(m) : 0)] & (ok ? ~0u : 0u);
-            m &= m - 1;
-        }
-        r += (v[0] + v[1]) + (v[2] + v[3]);
-        row += 4 * (n + 1);
-    }
-    return r;
-}
-
-__device__ __forceinline__ uint32_t spin_rank(const uint32_t *binom, int n, uint64_t s)
-{
-    if (n <= 32) return spin_rank_m<uint32_t>(binom, n, (uint32_t)s);
-    return spin_rank_m<uint64_t>(binom, n, s);
-}
-
-__device__ __forceinline__ double cross_col(const double *J, int n, uint64_t a, int q)
-{
-    if (n <= 32) return cross_col_m<uint32_t>(J, n, (uint32_t)a, q);
-    return cross_col_m<uint64_t>(J, n, a, q);
-}
-
 }  // namespace asci

@@ -7,9 +7,10 @@
 //   generate: one wavefront per (class, core); each lane unranks its record
 //             index into an excitation, evaluates H_ai and writes
 //             (key, H_ai * C_i) at its offset
-//   sort    : stable LSD radix sort on the key (equal keys keep ascending core
-//             order, the summation order)
-//   reduce  : one thread per run of equal keys sums in record order, drops
+//   sort    : split into segments that one wavefront's LDS share holds, each
+//             sorted there (stable: equal keys keep ascending core order, the
+//             summation order)
+//   reduce  : one lane per run of equal keys sums in record order, drops
 //             input determinants, forms H_aa and A_a = N_a / (E0 - H_aa)
 //   append  : surviving candidates join a pool kept in ascending key order
 // then radix selection of the k largest |A_a| (ties: smaller key) and a final
@@ -914,9 +915,7 @@ static SpinTables build_spin_tables(asci_ctx *ctx, const SpinTablePlan &pl, cons
     ar.reset();
     ar.reserve(pl.bytes);
     ar.reset();
-    // rows 0..kmax, and three zero rows that the rank's unconditional loads may
-    // touch past the last electron
-    std::vector<uint32_t> hb((size_t)(pl.kmax + 4) * (n + 1), 0u);
+    std::vector<uint32_t> hb((size_t)(pl.kmax + 1) * (n + 1), 0u);
     for (int k = 0; k <= pl.kmax; ++k)
         for (int p = 0; p <= n; ++p)
             hb[(size_t)k * (n + 1) + p] = (uint32_t)std::min<uint64_t>(binom_sat(p, k), UINT32_MAX);
@@ -930,6 +929,7 @@ static SpinTables build_spin_tables(asci_ctx *ctx, const SpinTablePlan &pl, cons
     const int ne[2] = {na, nb};
     for (int i = 0; i < 2; ++i) {
         if (pl.count[i] == 0) continue;
+        st.last[i] = (uint32_t)(pl.count[i] - 1);
         if (i == 1 && pl.share) {
             st.e[1] = st.e[0];
             continue;
@@ -1389,11 +1389,11 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
         // steps 6-9: bucket sort-and-accumulate, exclusion, diagonal, score
         BucketArgs ba;
         ba.P = P;
-        ba.c0 = c0;
         ba.nc = nc;
         ba.nq = (uint32_t)nq;
         ba.n = n;
-        ba.cls = pp.d_cls;
+        ba.na = in.na;
+        ba.nb = in.nb;
         ba.offsets = offs;
         ba.total = d_cnt + 2;
         ba.klo[0] = k_lo[0];
@@ -1404,7 +1404,6 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
         ba.val[1] = v[1];
         ba.psi = pp.psi;
         ba.jk = pp.d_jk;
-        ba.h = in.h;
         ba.st = st;
         ba.thr = topk ? d_thr : nullptr;
         ba.ecore = in.opt.ecore;
@@ -1693,14 +1692,15 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     // ---- spin-string tables (binomials built on the device)
     SpinTables st;
     if (pl.bytes) {
-        uint32_t *d_binom = ar.take<uint32_t>((size_t)(pl.kmax + 4) * (n + 1));
-        k_binom_table<<<1, 64, 0, s>>>(d_binom, n, pl.kmax, pl.kmax + 4);
+        uint32_t *d_binom = ar.take<uint32_t>((size_t)(pl.kmax + 1) * (n + 1));
+        k_binom_table<<<1, 64, 0, s>>>(d_binom, n, pl.kmax, pl.kmax + 1);
         ASCI_LAUNCH_CHECK();
         st.binom = d_binom;
         st.kmax = pl.kmax;
         const int ne[2] = {na, nb};
         for (int i = 0; i < 2; ++i) {
             if (pl.count[i] == 0) continue;
+            st.last[i] = (uint32_t)(pl.count[i] - 1);
             if (i == 1 && pl.share) {
                 st.e[1] = st.e[0];
                 continue;
@@ -1775,11 +1775,11 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     // ---- sort and accumulate, exclusion, diagonal and score (device-driven)
     BucketArgs ba;
     ba.P = Pb;
-    ba.c0 = 0;
     ba.nc = (uint32_t)ncls;
     ba.nq = (uint32_t)nq;
     ba.n = n;
-    ba.cls = d_cls;
+    ba.na = na;
+    ba.nb = nb;
     ba.offsets = offs;
     ba.total = d_cnt + 2;
     ba.klo[0] = k_lo[0];
@@ -1790,7 +1790,6 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     ba.val[1] = v[1];
     ba.psi = psi;
     ba.jk = d_jk;
-    ba.h = in.h;
     ba.st = st;
     ba.thr = nullptr;
     ba.ecore = in.opt.ecore;
