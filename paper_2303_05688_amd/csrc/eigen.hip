@@ -6,8 +6,7 @@
 // H: rows in the order of the determinant set, columns ascending, both
 // triangles and the diagonal stored.  Matrix elements use the same
 // Slater-Condon routines (and the same operation order) as the search.
-#include "asci_internal.h"
-#include "hamiltonian.h"
+#include "pairs.h"
 
 #include <cmath>
 #include <cstring>
@@ -16,114 +15,15 @@ namespace asci {
 
 namespace {
 
-constexpr int kHBlock = 256;      // 4 wavefronts
-constexpr int kHRows = 4;         // rows per wavefront
-constexpr int kHTile = 2048;      // column determinants staged in LDS per tile
-constexpr int kChunk = 4096;      // rows per chunk of the row-pointer scan
+constexpr int kChunk = 4096;      // counts per chunk of the row-pointer scan
 
-// J_pq = (pp|qq), X_pq = (pp|qq) - (pq|qp), h_pp: the tables of H_aa
-__global__ __launch_bounds__(kHBlock) void k_hm_table(const double *__restrict__ eri, const double *__restrict__ h,
-                                                      int n, double *__restrict__ jk)
-{
-    const int t = blockIdx.x * kHBlock + threadIdx.x;
-    if (t >= n * n) return;
-    const int p = t / n, q = t % n;
-    jk[t] = eri4(eri, n, p, p, q, q);
-    jk[n * n + t] = eri4(eri, n, p, p, q, q) - eri4(eri, n, p, q, q, p);
-    if (q == 0) jk[2 * n * n + p] = h[(size_t)p * n + p];
-}
-
-// <a|H|i> for determinants a = (aa, ab) and i = (ia, ib) that differ by at
-// most a double excitation: the excitation is read from i to a
-__device__ __forceinline__ double helem_value(const double *__restrict__ h, const double *__restrict__ eri,
-                                              const double *jk, int n, double ecore, uint64_t aa, uint64_t ab,
-                                              uint64_t ia, uint64_t ib)
-{
-    const int ea = popc64(aa ^ ia) >> 1, eb = popc64(ab ^ ib) >> 1;
-    if (ea + eb == 0) return diag_value(jk, jk + n * n, jk + 2 * n * n, n, ecore, aa, ab);
-    if (ea == 1 && eb == 0) return single_value(h, eri, n, ia, ib, lowbit(ia & ~aa), lowbit(aa & ~ia));
-    if (ea == 0 && eb == 1) return single_value(h, eri, n, ib, ia, lowbit(ib & ~ab), lowbit(ab & ~ib));
-    if (ea == 1 && eb == 1)
-        return double_opp_value(eri, n, ia, ib, lowbit(ia & ~aa), lowbit(aa & ~ia), lowbit(ib & ~ab),
-                                lowbit(ab & ~ib));
-    if (ea == 2) return double_same_value(eri, n, ia, ia & ~aa, aa & ~ia);
-    return double_same_value(eri, n, ib, ib & ~ab, ab & ~ib);
-}
-
-struct HBuildArgs {
-    const uint64_t *dets;
-    uint32_t nd;
-    int n;
-    double ecore;
-    const double *h, *eri, *jk;
-    uint32_t *rowcnt;        // count pass: nonzeros per row
-    const int64_t *rowptr;   // fill pass
-    int32_t *cols;
-    double *vals, *diag;
-};
-
-// The double loop: every wavefront owns kHRows rows and tests them against all
-// determinants, staged tile by tile in LDS; a pair is coupled when the two
-// strings differ in at most four spin orbitals.  The count pass stores the
-// number of couplings per row; the fill pass writes them in ascending column
-// order (ballot + prefix count inside each 64-column chunk).
-template <bool FILL>
-__global__ __launch_bounds__(kHBlock) void k_hbuild(HBuildArgs g)
-{
-    __shared__ uint64_t ta[kHTile], tb[kHTile];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint64_t lt = (1ull << lane) - 1ull;
-    const uint32_t row0 = (blockIdx.x * (kHBlock / 64) + wv) * kHRows;
-    uint64_t ra[kHRows], rb[kHRows];
-    int64_t run[kHRows];
-#pragma unroll
-    for (int t = 0; t < kHRows; ++t) {
-        const bool ok = row0 + t < g.nd;
-        ra[t] = ok ? g.dets[2 * (size_t)(row0 + t)] : 0ull;
-        rb[t] = ok ? g.dets[2 * (size_t)(row0 + t) + 1] : 0ull;
-        run[t] = (FILL && ok) ? g.rowptr[row0 + t] : 0;
-    }
-    for (uint32_t j0 = 0; j0 < g.nd; j0 += kHTile) {
-        const uint32_t tn = min((uint32_t)kHTile, g.nd - j0);
-        __syncthreads();
-        for (uint32_t k = threadIdx.x; k < tn; k += kHBlock) {
-            ta[k] = g.dets[2 * (size_t)(j0 + k)];
-            tb[k] = g.dets[2 * (size_t)(j0 + k) + 1];
-        }
-        __syncthreads();
-        for (uint32_t c = 0; c < tn; c += 64) {
-            const uint32_t jl = c + lane;
-            const bool in = jl < tn;
-            const uint64_t ca = in ? ta[jl] : 0ull, cb = in ? tb[jl] : 0ull;
-#pragma unroll
-            for (int t = 0; t < kHRows; ++t) {
-                if (row0 + t >= g.nd) break;  // the same for the whole wavefront
-                const bool hit = in && (popc64(ra[t] ^ ca) + popc64(rb[t] ^ cb)) <= 4;
-                const uint64_t m = __ballot(hit);
-                if (FILL && hit) {
-                    const int64_t pos = run[t] + (int64_t)__popcll(m & lt);
-                    const double v = helem_value(g.h, g.eri, g.jk, g.n, g.ecore, ra[t], rb[t], ca, cb);
-                    g.cols[pos] = (int32_t)(j0 + jl);
-                    g.vals[pos] = v;
-                    if (j0 + jl == row0 + t) g.diag[row0 + t] = v;
-                }
-                run[t] += (int64_t)__popcll(m);
-            }
-        }
-    }
-    if (!FILL && lane == 0) {
-#pragma unroll
-        for (int t = 0; t < kHRows; ++t)
-            if (row0 + t < g.nd) g.rowcnt[row0 + t] = (uint32_t)run[t];
-    }
-}
-
-// 64-bit exclusive scan of the row counts, chunk by chunk
-__global__ __launch_bounds__(256) void k_chunk_sums(const uint32_t *__restrict__ cnt, uint32_t n,
+// 64-bit exclusive scan of the counts by row and share, chunk by chunk; a
+// row starts with its first share
+__global__ __launch_bounds__(256) void k_chunk_sums(const uint32_t *__restrict__ cnt, size_t n,
                                                     unsigned long long *__restrict__ sums)
 {
     __shared__ unsigned long long s[256];
-    const uint32_t base = blockIdx.x * kChunk;
+    const size_t base = (size_t)blockIdx.x * kChunk;
     unsigned long long acc = 0;
     for (uint32_t i = threadIdx.x; i < kChunk && base + i < n; i += 256) acc += cnt[base + i];
     s[threadIdx.x] = acc;
@@ -135,13 +35,13 @@ __global__ __launch_bounds__(256) void k_chunk_sums(const uint32_t *__restrict__
     if (threadIdx.x == 0) sums[blockIdx.x] = s[0];
 }
 
-__global__ __launch_bounds__(256) void k_chunk_scan(const uint32_t *__restrict__ cnt, uint32_t n,
+__global__ __launch_bounds__(256) void k_chunk_scan(const uint32_t *__restrict__ cnt, size_t n, uint32_t shares,
                                                     const unsigned long long *__restrict__ base,
-                                                    int64_t *__restrict__ rowptr)
+                                                    int64_t *__restrict__ start, int64_t *__restrict__ rowptr)
 {
     constexpr int per = kChunk / 256;
     __shared__ unsigned long long s[256];
-    const uint32_t c0 = blockIdx.x * kChunk + threadIdx.x * per;
+    const size_t c0 = (size_t)blockIdx.x * kChunk + threadIdx.x * per;
     uint32_t v[per];
     unsigned long long tot = 0;
 #pragma unroll
@@ -161,7 +61,10 @@ __global__ __launch_bounds__(256) void k_chunk_scan(const uint32_t *__restrict__
     unsigned long long run = base[blockIdx.x] + s[threadIdx.x] - tot;
 #pragma unroll
     for (int k = 0; k < per; ++k) {
-        if (c0 + k < n) rowptr[c0 + k] = (int64_t)run;
+        if (c0 + k < n) {
+            start[c0 + k] = (int64_t)run;
+            if ((c0 + k) % shares == 0) rowptr[(c0 + k) / shares] = (int64_t)run;
+        }
         run += v[k];
     }
 }
@@ -350,43 +253,40 @@ void hmat_build(asci_ctx *ctx, const double *h, const double *eri, int n, int na
     H.release();
     H.device = ctx->device;
     const uint32_t nd = (uint32_t)ndets;
-    const uint32_t nchunks = (nd + kChunk - 1) / kChunk;
+    // couplings are counted and placed by row and column share
+    const uint32_t shares = pair_shares(nd);
+    const size_t ncnt = (size_t)nd * shares;
+    const uint32_t nchunks = (uint32_t)((ncnt + kChunk - 1) / kChunk);
     Arena &ar = ctx->main;
     ar.reset();
-    ar.reserve((size_t)(2 * n * n + n) * 8 + (size_t)nd * 4 + (size_t)nchunks * 8 + 4096);
+    ar.reserve((size_t)(2 * n * n + n) * 8 + ncnt * 12 + (size_t)nchunks * 8 + 4096);
     ar.reset();
     double *jk = ar.take<double>((size_t)2 * n * n + n);
-    uint32_t *cnt = ar.take<uint32_t>(nd);
+    uint32_t *cnt = ar.take<uint32_t>(ncnt);
+    int64_t *start = ar.take<int64_t>(ncnt);
     unsigned long long *csum = ar.take<unsigned long long>(nchunks);
     ASCI_HIP(hipMalloc((void **)&H.rowptr, ((size_t)nd + 1) * sizeof(int64_t)));
     ASCI_HIP(hipMalloc((void **)&H.diag, (size_t)nd * sizeof(double)));
     fault_clear(s);
-    k_hm_table<<<(unsigned)((n * n + kHBlock - 1) / kHBlock), kHBlock, 0, s>>>(eri, h, n, jk);
-    ASCI_LAUNCH_CHECK();
+    pair_prepare(h, eri, n, dets, nd, ecore, jk, H.diag, s);
 
-    HBuildArgs g;
+    PairArgs g{};
     g.dets = dets;
     g.nd = nd;
     g.n = n;
-    g.ecore = ecore;
     g.h = h;
     g.eri = eri;
-    g.jk = jk;
-    g.rowcnt = cnt;
-    g.rowptr = H.rowptr;
-    g.cols = nullptr;
-    g.vals = nullptr;
-    g.diag = H.diag;
-    const unsigned grid = (unsigned)((nd + (kHBlock / 64) * kHRows - 1) / ((kHBlock / 64) * kHRows));
+    g.hdiag = H.diag;
+    g.cnt = cnt;
+    g.start = start;
     Profiler *prof = &ctx->prof;
     {
         ProfScope ps(prof, "hbuild_count", 0.0, s);
-        k_hbuild<false><<<grid, kHBlock, 0, s>>>(g);
-        ASCI_LAUNCH_CHECK();
+        launch_pairs<kPairCount>(g, s);
     }
-    k_chunk_sums<<<nchunks, 256, 0, s>>>(cnt, nd, csum);
+    k_chunk_sums<<<nchunks, 256, 0, s>>>(cnt, ncnt, csum);
     ASCI_LAUNCH_CHECK();
-    // chunk bases on the host (one value per 4096 rows)
+    // chunk bases on the host (one value per 4096 counts)
     std::vector<unsigned long long> hb(nchunks);
     ASCI_HIP(hipMemcpyAsync(hb.data(), csum, nchunks * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
     ASCI_HIP(hipStreamSynchronize(s));
@@ -397,7 +297,7 @@ void hmat_build(asci_ctx *ctx, const double *h, const double *eri, int n, int na
         tot += v;
     }
     ASCI_HIP(hipMemcpyAsync(csum, hb.data(), nchunks * sizeof(unsigned long long), hipMemcpyHostToDevice, s));
-    k_chunk_scan<<<nchunks, 256, 0, s>>>(cnt, nd, csum, H.rowptr);
+    k_chunk_scan<<<nchunks, 256, 0, s>>>(cnt, ncnt, shares, csum, start, H.rowptr);
     ASCI_LAUNCH_CHECK();
     const int64_t nnz = (int64_t)tot;
     ASCI_HIP(hipMemcpyAsync(H.rowptr + nd, &nnz, sizeof(int64_t), hipMemcpyHostToDevice, s));
@@ -407,8 +307,7 @@ void hmat_build(asci_ctx *ctx, const double *h, const double *eri, int n, int na
     g.vals = H.vals;
     {
         ProfScope ps(prof, "hbuild_fill", 12.0 * (double)nnz, s);
-        k_hbuild<true><<<grid, kHBlock, 0, s>>>(g);
-        ASCI_LAUNCH_CHECK();
+        launch_pairs<kPairFill>(g, s);
     }
     HostStage &hst = ctx->stage;
     hst.reserve(256);
