@@ -4,10 +4,12 @@
 // (exclusive or and popcount); the pairs that pass, a few in a thousand, go to
 // a queue of the wavefront and are evaluated 64 at a time, so that every lane
 // has an element to form.  Evaluated where they were found, a test's few hits
-// left most lanes idle for the length of an element: 20,000 determinants of
-// (16e,20o) took 2.86 ms to fill and 0.26 ms to test (count), now @FILL@ ms and
-// @COUNT@; the energy of 10,000 took 21.3 ms, now @ENERGY@.  Singles, whose
-// elements are sums over the occupied orbitals, have a queue of their own.
+// left most lanes idle for the length of an element.  20,000 determinants of
+// (16e,20o) took 0.26 ms to test (count) and 2.86 ms to fill, now 0.12 and 0.33
+// ms; the energy of 10,000 took 21.3 ms on 40 workgroups of one row a thread,
+// now 0.077 ms.  Bound by the latency of the elements' scattered reads.
+// Singles, whose elements are sums over the occupied orbitals, have a queue of
+// their own.
 #pragma once
 
 #include "hamiltonian.h"
@@ -174,8 +176,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs g)
 
 // Rows per wavefront: eight share each column read, but a set of less than
 // 131,072 determinants then has fewer than 16 wavefronts a CU to hide the
-// elements' reads behind (H of 20,000 filled in 1.35 ms with eight rows, @TWO@
-// with two).
+// elements' reads behind (H of 20,000 filled in 1.35 ms with eight rows, 0.51
+// ms with two).
 inline int pair_rows(uint32_t nd) { return nd >= 131072u ? 8 : (nd >= 65536u ? 4 : 2); }
 inline unsigned pair_blocks(uint32_t nd)
 {
@@ -185,7 +187,7 @@ inline unsigned pair_blocks(uint32_t nd)
 
 // Column shares of a row: the reference and the singles couple to most of a set,
 // so that the wavefront with their rows would run long after the others
-// (energy of 10,000 determinants 0.28 ms in one share, @SHARES@ in ten).
+// (energy of 10,000 determinants 0.28 ms in one share, 0.077 ms in ten).
 inline uint32_t pair_shares(uint32_t nd)
 {
     return std::max(1u, std::min((nd + kPairTile - 1) / kPairTile, 16384u / pair_blocks(nd)));
@@ -224,9 +226,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_table(const double *__restr
 }
 
 // H_ii of every determinant, the tables in LDS.  A diagonal element is a sum
-// over all its orbital pairs, read one after the other: formed in the pair
-// sweep by the one lane that met it, it held 63 others for that long (energy
-// of 10,000 determinants of (16e,20o): 0.29 ms, @DIAG@ with this kernel).
+// over all its orbital pairs, read one after the other: in the pair sweep it
+// would hold the 63 other lanes of its queue's turn for that long.
 __global__ __launch_bounds__(64) void k_pair_diag(const uint64_t *__restrict__ dets, uint32_t nd,
                                                   const double *__restrict__ jk, int n, double ecore,
                                                   double *__restrict__ out)
