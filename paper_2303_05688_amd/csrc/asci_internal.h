@@ -63,6 +63,7 @@ class Arena {
     }
     size_t used() const { return used_; }
     size_t capacity() const { return cap_; }
+    bool fixed() const { return fixed_; }
     void release();
 
   private:
@@ -274,18 +275,14 @@ void scan_u32(const uint32_t *in, uint32_t *out, size_t n, uint32_t *d_total, Ar
 __global__ void k_fill_u32(uint32_t *p, uint32_t n, uint32_t v);
 void fill_u32(uint32_t *p, size_t n, uint32_t v, hipStream_t s);
 
-// stable LSD radix sort by selected 8-bit digits of a 1- or 2-word key, with a
-// payload.  keys_lo/keys_hi/vals are ping-pong pairs; `digits` lists (word,
-// shift) from least significant.  Returns the index (0/1) of the buffer that
-// holds the result.
-struct Digit {
-    int word;   // 0 = lo word, 1 = hi word
-    int shift;  // bit offset of the 8-bit digit
-};
-template <typename V>
-int radix_sort(uint64_t *keys_lo[2], uint64_t *keys_hi[2], V *vals[2], size_t n, int words,
-               const std::vector<Digit> &digits, Arena &ar, hipStream_t s, Profiler *prof = nullptr,
-               const uint32_t *dn = nullptr);
+// Stable sort by keys of KW words, the first the most significant (ties keep
+// their position): keys[i] and vals are ping-pong pairs, the keys' input in [0];
+// vals becomes the sorted positions.  score (KW = 1): the keys are ~|score|,
+// and keys[0][0] need not be set.  Returns the index (0/1) of the buffers that
+// hold the result.
+template <int KW>
+int merge_sort(uint64_t *(*keys)[2], uint32_t *vals[2], const double *score, size_t n, hipStream_t s,
+               Profiler *prof = nullptr, const uint32_t *dn = nullptr);
 
 // radix selection on the IEEE bit pattern of |score[j]|, j < n: finds t, the
 // k-th largest value (1 <= k <= n), and how many entries equal to t must be
@@ -295,17 +292,17 @@ struct SelectState {
     uint64_t prefix;
     uint64_t mask;
     uint64_t krem;  // after the passes: number of entries equal to t to take
-    uint32_t hist[256];
+    uint32_t done;  // workgroups of the running pass that have finished
+    uint32_t hist[2048];
 };
 // optional workspace: after two digit passes the entries that still match the
 // selected prefix are copied to tmp (capacity n) and the remaining passes run
-// on the copy; d_count (device) and h_count (pinned host) hold its length
+// on the copy, whose length is *d_count
 struct SelectWork {
     double *tmp;
     unsigned int *d_count;
-    unsigned int *h_count;
 };
-// With dn (and dk: k = min(k, *dk), device) the compaction is skipped.
+// dk: k = min(k, *dk) (device)
 void radix_select_abs(const double *score, size_t n, uint64_t k, SelectState *d_state,
                       hipStream_t s, Profiler *prof = nullptr, const SelectWork *work = nullptr,
                       const uint32_t *dn = nullptr, const uint32_t *dk = nullptr);
@@ -419,7 +416,9 @@ struct BucketArgs {
     Profiler *prof = nullptr;       // the finish launch's profiler token, for its byte count
     int finish_tok = -1;
     // the device-driven variant: nfinal and V are then bounds, the count is on the device
-    const uint32_t *dn_V = nullptr;
+    const uint32_t *dn_V = nullptr, *dn_nfinal = nullptr;
+    const uint32_t *dn_levels = nullptr, *dn_nlarge = nullptr, *dn_overflow = nullptr;  // nonzero: not divided / a list overflowed
+    int dev_levels = 0, dev_rounds = 1;  // split levels and small-split rounds queued
     // where the candidates lie: a bit per slot, a count and an output offset per tile of slots
     unsigned long long *mask = nullptr;
     uint32_t *tcnt = nullptr, ntile = 0;
@@ -438,10 +437,10 @@ void bucket_read_v(BucketArgs &b, hipStream_t s);
 // sum over the batch's candidates of N_a * A_a (deterministic order)
 double bucket_pt2(BucketArgs &b, Arena &ar, hipStream_t s, HostStage &hs);
 // The same sort-and-accumulate with no count read back (asynchronous search):
-// launches sized for host bounds, a fixed number of split levels, the count in
-// b.dn_V.  A failure sets bits of *d_stat (kStat*).
+// launches sized for host bounds, b.dev_levels split levels, the counts in
+// b.dn_*.
 template <int W>
-void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s, uint32_t *d_stat);
+void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s);
 template <int W>
 void bucket_collect_dev(BucketArgs &b, hipStream_t s);
 // status bits of a search that reads nothing back
@@ -452,10 +451,9 @@ constexpr uint32_t kStatPool = 8u;       // candidate pool overflow
 constexpr uint32_t kStatFault = 16u;     // a kernel consistency fault (see hamiltonian.h)
 constexpr uint32_t kStatIntegrals = 32u; // two-electron integrals not 8-fold symmetric
 
-// the fault word of the bucket kernels (see hamiltonian.h): clear / queue a copy to pinned *dst
-void bucket_fault_clear(hipStream_t s);
-void bucket_fault_reset_dev(hipStream_t s);                          // by a kernel
-void bucket_fault_take_dev(uint32_t *stat, uint32_t bit, hipStream_t s);  // stat |= bit if set
+// the fault word of the bucket kernels (see hamiltonian.h): its device address
+// / queue a copy to pinned *dst
+uint32_t *bucket_fault_word();
 void bucket_fault_fetch(unsigned int *dst, hipStream_t s);
 
 // ---------------------------------------------------------------- search (search.hip)

@@ -263,13 +263,27 @@ __global__ __launch_bounds__(T) void k_seg_splitters(const Seg *__restrict__ seg
     }
 }
 
+// the segment of a tile: the last one that starts at or before it
+__device__ __forceinline__ uint32_t seg_of_tile(const uint32_t *tile_base, uint32_t ns, uint32_t t)
+{
+    uint32_t l = 0, r = ns;  // tile_base[l] <= t
+    while (r - l > 1u) {
+        const uint32_t m = (l + r) >> 1;
+        if (tile_base[m] <= t) l = m;
+        else r = m;
+    }
+    return l;
+}
+
 // One workgroup lays a level out: first tile and first histogram entry of
-// every large segment, the totals, cleared skip flags and next-level count.
+// every large segment, the totals, cleared skip flags and next-level count, and
+// (tile_seg given: few tiles) the segment of every tile.
 __global__ __launch_bounds__(1024) void k_level_plan(const Seg *__restrict__ segs, uint32_t nseg, uint32_t cap,
                                                      uint32_t *__restrict__ tile_base,
                                                      uint32_t *__restrict__ hist_base, uint32_t *__restrict__ skip,
                                                      uint32_t *__restrict__ lev, uint32_t *__restrict__ nnext,
-                                                     const uint32_t *dn_seg)
+                                                     uint32_t *__restrict__ tile_seg, const uint32_t *dn_seg,
+                                                     uint32_t *__restrict__ nlevels)
 {
     __shared__ uint32_t s_tmp[16];
     const uint32_t ns = dev_count(nseg, dn_seg);
@@ -307,24 +321,20 @@ __global__ __launch_bounds__(1024) void k_level_plan(const Seg *__restrict__ seg
         lev[0] = tiles;
         lev[1] = entries;
         *nnext = 0u;
+        if (nlevels && ns > 0u) ++*nlevels;
     }
+    if (!tile_seg) return;
+    __syncthreads();  // the block's own writes of tile_base
+    for (uint32_t t = threadIdx.x; t < tiles; t += 1024) tile_seg[t] = seg_of_tile(tile_base, ns, t);
 }
 
-// the segment of every tile: the last one that starts at or before it
 __global__ __launch_bounds__(256) void k_tile_seg(const uint32_t *__restrict__ tile_base, uint32_t nseg,
                                                   const uint32_t *__restrict__ lev, uint32_t *__restrict__ tile_seg,
                                                   const uint32_t *dn_seg)
 {
     const uint32_t ns = dev_count(nseg, dn_seg), nt = lev[0];
-    for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < nt; t += gridDim.x * 256) {
-        uint32_t l = 0, r = ns;  // tile_base[l] <= t
-        while (r - l > 1u) {
-            const uint32_t m = (l + r) >> 1;
-            if (tile_base[m] <= t) l = m;
-            else r = m;
-        }
-        tile_seg[t] = l;
-    }
+    for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < nt; t += gridDim.x * 256)
+        tile_seg[t] = seg_of_tile(tile_base, ns, t);
 }
 
 // Tiles of a level, XCD-contiguous: the tiles [x * per, (x + 1) * per) go to
@@ -1711,31 +1721,18 @@ static void finish_bytes(const BucketArgs &b, int W)
                                             (8.0 * W + 8.0 + (b.cnum ? 8.0 : 0.0)) * (double)b.V);
 }
 
-// Split levels run when no count is read back: three take the largest batch
-// (below 2^31 records) to ranges of one tile, one more isolates single keys,
-// one is spare; the last one takes what the small split could not divide.
-constexpr int kDevLevels = 5;
-
 // device counters of one batch
-enum { kCtrFinal = 0, kCtrLarge = 1 /* and 2: per level parity */, kCtrOverflow = 3, kCtrSmall = 4 /* and 5: per round */ };
+enum { kCtrFinal = 0, kCtrLarge = 1 /* and 2: per level parity */, kCtrOverflow = 3, kCtrSmall = 4 /* and 5: per round */,
+       kCtrLevels = 6 };
 
-// after the last level: segments still too large for the finish, or a list
-// that overflowed its capacity, fail the call
-__global__ __launch_bounds__(64) void k_levels_done(const uint32_t *__restrict__ ctr, int last_parity,
-                                                    uint32_t *__restrict__ stat)
-{
-    if (threadIdx.x != 0) return;
-    if (ctr[kCtrLarge + last_parity] != 0u || ctr[kCtrOverflow] != 0u) atomicOr(stat, kStatSplit);
-}
-
-// Split levels, finish, and the scan that places the candidates.  With d_stat
-// nothing is read back: a fixed number of levels runs on launch shapes sized
-// for bounds, and a failure sets bits of *d_stat; else the host reads the
-// number of large segments once per level and stops when none is left.
+// Split levels, finish, and the scan that places the candidates.  With dev
+// nothing is read back: b.dev_levels levels and b.dev_rounds small splits run
+// on launch shapes sized for bounds (the caller checks b.dn_nlarge and
+// b.dn_overflow); else the host reads the number of large segments once per
+// level and stops when none is left.
 template <int W>
-static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, HostStage *hs, uint32_t *d_stat)
+static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, HostStage *hs, bool dev)
 {
-    const bool dev = d_stat != nullptr;
     const uint32_t cap = (uint32_t)wave_cap(b.finish_cap);
     const size_t P = b.P;
     const uint32_t finals_cap = (uint32_t)std::min<size_t>(b.nc + P / 8 + 65536, 0xFFFFFFF0u);
@@ -1783,10 +1780,14 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         // tile kernels over its tiles (eight XCD groups of workgroups)
         const unsigned g_seg = dev ? std::min(nlarge, 2048u) : nlarge;
         const unsigned g_tiles = 8u * (dev ? std::min((ntiles + 7) / 8, 256u) : (ntiles + 7) / 8);
-        k_level_plan<<<1, 1024, 0, s>>>(segs, nlarge, cap, tbase, hbase, skip, lev_tot, lists.nnext, dn_seg);
+        const bool few = ntiles <= 8192;
+        k_level_plan<<<1, 1024, 0, s>>>(segs, nlarge, cap, tbase, hbase, skip, lev_tot, lists.nnext, few ? tseg : nullptr,
+                                        dn_seg, dev ? ctr + kCtrLevels : nullptr);
         ASCI_LAUNCH_CHECK();
-        k_tile_seg<<<std::min((ntiles + 255) / 256, 1024u), 256, 0, s>>>(tbase, nlarge, lev_tot, tseg, dn_seg);
-        ASCI_LAUNCH_CHECK();
+        if (!few) {
+            k_tile_seg<<<std::min((ntiles + 255) / 256, 1024u), 256, 0, s>>>(tbase, nlarge, lev_tot, tseg, dn_seg);
+            ASCI_LAUNCH_CHECK();
+        }
         {
             ProfScope ps(prof, "split_sample", 0.0, s);
             // class-sized segments of the first level sort up to 2048 samples:
@@ -1839,15 +1840,17 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         ASCI_LAUNCH_CHECK();
     };
     if (dev) {
-        for (int l = 0; l < kDevLevels; ++l) split_level(level_cap);
-        for (int round = 0; round < 2; ++round) {
-            // round 1 takes what the small split of round 0 left, from list lev & 1
-            lists.nsmall = ctr + kCtrSmall + (round ^ 1);
-            small_split(level_cap, ctr + kCtrSmall + round);
-            if (round == 0) split_level(level_cap);
+        for (int l = 0; l < b.dev_levels; ++l) split_level(level_cap);
+        for (int round = 0; round < b.dev_rounds; ++round) {
+            // the next round takes what the small split of this one left, from list lev & 1
+            lists.nsmall = ctr + kCtrSmall + ((round & 1) ^ 1);
+            small_split(level_cap, ctr + kCtrSmall + (round & 1));
+            if (round + 1 < b.dev_rounds) split_level(level_cap);
         }
-        k_levels_done<<<1, 64, 0, s>>>(ctr, lev & 1, d_stat);
-        ASCI_LAUNCH_CHECK();
+        // what is left in list lev & 1 fails the call
+        b.dn_nlarge = ctr + kCtrLarge + (lev & 1);
+        b.dn_overflow = ctr + kCtrOverflow;
+        b.dn_levels = ctr + kCtrLevels;
     } else {
         read_counts();
         for (int round = 0;; ++round) {
@@ -1916,12 +1919,13 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
     scan_u32(b.tcnt, off, ntile, d_v, ar, s, nullptr);
     b.off = off;
     b.dn_V = d_v;
+    b.dn_nfinal = ctr + kCtrFinal;
 }
 
 template <int W>
 void bucket_accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, HostStage &hs)
 {
-    accumulate<W>(b, ar, s, prof, &hs, nullptr);
+    accumulate<W>(b, ar, s, prof, &hs, false);
     uint32_t *hcnt = (uint32_t *)hs.ptr;
     ASCI_HIP(hipMemcpyAsync(hcnt + 6, b.dn_V, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     b.h_v = hcnt + 6;
@@ -1935,9 +1939,9 @@ void bucket_accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
 }
 
 template <int W>
-void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s, uint32_t *d_stat)
+void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s)
 {
-    accumulate<W>(b, ar, s, nullptr, nullptr, d_stat);
+    accumulate<W>(b, ar, s, nullptr, nullptr, true);
     b.V = (uint32_t)std::min<size_t>(b.P, 0xFFFFFFFFu);  // a bound: the count is *dn_V
 }
 
@@ -2034,22 +2038,12 @@ void bucket_collect_dev(BucketArgs &b, hipStream_t s)
     ASCI_LAUNCH_CHECK();
 }
 
-template void bucket_accumulate_dev<1>(BucketArgs &, Arena &, hipStream_t, uint32_t *);
-template void bucket_accumulate_dev<2>(BucketArgs &, Arena &, hipStream_t, uint32_t *);
+template void bucket_accumulate_dev<1>(BucketArgs &, Arena &, hipStream_t);
+template void bucket_accumulate_dev<2>(BucketArgs &, Arena &, hipStream_t);
 template void bucket_collect_dev<1>(BucketArgs &, hipStream_t);
 template void bucket_collect_dev<2>(BucketArgs &, hipStream_t);
 
-void bucket_fault_clear(hipStream_t s) { fault_clear(s); }
-void bucket_fault_reset_dev(hipStream_t s)
-{
-    k_fault_reset<<<1, 64, 0, s>>>();
-    ASCI_LAUNCH_CHECK();
-}
-void bucket_fault_take_dev(uint32_t *stat, uint32_t bit, hipStream_t s)
-{
-    k_fault_take<<<1, 64, 0, s>>>(stat, bit);
-    ASCI_LAUNCH_CHECK();
-}
+uint32_t *bucket_fault_word() { return fault_word(); }
 void bucket_fault_fetch(unsigned int *dst, hipStream_t s) { fault_fetch(dst, s); }
 
 template void bucket_accumulate<1>(BucketArgs &, Arena &, hipStream_t, Profiler *, HostStage &);

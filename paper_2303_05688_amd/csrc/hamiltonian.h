@@ -37,14 +37,15 @@ __device__ __forceinline__ int orb(int p, int n)
     return p;
 }
 
-// Host side: clear the word (queued on s), and queue its copy to pinned host
-// memory *dst (valid once s has been synchronised).
-static inline void fault_clear(hipStream_t s)
+// Host side: the word's device address; clear it (queued on s); queue its copy
+// to pinned host memory *dst (valid once s has been synchronised).
+static inline uint32_t *fault_word()
 {
     void *p = nullptr;
     ASCI_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(g_fault)));
-    ASCI_HIP(hipMemsetAsync(p, 0, sizeof(unsigned int), s));
+    return (uint32_t *)p;
 }
+static inline void fault_clear(hipStream_t s) { ASCI_HIP(hipMemsetAsync(fault_word(), 0, sizeof(unsigned int), s)); }
 
 static inline void fault_fetch(unsigned int *dst, hipStream_t s)
 {
@@ -52,20 +53,6 @@ static inline void fault_fetch(unsigned int *dst, hipStream_t s)
     ASCI_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(g_fault)));
     ASCI_HIP(hipMemcpyAsync(dst, p, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
 }
-
-// The same word handled on the device (no host readback): cleared by a kernel
-// (a fill that a captured graph replays correctly), and folded into a status
-// word at the end of a call.
-namespace {
-__global__ __launch_bounds__(64) void k_fault_reset()
-{
-    if (threadIdx.x == 0) atomicAnd(&g_fault, 0u);
-}
-__global__ __launch_bounds__(64) void k_fault_take(uint32_t *stat, uint32_t bit)
-{
-    if (threadIdx.x == 0 && atomicOr(&g_fault, 0u) != 0u) atomicOr(stat, bit);
-}
-}  // namespace
 
 // after the stream has been synchronised: fail on any recorded fault
 static inline void fault_check(unsigned int word, const char *where)

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kBlock) void k_union_keys(const uint64_t *__restric
                                                        uint32_t nd, const uint64_t *__restrict__ cand,
                                                        const double *__restrict__ cscore, uint32_t nc, int n,
                                                        uint64_t *__restrict__ klo, uint64_t *__restrict__ khi,
-                                                       uint64_t *__restrict__ ord, uint32_t *__restrict__ idx)
+                                                       uint64_t *__restrict__ ord)
 {
     const uint32_t j = blockIdx.x * kBlock + threadIdx.x;
     if (j >= nd + nc) return;
@@ -43,15 +43,6 @@ __global__ __launch_bounds__(kBlock) void k_union_keys(const uint64_t *__restric
         khi[j] = a;
     }
     ord[j] = ~abs_order(v);
-    idx[j] = j;
-}
-
-__global__ __launch_bounds__(kBlock) void k_gather_ord(const uint32_t *__restrict__ idx,
-                                                       const uint64_t *__restrict__ ord_by_index, uint32_t m,
-                                                       uint64_t *__restrict__ out)
-{
-    const uint32_t j = blockIdx.x * kBlock + threadIdx.x;
-    if (j < m) out[j] = ord_by_index[idx[j]];
 }
 
 // the first `take` entries of the sorted union: determinants and the guess
@@ -69,18 +60,6 @@ __global__ __launch_bounds__(kBlock) void k_take(const uint32_t *__restrict__ id
     out_dets[2 * (size_t)j + 1] = old ? dets[2 * (size_t)u + 1] : cand[2 * (size_t)(u - nd) + 1];
     guess[j] = old ? c[u] : 0.0;
     if (old) atomicAdd(kept, 1u);
-}
-
-std::vector<Digit> key_digits(int n, int W)
-{
-    std::vector<Digit> d;
-    if (W == 1) {
-        for (int sh = 0; sh < 2 * n; sh += 8) d.push_back({0, sh});
-    } else {
-        for (int sh = 0; sh < n; sh += 8) d.push_back({0, sh});
-        for (int sh = 0; sh < n; sh += 8) d.push_back({1, sh});
-    }
-    return d;
 }
 
 double ms_since(std::chrono::steady_clock::time_point t0)
@@ -117,29 +96,20 @@ int64_t select_next(asci_ctx *ctx, int n, const uint64_t *dets, const double *c,
     const size_t take = (size_t)std::min<int64_t>((int64_t)U, ntdets);
     Arena &ar = ctx->main;
     ar.reset();
-    const size_t nb = (U + kScanTile - 1) / kScanTile;
-    ar.reserve(U * (8 * 2 * W + 8 * 3 + 4 * 2) + 4 * (nb * 256 * 4 + (1 << 16)) + 64 * 256);
+    ar.reserve(U * (8 * 2 * (W + 1) + 4 * 2) + 64 * 256);
     ar.reset();
-    uint64_t *klo[2] = {ar.take<uint64_t>(U), ar.take<uint64_t>(U)};
-    uint64_t *khi[2] = {W == 2 ? ar.take<uint64_t>(U) : nullptr, W == 2 ? ar.take<uint64_t>(U) : nullptr};
-    uint64_t *ord_by_index = ar.take<uint64_t>(U);
-    uint64_t *ord[2] = {ar.take<uint64_t>(U), ar.take<uint64_t>(U)};
+    // (~|score|, key) words, most significant first: score descending, ties by key ascending
+    uint64_t *keys[W + 1][2];
+    for (auto &k : keys)
+        for (auto &b : k) b = ar.take<uint64_t>(U);
     uint32_t *idx[2] = {ar.take<uint32_t>(U), ar.take<uint32_t>(U)};
     unsigned int *d_kept = ar.take<unsigned int>(4);
-    k_union_keys<W><<<grid_for(U), kBlock, 0, s>>>(dets, c, (uint32_t)nd, cand, cscore, (uint32_t)nc, n, klo[0],
-                                                   khi[0], ord_by_index, idx[0]);
+    k_union_keys<W><<<grid_for(U), kBlock, 0, s>>>(dets, c, (uint32_t)nd, cand, cscore, (uint32_t)nc, n, keys[W][0],
+                                                   keys[W - 1][0], keys[0][0]);
     ASCI_LAUNCH_CHECK();
-    // stable: key ascending, then ~|score| ascending (score descending, ties by key)
-    const int r1 = radix_sort<uint32_t>(klo, khi, idx, U, W, key_digits(n, W), ar, s);
-    k_gather_ord<<<grid_for(U), kBlock, 0, s>>>(idx[r1], ord_by_index, (uint32_t)U, ord[0]);
-    ASCI_LAUNCH_CHECK();
-    uint32_t *idx2[2] = {idx[r1], idx[r1 ^ 1]};
-    uint64_t *nohi[2] = {nullptr, nullptr};
-    std::vector<Digit> od;
-    for (int sh = 0; sh < 64; sh += 8) od.push_back({0, sh});
-    const int r2 = radix_sort<uint32_t>(ord, nohi, idx2, U, 1, od, ar, s);
+    const int r = merge_sort<W + 1>(keys, idx, nullptr, U, s);
     ASCI_HIP(hipMemsetAsync(d_kept, 0, sizeof(unsigned int), s));
-    k_take<<<grid_for(take), kBlock, 0, s>>>(idx2[r2], (uint32_t)take, dets, c, (uint32_t)nd, cand, out_dets, guess,
+    k_take<<<grid_for(take), kBlock, 0, s>>>(idx[r], (uint32_t)take, dets, c, (uint32_t)nd, cand, out_dets, guess,
                                              d_kept);
     ASCI_LAUNCH_CHECK();
     HostStage &hs = ctx->stage;

@@ -1,7 +1,7 @@
-// Device primitives for the search: exclusive scan, stable LSD radix sort and
+// Device primitives for the search: exclusive scan, stable merge sort and
 // radix selection.  Written for 64-wide wavefronts (gfx950): ranking inside a
 // wave uses ballots, blocks are 256 threads (4 waves).
-#include <type_traits>
+#include <algorithm>
 #include "asci_internal.h"
 
 namespace asci {
@@ -92,28 +92,52 @@ __global__ __launch_bounds__(1024) void k_scan_partials(uint32_t *__restrict__ p
 }
 
 // short inputs (at most kScanSmall elements): one workgroup, one launch,
-// chunks of 4096 scanned in turn with a running carry
+// chunks of 16384 scanned in turn with a running carry, 16-byte loads (33,000
+// elements took 20 us in chunks of 4096 of single words: each chunk waits for
+// its loads)
 constexpr size_t kScanSmall = 65536;
 __global__ __launch_bounds__(1024) void k_scan_small(const uint32_t *in, uint32_t *out, uint32_t n,
                                                      uint32_t *__restrict__ d_total, const uint32_t *dn)
 {
     __shared__ uint32_t s_tmp[16];
     n = (uint32_t)dev_n(n, dn);
+    const bool aligned = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15u) == 0;
     uint32_t carry = 0;
-    for (uint32_t c0 = 0; c0 < n; c0 += 4096) {
-        const uint32_t j0 = c0 + threadIdx.x * 4u;
-        uint32_t v[4], sum = 0;
+    for (uint32_t c0 = 0; c0 < n; c0 += 1024u * kItems) {
+        const uint32_t j0 = c0 + threadIdx.x * (uint32_t)kItems;
+        const bool full = aligned && j0 + kItems <= n;
+        uint32_t v[kItems], sum = 0;
+        if (full) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[i] = j0 + i < n ? in[j0 + i] : 0u;
-            sum += v[i];
+            for (int i = 0; i < kItems / 4; ++i) {
+                const uint4 q = reinterpret_cast<const uint4 *>(in + j0)[i];
+                v[4 * i] = q.x;
+                v[4 * i + 1] = q.y;
+                v[4 * i + 2] = q.z;
+                v[4 * i + 3] = q.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kItems; ++i) v[i] = j0 + i < n ? in[j0 + i] : 0u;
         }
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) sum += v[i];
         uint32_t tot;
         uint32_t e = carry + block_excl_scan<16>(sum, s_tmp, tot);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (j0 + i < n) out[j0 + i] = e;
-            e += v[i];
+        for (int i = 0; i < kItems; ++i) {
+            const uint32_t x = v[i];
+            v[i] = e;
+            e += x;
+        }
+        if (full) {
+#pragma unroll
+            for (int i = 0; i < kItems / 4; ++i)
+                reinterpret_cast<uint4 *>(out + j0)[i] = make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kItems; ++i)
+                if (j0 + i < n) out[j0 + i] = v[i];
         }
         carry += tot;
     }
@@ -179,172 +203,253 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t *in, uint
     }
 }
 
-// ---------------------------------------------------------------- radix sort
-template <int W>
-__device__ __forceinline__ uint32_t digit_of(uint64_t lo, uint64_t hi, int word, int shift)
+// ---------------------------------------------------------------- merge sort
+// Keys of KW words, the first the most significant, ties by position (a stable
+// sort), a 32-bit payload: chunks sorted in LDS by a bitonic network, then four
+// runs at a time merged, every element finding its place by a binary search in
+// the three other runs.  One launch for the chunks, one more for each factor of
+// four, where a radix sort of 8-bit digits takes three launches a digit (the
+// 2000 scores of a small search took 24 launches, about 110 us, now two).
+constexpr int kSortT = 512;
+constexpr int kSortChunk = 1024;  // one pair a thread and stage: 17 us (a chunk of 4096 took 47)
+
+template <int KW>
+struct SortKeys {
+    uint64_t *w[KW];
+};
+
+template <int KW>
+__device__ __forceinline__ bool words_less(const uint64_t (&a)[KW], const uint64_t (&b)[KW])
 {
-    uint64_t k = (W == 2 && word == 1) ? hi : lo;
-    return (uint32_t)(k >> shift) & 0xFFu;
+#pragma unroll
+    for (int k = 0; k + 1 < KW; ++k)
+        if (a[k] != b[k]) return a[k] < b[k];
+    return a[KW - 1] < b[KW - 1];
 }
 
-// IT records per thread: a tile of kThreads * IT records per workgroup (small
-// sorts take small tiles, so that they still spread over the CUs)
-template <int W, int IT>
-__global__ __launch_bounds__(kThreads) void k_rs_hist(const uint64_t *__restrict__ klo,
-                                                      const uint64_t *__restrict__ khi, size_t n,
-                                                      int word, int shift,
-                                                      uint32_t *__restrict__ hist, uint32_t nblocks,
-                                                      const uint32_t *dn)
+// orders a wavefront's LDS accesses (see the stages that need no barrier)
+__device__ __forceinline__ void wave_order()
 {
-    constexpr int TILE = kThreads * IT;
-    n = dev_n(n, dn);
-    __shared__ uint32_t h[kWaves][256];
-    const int tid = threadIdx.x, w = tid >> 6;
-    for (int i = tid; i < kWaves * 256; i += kThreads) (&h[0][0])[i] = 0u;
-    __syncthreads();
-    const size_t base = (size_t)blockIdx.x * TILE;
-    for (int i = tid; i < TILE; i += kThreads) {
-        size_t j = base + i;
-        if (j < n) {
-            uint64_t lo = klo[j];
-            uint64_t hi = (W == 2) ? khi[j] : 0ull;
-            atomicAdd(&h[w][digit_of<W>(lo, hi, word, shift)], 1u);
-        }
-    }
-    __syncthreads();
-    uint32_t c = 0;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) c += h[i][tid];
-    hist[(size_t)tid * nblocks + blockIdx.x] = c;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Stable scatter of one tile.  Tile order is (wave, slot, lane), which is the
-// input index order, so equal digits keep their input order.
-template <int W, typename V, int IT>
-__global__ __launch_bounds__(kThreads) void k_rs_scatter(
-    const uint64_t *__restrict__ ilo, const uint64_t *__restrict__ ihi, const V *__restrict__ ival,
-    uint64_t *__restrict__ olo, uint64_t *__restrict__ ohi, V *__restrict__ oval, size_t n, int word,
-    int shift, const uint32_t *__restrict__ hist, uint32_t nblocks, const uint32_t *dn)
+// The payload is the position.  score: the key (of one word) is
+// ~|score|, so that ascending keys are descending |score|
+template <int KW>
+__global__ __launch_bounds__(kSortT) void k_sort_chunks(SortKeys<KW> in, const double *__restrict__ score,
+                                                        SortKeys<KW> out, uint32_t *__restrict__ oval, size_t n,
+                                                        const uint32_t *dn)
 {
-    constexpr int kTile = kThreads * IT, kItems = IT;
+    constexpr int CH = kSortChunk;
+    __shared__ uint64_t x[KW][CH];
+    __shared__ uint16_t ix[CH];
     n = dev_n(n, dn);
-    __shared__ uint64_t s_lo[kTile];
-    __shared__ uint64_t s_hi[W == 2 ? kTile : 1];
-    __shared__ V s_val[kTile];
-    __shared__ uint32_t s_wcnt[kWaves][256];
-    __shared__ uint32_t s_dbase[256];
-    __shared__ uint32_t s_gbase[256];
-    __shared__ uint32_t s_tmp[kWaves];
-
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const size_t tile0 = (size_t)blockIdx.x * kTile;
-    if (tile0 >= n) return;  // uniform: a tile past a device-side count
-    for (int i = tid; i < kWaves * 256; i += kThreads) (&s_wcnt[0][0])[i] = 0u;
-    __syncthreads();
-
-    uint64_t rlo[kItems], rhi[kItems];
-    V rv[kItems];
-    uint32_t rrank[kItems];
-    const uint64_t lt = (1ull << lane) - 1ull;
-    const size_t wbase = tile0 + (size_t)w * 64 * kItems;
+    const size_t base = (size_t)blockIdx.x * CH;
+    if (base >= n) return;  // uniform
+    const uint32_t m = (uint32_t)min(n - base, (size_t)CH);
+    uint32_t p = 2;
+    while (p < m) p <<= 1;
+    for (uint32_t i = threadIdx.x; i < p; i += kSortT) {
 #pragma unroll
-    for (int s = 0; s < kItems; ++s) {
-        size_t j = wbase + (size_t)s * 64 + lane;
-        bool valid = j < n;
-        rlo[s] = valid ? ilo[j] : 0ull;
-        rhi[s] = (W == 2 && valid) ? ihi[j] : 0ull;
-        rv[s] = valid ? ival[j] : V(0);
-        uint32_t d = digit_of<W>(rlo[s], rhi[s], word, shift);
-        const uint64_t peers = wave_match(d, valid, 8);
-        uint32_t before = s_wcnt[w][d];
-        rrank[s] = before + (uint32_t)__popcll(peers & lt);
-        if (valid && (peers & lt) == 0ull) s_wcnt[w][d] = before + (uint32_t)__popcll(peers);
+        for (int k = 0; k < KW; ++k)
+            x[k][i] = i < m ? (score ? ~abs_order(score[base + i]) : in.w[k][base + i]) : ~0ull;
+        ix[i] = (uint16_t)i;  // a pad's position is above every record's
     }
     __syncthreads();
-    {
-        const int d = tid;
-        uint32_t c0 = s_wcnt[0][d], c1 = s_wcnt[1][d], c2 = s_wcnt[2][d], c3 = s_wcnt[3][d];
-        s_wcnt[0][d] = 0u;
-        s_wcnt[1][d] = c0;
-        s_wcnt[2][d] = c0 + c1;
-        s_wcnt[3][d] = c0 + c1 + c2;
-        uint32_t tot;
-        s_dbase[d] = block_excl_scan<kWaves>(c0 + c1 + c2 + c3, s_tmp, tot);
-        s_gbase[d] = hist[(size_t)d * nblocks + blockIdx.x];
-    }
-    __syncthreads();
+    // pair t of a stage is (i, i + jj); up to jj = 64 a wavefront's pairs lie in
+    // its own 128 elements, so those stages need no barrier between them
+    for (uint32_t k2 = 2; k2 <= p; k2 <<= 1) {
+        for (uint32_t jj = k2 >> 1; jj > 0; jj >>= 1) {
+            for (uint32_t t = threadIdx.x; t < p / 2; t += kSortT) {
+                const uint32_t i = 2u * (t & ~(jj - 1u)) + (t & (jj - 1u)), o = i + jj;
+                uint64_t a[KW], b[KW];
 #pragma unroll
-    for (int s = 0; s < kItems; ++s) {
-        size_t j = wbase + (size_t)s * 64 + lane;
-        if (j < n) {
-            uint32_t d = digit_of<W>(rlo[s], rhi[s], word, shift);
-            uint32_t pos = min(s_dbase[d] + s_wcnt[w][d] + rrank[s], (uint32_t)kTile - 1u);
-            s_lo[pos] = rlo[s];
-            if (W == 2) s_hi[pos] = rhi[s];
-            s_val[pos] = rv[s];
+                for (int k = 0; k < KW; ++k) {
+                    a[k] = x[k][i];
+                    b[k] = x[k][o];
+                }
+                const uint16_t ia = ix[i], ib = ix[o];
+                const bool gt = words_less<KW>(b, a) || (!words_less<KW>(a, b) && ib < ia);
+                if (gt == ((i & k2) == 0u)) {
+#pragma unroll
+                    for (int k = 0; k < KW; ++k) {
+                        x[k][i] = b[k];
+                        x[k][o] = a[k];
+                    }
+                    ix[i] = ib;
+                    ix[o] = ia;
+                }
+            }
+            if (jj > 64u || (jj == 1u && k2 >= 128u)) __syncthreads();
+            else wave_order();
         }
     }
     __syncthreads();
-    const uint32_t tn = (uint32_t)((n - tile0) < (size_t)kTile ? (n - tile0) : (size_t)kTile);
-    for (uint32_t i = tid; i < tn; i += kThreads) {
-        uint64_t lo = s_lo[i];
-        uint64_t hi = (W == 2) ? s_hi[i] : 0ull;
-        uint32_t d = digit_of<W>(lo, hi, word, shift);
-        size_t g = (size_t)s_gbase[d] + (i - s_dbase[d]);
-        if (g < n) {
-            olo[g] = lo;
-            if (W == 2) ohi[g] = hi;
-            oval[g] = s_val[i];
+    for (uint32_t i = threadIdx.x; i < m; i += kSortT) {
+#pragma unroll
+        for (int k = 0; k < KW; ++k) out.w[k][base + i] = x[k][i];
+        oval[base + i] = (uint32_t)(base + ix[i]);
+    }
+}
+
+// merges the runs of `width` elements four at a time
+template <int KW>
+__global__ __launch_bounds__(kThreads) void k_sort_merge(SortKeys<KW> in, const uint32_t *__restrict__ ival,
+                                                         SortKeys<KW> out, uint32_t *__restrict__ oval, size_t n,
+                                                         size_t width, const uint32_t *dn)
+{
+    n = dev_n(n, dn);
+    const size_t g = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    if (g >= n) return;
+    const size_t base = g / (4 * width) * (4 * width), off = g - base;
+    const uint32_t run = (uint32_t)(off / width);
+    uint64_t key[KW];
+#pragma unroll
+    for (int k = 0; k < KW; ++k) key[k] = in.w[k][g];
+    // elements of the other runs that come first: smaller ones, and in the runs
+    // before this element's equal ones too
+    size_t d = base + (off - run * width);
+    size_t l[4], r[4];
+#pragma unroll
+    for (uint32_t o = 0; o < 4; ++o) {
+        l[o] = min(base + o * width, n);
+        r[o] = o == run ? l[o] : min(base + (o + 1) * width, n);
+        d -= l[o];
+    }
+    // the searches run in step, so that their reads overlap
+    for (bool more = true; more;) {
+        more = false;
+#pragma unroll
+        for (uint32_t o = 0; o < 4; ++o) {
+            if (l[o] >= r[o]) continue;
+            const size_t m = (l[o] + r[o]) >> 1;
+            uint64_t y[KW];
+#pragma unroll
+            for (int k = 0; k < KW; ++k) y[k] = in.w[k][m];
+            const bool before = o < run ? !words_less<KW>(key, y) : words_less<KW>(y, key);
+            if (before) l[o] = m + 1;
+            else r[o] = m;
+            more = true;
         }
     }
+    d += l[0] + l[1] + l[2] + l[3];
+#pragma unroll
+    for (int k = 0; k < KW; ++k) out.w[k][d] = key[k];
+    oval[d] = ival[g];
 }
 
 // ---------------------------------------------------------------- radix select
-__global__ __launch_bounds__(kThreads) void k_sel_init(SelectState *st, uint64_t k, const uint32_t *dk)
+constexpr int kSelBins = 2048;
+static_assert(sizeof(SelectState::hist) == kSelBins * sizeof(uint32_t), "one counter a bin");
+
+__global__ __launch_bounds__(1024) void k_sel_init(SelectState *st, uint64_t k, const uint32_t *dk,
+                                                   unsigned int *count)
 {
     if (threadIdx.x == 0) {
         st->prefix = 0ull;
         st->mask = 0ull;
         st->krem = dk ? min(k, (uint64_t)*dk) : k;
+        st->done = 0u;
+        if (count) *count = 0u;
     }
-    st->hist[threadIdx.x] = 0u;
+    for (int i = threadIdx.x; i < kSelBins; i += 1024) st->hist[i] = 0u;
 }
 
-__global__ __launch_bounds__(kThreads) void k_sel_hist(const double *__restrict__ score, size_t n,
-                                                       int shift, SelectState *st, const uint32_t *dn)
+// takes a digit from the counters of a pass (the largest whose entries, with
+// those above it, reach krem) and clears them for the next one
+__device__ __forceinline__ void sel_pick(SelectState *st, int shift, int bits, uint64_t prefix, uint64_t mask,
+                                         uint32_t *s_tmp)
 {
-    __shared__ uint32_t h[256];
+    // thread t holds bins kSelBins - 1 - 8t downwards: a scan over the threads
+    // counts the entries above every bin
+    constexpr int PER = kSelBins / kThreads;
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        c[k] = __hip_atomic_load(&st->hist[kSelBins - 1 - PER * (int)threadIdx.x - k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sum += c[k];
+    }
+    uint32_t tot;
+    uint64_t above = block_excl_scan<kWaves>(sum, s_tmp, tot);
+    const uint64_t need = st->krem;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = kSelBins - 1 - PER * (int)threadIdx.x - k;
+        // one thread holds the digit: above < need <= above + its count (need
+        // is at most the number of entries)
+        if (above < need && above + c[k] >= need) {
+            st->krem = need - above;
+            st->prefix = prefix | ((uint64_t)d << shift);
+            st->mask = mask | (((1ull << bits) - 1ull) << shift);
+        }
+        above += c[k];
+        st->hist[d] = 0u;
+    }
+    if (threadIdx.x == 0) st->done = 0u;
+}
+
+__global__ __launch_bounds__(kThreads) void k_sel_pick(SelectState *st, int shift, int bits)
+{
+    __shared__ uint32_t s_tmp[kWaves];
+    sel_pick(st, shift, bits, st->prefix, st->mask, s_tmp);
+}
+
+// One digit: every workgroup counts its entries of the selected prefix.  PICK:
+// the last one to finish takes the digit, which saves a launch but has every
+// workgroup report to one counter in turn (about 50 ns each): only for the few
+// workgroups of a short input.
+template <bool PICK>
+__global__ __launch_bounds__(kThreads) void k_sel_hist(const double *__restrict__ score, size_t n, int shift, int bits,
+                                                       SelectState *st, const uint32_t *dn)
+{
+    __shared__ uint32_t h[kSelBins];
+    __shared__ uint32_t s_tmp[kWaves];
+    __shared__ bool last;
     n = dev_n(n, dn);
-    h[threadIdx.x] = 0u;
+    for (int i = threadIdx.x; i < kSelBins; i += kThreads) h[i] = 0u;
     __syncthreads();
     const uint64_t prefix = st->prefix, mask = st->mask;
+    const uint32_t dmask = (1u << bits) - 1u;
     // the workgroups stride over the tiles, so that few of them add their
     // counts to the global bins (the leading digits of |A| fall into very few
     // bins, and atomics on one address serialise)
     for (size_t base = (size_t)blockIdx.x * kTile; base < n; base += (size_t)gridDim.x * kTile) {
         for (int i = threadIdx.x; i < kTile; i += kThreads) {
-            size_t j = base + i;
+            const size_t j = base + i;
             if (j < n) {
-                uint64_t o = abs_order(score[j]);
-                if ((o & mask) == prefix) atomicAdd(&h[(o >> shift) & 0xFFu], 1u);
+                const uint64_t o = abs_order(score[j]);
+                if ((o & mask) == prefix) atomicAdd(&h[(uint32_t)(o >> shift) & dmask], 1u);
             }
         }
     }
     __syncthreads();
-    uint32_t c = h[threadIdx.x];
-    if (c) atomicAdd(&st->hist[threadIdx.x], c);
+    for (int i = threadIdx.x; i < kSelBins; i += kThreads)
+        if (h[i]) atomicAdd(&st->hist[i], h[i]);
+    if (!PICK) return;
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(&st->done, 1u) + 1u == gridDim.x;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    sel_pick(st, shift, bits, prefix, mask, s_tmp);
 }
 
 // the entries that still match the selected prefix, copied (in any order:
 // only their count per digit matters) to a smaller array
 __global__ __launch_bounds__(kThreads) void k_sel_compact(const double *__restrict__ score, size_t n,
                                                           const SelectState *__restrict__ st, double *__restrict__ out,
-                                                          unsigned int *__restrict__ count)
+                                                          unsigned int *__restrict__ count, const uint32_t *dn)
 {
+    n = dev_n(n, dn);
     const uint64_t prefix = st->prefix, mask = st->mask;
     const size_t base = (size_t)blockIdx.x * kTile;
     const int lane = threadIdx.x & 63;
     const uint64_t lt = (1ull << lane) - 1ull;
+    if (base >= n) return;  // uniform
     for (int i = threadIdx.x; i < kTile; i += kThreads) {
         const size_t j = base + i;
         const double v = j < n ? score[j] : 0.0;
@@ -354,50 +459,6 @@ __global__ __launch_bounds__(kThreads) void k_sel_compact(const double *__restri
         if (lane == 0 && b) at = atomicAdd(count, (unsigned int)__popcll(b));
         at = __shfl(at, 0, 64);
         if (keep) out[at + __popcll(b & lt)] = v;
-    }
-}
-
-// one wavefront: lane l holds digits 255 - 4l .. 252 - 4l, so a scan across
-// the lanes counts the entries above every digit; the digit taken is the
-// largest d >= 1 with (entries above d) + hist[d] >= krem, else 0
-__global__ __launch_bounds__(64) void k_sel_pick(SelectState *st, int shift)
-{
-    const int lane = threadIdx.x;
-    uint32_t c[4];
-    uint64_t sum = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        c[k] = st->hist[255 - 4 * lane - k];
-        sum += c[k];
-    }
-    uint64_t incl = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t ylo = __shfl_up((uint32_t)incl, d, 64), yhi = __shfl_up((uint32_t)(incl >> 32), d, 64);
-        if (lane >= d) incl += (uint64_t)ylo | ((uint64_t)yhi << 32);
-    }
-    const uint64_t need = st->krem;
-    uint64_t cum = incl - sum, above = 0;
-    int found = -1;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int dg = 255 - 4 * lane - k;
-        if (found < 0 && (dg == 0 || cum + c[k] >= need)) {
-            found = dg;
-            above = cum;
-        }
-        cum += c[k];
-    }
-    const uint64_t bal = __ballot(found >= 0);
-    const int src = __ffsll((long long)bal) - 1;
-    const int d = __shfl(found, src, 64);
-    const uint32_t alo = __shfl((uint32_t)above, src, 64), ahi = __shfl((uint32_t)(above >> 32), src, 64);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) st->hist[4 * lane + k] = 0u;
-    if (lane == 0) {
-        st->krem = need - ((uint64_t)alo | ((uint64_t)ahi << 32));
-        st->prefix |= (uint64_t)d << shift;
-        st->mask |= 0xFFull << shift;
     }
 }
 
@@ -444,70 +505,32 @@ void scan_u32(const uint32_t *in, uint32_t *out, size_t n, uint32_t *d_total, Ar
     (void)mark;
 }
 
-template <typename V>
-int radix_sort(uint64_t *keys_lo[2], uint64_t *keys_hi[2], V *vals[2], size_t n, int words,
-               const std::vector<Digit> &digits, Arena &ar, hipStream_t s, Profiler *prof, const uint32_t *dn)
+template <int KW>
+int merge_sort(uint64_t *(*keys)[2], uint32_t *vals[2], const double *score, size_t n, hipStream_t s, Profiler *prof,
+               const uint32_t *dn)
 {
-    int cur = 0;
-    if (n <= 1 || digits.empty()) return cur;
-    require(n < (1ull << 32), ASCI_EINVAL, "radix sort: too many records");
-    // the smallest tile that keeps the histogram short (its scan is one small launch)
-    int it = 16;
-    for (int c : {2, 4, 8})
-        if ((n + (size_t)kThreads * c - 1) / ((size_t)kThreads * c) <= 64) {
-            it = c;
-            break;
-        }
-    const size_t tile = (size_t)kThreads * it;
-    size_t nb = (n + tile - 1) / tile;
-    uint32_t *hist = ar.take<uint32_t>(nb * 256);
-    for (const Digit &d : digits) {
-        const int nxt = cur ^ 1;
-        const double kb = 8.0 * words, rb = kb + sizeof(V);
-        {
-        ProfScope ps(prof, "rs_hist", kb * n, s);
-        auto hist_k = [&](auto itc) {
-            constexpr int I = decltype(itc)::value;
-            if (words == 2)
-                k_rs_hist<2, I><<<(unsigned)nb, kThreads, 0, s>>>(keys_lo[cur], keys_hi[cur], n, d.word, d.shift,
-                                                                  hist, (uint32_t)nb, dn);
-            else
-                k_rs_hist<1, I><<<(unsigned)nb, kThreads, 0, s>>>(keys_lo[cur], nullptr, n, 0, d.shift, hist,
-                                                                  (uint32_t)nb, dn);
-        };
-        if (it == 2) hist_k(std::integral_constant<int, 2>{});
-        else if (it == 4) hist_k(std::integral_constant<int, 4>{});
-        else if (it == 8) hist_k(std::integral_constant<int, 8>{});
-        else hist_k(std::integral_constant<int, 16>{});
+    require(n < (1ull << 32), ASCI_EINVAL, "sort: too many records");
+    if (n == 0) return 0;
+    constexpr size_t CH = kSortChunk;
+    ProfScope ps(prof, "sort", (8.0 * KW + 4.0) * 2.0 * n, s);
+    SortKeys<KW> k[2];
+    for (int i = 0; i < KW; ++i)
+        for (int b = 0; b < 2; ++b) k[b].w[i] = keys[i][b];
+    k_sort_chunks<KW><<<(unsigned)((n + CH - 1) / CH), kSortT, 0, s>>>(k[0], score, k[1], vals[1], n, dn);
+    ASCI_LAUNCH_CHECK();
+    int cur = 1;
+    for (size_t width = CH; width < n; width *= 4) {
+        k_sort_merge<KW><<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(k[cur], vals[cur], k[cur ^ 1],
+                                                                                      vals[cur ^ 1], n, width, dn);
         ASCI_LAUNCH_CHECK();
-        }
-        scan_u32(hist, hist, nb * 256, nullptr, ar, s, prof);  // every block writes its column
-        ProfScope ps(prof, "rs_scatter", 2.0 * rb * n, s);
-        auto scat_k = [&](auto itc) {
-            constexpr int I = decltype(itc)::value;
-            if (words == 2)
-                k_rs_scatter<2, V, I><<<(unsigned)nb, kThreads, 0, s>>>(
-                    keys_lo[cur], keys_hi[cur], vals[cur], keys_lo[nxt], keys_hi[nxt], vals[nxt], n, d.word,
-                    d.shift, hist, (uint32_t)nb, dn);
-            else
-                k_rs_scatter<1, V, I><<<(unsigned)nb, kThreads, 0, s>>>(keys_lo[cur], nullptr, vals[cur],
-                                                                        keys_lo[nxt], nullptr, vals[nxt], n, 0,
-                                                                        d.shift, hist, (uint32_t)nb, dn);
-        };
-        if (it == 2) scat_k(std::integral_constant<int, 2>{});
-        else if (it == 4) scat_k(std::integral_constant<int, 4>{});
-        else if (it == 8) scat_k(std::integral_constant<int, 8>{});
-        else scat_k(std::integral_constant<int, 16>{});
-        ASCI_LAUNCH_CHECK();
-        cur = nxt;
+        cur ^= 1;
     }
     return cur;
 }
 
-template int radix_sort<double>(uint64_t *[2], uint64_t *[2], double *[2], size_t, int,
-                                const std::vector<Digit> &, Arena &, hipStream_t, Profiler *, const uint32_t *);
-template int radix_sort<uint32_t>(uint64_t *[2], uint64_t *[2], uint32_t *[2], size_t, int,
-                                  const std::vector<Digit> &, Arena &, hipStream_t, Profiler *, const uint32_t *);
+template int merge_sort<1>(uint64_t *(*)[2], uint32_t *[2], const double *, size_t, hipStream_t, Profiler *, const uint32_t *);
+template int merge_sort<2>(uint64_t *(*)[2], uint32_t *[2], const double *, size_t, hipStream_t, Profiler *, const uint32_t *);
+template int merge_sort<3>(uint64_t *(*)[2], uint32_t *[2], const double *, size_t, hipStream_t, Profiler *, const uint32_t *);
 
 Profiler::~Profiler()
 {
@@ -578,34 +601,36 @@ void radix_select_abs(const double *score, size_t n, uint64_t k, SelectState *d_
                       Profiler *prof, const SelectWork *work, const uint32_t *dn, const uint32_t *dk)
 {
     require(k >= 1 && k <= n, ASCI_EINVAL, "radix select: k out of range");
-    if (dn) work = nullptr;  // the compaction reads its count back on the host
-    size_t nb = (n + kTile - 1) / kTile;
-    k_sel_init<<<1, kThreads, 0, s>>>(d_state, k, dk);
+    // a copy of the entries that match two digits pays where a pass over all of
+    // them costs more than a launch
+    if (n <= ((size_t)1 << 20)) work = nullptr;
+    const unsigned nb = (unsigned)((n + kTile - 1) / kTile);
+    k_sel_init<<<1, 1024, 0, s>>>(d_state, k, dk, work ? work->d_count : nullptr);
     ASCI_LAUNCH_CHECK();
     const double *x = score;
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        if (shift == 40 && work) {
-            // after 16 bits only the entries of the selected prefix matter:
-            // copy them out and run the remaining passes on the copy
-            ASCI_HIP(hipMemsetAsync(work->d_count, 0, sizeof(unsigned int), s));
-            {
-                ProfScope ps(prof, "select_compact", 8.0 * n, s);
-                k_sel_compact<<<(unsigned)nb, kThreads, 0, s>>>(x, n, d_state, work->tmp, work->d_count);
-                ASCI_LAUNCH_CHECK();
-            }
-            ASCI_HIP(hipMemcpyAsync(work->h_count, work->d_count, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
-            ASCI_HIP(hipStreamSynchronize(s));
+    bool few = n <= ((size_t)1 << 20);
+    // the 63 bits of |A|, most significant first
+    for (int pass = 0, shift = 63; pass < 6; ++pass) {
+        const int bits = pass < 3 ? 11 : 10;
+        shift -= bits;
+        if (pass == 2 && work) {
+            ProfScope ps(prof, "select_compact", 8.0 * n, s);
+            k_sel_compact<<<nb, kThreads, 0, s>>>(x, n, d_state, work->tmp, work->d_count, dn);
+            ASCI_LAUNCH_CHECK();
             x = work->tmp;
-            n = *work->h_count;
-            nb = (n + kTile - 1) / kTile;
+            dn = work->d_count;
+            few = true;
         }
-        if (nb) {
-            ProfScope ps(prof, "select_hist", 8.0 * n, s);
-            k_sel_hist<<<(unsigned)std::min<size_t>(nb, 2048), kThreads, 0, s>>>(x, n, shift, d_state, dn);
+        ProfScope ps(prof, "select_hist", 8.0 * n, s);
+        if (few) {
+            k_sel_hist<true><<<std::min(nb, 32u), kThreads, 0, s>>>(x, n, shift, bits, d_state, dn);
+            ASCI_LAUNCH_CHECK();
+        } else {
+            k_sel_hist<false><<<std::min(nb, 2048u), kThreads, 0, s>>>(x, n, shift, bits, d_state, dn);
+            ASCI_LAUNCH_CHECK();
+            k_sel_pick<<<1, kThreads, 0, s>>>(d_state, shift, bits);
             ASCI_LAUNCH_CHECK();
         }
-        k_sel_pick<<<1, 64, 0, s>>>(d_state, shift);
-        ASCI_LAUNCH_CHECK();
     }
 }
 

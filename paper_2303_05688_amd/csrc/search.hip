@@ -629,17 +629,6 @@ __global__ __launch_bounds__(kBlock) void k_keep_scatter(const uint64_t *__restr
     }
 }
 
-// sort key for the final order: ~|score| bits so that ascending = descending |score|
-__global__ __launch_bounds__(kBlock) void k_final_keys(const double *__restrict__ score, size_t n,
-                                                       uint64_t *__restrict__ key, uint32_t *__restrict__ idx,
-                                                       const uint32_t *dn)
-{
-    const size_t j = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j >= dcount(n, dn)) return;
-    key[j] = ~abs_order(score[j]);
-    idx[j] = (uint32_t)j;
-}
-
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_final_gather(const uint32_t *__restrict__ idx, size_t n,
                                                          const uint64_t *__restrict__ slo,
@@ -673,7 +662,7 @@ __global__ __launch_bounds__(kBlock) void k_unpack(const uint64_t *__restrict__ 
 }
 
 // ---------------------------------------------------------------- input preparation
-// validation flags: bit 0 = wrong electron count or orbital out of range
+// kStatInvalid: wrong electron count or orbital out of range
 __global__ __launch_bounds__(kBlock) void k_validate(const uint64_t *__restrict__ dets, size_t nd,
                                                      uint64_t full, int na, int nb,
                                                      unsigned int *__restrict__ err)
@@ -681,19 +670,14 @@ __global__ __launch_bounds__(kBlock) void k_validate(const uint64_t *__restrict_
     const size_t j = (size_t)blockIdx.x * kBlock + threadIdx.x;
     if (j >= nd) return;
     const uint64_t a = dets[2 * j], b = dets[2 * j + 1];
-    if ((a & ~full) || (b & ~full) || popc64(a) != na || popc64(b) != nb) atomicOr(err, 1u);
+    if ((a & ~full) || (b & ~full) || popc64(a) != na || popc64(b) != nb) atomicOr(err, kStatInvalid);
 }
 
-// insert every input key into the hash set (keys as (lo, hi) words)
+// inserts an input key into the hash set (keys as (lo, hi) words)
 template <int W>
-__global__ __launch_bounds__(kBlock) void k_psi_insert(const uint64_t *__restrict__ dets, size_t nd, int n,
-                                                       uint64_t *__restrict__ tlo, uint64_t *__restrict__ thi,
-                                                       uint32_t *__restrict__ state, uint32_t mask,
-                                                       unsigned long long *__restrict__ filter, uint32_t fmask)
+__device__ __forceinline__ void psi_insert(uint64_t a, uint64_t b, int n, uint64_t *tlo, uint64_t *thi, uint32_t *state,
+                                           uint32_t mask, unsigned long long *filter, uint32_t fmask)
 {
-    const size_t j = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j >= nd) return;
-    const uint64_t a = dets[2 * j], b = dets[2 * j + 1];
     const uint64_t lo = W == 1 ? ((a << n) | b) : b, hi = W == 1 ? 0ull : a;
     const uint64_t fh = psi_filter_hash(lo, hi);
     atomicOr(&filter[psi_filter_word(fh, fmask)], (unsigned long long)psi_filter_bits(fh));
@@ -708,7 +692,7 @@ __global__ __launch_bounds__(kBlock) void k_psi_insert(const uint64_t *__restric
     }
 }
 
-// bit 1 of err: an input determinant stored twice in the hash set (every insert
+// kStatDuplicate: an input determinant stored twice in the hash set (every insert
 // has finished: this runs as a kernel of its own)
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_psi_dups(const uint64_t *__restrict__ dets, size_t nd, int n, PsiSet t,
@@ -723,17 +707,7 @@ __global__ __launch_bounds__(kBlock) void k_psi_dups(const uint64_t *__restrict_
         if (t.lo[sl] == lo && t.hi[sl] == hi) ++seen;
         sl = (sl + 1u) & t.mask;
     }
-    if (seen > 1) atomicOr(err, 2u);
-}
-
-// core-selection sort key: ~|C| bits, so ascending order is |C| descending
-__global__ __launch_bounds__(kBlock) void k_core_keys(const double *__restrict__ c, size_t nd,
-                                                      uint64_t *__restrict__ key, uint32_t *__restrict__ idx)
-{
-    const size_t j = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j >= nd) return;
-    key[j] = ~abs_order(c[j]);
-    idx[j] = (uint32_t)j;
+    if (seen > 1) atomicOr(err, kStatDuplicate);
 }
 
 __global__ __launch_bounds__(kBlock) void k_index_keys(const uint32_t *__restrict__ idx, size_t n,
@@ -757,44 +731,138 @@ __global__ __launch_bounds__(kBlock) void k_gather_core(const uint64_t *__restri
     qc[j] = c[i];
 }
 
-// J_pq = (pp|qq), X_pq = (pp|qq) - (pq|qp), then h_pp: the tables of the diagonal H_aa
-__global__ __launch_bounds__(kBlock) void k_jk(const double *__restrict__ eri, const double *__restrict__ h, int n,
-                                               double *__restrict__ jk)
+// C(p, k), saturated at 2^32 - 1
+__device__ __forceinline__ uint32_t binom_u32(int p, int k)
 {
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= n * n) return;
-    const int p = t / n, q = t % n;
-    jk[t] = eri4(eri, n, p, p, q, q);
-    jk[n * n + t] = eri4(eri, n, p, p, q, q) - eri4(eri, n, p, q, q, p);
-    if (q == 0) jk[2 * n * n + p] = h[(size_t)p * n + p];
+    if (k < 0 || k > p) return 0u;
+    if (k > p - k) k = p - k;
+    // every product is below 2^38 and every quotient an integer, so both are
+    // exact in a double; c grows with i: once past 2^32 it stays there
+    double c = 1.0;
+    for (int i = 1; i <= k; ++i) {
+        c = c * (double)(p - k + i) / (double)i;
+        if (c > 4294967295.0) return 0xFFFFFFFFu;
+    }
+    return (uint32_t)c;
 }
 
-// The 8-fold packed copy of the integrals (the form the generator reads: a
-// few hundred KB that stay in L2, where the full tensor does not), written by
-// the canonical entry of each set of equal ones (p >= q, r >= s, pq >= rs).
-__global__ __launch_bounds__(kBlock) void k_eri_pack(const double *__restrict__ eri, int n,
-                                                     double *__restrict__ packed)
+// class c of level L in ascending mask order: the c-th L-subset (colex rank)
+// of the orbitals na - L .. n - 1, unranked in the combinatorial number system
+__device__ __forceinline__ uint64_t class_mask(uint32_t c, int n, int na, int L)
 {
-    const uint32_t un = (uint32_t)n;
-    const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= un * un * un * un) return;
-    const uint32_t s_ = t % un, r = (t / un) % un, q = (t / (un * un)) % un, p = t / (un * un * un);
-    if (p < q || r < s_) return;
-    const uint32_t pq = tri(p, q), rs = tri(r, s_);
-    if (pq >= rs) packed[tri(pq, rs)] = eri[t];
+    uint64_t m = 0;
+    uint32_t r = c;
+    int x = n - na + L - 1;
+    for (int j = L; j >= 1; --j) {
+        while (x > 0 && binom_u32(x, j) > r) --x;
+        m |= 1ull << (x + na - L);
+        r -= binom_u32(x, j);
+        --x;
+    }
+    return m;
 }
 
-// every entry equals its packed representative bit for bit, else the
-// integrals are not 8-fold symmetric: err |= 4
-__global__ __launch_bounds__(kBlock) void k_eri_check(const double *__restrict__ eri, int n,
-                                                      const double *__restrict__ packed, unsigned int *err)
+// What a search reads besides its inputs, in two launches (nine before, most of
+// them shorter than the gap to the next):
+// first, all independent of each other: the integral tables J_pq = (pp|qq),
+// X_pq = (pp|qq) - (pq|qp), h_pp; the 8-fold packed copy of the integrals (the
+// form the generator reads: a few hundred KB that stay in L2, where the full
+// tensor does not), written by the canonical entry of each set of equal ones
+// (p >= q, r >= s, pq >= rs); binomials; class masks; cleared words.
+struct PrepArgs {
+    const double *eri, *h;
+    int n;
+    double *jk, *packed;
+    uint32_t *binom;        // (kmax + 1) rows of n + 1
+    int kmax;
+    uint64_t *cls;          // ncls masks of level L
+    uint32_t ncls;
+    int na, L;
+    uint32_t *zero[5];      // words to clear
+    uint32_t nzero[5];
+};
+
+__global__ __launch_bounds__(kBlock) void k_prep_tables(PrepArgs g)
 {
-    const uint32_t un = (uint32_t)n;
-    const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= un * un * un * un) return;
-    const uint32_t s_ = t % un, r = (t / un) % un, q = (t / (un * un)) % un, p = t / (un * un * un);
-    const double v = packed[tri(tri(p, q), tri(r, s_))];
-    if (__double_as_longlong(v) != __double_as_longlong(eri[t])) atomicOr(err, 4u);
+    const uint32_t un = (uint32_t)g.n, n2 = un * un, n4 = g.eri ? n2 * n2 : 0u;
+    const uint32_t nbin = g.binom ? (uint32_t)(g.kmax + 1) * (un + 1u) : 0u;
+    uint32_t t = blockIdx.x * kBlock + threadIdx.x;
+    if (t < n4) {
+        const uint32_t s_ = t % un, r = (t / un) % un, q = (t / n2) % un, p = t / (n2 * un);
+        if (p >= q && r >= s_) {
+            const uint32_t pq = tri(p, q), rs = tri(r, s_);
+            if (pq >= rs) g.packed[tri(pq, rs)] = g.eri[t];
+        }
+        if (t < n2) {
+            const int tp = (int)(t / un), tq = (int)(t % un);
+            g.jk[t] = eri4(g.eri, g.n, tp, tp, tq, tq);
+            g.jk[n2 + t] = eri4(g.eri, g.n, tp, tp, tq, tq) - eri4(g.eri, g.n, tp, tq, tq, tp);
+            if (tq == 0) g.jk[2 * n2 + tp] = g.h[(size_t)tp * un + tp];
+        }
+        return;
+    }
+    t -= n4;
+    if (t < nbin) {
+        g.binom[t] = binom_u32((int)(t % (un + 1u)), (int)(t / (un + 1u)));
+        return;
+    }
+    t -= nbin;
+    if (t < g.ncls) {
+        g.cls[t] = class_mask(t, g.n, g.na, g.L);
+        return;
+    }
+    t -= g.ncls;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        if (t < g.nzero[i]) {
+            g.zero[i][t] = 0u;
+            return;
+        }
+        t -= g.nzero[i];
+    }
+}
+
+// then, with the cleared words and the packed integrals in place: every entry
+// equals its packed representative bit for bit, else the integrals are not
+// 8-fold symmetric (kStatIntegrals); determinants validated, entered into the
+// exclusion set, and, where all of them are the core set, copied to it
+struct InputArgs {
+    const double *eri, *packed;
+    int n, na, nb;
+    uint64_t full;
+    const uint64_t *dets;
+    const double *coeffs;
+    uint32_t nd;
+    unsigned int *err;
+    uint64_t *tlo, *thi;  // null: no exclusion set
+    uint32_t *state;
+    uint32_t mask, fmask;
+    unsigned long long *filter;
+    uint64_t *qa, *qb;    // null: the core set is selected apart
+    double *qc;
+};
+
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_prep_inputs(InputArgs g)
+{
+    const uint32_t un = (uint32_t)g.n, n4 = g.eri ? un * un * un * un : 0u;
+    uint32_t t = blockIdx.x * kBlock + threadIdx.x;
+    if (t < n4) {
+        const uint32_t s_ = t % un, r = (t / un) % un, q = (t / (un * un)) % un, p = t / (un * un * un);
+        const double v = g.packed[tri(tri(p, q), tri(r, s_))];
+        if (__double_as_longlong(v) != __double_as_longlong(g.eri[t])) atomicOr(g.err, kStatIntegrals);
+        return;
+    }
+    t -= n4;
+    if (t >= g.nd) return;
+    const uint64_t a = g.dets[2 * (size_t)t], b = g.dets[2 * (size_t)t + 1];
+    if ((a & ~g.full) || (b & ~g.full) || popc64(a) != g.na || popc64(b) != g.nb) atomicOr(g.err, kStatInvalid);
+    if (g.tlo) psi_insert<W>(a, b, g.n, g.tlo, g.thi, g.state, g.mask, g.filter, g.fmask);
+    if (g.qa) {
+        g.qa[t] = a;
+        g.qb[t] = b;
+        g.qc[t] = g.coeffs[t];
+    }
 }
 
 inline unsigned grid_for(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -905,25 +973,17 @@ SpinTablePlan spin_table_plan(int n, int na, int nb, uint64_t pairs, bool enable
     return pl;
 }
 
-// Build the tables of `pl` for the integrals' J / J-K / h_pp table `jk`.
-static SpinTables build_spin_tables(asci_ctx *ctx, const SpinTablePlan &pl, const double *jk, int n, int na, int nb,
-                                    hipStream_t s)
+// The tables of `pl` for the integrals' J / J-K / h_pp table `jk`, in ar; the
+// binomials (first in ar, at take_binom) are written by the prep kernel.
+static uint32_t *take_binom(const SpinTablePlan &pl, int n, Arena &ar)
+{
+    return pl.bytes ? ar.take<uint32_t>((size_t)(pl.kmax + 1) * (n + 1)) : nullptr;
+}
+static SpinTables build_spin_tables(const SpinTablePlan &pl, const uint32_t *d_binom, const double *jk, int n, int na,
+                                    int nb, Arena &ar, hipStream_t s)
 {
     SpinTables st;
     if (pl.bytes == 0) return st;
-    Arena &ar = ctx->tables;
-    ar.reset();
-    ar.reserve(pl.bytes);
-    ar.reset();
-    std::vector<uint32_t> hb((size_t)(pl.kmax + 1) * (n + 1), 0u);
-    for (int k = 0; k <= pl.kmax; ++k)
-        for (int p = 0; p <= n; ++p)
-            hb[(size_t)k * (n + 1) + p] = (uint32_t)std::min<uint64_t>(binom_sat(p, k), UINT32_MAX);
-    uint32_t *d_binom = ar.take<uint32_t>(hb.size());
-    HostStage &hs = ctx->stage;
-    hs.reserve(hb.size() * 4);
-    std::memcpy(hs.ptr, hb.data(), hb.size() * 4);
-    ASCI_HIP(hipMemcpyAsync(d_binom, hs.ptr, hb.size() * 4, hipMemcpyHostToDevice, s));
     st.binom = d_binom;
     st.kmax = pl.kmax;
     const int ne[2] = {na, nb};
@@ -940,8 +1000,6 @@ static SpinTables build_spin_tables(asci_ctx *ctx, const SpinTablePlan &pl, cons
         ASCI_LAUNCH_CHECK();
         st.e[i] = t;
     }
-    // the staged binomials are read by the copy above
-    ASCI_HIP(hipStreamSynchronize(s));
     return st;
 }
 
@@ -972,7 +1030,9 @@ struct Prepared {
     size_t nd = 0, nq = 0;
     uint64_t *q_a = nullptr, *q_b = nullptr;         // core set, ascending input index
     double *q_c = nullptr;
+    unsigned int *d_err = nullptr;                   // 16 words; [0]: kStat* bits of the inputs
     uint64_t *d_cls = nullptr;
+    unsigned long long *d_tot = nullptr;
     double *d_jk = nullptr;
     double *d_eri8 = nullptr;  // the integrals, 8-fold packed (when given)
     std::vector<uint64_t> cls, totals;  // final classes (ascending mask) and their pair counts
@@ -981,6 +1041,26 @@ struct Prepared {
     PsiSet psi;
     ClassMap cmap(int na) const { return ClassMap{Lr, na, d_tree}; }
 };
+
+// Core set: the nq inputs of largest |C| (ties: lower index), ascending index.
+static void select_core(const uint64_t *dets, const double *coeffs, size_t nd, size_t nq, uint64_t *q_a, uint64_t *q_b,
+                        double *q_c, Arena &ar, hipStream_t s)
+{
+    const uint64_t *sel = nullptr;
+    if (nq < nd) {
+        uint64_t *ck[1][2] = {{ar.take<uint64_t>(nd), ar.take<uint64_t>(nd)}};
+        uint32_t *ci[2] = {ar.take<uint32_t>(nd), ar.take<uint32_t>(nd)};
+        const int r1 = merge_sort<1>(ck, ci, coeffs, nd, s);
+        // the first nq positions, sorted ascending (payload unused)
+        uint64_t *ik[1][2] = {{ck[0][r1 ^ 1], ar.take<uint64_t>(nq)}};
+        uint32_t *ii[2] = {ci[r1 ^ 1], ar.take<uint32_t>(nq)};
+        k_index_keys<<<grid_for(nq), kBlock, 0, s>>>(ci[r1], nq, ik[0][0]);
+        ASCI_LAUNCH_CHECK();
+        sel = ik[0][merge_sort<1>(ik, ii, nullptr, nq, s)];
+    }
+    k_gather_core<<<grid_for(nq), kBlock, 0, s>>>(dets, coeffs, sel, nq, q_a, q_b, q_c);
+    ASCI_LAUNCH_CHECK();
+}
 
 // pair totals of a list of classes (step 4 without the matrix), on the host
 static void count_classes(const uint64_t *q_a, uint32_t nq, const std::vector<uint64_t> &masks, uint64_t *d_cls,
@@ -1089,29 +1169,16 @@ static void plan_classes(int n, int na, int L, int64_t split_pairs, uint64_t fit
     for (size_t r = 0; r < roots.size(); ++r) place(r, r);
 }
 
-// Validate the determinants, sort their keys, pick the core set and count the
-// pairs of every constraint class.  All buffers live in ctx->setup.
+// the setup arena's buffers (the same in every kind of search)
 template <int W>
-static void prepare(asci_ctx *ctx, const double *d_h, const double *d_eri, int n, int na, int nb, const uint64_t *dets,
-                    const double *coeffs, int64_t ndets, const asci_options &opt, uint64_t fit, bool need_psi,
-                    Prepared<W> &pp, hipStream_t s)
+static void carve_setup(Arena &ar, size_t nd, size_t nq, int n, Prepared<W> &pp, uint32_t *&d_tree)
 {
-    const size_t nd = (size_t)ndets;
-    const uint64_t full = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
-    const BetaFactors bf = beta_factors(n, nb);
-    const int64_t ncore = opt.ncore;
     pp.nd = nd;
-    pp.nq = (ncore > 0 && (size_t)ncore < nd) ? (size_t)ncore : nd;
-    const size_t nq = pp.nq;
-
-    Arena &ar = ctx->setup;
-    ar.reset();
-    ar.reserve(setup_bytes(nd, nq, n, W));
-    ar.reset();
-    unsigned int *d_err = ar.take<unsigned int>(16);
+    pp.nq = nq;
+    pp.d_err = ar.take<unsigned int>(16);
     pp.d_cls = ar.take<uint64_t>(kMaxClasses);
-    unsigned long long *d_tot = ar.take<unsigned long long>(kMaxClasses);
-    uint32_t *d_tree = ar.take<uint32_t>(kMaxClasses);
+    pp.d_tot = ar.take<unsigned long long>(kMaxClasses);
+    d_tree = ar.take<uint32_t>(kMaxClasses);
     pp.d_jk = ar.take<double>((size_t)2 * n * n + n);
     pp.d_eri8 = ar.take<double>(eri_packed_count(n));
     pp.q_a = ar.take<uint64_t>(nq);
@@ -1119,75 +1186,128 @@ static void prepare(asci_ctx *ctx, const double *d_h, const double *d_eri, int n
     pp.q_c = ar.take<double>(nq);
     uint32_t tsize = 1024;
     while (tsize < 4 * nd) tsize <<= 1;
-    uint64_t *t_lo = ar.take<uint64_t>(tsize), *t_hi = ar.take<uint64_t>(tsize);
-    uint32_t *t_state = ar.take<uint32_t>(tsize);
+    pp.psi.lo = ar.take<uint64_t>(tsize);
+    pp.psi.hi = ar.take<uint64_t>(tsize);
+    pp.psi.state = ar.take<uint32_t>(tsize);
     // exclusion filter: 32 bits per input determinant (a power of two, at least 2^16)
     size_t fbits = (size_t)1 << 16;
     while (fbits < 32 * nd && fbits < ((size_t)1 << 34)) fbits <<= 1;
-    unsigned long long *t_filter = ar.take<unsigned long long>(fbits / 64);
-    pp.psi.lo = t_lo;
-    pp.psi.hi = t_hi;
-    pp.psi.state = t_state;
+    pp.psi.filter = ar.take<unsigned long long>(fbits / 64);
     pp.psi.mask = tsize - 1;
-    pp.psi.filter = t_filter;
     pp.psi.fmask = (uint32_t)(fbits / 64 - 1);
+}
 
-    ASCI_HIP(hipMemsetAsync(d_err, 0, 16 * sizeof(unsigned int), s));
-    k_validate<<<grid_for(nd), kBlock, 0, s>>>(dets, nd, full, na, nb, d_err);
+// Queues the preparation of a search's inputs into pp: integral tables,
+// validation flags, exclusion set, core set, cleared fault words; binom (with
+// kmax) and ncls class masks of level L where given.  Without integrals
+// (in.eri null) only determinants and core set, and no exclusion set.
+template <int W>
+static void queue_inputs(const SearchArgs &in, Prepared<W> &pp, uint32_t *binom, int kmax, uint32_t ncls, int L,
+                         Arena &ar, hipStream_t s)
+{
+    const int n = in.n;
+    const size_t n4 = in.eri ? (size_t)n * n * n * n : 0;
+    PrepArgs a{};
+    a.eri = in.eri;
+    a.h = in.h;
+    a.n = n;
+    a.jk = pp.d_jk;
+    a.packed = pp.d_eri8;
+    a.binom = binom;
+    a.kmax = kmax;
+    a.cls = pp.d_cls;
+    a.ncls = ncls;
+    a.na = in.na;
+    a.L = L;
+    a.zero[0] = pp.d_err;
+    a.nzero[0] = 16;
+    if (in.eri) {
+        a.zero[1] = const_cast<uint32_t *>(pp.psi.state);
+        a.nzero[1] = pp.psi.mask + 1u;
+        a.zero[2] = (uint32_t *)const_cast<unsigned long long *>(pp.psi.filter);
+        a.nzero[2] = 2u * (pp.psi.fmask + 1u);
+        a.zero[3] = fault_word();
+        a.zero[4] = bucket_fault_word();
+        a.nzero[3] = a.nzero[4] = 1;
+    }
+    size_t items = n4 + (binom ? (size_t)(kmax + 1) * (n + 1) : 0) + ncls;
+    for (uint32_t z : a.nzero) items += z;
+    k_prep_tables<<<grid_for(items), kBlock, 0, s>>>(a);
     ASCI_LAUNCH_CHECK();
-    if (d_eri && d_h) {
-        k_jk<<<grid_for((size_t)n * n), kBlock, 0, s>>>(d_eri, d_h, n, pp.d_jk);
-        ASCI_LAUNCH_CHECK();
-        const size_t n4 = (size_t)n * n * n * n;
-        k_eri_pack<<<grid_for(n4), kBlock, 0, s>>>(d_eri, n, pp.d_eri8);
-        ASCI_LAUNCH_CHECK();
-        k_eri_check<<<grid_for(n4), kBlock, 0, s>>>(d_eri, n, pp.d_eri8, d_err);
-        ASCI_LAUNCH_CHECK();
+    InputArgs b{};
+    b.eri = in.eri;
+    b.packed = pp.d_eri8;
+    b.n = n;
+    b.na = in.na;
+    b.nb = in.nb;
+    b.full = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
+    b.dets = in.dets;
+    b.coeffs = in.coeffs;
+    b.nd = (uint32_t)pp.nd;
+    b.err = pp.d_err;
+    if (in.eri) {
+        b.tlo = const_cast<uint64_t *>(pp.psi.lo);
+        b.thi = const_cast<uint64_t *>(pp.psi.hi);
+        b.state = const_cast<uint32_t *>(pp.psi.state);
+        b.mask = pp.psi.mask;
+        b.filter = const_cast<unsigned long long *>(pp.psi.filter);
+        b.fmask = pp.psi.fmask;
     }
-    if (need_psi) {
-        ASCI_HIP(hipMemsetAsync(t_state, 0, (size_t)tsize * sizeof(uint32_t), s));
-        ASCI_HIP(hipMemsetAsync(t_filter, 0, (size_t)fbits / 8, s));
-        k_psi_insert<W><<<grid_for(nd), kBlock, 0, s>>>(dets, nd, n, t_lo, t_hi, t_state, tsize - 1, t_filter,
-                                                        pp.psi.fmask);
-        ASCI_LAUNCH_CHECK();
-        k_psi_dups<W><<<grid_for(nd), kBlock, 0, s>>>(dets, nd, n, pp.psi, d_err);
-        ASCI_LAUNCH_CHECK();
+    if (pp.nq == pp.nd) {
+        b.qa = pp.q_a;
+        b.qb = pp.q_b;
+        b.qc = pp.q_c;
     }
-    // core set: the nq inputs of largest |C| (ties: lower index), ascending index
-    if (nq < nd) {
-        uint64_t *ck[2] = {ar.take<uint64_t>(nd), ar.take<uint64_t>(nd)};
-        uint32_t *ci[2] = {ar.take<uint32_t>(nd), ar.take<uint32_t>(nd)};
-        uint64_t *nohi[2] = {nullptr, nullptr};
-        k_core_keys<<<grid_for(nd), kBlock, 0, s>>>(coeffs, nd, ck[0], ci[0]);
-        ASCI_LAUNCH_CHECK();
-        std::vector<Digit> cd;
-        for (int sh = 0; sh < 64; sh += 8) cd.push_back({0, sh});
-        const int r1 = radix_sort<uint32_t>(ck, nohi, ci, nd, 1, cd, ar, s);
-        // first nq indices as keys, sorted ascending (payload unused)
-        uint64_t *ik[2] = {ck[r1 ^ 1], ar.take<uint64_t>(nq)};
-        uint32_t *ii[2] = {ci[r1 ^ 1], ar.take<uint32_t>(nq)};
-        k_index_keys<<<grid_for(nq), kBlock, 0, s>>>(ci[r1], nq, ik[0]);
-        ASCI_LAUNCH_CHECK();
-        std::vector<Digit> id;
-        for (int sh = 0; sh < 32; sh += 8) id.push_back({0, sh});
-        const int r2 = radix_sort<uint32_t>(ik, nohi, ii, nq, 1, id, ar, s);
-        k_gather_core<<<grid_for(nq), kBlock, 0, s>>>(dets, coeffs, ik[r2], nq, pp.q_a, pp.q_b, pp.q_c);
-    } else {
-        k_gather_core<<<grid_for(nq), kBlock, 0, s>>>(dets, coeffs, nullptr, nq, pp.q_a, pp.q_b, pp.q_c);
-    }
+    k_prep_inputs<W><<<grid_for(n4 + pp.nd), kBlock, 0, s>>>(b);
     ASCI_LAUNCH_CHECK();
+    if (in.eri) {
+        k_psi_dups<W><<<grid_for(pp.nd), kBlock, 0, s>>>(in.dets, pp.nd, n, pp.psi, pp.d_err);
+        ASCI_LAUNCH_CHECK();
+    }
+    if (pp.nq < pp.nd) select_core(in.dets, in.coeffs, pp.nd, pp.nq, pp.q_a, pp.q_b, pp.q_c, ar, s);
+}
+
+// the error of a set of kStat* input bits
+static void throw_input_error(uint32_t bits)
+{
+    if (bits & kStatInvalid) throw Error{ASCI_EINVAL, "input determinant with wrong electron count or orbital >= norb"};
+    if (bits & kStatDuplicate) throw Error{ASCI_EINVAL, "duplicate input determinants"};
+    if (bits & kStatIntegrals) throw Error{ASCI_EINVAL, "two-electron integrals are not 8-fold symmetric"};
+}
+
+static size_t core_count(const SearchArgs &in)
+{
+    const size_t nd = (size_t)in.ndets;
+    return (in.opt.ncore > 0 && (size_t)in.opt.ncore < nd) ? (size_t)in.opt.ncore : nd;
+}
+
+// Validate the determinants, enter their keys, pick the core set and count the
+// pairs of every constraint class.  All buffers live in ctx->setup.
+template <int W>
+static void prepare(asci_ctx *ctx, const SearchArgs &in, uint64_t fit, uint32_t *binom, int kmax, Prepared<W> &pp,
+                    hipStream_t s)
+{
+    const size_t nd = (size_t)in.ndets, nq = core_count(in);
+    const int n = in.n;
+    const uint64_t full = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
+    const BetaFactors bf = beta_factors(n, in.nb);
+    Arena &ar = ctx->setup;
+    ar.reset();
+    ar.reserve(setup_bytes(nd, nq, n, W));
+    ar.reset();
+    uint32_t *d_tree;
+    carve_setup<W>(ar, nd, nq, n, pp, d_tree);
+    queue_inputs<W>(in, pp, binom, kmax, 0, 0, ar, s);
     HostStage &hs = ctx->stage;
     hs.reserve(256);
     unsigned int *h_err = (unsigned int *)hs.ptr;
-    ASCI_HIP(hipMemcpyAsync(h_err, d_err, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
+    ASCI_HIP(hipMemcpyAsync(h_err, pp.d_err, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
     ASCI_HIP(hipStreamSynchronize(s));
-    if (h_err[0] & 1u) throw Error{ASCI_EINVAL, "input determinant with wrong electron count or orbital >= norb"};
-    if (h_err[0] & 2u) throw Error{ASCI_EINVAL, "duplicate input determinants"};
-    if (h_err[0] & 4u) throw Error{ASCI_EINVAL, "two-electron integrals are not 8-fold symmetric"};
+    throw_input_error(h_err[0]);
     // step 4, totals per class (and the split of heavy classes)
     std::vector<uint32_t> tree;
-    plan_classes(n, na, opt.constraint_level, opt.split_pairs, fit, pp.q_a, (uint32_t)nq, pp.d_cls, d_tot, full, bf,
-                 hs, pp.cls, pp.totals, tree, pp.Lr, s);
+    plan_classes(n, in.na, in.opt.constraint_level, in.opt.split_pairs, fit, pp.q_a, (uint32_t)nq, pp.d_cls, pp.d_tot,
+                 full, bf, hs, pp.cls, pp.totals, tree, pp.Lr, s);
     ASCI_HIP(hipMemcpyAsync(pp.d_cls, pp.cls.data(), pp.cls.size() * sizeof(uint64_t), hipMemcpyHostToDevice, s));
     if (!tree.empty()) {
         ASCI_HIP(hipMemcpyAsync(d_tree, tree.data(), tree.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
@@ -1196,6 +1316,13 @@ static void prepare(asci_ctx *ctx, const double *d_h, const double *d_eri, int n
     // the host vectors are read by the copies above: finish them before returning
     ASCI_HIP(hipStreamSynchronize(s));
 }
+
+// Searches of one class batch of at most this many pairs run without a host
+// round trip until their result is there: read back step by step, a search of
+// 3e5 pairs spent most of its time between launches.
+constexpr uint64_t kSmallPairs = (uint64_t)1 << 22;
+template <int W>
+static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipStream_t s);
 
 template <int W>
 static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipStream_t s)
@@ -1207,6 +1334,7 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
     const uint64_t full = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
     const BetaFactors bf = beta_factors(n, in.nb);
     const bool topk = out.k > 0;
+    if (topk && !out.pt2 && run_search_small<W>(ctx, in, out, s)) return;
 
     Profiler *prof = &ctx->prof;
     // ---- pair-buffer capacity (records of one class batch)
@@ -1222,14 +1350,18 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
     }
     cap = std::max<uint64_t>(cap, 1);
 
+    const SpinTablePlan pl = spin_table_plan(n, in.na, in.nb, search_pairs(in), ctx->spin_tables != 0);
+    ctx->tables.reset();
+    if (pl.bytes) {
+        ctx->tables.reserve(pl.bytes);
+        ctx->tables.reset();
+    }
+    uint32_t *d_binom = take_binom(pl, n, ctx->tables);
     Prepared<W> pp;
-    prepare<W>(ctx, in.h, in.eri, n, in.na, in.nb, in.dets, in.coeffs, in.ndets, in.opt, cap, true, pp, s);
+    prepare<W>(ctx, in, cap, d_binom, pl.kmax, pp, s);
     const size_t nq = pp.nq;
     const uint32_t ncls = (uint32_t)pp.cls.size();
-    uint64_t all_pairs = 0;
-    for (uint64_t t : pp.totals) all_pairs += t;
-    const SpinTables st = build_spin_tables(ctx, spin_table_plan(n, in.na, in.nb, all_pairs, ctx->spin_tables != 0),
-                                            pp.d_jk, n, in.na, in.nb, s);
+    const SpinTables st = build_spin_tables(pl, d_binom, pp.d_jk, n, in.na, in.nb, ctx->tables, s);
 
     // ---- batch plan: consecutive classes up to the pair-buffer capacity
     std::vector<std::pair<uint32_t, uint32_t>> batches;
@@ -1284,8 +1416,6 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
 
     HostStage &hs = ctx->stage;
     hs.reserve(256);
-    fault_clear(s);
-    bucket_fault_clear(s);
     // the end of every path: both fault words read with the last sync
     unsigned int *h_fault = (unsigned int *)((char *)hs.ptr + 224);
     auto finish = [&]() {
@@ -1302,7 +1432,7 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
     // keep the pool's keepk entries of largest |score|, in ascending key order
     auto prune = [&](size_t keepk) {
         const size_t entry_mark = ar.used();
-        const SelectWork sw{p_score[pcur ^ 1], d_cnt + 8, (unsigned int *)((char *)hs.ptr + 192)};
+        const SelectWork sw{p_score[pcur ^ 1], d_cnt + 8};
         radix_select_abs(p_score[pcur], pool_n, keepk, d_sel, s, prof, &sw);
         const uint32_t ntile = (uint32_t)((pool_n + kKeepTile - 1) / kKeepTile);
         uint32_t *tgt = ar.take<uint32_t>(ntile), *teq = ar.take<uint32_t>(ntile);
@@ -1492,14 +1622,9 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
     }
     if (kk < pool_n) prune(kk);
     {
-        uint64_t *fk[2] = {ar.take<uint64_t>(kk), ar.take<uint64_t>(kk)};
+        uint64_t *fk[1][2] = {{ar.take<uint64_t>(kk), ar.take<uint64_t>(kk)}};
         uint32_t *fi[2] = {ar.take<uint32_t>(kk), ar.take<uint32_t>(kk)};
-        uint64_t *nohi[2] = {nullptr, nullptr};
-        k_final_keys<<<grid_for(kk), kBlock, 0, s>>>(p_score[pcur], kk, fk[0], fi[0], nullptr);
-        ASCI_LAUNCH_CHECK();
-        std::vector<Digit> fd;
-        for (int sh = 0; sh < 64; sh += 8) fd.push_back({0, sh});
-        const int rr = radix_sort<uint32_t>(fk, nohi, fi, kk, 1, fd, ar, s, prof);
+        const int rr = merge_sort<1>(fk, fi, p_score[pcur], kk, s, prof);
         k_final_gather<W><<<grid_for(kk), kBlock, 0, s>>>(fi[rr], kk, p_lo[pcur], p_hi[pcur], p_score[pcur], n,
                                                           out.out_dets, out.out_scores, nullptr, nullptr);
         ASCI_LAUNCH_CHECK();
@@ -1510,80 +1635,57 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
 // ---------------------------------------------------------------- the search with nothing read back
 namespace {
 
-// class c of level L in ascending mask order: the c-th L-subset (colex rank)
-// of the orbitals na - L .. n - 1, unranked in the combinatorial number system
-__global__ __launch_bounds__(kBlock) void k_class_masks(uint64_t *__restrict__ cls, uint32_t ncls, int n, int na,
-                                                        int L)
-{
-    const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
-    if (c >= ncls) return;
-    uint64_t m = 0;
-    uint32_t r = c;
-    int x = n - na + L - 1;
-    for (int j = L; j >= 1; --j) {
-        while (x > 0 && choose_le6((uint32_t)x, j) > r) --x;
-        m |= 1ull << (x + na - L);
-        r -= choose_le6((uint32_t)x, j);
-        --x;
-    }
-    cls[c] = m;
-}
-
-// C(p, k) for k < rows, p <= n, saturated at 2^32 - 1; rows past kmax are zero
-__global__ __launch_bounds__(64) void k_binom_table(uint32_t *__restrict__ out, int n, int kmax, int rows)
-{
-    if (threadIdx.x != 0) return;
-    // Pascal's rule row by row over p (64-bit, saturating)
-    uint64_t prev[65], cur[65];
-    for (int k = 0; k <= 64; ++k) prev[k] = k == 0 ? 1ull : 0ull;  // p = 0
-    for (int p = 0; p <= n; ++p) {
-        if (p > 0) {
-            cur[0] = 1ull;
-            for (int k = 1; k <= 64; ++k) {
-                const uint64_t v = prev[k - 1] + prev[k];
-                cur[k] = v > 0xFFFFFFFFull ? 0xFFFFFFFFull : v;
-            }
-            for (int k = 0; k <= 64; ++k) prev[k] = cur[k];
-        }
-        for (int k = 0; k < rows; ++k) out[(size_t)k * (n + 1) + p] = k <= kmax ? (uint32_t)prev[k] : 0u;
-    }
-}
-
 // *dst = min(k, *n)
 __global__ __launch_bounds__(64) void k_min_count(const uint32_t *__restrict__ n, uint64_t k, uint32_t *__restrict__ dst)
 {
     if (threadIdx.x == 0) *dst = (uint32_t)min((uint64_t)*n, k);
 }
 
-// the validation flags of the setup arena folded into the status word
-__global__ __launch_bounds__(64) void k_stat_or(const unsigned int *__restrict__ err, uint32_t *__restrict__ stat)
-{
-    if (threadIdx.x == 0 && *err)
-        atomicOr(stat, (*err & (kStatInvalid | kStatDuplicate)) | ((*err & 4u) ? kStatIntegrals : 0u));
-}
-
-__global__ __launch_bounds__(64) void k_async_done(const uint32_t *__restrict__ stat, const uint32_t *__restrict__ kk,
-                                                   asci_async_result *__restrict__ res)
+// The end of a call, before its outputs are written (a failed call writes
+// none): both fault words, and segments still too large for the finish or a
+// list that overflowed, folded into the status word; the result record; counts
+// for the host.
+struct DoneArgs {
+    const uint32_t *f0, *f1, *nlarge, *overflow, *V, *nfinal, *levels;
+    uint64_t k;
+    uint32_t *stat;
+    asci_async_result *res;
+};
+__global__ __launch_bounds__(64) void k_async_done(DoneArgs g)
 {
     if (threadIdx.x != 0) return;
-    const uint32_t f = *stat;
-    res->flags = (int32_t)f;
-    res->status = f == 0u ? ASCI_OK
-                          : ((f & (kStatInvalid | kStatDuplicate | kStatIntegrals)) ? ASCI_EINVAL : ASCI_EDEVICE);
-    res->count = f == 0u ? (int64_t)*kk : 0;
+    uint32_t f = g.stat[0];
+    if (*g.f0 | *g.f1) f |= kStatFault;
+    if (*g.nlarge | *g.overflow) f |= kStatSplit;
+    const uint32_t count = (uint32_t)min((uint64_t)*g.V, g.k);
+    g.stat[0] = f;
+    g.stat[1] = count;
+    g.stat[2] = *g.V;
+    g.stat[3] = *g.nfinal;
+    g.stat[4] = *g.levels;
+    g.res->flags = (int32_t)f;
+    g.res->status = f == 0u ? ASCI_OK
+                            : ((f & (kStatInvalid | kStatDuplicate | kStatIntegrals)) ? ASCI_EINVAL : ASCI_EDEVICE);
+    g.res->count = f == 0u ? (int64_t)count : 0;
 }
 
 }  // namespace
 
+// up to this many pairs every candidate is sorted instead of selected first
+constexpr size_t kSortAllPairs = (size_t)1 << 19;
+
+// dev_levels, dev_rounds: split levels and small-split rounds queued (what they
+// leave undivided fails the call with kStatSplit)
 template <int W>
 static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uint64_t *out_dets, double *out_scores,
-                             asci_async_result *d_result, hipStream_t s, bool plan_only)
+                             asci_async_result *d_result, hipStream_t s, bool plan_only, int dev_levels, int dev_rounds,
+                             uint32_t **stat_out = nullptr)
 {
     const int n = in.n, na = in.na, nb = in.nb;
     const uint64_t full = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
     const BetaFactors bf = beta_factors(n, nb);
     const size_t nd = (size_t)in.ndets;
-    const size_t nq = (in.opt.ncore > 0 && (size_t)in.opt.ncore < nd) ? (size_t)in.opt.ncore : nd;
+    const size_t nq = core_count(in);
     const uint64_t P = search_pairs(in);
     // the requested level, or the highest lower one whose classes fit one batch
     // (the classes only partition the targets: the result is the same)
@@ -1610,8 +1712,8 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     Arena &ar = ctx->main;
     ar.reset();
     const SpinTablePlan pl = spin_table_plan(n, na, nb, P, ctx->spin_tables != 0);
-    // the bound of the one-batch search, the tables, and the collect's sort of
-    // final segments sized for their bound instead of their count
+    // the bound of the one-batch search, the tables, and what is sized for its
+    // bound instead of its count
     const int fcap = effective_finish_cap(ctx, n, na, P);
     ar.reserve(main_bytes(E, Pb, pool_cap, (uint32_t)ncls, (size_t)kh, true, W, fcap) + pl.bytes + Pb / 4 +
                ((size_t)16 << 20));
@@ -1619,99 +1721,18 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     if (plan_only) return;  // workspaces sized, nothing queued
 
     // ---- inputs: validation (flags on the device), integral tables, psi set, core set, class masks
-    unsigned int *d_err = su.take<unsigned int>(16);
-    uint64_t *d_cls = su.take<uint64_t>(kMaxClasses);
-    (void)su.take<unsigned long long>(kMaxClasses);
-    (void)su.take<uint32_t>(kMaxClasses);
-    double *d_jk = su.take<double>((size_t)2 * n * n + n);
-    double *d_eri8 = su.take<double>(eri_packed_count(n));
-    uint64_t *q_a = su.take<uint64_t>(nq), *q_b = su.take<uint64_t>(nq);
-    double *q_c = su.take<double>(nq);
-    uint32_t tsize = 1024;
-    while (tsize < 4 * nd) tsize <<= 1;
-    uint64_t *t_lo = su.take<uint64_t>(tsize), *t_hi = su.take<uint64_t>(tsize);
-    uint32_t *t_state = su.take<uint32_t>(tsize);
-    size_t fbits = (size_t)1 << 16;
-    while (fbits < 32 * nd && fbits < ((size_t)1 << 34)) fbits <<= 1;
-    unsigned long long *t_filter = su.take<unsigned long long>(fbits / 64);
-    PsiSet psi;
-    psi.lo = t_lo;
-    psi.hi = t_hi;
-    psi.state = t_state;
-    psi.mask = tsize - 1;
-    psi.filter = t_filter;
-    psi.fmask = (uint32_t)(fbits / 64 - 1);
-    uint32_t *d_stat = ar.take<uint32_t>(16);  // [0] status bits, [1] selection size
-    fill_u32(d_stat, 16, 0u, s);
-    fill_u32((uint32_t *)d_err, 16, 0u, s);
-    k_fault_reset<<<1, 64, 0, s>>>();
-    bucket_fault_reset_dev(s);
-    k_validate<<<grid_for(nd), kBlock, 0, s>>>(in.dets, nd, full, na, nb, d_err);
-    ASCI_LAUNCH_CHECK();
-    k_jk<<<grid_for((size_t)n * n), kBlock, 0, s>>>(in.eri, in.h, n, d_jk);
-    ASCI_LAUNCH_CHECK();
-    {
-        const size_t n4 = (size_t)n * n * n * n;
-        k_eri_pack<<<grid_for(n4), kBlock, 0, s>>>(in.eri, n, d_eri8);
-        ASCI_LAUNCH_CHECK();
-        k_eri_check<<<grid_for(n4), kBlock, 0, s>>>(in.eri, n, d_eri8, d_err);
-        ASCI_LAUNCH_CHECK();
-    }
-    fill_u32(t_state, tsize, 0u, s);
-    fill_u32((uint32_t *)t_filter, fbits / 32, 0u, s);
-    k_psi_insert<W><<<grid_for(nd), kBlock, 0, s>>>(in.dets, nd, n, t_lo, t_hi, t_state, tsize - 1, t_filter, psi.fmask);
-    ASCI_LAUNCH_CHECK();
-    k_psi_dups<W><<<grid_for(nd), kBlock, 0, s>>>(in.dets, nd, n, psi, d_err);
-    ASCI_LAUNCH_CHECK();
-    k_stat_or<<<1, 64, 0, s>>>(d_err, d_stat);
-    ASCI_LAUNCH_CHECK();
-    if (nq < nd) {
-        uint64_t *ck[2] = {su.take<uint64_t>(nd), su.take<uint64_t>(nd)};
-        uint32_t *ci[2] = {su.take<uint32_t>(nd), su.take<uint32_t>(nd)};
-        uint64_t *nohi[2] = {nullptr, nullptr};
-        k_core_keys<<<grid_for(nd), kBlock, 0, s>>>(in.coeffs, nd, ck[0], ci[0]);
-        ASCI_LAUNCH_CHECK();
-        std::vector<Digit> cd;
-        for (int sh = 0; sh < 64; sh += 8) cd.push_back({0, sh});
-        const int r1 = radix_sort<uint32_t>(ck, nohi, ci, nd, 1, cd, su, s);
-        uint64_t *ik[2] = {ck[r1 ^ 1], su.take<uint64_t>(nq)};
-        uint32_t *ii[2] = {ci[r1 ^ 1], su.take<uint32_t>(nq)};
-        k_index_keys<<<grid_for(nq), kBlock, 0, s>>>(ci[r1], nq, ik[0]);
-        ASCI_LAUNCH_CHECK();
-        std::vector<Digit> id;
-        for (int sh = 0; sh < 32; sh += 8) id.push_back({0, sh});
-        const int r2 = radix_sort<uint32_t>(ik, nohi, ii, nq, 1, id, su, s);
-        k_gather_core<<<grid_for(nq), kBlock, 0, s>>>(in.dets, in.coeffs, ik[r2], nq, q_a, q_b, q_c);
-    } else {
-        k_gather_core<<<grid_for(nq), kBlock, 0, s>>>(in.dets, in.coeffs, nullptr, nq, q_a, q_b, q_c);
-    }
-    ASCI_LAUNCH_CHECK();
-    k_class_masks<<<grid_for(ncls), kBlock, 0, s>>>(d_cls, (uint32_t)ncls, n, na, L);
-    ASCI_LAUNCH_CHECK();
-
-    // ---- spin-string tables (binomials built on the device)
-    SpinTables st;
-    if (pl.bytes) {
-        uint32_t *d_binom = ar.take<uint32_t>((size_t)(pl.kmax + 1) * (n + 1));
-        k_binom_table<<<1, 64, 0, s>>>(d_binom, n, pl.kmax, pl.kmax + 1);
-        ASCI_LAUNCH_CHECK();
-        st.binom = d_binom;
-        st.kmax = pl.kmax;
-        const int ne[2] = {na, nb};
-        for (int i = 0; i < 2; ++i) {
-            if (pl.count[i] == 0) continue;
-            st.last[i] = (uint32_t)(pl.count[i] - 1);
-            if (i == 1 && pl.share) {
-                st.e[1] = st.e[0];
-                continue;
-            }
-            double *t = ar.take<double>(pl.count[i]);
-            k_spin_table<<<(unsigned)((pl.count[i] + kBlock - 1) / kBlock), kBlock, 0, s>>>(d_jk, n, ne[i], d_binom,
-                                                                                        (uint32_t)pl.count[i], t);
-            ASCI_LAUNCH_CHECK();
-            st.e[i] = t;
-        }
-    }
+    Prepared<W> pp;
+    uint32_t *d_tree;
+    carve_setup<W>(su, nd, nq, n, pp, d_tree);
+    uint32_t *d_stat = pp.d_err;  // [0] status bits, [1] selection size, [2] candidates, [3] final segments
+    if (stat_out) *stat_out = d_stat;
+    uint32_t *d_binom = take_binom(pl, n, ar);
+    queue_inputs<W>(in, pp, d_binom, pl.kmax, (uint32_t)ncls, L, su, s);
+    uint64_t *d_cls = pp.d_cls;
+    uint64_t *q_a = pp.q_a, *q_b = pp.q_b;
+    double *q_c = pp.q_c, *d_jk = pp.d_jk, *d_eri8 = pp.d_eri8;
+    const PsiSet &psi = pp.psi;
+    const SpinTables st = build_spin_tables(pl, d_binom, d_jk, n, na, nb, ar, s);
 
     // ---- count matrix, record offsets, generation (one batch: every class)
     uint32_t *counts = ar.take<uint32_t>(E);
@@ -1806,15 +1827,34 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     ba.pool_score = p_score[0];
     ba.pool_base = 0;
     ba.pool_cap = pool_cap;
-    bucket_accumulate_dev<W>(ba, ar, s, d_stat);
+    ba.dev_levels = dev_levels;
+    ba.dev_rounds = dev_rounds;
+    bucket_accumulate_dev<W>(ba, ar, s);
     bucket_collect_dev<W>(ba, s);
     const uint32_t *d_V = ba.dn_V;
 
     // ---- the k largest |A| (ties: smaller key), then |A| descending
+    const DoneArgs da{fault_word(), bucket_fault_word(), ba.dn_nlarge, ba.dn_overflow, d_V, ba.dn_nfinal, ba.dn_levels,
+                      (uint64_t)k, d_stat, d_result};
+    if (Pb <= kSortAllPairs) {
+        // all candidates sorted (the record buffers are free by now): the pool
+        // is in key order, so ties keep ascending keys.  A selection of
+        // twelve launches ahead of the sort of k took 110 us, this 60.
+        uint64_t *fk[1][2] = {{k_lo[0], k_lo[1]}};
+        uint32_t *fi[2] = {(uint32_t *)v[0], (uint32_t *)v[1]};
+        const int rr = merge_sort<1>(fk, fi, p_score[0], Pb, s, nullptr, d_V);
+        k_async_done<<<1, 64, 0, s>>>(da);
+        ASCI_LAUNCH_CHECK();
+        k_final_gather<W><<<grid_for(kh), kBlock, 0, s>>>(fi[rr], kh, p_lo[0], p_hi[0], p_score[0], n, out_dets,
+                                                          out_scores, d_stat + 1, d_stat);
+        ASCI_LAUNCH_CHECK();
+        return;
+    }
     uint32_t *d_kk = d_stat + 1;
     k_min_count<<<1, 64, 0, s>>>(d_V, (uint64_t)k, d_kk);
     ASCI_LAUNCH_CHECK();
-    radix_select_abs(p_score[0], Pb, kh, d_sel, s, nullptr, nullptr, d_V, d_kk);
+    const SelectWork sw{p_score[1], d_cnt + 8};
+    radix_select_abs(p_score[0], Pb, kh, d_sel, s, nullptr, &sw, d_V, d_kk);
     const uint32_t ntile = (uint32_t)((Pb + kKeepTile - 1) / kKeepTile);
     uint32_t *tgt = ar.take<uint32_t>(ntile), *teq = ar.take<uint32_t>(ntile);
     uint32_t *eqb = ar.take<uint32_t>(ntile), *kbs = ar.take<uint32_t>(ntile);
@@ -1825,33 +1865,68 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     k_keep_scatter<W><<<ntile, kBlock, 0, s>>>(p_lo[0], p_hi[0], p_score[0], Pb, d_sel, eqb, kbs, p_lo[1], p_hi[1],
                                                p_score[1], (size_t)kh, d_V);
     ASCI_LAUNCH_CHECK();
-    {
-        uint64_t *fk[2] = {ar.take<uint64_t>(kh), ar.take<uint64_t>(kh)};
-        uint32_t *fi[2] = {ar.take<uint32_t>(kh), ar.take<uint32_t>(kh)};
-        uint64_t *nohi[2] = {nullptr, nullptr};
-        k_final_keys<<<grid_for(kh), kBlock, 0, s>>>(p_score[1], kh, fk[0], fi[0], d_kk);
-        ASCI_LAUNCH_CHECK();
-        std::vector<Digit> fd;
-        for (int sh = 0; sh < 64; sh += 8) fd.push_back({0, sh});
-        const int rr = radix_sort<uint32_t>(fk, nohi, fi, kh, 1, fd, ar, s, nullptr, d_kk);
-        // every fault raised so far fails the call before any output is written
-        k_fault_take<<<1, 64, 0, s>>>(d_stat, kStatFault);
-        ASCI_LAUNCH_CHECK();
-        bucket_fault_take_dev(d_stat, kStatFault, s);
-        k_final_gather<W><<<grid_for(kh), kBlock, 0, s>>>(fi[rr], kh, p_lo[1], p_hi[1], p_score[1], n, out_dets,
-                                                          out_scores, d_kk, d_stat);
-        ASCI_LAUNCH_CHECK();
-    }
-    k_async_done<<<1, 64, 0, s>>>(d_stat, d_kk, d_result);
+    uint64_t *fk[1][2] = {{ar.take<uint64_t>(kh), ar.take<uint64_t>(kh)}};
+    uint32_t *fi[2] = {ar.take<uint32_t>(kh), ar.take<uint32_t>(kh)};
+    const int rr = merge_sort<1>(fk, fi, p_score[1], kh, s, nullptr, d_kk);
+    k_async_done<<<1, 64, 0, s>>>(da);
+    ASCI_LAUNCH_CHECK();
+    k_final_gather<W><<<grid_for(kh), kBlock, 0, s>>>(fi[rr], kh, p_lo[1], p_hi[1], p_score[1], n, out_dets, out_scores,
+                                                      d_kk, d_stat);
     ASCI_LAUNCH_CHECK();
 }
+
+// A search of one small class batch through the asynchronous search with as
+// many split levels as it should need, its result and counts read back once.
+// false: outside that scope, or (never seen) not divided in those levels; the
+// caller then runs the search step by step.
+template <int W>
+static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipStream_t s)
+{
+    const uint64_t P = search_pairs(in);
+    const int L = std::min(in.opt.constraint_level, in.na);
+    if (ctx->prof.on || P < 1 || P > kSmallPairs || in.opt.split_pairs != 0 || L < 0) return false;
+    if (ctx->main.fixed() || ctx->setup.fixed()) return false;  // sized for the step-by-step search
+    if (in.opt.pair_buffer_bytes > 0 && P > (uint64_t)in.opt.pair_buffer_bytes / (2 * (8 * W + 8))) return false;
+    const uint64_t ncls = std::max<uint64_t>(choose_u64((uint64_t)(in.n - in.na + L), L), 1);
+    if (ncls > kMaxBatchClasses) return false;
+    if (ncls * core_count(in) > 4 * kSmallPairs) return false;  // a count matrix larger than the records
+    // one level divides a class of up to 256 * 4096 records into ranges of one
+    // tile, which the small split finishes
+    const int levels = P <= ((uint64_t)1 << 19) ? 1 : 2;
+    HostStage &hs = ctx->stage;
+    hs.reserve(256);
+    ctx->setup.reset();
+    // the result record lies behind the status words, which the setup arena holds first
+    ctx->setup.reserve(setup_bytes((size_t)in.ndets, core_count(in), in.n, W));
+    ctx->setup.reset();
+    uint32_t *d_stat = ctx->setup.take<uint32_t>(16);
+    run_search_async<W>(ctx, in, out.k, out.out_dets, out.out_scores, (asci_async_result *)(d_stat + 8), s, false, levels, 1,
+                        &d_stat);
+    const uint32_t *h = (const uint32_t *)hs.ptr;
+    ASCI_HIP(hipMemcpyAsync(hs.ptr, d_stat, 16 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    ASCI_HIP(hipStreamSynchronize(s));
+    throw_input_error(h[0]);
+    if (h[0] & kStatSplit) return false;
+    if (h[0]) throw Error{ASCI_EDEVICE, "internal consistency fault in the search"};
+    out.count = (int64_t)h[1];
+    ctx->last_batches = 1;
+    ctx->last_candidates = (int64_t)h[2];
+    ctx->last_finals = (int64_t)h[3];
+    ctx->last_levels = (int64_t)h[4];
+    return true;
+}
+
+// Three levels take the largest batch (below 2^31 records) to ranges of one
+// tile, one more isolates single keys, one is spare; another lies between the
+// two rounds of the small split.
+constexpr int kAsyncLevels = 5;
 
 void search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uint64_t *out_dets, double *out_scores,
                   asci_async_result *d_result, hipStream_t s, bool plan_only)
 {
     require(k >= 1, ASCI_EINVAL, "k must be >= 1");
-    if (in.n <= 32) run_search_async<1>(ctx, in, k, out_dets, out_scores, d_result, s, plan_only);
-    else run_search_async<2>(ctx, in, k, out_dets, out_scores, d_result, s, plan_only);
+    if (in.n <= 32) run_search_async<1>(ctx, in, k, out_dets, out_scores, d_result, s, plan_only, kAsyncLevels, 2);
+    else run_search_async<2>(ctx, in, k, out_dets, out_scores, d_result, s, plan_only, kAsyncLevels, 2);
 }
 
 size_t search_async_bytes(const SearchArgs &in, int64_t k, int finish_cap, bool spin_tables)
@@ -1945,13 +2020,14 @@ void class_counts_device(asci_ctx *ctx, int n, int na, int nb, const uint64_t *d
             }
     };
     const uint64_t no_fit = ~0ull;
+    const SearchArgs in{nullptr, nullptr, n, na, nb, dets, coeffs, ndets, 0.0, opt};
     if (n <= 32) {
         Prepared<1> pp;
-        prepare<1>(ctx, nullptr, nullptr, n, na, nb, dets, coeffs, ndets, opt, no_fit, false, pp, s);
+        prepare<1>(ctx, in, no_fit, nullptr, 0, pp, s);
         collect(pp.cls, pp.totals);
     } else {
         Prepared<2> pp;
-        prepare<2>(ctx, nullptr, nullptr, n, na, nb, dets, coeffs, ndets, opt, no_fit, false, pp, s);
+        prepare<2>(ctx, in, no_fit, nullptr, 0, pp, s);
         collect(pp.cls, pp.totals);
     }
 }

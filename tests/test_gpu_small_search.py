@@ -1,0 +1,99 @@
+"""Searches of one small class batch (read back once, at the end) against the
+step-by-step path, which candidates() takes: the k largest of every candidate
+in exact (|A| descending, key ascending) order, bit for bit, on both sides of
+each rule (a sort of every candidate up to 2^19 pairs, a selection above; the
+step-by-step path from 2^22 pairs), with k at the edges of the sort's chunks,
+and among scores of which most are tied.  The same errors on both paths."""
+from math import comb
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _pairs(n, na, nb):
+    va, vb = n - na, n - nb
+    return (na * va + nb * vb + comb(na, 2) * comb(va, 2) + comb(nb, 2) * comb(vb, 2) + na * va * nb * vb)
+
+
+def _case(n, na, nb, ndets, seed, quantum=None):
+    import asci_synth as syn
+
+    rng = np.random.default_rng(seed)
+    h, eri = syn.integrals(n, rng)
+    dets = np.array(syn.uniform_dets(n, na, nb, ndets, rng), dtype=np.uint64)
+    c = syn.coefficients(ndets, ndets, rng)
+    if quantum is not None:  # sums of few multiples of a power of two: many exact ties, many exact zeros
+        h, eri = np.round(h / quantum) * quantum, np.round(eri / quantum) * quantum
+        c = np.sign(c + 1e-30) * 2.0 ** -np.ceil(np.log2(ndets) / 2)
+    return {"h": h, "eri": eri, "dets": dets, "coeffs": c}
+
+
+def _expected(d, n, na, nb, E0, **kw):
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+
+    k, _, sc = (gu.host(x) for x in asci.candidates(d["h"], d["eri"], n, na, nb, d["dets"], d["coeffs"], E0, **kw))
+    order = np.lexsort((k[:, 1], k[:, 0], ~gu.abs_bits(sc)))
+    return k[order], sc[order]
+
+
+def _compare(d, n, na, nb, E0, ks, want, **kw):
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+
+    for k in ks:
+        gk, gs = (gu.host(x) for x in asci.search(d["h"], d["eri"], n, na, nb, d["dets"], d["coeffs"], E0, k, **kw))
+        m = min(k, len(want[1]))
+        assert len(gs) == m, (k, len(gs), m)
+        assert (gk == want[0][:m]).all() and (gs.view(np.uint64) == want[1][:m].view(np.uint64)).all(), k
+
+
+@pytest.mark.parametrize("n,na,nb", [(12, 6, 6), (34, 3, 3)])
+@pytest.mark.parametrize("log_pairs,over", [(12, 0), (19, 0), (19, 1), (22, 0), (22, 1)])
+def test_small_search_edges(n, na, nb, log_pairs, over):
+    import gpu_util as gu
+
+    nd = max((1 << log_pairs) // _pairs(n, na, nb) + over, 1)
+    d = gu.to_dev(_case(n, na, nb, nd, 900 + n + log_pairs))
+    want = _expected(d, n, na, nb, -3.5)
+    ks = [1, 1023, 1024, 1025, 4097, len(want[1]) - 1, len(want[1]), len(want[1]) + 1]
+    _compare(d, n, na, nb, -3.5, [k for k in ks if k > 0], want)
+    for kw in ({"ncore": (nd + 1) // 2}, {"eps": 1e-3}, {"constraint_level": 1}, {"constraint_level": 5}):
+        _compare(d, n, na, nb, -3.5, [500], _expected(d, n, na, nb, -3.5, **kw), **kw)
+
+
+@pytest.mark.parametrize("n,na,nb,ndets", [(12, 6, 6, 40), (12, 6, 6, 300), (34, 3, 3, 60)])
+def test_small_search_tied_scores(n, na, nb, ndets):
+    import gpu_util as gu
+
+    d = gu.to_dev(_case(n, na, nb, ndets, 31 + ndets, quantum=0.5))
+    want = _expected(d, n, na, nb, -1000.25)
+    assert len(np.unique(gu.abs_bits(want[1]))) < len(want[1]) // 2
+    _compare(d, n, na, nb, -1000.25, [1, 2, 1024, 1025, 2049, 8193, len(want[1]) - 1, len(want[1])], want)
+
+
+@pytest.mark.parametrize("n,na,nb", [(12, 6, 6), (34, 3, 3)])
+@pytest.mark.parametrize("fault", ["electrons", "duplicate", "eri"])
+def test_small_search_errors(n, na, nb, fault):
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+
+    good = _case(n, na, nb, 24, 7)
+    bad = {k: v.copy() for k, v in good.items()}
+    if fault == "electrons":
+        bad["dets"][11, 0] = (1 << (na + 1)) - 1
+    elif fault == "duplicate":
+        bad["dets"][23] = bad["dets"][2]
+    else:
+        bad["eri"].reshape(n, n, n, n)[0, 1, 2, 3] += 1e-3
+    said = []
+    for kw in ({}, {"pair_buffer_bytes": 32 * 12 * _pairs(n, na, nb)}):  # the second: several batches
+        d = gu.to_dev(bad)
+        with pytest.raises(asci.AsciError) as e:
+            asci.search(d["h"], d["eri"], n, na, nb, d["dets"], d["coeffs"], -3.5, 100, **kw)
+        said.append((e.value.code if hasattr(e.value, "code") else None, str(e.value)))
+    assert said[0] == said[1]
+    d = gu.to_dev(good)
+    _compare(d, n, na, nb, -3.5, [100], _expected(d, n, na, nb, -3.5))
