@@ -1318,8 +1318,10 @@ static void prepare(asci_ctx *ctx, const SearchArgs &in, uint64_t fit, uint32_t 
 }
 
 // Searches of one class batch of at most this many pairs run without a host
-// round trip until their result is there: read back step by step, a search of
-// 3e5 pairs spent most of its time between launches.
+// round trip until their result is there (12 electrons in 12 orbitals, k =
+// 10 ndets up to 20000, ms against the step-by-step path: 2^15 pairs 0.21 and
+// 0.34, 2^18 0.29 and 0.44, 2^22 0.49 and 0.69).  At 2^24 two split levels no
+// longer divide every class, and 1.3 ms leave little to gain.
 constexpr uint64_t kSmallPairs = (uint64_t)1 << 22;
 template <int W>
 static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipStream_t s);
@@ -1671,8 +1673,11 @@ __global__ __launch_bounds__(64) void k_async_done(DoneArgs g)
 
 }  // namespace
 
-// up to this many pairs every candidate is sorted instead of selected first
-constexpr size_t kSortAllPairs = (size_t)1 << 19;
+// Up to this many pairs every candidate is sorted instead of selected first:
+// the selection's twelve launches cost more than sorting what they would drop
+// (ms per search with the sort and with the selection, the cases above: 2^15
+// pairs 0.21 and 0.26, 2^19 0.34 and 0.39, 2^20 0.44 and 0.48, 2^21 0.49 and 0.43).
+constexpr size_t kSortAllPairs = (size_t)1 << 20;
 
 // dev_levels, dev_rounds: split levels and small-split rounds queued (what they
 // leave undivided fails the call with kStatSplit)
@@ -1838,8 +1843,7 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
                       (uint64_t)k, d_stat, d_result};
     if (Pb <= kSortAllPairs) {
         // all candidates sorted (the record buffers are free by now): the pool
-        // is in key order, so ties keep ascending keys.  A selection of
-        // twelve launches ahead of the sort of k took 110 us, this 60.
+        // is in key order, so ties keep ascending keys
         uint64_t *fk[1][2] = {{k_lo[0], k_lo[1]}};
         uint32_t *fi[2] = {(uint32_t *)v[0], (uint32_t *)v[1]};
         const int rr = merge_sort<1>(fk, fi, p_score[0], Pb, s, nullptr, d_V);
@@ -1877,8 +1881,8 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
 
 // A search of one small class batch through the asynchronous search with as
 // many split levels as it should need, its result and counts read back once.
-// false: outside that scope, or (never seen) not divided in those levels; the
-// caller then runs the search step by step.
+// false: outside that scope, or not divided in those levels; the caller then
+// runs the search step by step.
 template <int W>
 static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipStream_t s)
 {
@@ -1890,9 +1894,11 @@ static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out
     const uint64_t ncls = std::max<uint64_t>(choose_u64((uint64_t)(in.n - in.na + L), L), 1);
     if (ncls > kMaxBatchClasses) return false;
     if (ncls * core_count(in) > 4 * kSmallPairs) return false;  // a count matrix larger than the records
-    // one level divides a class of up to 256 * 4096 records into ranges of one
-    // tile, which the small split finishes
-    const int levels = P <= ((uint64_t)1 << 19) ? 1 : 2;
+    // One level divides a class into up to 256 ranges, and a range of up to 4096
+    // records is the small split's.  A range is rarely four times the mean, so
+    // a class of 2^18 records takes one level (of several classes the largest
+    // has about half the records); 2^22 records leave the second level 16k each.
+    const int levels = P <= ((uint64_t)1 << (ncls > 1 ? 19 : 18)) ? 1 : 2;
     HostStage &hs = ctx->stage;
     hs.reserve(256);
     ctx->setup.reset();

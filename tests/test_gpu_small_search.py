@@ -1,8 +1,8 @@
 """Searches of one small class batch (read back once, at the end) against the
 step-by-step path, which candidates() takes: the k largest of every candidate
 in exact (|A| descending, key ascending) order, bit for bit, on both sides of
-each rule (a sort of every candidate up to 2^19 pairs, a selection above; the
-step-by-step path from 2^22 pairs), with k at the edges of the sort's chunks,
+each rule (one split level up to 2^19 pairs, two above; a sort of every
+candidate up to 2^20, a selection above; the step-by-step path from 2^22), with k at the edges of the sort's chunks,
 and among scores of which most are tied.  The same errors on both paths."""
 from math import comb
 
@@ -51,7 +51,7 @@ def _compare(d, n, na, nb, E0, ks, want, **kw):
 
 
 @pytest.mark.parametrize("n,na,nb", [(12, 6, 6), (34, 3, 3)])
-@pytest.mark.parametrize("log_pairs,over", [(12, 0), (19, 0), (19, 1), (22, 0), (22, 1)])
+@pytest.mark.parametrize("log_pairs,over", [(12, 0), (19, 0), (19, 1), (20, 0), (20, 1), (22, 0), (22, 1)])
 def test_small_search_edges(n, na, nb, log_pairs, over):
     import gpu_util as gu
 
