@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from math import comb
 
 import numpy as np
 
@@ -313,6 +314,19 @@ def candidates(h, eri, norb, nalpha, nbeta, dets, coeffs, E0, ncore=0, eps=0.0, 
     cnt = C.c_int64(0)
     args = (ctx.ptr, _dev(h, torch.float64), _dev(eri, torch.float64), norb, nalpha, nbeta,
             _dev(dets, torch.uint64), _dev(coeffs, torch.float64), dets.shape[0], float(E0), C.byref(o))
+    # One pass into buffers for every pair where these are small (4.9 million
+    # candidates of 14.6 million pairs: 2.1 ms with a pass that only counts
+    # first, 1.1 so), the used part copied out; else count, then fill.
+    bound = _pair_bound(norb, nalpha, nbeta, dets.shape[0], ncore)
+    if 0 < bound <= 1 << 26:
+        try:
+            room = [torch.empty(sh, dtype=t, device=h.device) for sh, t in (
+                ((bound, 2), torch.uint64), ((bound,), torch.float64), ((bound,), torch.float64))]
+        except torch.cuda.OutOfMemoryError:
+            room = None
+        if room is not None:
+            _check(_lib.asci_candidates_device(*args, bound, *(t.data_ptr() for t in room), C.byref(cnt), _stream(dev)))
+            return tuple(t[:cnt.value].clone() for t in room)
     rc = _lib.asci_candidates_device(*args, 0, None, None, None, C.byref(cnt), _stream(dev))
     if rc not in (ASCI_OK, ASCI_ENOMEM) or (rc == ASCI_ENOMEM and cnt.value == 0):
         _check(rc)
@@ -323,6 +337,17 @@ def candidates(h, eri, norb, nalpha, nbeta, dets, coeffs, E0, ncore=0, eps=0.0, 
     _check(_lib.asci_candidates_device(*args, U, out_d.data_ptr(), out_n.data_ptr(), out_s.data_ptr(),
                                        C.byref(cnt), _stream(dev)))
     return out_d[:U], out_n[:U], out_s[:U]
+
+
+def _pair_bound(norb, nalpha, nbeta, ndets, ncore):
+    """Pairs of a core determinant and a single or double of it, which bound the
+    candidates; 0 for sizes the library refuses."""
+    if not (0 <= nalpha <= norb <= 64 and 0 <= nbeta <= norb) or ndets < 1:
+        return 0
+    va, vb = norb - nalpha, norb - nbeta
+    per = (nalpha * va + nbeta * vb + comb(nalpha, 2) * comb(va, 2) + comb(nbeta, 2) * comb(vb, 2)
+           + nalpha * va * nbeta * vb)
+    return per * (min(ncore, ndets) if ncore > 0 else ndets)
 
 
 def pt2(h, eri, norb, nalpha, nbeta, dets, coeffs, E0, ncore=0, eps=0.0, ecore=0.0, pair_buffer_bytes=0,
