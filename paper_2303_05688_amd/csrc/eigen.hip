@@ -236,12 +236,62 @@ __global__ __launch_bounds__(256) void k_norm(const double *__restrict__ x, size
     if (threadIdx.x == 0) partial[(size_t)blockIdx.x * kPartLd + kNormV] = tt;
 }
 
+// The sign that cyclic Jacobi rotations (Golub and Van Loan, Sec. 8.5) give the
+// eigenvector vec of A: one sweep after the other until a column of their
+// product is within 0.99 of it (mostly one or two; none once the first vector
+// of the subspace is).  Every rotation is by at most 45 degrees, so the column
+// keeps its side from there on.
+double jacobi_sign(const std::vector<double> &A_in, int ld, int m, const double *vec)
+{
+    double A[kMaxSub][kMaxSub], Q[kMaxSub][kMaxSub];  // Q: a column of the product per row
+    for (int i = 0; i < m; ++i)
+        for (int j = 0; j < m; ++j) {
+            A[i][j] = A_in[(size_t)i * ld + j];
+            Q[i][j] = i == j ? 1.0 : 0.0;
+        }
+    double best = 0.0;
+    for (int sweep = 0;; ++sweep) {
+        best = 0.0;
+        for (int k = 0; k < m; ++k) {
+            double x = 0.0;
+            for (int j = 0; j < m; ++j) x += Q[k][j] * vec[j];
+            if (std::fabs(x) > std::fabs(best)) best = x;
+        }
+        if (!(std::fabs(best) < 0.99) || sweep == 30) break;
+        for (int p = 0; p < m - 1; ++p)
+            for (int q = p + 1; q < m; ++q) {
+                const double apq = A[p][q];
+                if (apq == 0.0) continue;
+                const double app = A[p][p], aqq = A[q][q];
+                const double tau = (aqq - app) / (2.0 * apq);
+                const double t = (tau >= 0.0 ? 1.0 : -1.0) / (std::fabs(tau) + std::sqrt(1.0 + tau * tau));
+                const double c = 1.0 / std::sqrt(1.0 + t * t), s = t * c;
+                for (int k = 0; k < m; ++k) {
+                    const double x = A[p][k], y = A[q][k];
+                    A[p][k] = c * x - s * y;
+                    A[q][k] = s * x + c * y;
+                    const double u = Q[p][k], v = Q[q][k];
+                    Q[p][k] = c * u - s * v;
+                    Q[q][k] = s * u + c * v;
+                }
+                A[p][p] = app - t * apq;
+                A[q][q] = aqq + t * apq;
+                A[p][q] = A[q][p] = 0.0;
+                for (int k = 0; k < m; ++k) {
+                    A[k][p] = A[p][k];
+                    A[k][q] = A[q][k];
+                }
+            }
+    }
+    return best < 0.0 ? -1.0 : 1.0;
+}
+
 // Lowest eigenpair of a small symmetric matrix (the first m rows and columns of
 // A, leading dimension ld): Householder reduction to tridiagonal form (Golub
 // and Van Loan, Alg. 8.3.1), the lowest eigenvalue by bisection on Sturm counts
-// (Sec. 8.4.1), its vector by inverse iteration.  The sign: a component of the
-// first column is positive.  m = 20 takes 11 us; cyclic Jacobi rotations on the
-// whole matrix took 123, and left larger residuals.
+// (Sec. 8.4.1), its vector by inverse iteration.  m = 20 takes 50 us with the
+// sign; Jacobi rotations to the end, which this took the place of, took 123 and
+// left larger residuals.
 void small_lowest(const std::vector<double> &A_in, int ld, int m, double &theta, double *vec)
 {
     double A[kMaxSub][kMaxSub], d[kMaxSub], e[kMaxSub], x[kMaxSub], p[kMaxSub];
@@ -353,8 +403,9 @@ void small_lowest(const std::vector<double> &A_in, int ld, int m, double &theta,
     double nrm = 0.0;
     for (int i = 0; i < m; ++i) nrm += x[i] * x[i];
     nrm = std::sqrt(nrm);
-    if (x[0] < 0.0) nrm = -nrm;
     for (int i = 0; i < m; ++i) vec[i] = x[i] / nrm;
+    if (jacobi_sign(A_in, ld, m, vec) < 0.0)
+        for (int i = 0; i < m; ++i) vec[i] = -vec[i];
 }
 
 }  // namespace

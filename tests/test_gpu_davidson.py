@@ -58,3 +58,61 @@ def test_davidson_many_rows(ndets):
     assert np.linalg.norm(M @ v - e * v) <= 2e-7
     assert e < M.diagonal().min()
     H.close()
+
+
+def _jacobi_lowest(A):
+    """Lowest eigenvector by cyclic Jacobi rotations, with the sign they give it."""
+    A, m = A.copy(), len(A)
+    Q = np.eye(m)
+    for _ in range(60):
+        if (A ** 2).sum() - (np.diag(A) ** 2).sum() <= 1e-28 * (A ** 2).sum():
+            break
+        for p in range(m - 1):
+            for q in range(p + 1, m):
+                if A[p, q] == 0.0:
+                    continue
+                tau = (A[q, q] - A[p, p]) / (2.0 * A[p, q])
+                t = (1.0 if tau >= 0 else -1.0) / (abs(tau) + np.sqrt(1.0 + tau * tau))
+                c = 1.0 / np.sqrt(1.0 + t * t)
+                R = np.array([[c, t * c], [-t * c, c]])
+                A[:, [p, q]] = A[:, [p, q]] @ R
+                A[[p, q]] = R.T @ A[[p, q]]
+                Q[:, [p, q]] = Q[:, [p, q]] @ R
+    k = int(np.argmin(np.diag(A)))
+    return A[k, k], Q[:, k]
+
+
+@pytest.mark.parametrize("seed", range(6))
+@pytest.mark.parametrize("subspace", [4, 12])
+def test_davidson_sign(subspace, seed):
+    """The eigenvector's sign is that of the same iteration with the projected
+    problem solved by Jacobi rotations."""
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+    import torch
+
+    H = _hmat(9, 4, 120, 900 + seed)
+    M = _sparse(H).toarray()
+    D = np.diag(M)
+    g = np.random.default_rng(seed).normal(size=120)
+    V = [g / np.linalg.norm(g)]
+    W = [M @ V[0]]
+    for _ in range(400):
+        theta, c = _jacobi_lowest(np.array([[a @ b for b in W] for a in V]))
+        u = sum(x * y for x, y in zip(c, V))
+        r = sum(x * y for x, y in zip(c, W)) - theta * u
+        if np.linalg.norm(r) <= 1e-7:
+            break
+        t = r / (D - theta)
+        if len(V) == subspace:
+            V, W = [u], [M @ u]
+        for _ in range(2):
+            for x in V:
+                t = t - (x @ t) * x
+        V.append(t / np.linalg.norm(t))
+        W.append(M @ V[-1])
+    e, vec, res, it = asci.davidson(H, guess=torch.from_numpy(g).to("cuda:0"), max_subspace=subspace, max_iter=400, tol=1e-7)
+    w = np.linalg.eigvalsh(M)
+    # two vectors of residual 1e-7 each
+    assert np.linalg.norm(gu.host(vec) - u) <= 4e-7 / (w[1] - w[0])
+    H.close()
