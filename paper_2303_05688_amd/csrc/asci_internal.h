@@ -417,6 +417,14 @@ struct BucketArgs {
     int finish_tok = -1;
     // the device-driven variant: nfinal and V are then bounds, the count is on the device
     const uint32_t *dn_V = nullptr, *dn_nfinal = nullptr;
+    // A pilot: the number of scores that the caller keeps (0: none).  A share of
+    // the final segments is finished first and their k-th |A| bounds the rest
+    // from below.  Then runs is required (distinct targets are added to it) and
+    // thr, dev and eps > 0 are excluded.
+    uint64_t pilot_k = 0;
+    uint32_t *runs = nullptr;
+    uint32_t h_runs = 0;                 // its value on the host, once V is there
+    const double *bounds = nullptr;      // with thr or a pilot and both tables: k_diag_bounds (optional)
     const uint32_t *dn_levels = nullptr, *dn_nlarge = nullptr, *dn_overflow = nullptr;  // nonzero: not divided / a list overflowed
     int dev_levels = 0, dev_rounds = 1;  // split levels and small-split rounds queued
     // where the candidates lie: a bit per slot, a count and an output offset per tile of slots
@@ -439,6 +447,11 @@ double bucket_pt2(BucketArgs &b, Arena &ar, hipStream_t s, HostStage &hs);
 // The same sort-and-accumulate with no count read back (asynchronous search):
 // launches sized for host bounds, b.dev_levels split levels, the counts in
 // b.dn_*.
+// out[4]: the bounds that reject targets under a threshold; etab: the table of
+// E(beta), ntab strings, tmp: a double for every 256 of them
+void bucket_diag_bounds(const double *jk, int n, int na, int nb, double E0, double ecore, const double *etab, uint32_t ntab,
+                        double *tmp, double *out, hipStream_t s);
+
 template <int W>
 void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s);
 template <int W>

@@ -849,15 +849,33 @@ struct FinishArgs {
     uint32_t *tcnt;             // candidates per tile of kSlotTile slots (cleared by the caller)
     uint32_t nfinal;
     const uint32_t *dn_final;   // device: final segments (nfinal is then a bound; optional)
+    int part;                   // kAll, or the final segments of a pilot, or all but those
+    uint32_t *runs;             // distinct targets are added to it (optional)
     PsiSet psi;                 // input determinants (exclusion)
     int na, nb;
     int stage_x;                // some strings have no table: J-K (triangle) and h_pp are staged in LDS
     uint32_t tab_bytes;         // LDS of the staged tables
     uint32_t wave_bytes;        // LDS of one wavefront
     uint32_t amax;              // alpha strings one wavefront caches (a power of two)
+    const double *bounds;       // k_diag_bounds: with a threshold, targets are rejected by a bound (optional)
+    uint32_t qcap;              // targets that a wavefront queues
 };
+constexpr uint32_t kMinRanks = 256;
 
 constexpr uint32_t kSlotTile = 4096;  // slots per collect tile
+enum { kAll = 0, kPilotPart = 1, kRestPart = 2 };
+constexpr uint32_t kPilot = 16;  // a pilot takes every 16th final segment
+
+// final segments of a part, and the i-th of them
+__host__ __device__ __forceinline__ uint32_t part_count(uint32_t nf, int part)
+{
+    const uint32_t np = (nf + kPilot - 1u) / kPilot;
+    return part == kAll ? nf : (part == kPilotPart ? np : nf - np);
+}
+__device__ __forceinline__ uint32_t part_index(uint32_t i, int part)
+{
+    return part == kAll ? i : (part == kPilotPart ? i * kPilot : i + i / (kPilot - 1u) + 1u);
+}
 
 // The tables a finish reads and the electron counts.  The counts are the same
 // for every string of a search, so that the walks over a string's set bits
@@ -1074,6 +1092,38 @@ __device__ __forceinline__ void scan_counters(uint32_t *cnt)
     }
 }
 
+// The values [p0, p1) added in order: eight or four whole ones at a time, then
+// the last three at most (past the end +0.0, which leaves the sum's bits alone:
+// it starts at +0.0 and so never is -0.0).  Eight at a time with a bound check
+// on each took three times the instructions.
+template <int IT>
+__device__ __forceinline__ double run_sum(const WaveLds<IT> &S, uint32_t p0, uint32_t p1)
+{
+    double sum = 0.0;
+    uint32_t j = p0;
+    for (; j + 8 <= p1; j += 8) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = S.val[j + (uint32_t)k];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sum = sum + v[k];
+    }
+    if (j + 4 <= p1) {
+        double v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = S.val[j + (uint32_t)k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum = sum + v[k];
+        j += 4;
+    }
+    double v[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] = S.val[j + (uint32_t)k < p1 ? j + (uint32_t)k : (uint32_t)WaveLds<IT>::CAP];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sum = sum + v[k];
+    return sum;
+}
+
 // marks the slots [start, start + written) and counts them in their tiles
 __device__ __forceinline__ void mark_slots(const FinishArgs &f, uint32_t start, uint32_t written)
 {
@@ -1144,10 +1194,115 @@ __device__ __forceinline__ void finish_single(const FinishArgs &f, const Diag<JL
     mark_slots(f, sg.start, 1u);
 }
 
-// one final segment of at most 64 * IT records, by one wavefront
+// Targets whose sum a bound on the diagonal element did not reject: a
+// wavefront's own queue in LDS, evaluated 64 at a time.
+template <int W>
+struct Queue {
+    uint64_t *lo, *hi;
+    double *sum;
+    uint32_t *slot;
+    uint32_t n;
+};
+template <int W>
+constexpr size_t queue_entry()
+{
+    return 8 * W + 12;
+}
+
+// the last (at most 64) targets of the queue: diagonal, score, exclusion, slot
+template <int W, bool JL>
+__device__ __forceinline__ void finish_queued(const FinishArgs &f, const Diag<JL> &D, Queue<W> &Q, uint64_t thr)
+{
+    const uint32_t lane = threadIdx.x & 63, cnt = min(Q.n, 64u);
+    wave_sync();
+    Q.n -= cnt;
+    if (lane < cnt) {
+        const uint32_t i = Q.n + lane;
+        const uint64_t lo = Q.lo[i], hi = W == 2 ? Q.hi[i] : 0ull;
+        const double sum = Q.sum[i];
+        const uint32_t at = Q.slot[i];
+        const int n = f.n;
+        const uint64_t nmask = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
+        const uint64_t a = W == 1 ? (lo >> n) : hi, b = W == 1 ? (lo & nmask) : lo;
+        const double den = f.E0 - (n <= 32 ? diag_tab<JL, uint32_t>(D, f.ecore, (uint32_t)a, (uint32_t)b)
+                                           : diag_tab<JL, uint64_t>(D, f.ecore, a, b));
+        const double score = sum / den;
+        if (abs_order(score) >= thr && !psi_contains(f.psi, lo, hi)) {
+            f.clo[at] = lo;
+            if (W == 2) f.chi[at] = hi;
+            if (f.cnum) f.cnum[at] = sum;
+            f.cscore[at] = score;
+            atomicOr(&f.mask[at >> 6], 1ull << (at & 63u));
+            atomicAdd(&f.tcnt[at / kSlotTile], 1u);
+        }
+    }
+    wave_sync();
+}
+
+__device__ __forceinline__ double readlane_f64(double x, int l)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    return __longlong_as_double((long long)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l) |
+                                            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l) << 32)));
+}
+
+// sum over the lanes, by register moves
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_from_f64(double x)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    return __longlong_as_double((long long)((uint64_t)dpp_from<CTRL, ROWS>((uint32_t)u) |
+                                            ((uint64_t)dpp_from<CTRL, ROWS>((uint32_t)(u >> 32)) << 32)));
+}
+__device__ __forceinline__ double wave_sum(double x)
+{
+    x = x + dpp_from_f64<0x111, 0xF>(x);
+    x = x + dpp_from_f64<0x112, 0xF>(x);
+    x = x + dpp_from_f64<0x114, 0xF>(x);
+    x = x + dpp_from_f64<0x118, 0xF>(x);
+    x = x + dpp_from_f64<0x142, 0xA>(x);
+    x = x + dpp_from_f64<0x143, 0xC>(x);
+    return readlane_f64(x, 63);
+}
+
+// the smaller one; NaN if either is
+__device__ __forceinline__ double min_nan(double x, double m)
+{
+    return m != m || m <= x ? m : x;
+}
+
+// A lower bound of the sum of nb of the lanes' v, all of the lanes in `fixed`
+// among them and the others from `free`: for every level l, the sum of the
+// nfree smallest v is at least nfree l + sum over free of min(v - l, 0), and
+// equal to it where l is the nfree-th smallest.  l follows the strings that
+// come by; it only decides how tight the bound is.
+__device__ __forceinline__ double least_columns(double v, uint64_t fixed, uint64_t free, int nb, double step, double &level)
+{
+    const int lane = threadIdx.x & 63;
+    const int nfree = nb - (int)__popcll(fixed);
+    const bool below = !(v >= level) && ((free >> lane) & 1ull);
+    const double sum = wave_sum(((fixed >> lane) & 1ull) ? v : (below ? v - level : 0.0)) + (double)nfree * level;
+    level = level + (double)(nfree - (int)__popcll(__ballot(below))) * step;
+    return sum;
+}
+
+// E(s) of one uniform string from its table, lane q the orbital q
+template <bool JL, typename M>
+__device__ __forceinline__ double spin_e_lanes(const Diag<JL> &D, int spin, M s)
+{
+    const uint32_t lane = threadIdx.x & 63, n = (uint32_t)D.n;
+    const uint64_t below = (uint64_t)s & ((1ull << lane) - 1ull);
+    uint32_t r = 0;
+    if (lane < n && (((uint64_t)s >> lane) & 1ull))
+        r = D.binom[min((uint32_t)__popcll(below) + 1u, (uint32_t)D.ne[spin]) * (n + 1u) + lane];
+    r = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(r), 63);
+    return D.e[spin][min(r, D.last[spin])];
+}
+
+// one final segment of at most 64 * IT records, by one wavefront; its distinct keys
 template <int W, int IT, bool JL>
-__device__ __forceinline__ void finish_segment(const FinishArgs &f, const Diag<JL> &D, WaveLds<IT> &S, double *acache,
-                                               const Seg &sg)
+__device__ __forceinline__ uint32_t finish_segment(const FinishArgs &f, const Diag<JL> &D, WaveLds<IT> &S, double *acache,
+                                               const Seg &sg, uint64_t thr, bool prune, double &level, Queue<W> &Q)
 {
     using M = std::conditional_t<W == 1, uint32_t, uint64_t>;  // a spin string
     constexpr int CAP = WaveLds<IT>::CAP;
@@ -1374,14 +1529,81 @@ __device__ __forceinline__ void finish_segment(const FinishArgs &f, const Diag<J
         if (lane == 0) S.ix[nruns] = (uint16_t)size;
         wave_sync();
     }
-    // Runs, 64 at a time: key, diagonal, sum in record order, score, exclusion;
-    // a ballot places the surviving candidates, compacted, in run order.
-    // thr: a lower bound of the final k-th |A| from earlier class batches, if any
-    const uint64_t thr = f.thr ? *f.thr : 0ull;
+    const auto run_key = [&](uint32_t w, uint64_t &lo, uint64_t &hi) {
+        if (multi) {
+            lo = gk[w];
+            hi = W == 2 ? gh[w] : 0ull;
+        } else if (packed) {
+            const int d = for_bit_runs(var_lo, 0, [&](int s, uint64_t m, int to) { lo |= ((uint64_t)(w >> to) & m) << s; });
+            if (W == 2)
+                (void)for_bit_runs(var_hi, d, [&](int s, uint64_t m, int to) { hi |= ((uint64_t)(w >> to) & m) << s; });
+        } else if (npass) {
+            key_put<W>(w, low, n, lo, hi);
+        }
+    };
     // a score is below thr for certain where |N| < tlow |E0 - H_aa| (the margin
     // covers the roundings of both sides; no test for a bound that is not finite)
     const double tlow = thr < 0x7FE0000000000000ull ? __longlong_as_double((long long)thr) * (1.0 - 0x1p-40) : 0.0;
     const uint32_t amask = f.amax - 1u;
+    if (prune) {
+        // Sums first; a run goes to the queue unless |N| < tlow times a bound of
+        // its denominator: E(alpha), a least E(beta) and the least sum of columns
+        // that the segment's beta strings can have, less a margin far above what
+        // the roundings of either side can amount to.
+        const uint64_t bfix = W == 1 ? (and_lo & nmask) : and_lo, bfree = W == 1 ? (var_lo & nmask) : var_lo;
+        const double margin = f.bounds[0], emin = f.bounds[1], step = f.bounds[3];
+        uint32_t nq = 0;
+        double lb_last = 0.0, lb_carry = 0.0;  // of the last alpha string so far, and at the batch's start
+        for (uint32_t base = 0; base < nruns; base += 64) {
+            const uint32_t u = base + (uint32_t)lane;
+            const bool act = u < nruns;
+            double sum = 0.0, lb = 0.0;
+            uint32_t w = 0;
+            uint64_t lo = and_lo, hi = and_hi;
+            bool ahead = false;
+            if (act) {
+                const uint32_t h0 = S.ix[u], p0 = h0 & 0x7FFFu, p1 = (uint32_t)S.ix[u + 1] & 0x7FFFu;
+                ahead = (h0 >> 15) != 0u;
+                w = S.ck[u];
+                sum = run_sum(S, p0, p1);
+                if (ahead) run_key(w, lo, hi);
+            }
+            const M a = (M)(W == 1 ? (lo >> n) : hi);
+            const uint64_t heads = __ballot(ahead);
+            for (uint64_t fresh = heads; fresh; fresh &= fresh - 1ull) {
+                const int hl = __ffsll((long long)fresh) - 1;
+                M as = (M)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)a, hl);
+                if (W == 2) as |= (M)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)a >> 32), hl) << 32);
+                const double e = spin_e_lanes(D, 0, as);
+                const double cq = lane < n ? column_sum(D, as, (uint32_t)lane) : 0.0;
+                const double x = least_columns(cq, bfix, bfree, D.ne[1], step, level);
+                const double b = (((f.ecore + e) + emin) + x - f.E0) - margin;
+                if (lane >= hl) lb = b;
+                lb_last = b;
+            }
+            if (heads == 0ull || lane < __ffsll((long long)heads) - 1) lb = lb_carry;
+            lb_carry = lb_last;
+            const double least = tlow * lb;
+            const bool keep = act && !(lb > 0.0 && least > 1e-280 && fabs(sum) < least);
+            const uint64_t kb = __ballot(keep);
+            const uint32_t cnt = (uint32_t)__popcll(kb);
+            while (Q.n + cnt > f.qcap) finish_queued<W, JL>(f, D, Q, thr);
+            if (keep) {
+                const uint32_t at = (uint32_t)__popcll(kb & lt), i = Q.n + at;
+                if (!ahead) run_key(w, lo, hi);
+                Q.lo[i] = lo;
+                if (W == 2) Q.hi[i] = hi;
+                Q.sum[i] = sum;
+                Q.slot[i] = sg.start + nq + at;
+            }
+            Q.n += cnt;
+            nq += cnt;
+        }
+        wave_sync();
+        return nruns;
+    }
+    // Runs, 64 at a time: key, diagonal, sum in record order, score, exclusion;
+    // a ballot places the surviving candidates, compacted, in run order.
     uint32_t written = 0, nalpha = 0;
     double ea_last = 0.0;  // E(alpha) of the last string so far
     for (uint32_t base = 0; base < nruns; base += 64) {
@@ -1397,17 +1619,7 @@ __device__ __forceinline__ void finish_segment(const FinishArgs &f, const Diag<J
             p0 = h0 & 0x7FFFu;
             p1 = (uint32_t)S.ix[u + 1] & 0x7FFFu;
             ahead = (h0 >> 15) != 0u;
-            const uint32_t w = S.ck[u];
-            if (multi) {
-                lo = gk[w];
-                hi = W == 2 ? gh[w] : 0ull;
-            } else if (packed) {
-                const int d = for_bit_runs(var_lo, 0, [&](int s, uint64_t m, int to) { lo |= ((uint64_t)(w >> to) & m) << s; });
-                if (W == 2)
-                    (void)for_bit_runs(var_hi, d, [&](int s, uint64_t m, int to) { hi |= ((uint64_t)(w >> to) & m) << s; });
-            } else if (npass) {
-                key_put<W>(w, low, n, lo, hi);
-            }
+            run_key(S.ck[u], lo, hi);
         }
         const M a = (M)(W == 1 ? (lo >> n) : hi), b = (M)(W == 1 ? (lo & nmask) : lo);
         // without a threshold every candidate asks the exclusion filter: its
@@ -1464,17 +1676,8 @@ __device__ __forceinline__ void finish_segment(const FinishArgs &f, const Diag<J
         if (!D.e[1] && act) eb = spin_energy_u(D, D.ne[1], b);
         if (act) {
             if (f.eps <= 0.0) {
-                // the run's values, in sorted (= record, ascending core) order,
-                // eight in flight at a time, added in order (past the end +0.0,
-                // which leaves the sum's bits alone: it starts at +0.0 and so
-                // never is -0.0)
-                for (uint32_t j = p0; j < p1; j += 8) {
-                    double v[8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) v[k] = S.val[j + (uint32_t)k < p1 ? j + (uint32_t)k : (uint32_t)CAP];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) sum = sum + v[k];
-                }
+                // the run's values, in sorted (= record, ascending core) order
+                sum = run_sum(S, p0, p1);
                 keep = true;
             }
             {
@@ -1533,6 +1736,7 @@ __device__ __forceinline__ void finish_segment(const FinishArgs &f, const Diag<J
         written += (uint32_t)__popcll(kb);
     }
     mark_slots(f, sg.start, written);
+    return nruns;
 }
 
 // A resident grid: every wavefront strides over the final segments on its own
@@ -1542,7 +1746,8 @@ __device__ __forceinline__ void finish_segment(const FinishArgs &f, const Diag<J
 // 4096 records, with a barrier between phases, issued VALU work 35 % of the time
 // and waited 72 %; per launch, then and now: 9.6e8 records of 24e30o 24.3 and
 // 14.4 ms, 1.3e8 of 16e20o 2.98 and 1.68 ms, 9.7e7 two-word ones of 20e36o 7.5
-// and 5.45 ms.
+// and 5.45 ms.  Under a threshold the bounds leave 2 of 134 targets a segment
+// of 24e30o to evaluate (8 of 103 of 16e20o): 10.1 ms per launch.
 template <int W, int IT, bool JL>
 __global__ __launch_bounds__(64 * kFinishWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_finish(FinishArgs f)
 {
@@ -1575,12 +1780,141 @@ __global__ __launch_bounds__(64 * kFinishWaves) __attribute__((amdgpu_waves_per_
     double *acache = reinterpret_cast<double *>(mine + ((sizeof(WaveLds<IT>) + 15) & ~size_t(15)));
     if ((tid & 63) < 2) S.zero[tid & 63] = 0.0;
     __syncthreads();
-    const uint32_t nf = dev_count(f.nfinal, f.dn_final);
-    for (uint32_t sidx = blockIdx.x + gridDim.x * wv; sidx < nf; sidx += gridDim.x * kFinishWaves) {
-        const Seg sg = f.finals[sidx];
-        if (seg_single(sg)) finish_single<W, IT, JL>(f, D, S, sg);
-        else finish_segment<W, IT, JL>(f, D, S, acache, sg);
+    const uint32_t nf = part_count(dev_count(f.nfinal, f.dn_final), f.part);
+    // thr: a lower bound of the final k-th |A|, from a pilot or earlier class batches, if any
+    const uint64_t thr = f.thr ? *f.thr : 0ull;
+    // the queue takes the place of the alpha cache, which the pruned path has no use for
+    const bool prune = thr != 0ull && !(f.eps > 0.0) && f.bounds;
+    double level = prune ? f.bounds[2] : 0.0;
+    Queue<W> Q;
+    Q.lo = reinterpret_cast<uint64_t *>(acache);
+    Q.hi = W == 2 ? Q.lo + f.qcap : nullptr;
+    Q.sum = reinterpret_cast<double *>(Q.lo + W * f.qcap);
+    Q.slot = reinterpret_cast<uint32_t *>(Q.sum + f.qcap);
+    Q.n = 0;
+    uint32_t runs = 0;
+    const uint32_t step = gridDim.x * kFinishWaves;
+    uint32_t i = blockIdx.x + gridDim.x * wv;
+    Seg next = i < nf ? f.finals[part_index(i, f.part)] : Seg{0u, 0u, 0u};
+    for (; i < nf; i += step) {
+        const Seg sg = next;
+        if (nf - i > step) next = f.finals[part_index(i + step, f.part)];
+        if (seg_single(sg)) {
+            finish_single<W, IT, JL>(f, D, S, sg);
+            ++runs;
+        } else {
+            runs += finish_segment<W, IT, JL>(f, D, S, acache, sg, thr, prune, level, Q);
+        }
     }
+    while (Q.n) finish_queued<W, JL>(f, D, Q, thr);
+    if (f.runs && (tid & 63) == 0 && runs) atomicAdd(f.runs, runs);
+}
+
+// ---------------------------------------------------------------- bounds
+// out[i] = least of x[256 i, 256 i + 256)
+__global__ __launch_bounds__(256) void k_block_min(const double *__restrict__ x, uint32_t n, double *__restrict__ out)
+{
+    __shared__ double s_m[4];
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    double m = i < n ? x[i] : __longlong_as_double(0x7FF0000000000000ll);
+    for (int d = 32; d >= 1; d >>= 1) m = min_nan(__shfl_xor(m, d, 64), m);
+    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) out[blockIdx.x] = min_nan(min_nan(s_m[0], s_m[1]), min_nan(s_m[2], s_m[3]));
+}
+
+// What bounds a diagonal element from below.
+//   out[0]  the margin that covers the roundings of a bound and of a diagonal
+//           element: each adds at most n^2 + n table entries, so it is off by
+//           less than 2^-40 of the sum of all their magnitudes (n <= 64)
+//   out[1]  the least E(beta)
+//   out[2]  a first level for least_columns, out[3] the step of its search: from
+//           the columns of na average orbitals
+__global__ __launch_bounds__(1024) void k_diag_bounds(const double *__restrict__ jk, int n, int na, int nb, double E0,
+                                                      double ecore, const double *__restrict__ emin, uint32_t nmin,
+                                                      double *__restrict__ out)
+{
+    __shared__ double s_t[16], s_m[16], s_c[64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int q = wv; q < n; q += 16) {
+        const double c = wave_sum(lane < n ? jk[q * n + lane] : 0.0);
+        if (lane == 0) s_c[q] = c * ((double)na / n);
+    }
+    double t = 0.0, m = __longlong_as_double(0x7FF0000000000000ll);
+    for (int i = threadIdx.x; i < 2 * n * n + n; i += 1024) t = t + fabs(jk[i]);
+    for (uint32_t i = threadIdx.x; i < nmin; i += 1024) m = min_nan(emin[i], m);
+    t = wave_sum(t);
+    for (int d = 32; d >= 1; d >>= 1) m = min_nan(__shfl_xor(m, d, 64), m);
+    if (lane == 0) {
+        s_t[wv] = t;
+        s_m[wv] = m;
+    }
+    __syncthreads();
+    if (wv == 0) {
+        const double c = lane < n ? s_c[lane] : 0.0;
+        int rank = 0;
+        for (int r = 0; r < n; ++r) rank += s_c[r] < c || (s_c[r] == c && r < lane) ? 1 : 0;
+        const double lo = readlane_f64(c, max(__ffsll((long long)__ballot(lane < n && rank == 0)) - 1, 0));
+        const double hi = readlane_f64(c, max(__ffsll((long long)__ballot(lane < n && rank == n - 1)) - 1, 0));
+        const double lev = readlane_f64(c, max(__ffsll((long long)__ballot(lane < n && rank == max(nb - 1, 0))) - 1, 0));
+        if (lane == 0) {
+            for (int i = 1; i < 16; ++i) {
+                t = t + s_t[i];
+                m = min_nan(s_m[i], m);
+            }
+            out[0] = 0x1p-36 * ((t + fabs(E0)) + fabs(ecore));
+            out[1] = m;
+            out[2] = lev;
+            out[3] = (hi - lo) / (2.0 * n);
+        }
+    }
+}
+
+// ---------------------------------------------------------------- pilot
+// |A| in bins of the exponent and five mantissa bits, 2^-56 to 2^8 (what lies
+// outside goes to the first or last)
+constexpr uint32_t kPilotBins = 2048, kPilotBase = (1023u - 56u) << 5;
+__device__ __forceinline__ uint32_t pilot_bin(double score)
+{
+    const uint32_t x = (uint32_t)(abs_order(score) >> 47);
+    return x <= kPilotBase ? 0u : min(x - kPilotBase, kPilotBins - 1u);
+}
+
+// the candidates of the pilot's segments by bin of |A|, one wavefront a segment
+__global__ __launch_bounds__(1024) void k_pilot_hist(const Seg *__restrict__ finals, uint32_t nf,
+                                                     const unsigned long long *__restrict__ mask,
+                                                     const double *__restrict__ score, uint32_t *__restrict__ hist)
+{
+    __shared__ uint32_t s_h[kPilotBins];
+    for (uint32_t t = threadIdx.x; t < kPilotBins; t += 1024) s_h[t] = 0u;
+    __syncthreads();
+    const uint32_t np = part_count(nf, kPilotPart), lane = threadIdx.x & 63;
+    for (uint32_t i = blockIdx.x * 16 + (threadIdx.x >> 6); i < np; i += gridDim.x * 16) {
+        const Seg sg = finals[part_index(i, kPilotPart)];
+        const uint32_t m = seg_single(sg) ? 1u : sg.size;
+        for (uint32_t r = lane; r < m; r += 64) {
+            const uint32_t at = sg.start + r;
+            if ((mask[at >> 6] >> (at & 63u)) & 1ull) atomicAdd(&s_h[pilot_bin(score[at])], 1u);
+        }
+    }
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < kPilotBins; t += 1024)
+        if (s_h[t]) atomicAdd(&hist[t], s_h[t]);
+}
+
+// the lower edge of the bin that holds the k-th largest |A|; 0 with fewer
+__global__ __launch_bounds__(1024) void k_pilot_pick(const uint32_t *__restrict__ hist, uint64_t k,
+                                                     uint64_t *__restrict__ thr)
+{
+    __shared__ uint32_t s_tmp[16];
+    // bins in descending order, two a thread
+    const uint32_t b = kPilotBins - 1u - 2u * threadIdx.x;
+    const uint32_t x = hist[b], y = hist[b - 1u];
+    uint32_t tot;
+    const uint64_t before = block_scan<16>(x + y, s_tmp, tot);
+    if (threadIdx.x == 0 && tot < k) *thr = 0ull;
+    if (before < k && k <= before + x) *thr = b ? (uint64_t)(b + kPilotBase) << 47 : 0ull;
+    else if (before + x < k && k <= before + x + y) *thr = b > 1u ? (uint64_t)(b - 1u + kPilotBase) << 47 : 0ull;
 }
 
 // ---------------------------------------------------------------- collect
@@ -1675,16 +2009,20 @@ size_t bucket_workspace_bytes(size_t P, size_t nc, int W, int finish_cap)
 constexpr size_t kFinishLdsBudget = 80 * 1024;
 
 template <int W, int IT>
-static int launch_finish(FinishArgs &fa, const BucketArgs &b, uint32_t nf, hipStream_t s, Profiler *prof)
+static int launch_finish(FinishArgs &fa, const BucketArgs &b, uint32_t nf, int part, hipStream_t s, Profiler *prof)
 {
+    fa.part = part;
+    nf = part_count(nf, part);
     const size_t base = (sizeof(WaveLds<IT>) + 15) & ~size_t(15);
     const size_t n = (size_t)b.n, entry = n * 8;  // of the alpha cache
     // strings without a table are evaluated from X and h_pp, those with one are
     // ranked; J is staged where every wavefront keeps room for two alpha strings
     fa.stage_x = !b.st.e[0] || !b.st.e[1] ? 1 : 0;
     size_t tab = (fa.stage_x ? (n * (n - 1) / 2 + n) * 8 : 0) + (b.st.binom ? (size_t)(b.st.kmax + 1) * (n + 1) * 4 : 0);
+    // a wavefront's alpha strings and its queue share one region
+    auto region = [&](size_t strings) { return std::max(strings * entry, fa.bounds ? 64 * queue_entry<W>() : 0); };
     auto total = [&](size_t tables, size_t strings) {
-        return ((tables + 15) & ~size_t(15)) + kFinishWaves * ((base + strings * entry + 15) & ~size_t(15));
+        return ((tables + 15) & ~size_t(15)) + kFinishWaves * ((base + region(strings) + 15) & ~size_t(15));
     };
     const bool jl = total(tab + n * (n + 1) / 2 * 8, 2) <= kFinishLdsBudget;
     if (jl) tab += n * (n + 1) / 2 * 8;
@@ -1692,7 +2030,8 @@ static int launch_finish(FinishArgs &fa, const BucketArgs &b, uint32_t nf, hipSt
     fa.amax = 1;
     while (fa.amax < 32 && total(tab, 2 * fa.amax) <= kFinishLdsBudget) fa.amax *= 2;
     fa.tab_bytes = (uint32_t)tab;
-    fa.wave_bytes = (uint32_t)((base + fa.amax * entry + 15) & ~size_t(15));
+    fa.wave_bytes = (uint32_t)((base + region(fa.amax) + 15) & ~size_t(15));
+    fa.qcap = (uint32_t)std::min<size_t>(region(fa.amax) / queue_entry<W>(), 128);
     const size_t lds = tab + (size_t)kFinishWaves * fa.wave_bytes;
     void (*kernel)(FinishArgs) = jl ? k_finish<W, IT, true> : k_finish<W, IT, false>;
     const void *fn = (const void *)kernel;
@@ -1706,7 +2045,8 @@ static int launch_finish(FinishArgs &fa, const BucketArgs &b, uint32_t nf, hipSt
     const uint32_t grid = std::min<uint32_t>(nf, (uint32_t)std::max(1, ncu * std::max(per_cu, 1)));
     // bytes: every record read once; the candidates it writes are added once
     // their number is known (finish_bytes)
-    ProfScope ps(prof, "finish", (8.0 * W + 8.0) * (double)b.P, s);
+    ProfScope ps(prof, part == kPilotPart ? "finish_pilot" : "finish",
+                 (8.0 * W + 8.0) * (double)b.P / (part == kPilotPart ? kPilot : 1), s);
     kernel<<<grid, NT, lds, s>>>(fa);
     ASCI_LAUNCH_CHECK();
     return ps.tok;
@@ -1909,10 +2249,29 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         fa.nfinal = nf;
         fa.dn_final = dev ? ctr + kCtrFinal : nullptr;
         fa.psi = b.psi;
+        fa.bounds = b.bounds;
         b.prof = prof;
-        if (cap == 512) b.finish_tok = launch_finish<W, 8>(fa, b, nf, s, prof);
-        else if (cap == 256) b.finish_tok = launch_finish<W, 4>(fa, b, nf, s, prof);
-        else b.finish_tok = launch_finish<W, 2>(fa, b, nf, s, prof);
+        auto finish = [&](int part) {
+            if (cap == 512) b.finish_tok = launch_finish<W, 8>(fa, b, nf, part, s, prof);
+            else if (cap == 256) b.finish_tok = launch_finish<W, 4>(fa, b, nf, part, s, prof);
+            else b.finish_tok = launch_finish<W, 2>(fa, b, nf, part, s, prof);
+        };
+        fa.runs = b.pilot_k > 0 ? b.runs : nullptr;
+        if (b.pilot_k > 0) {
+            uint64_t *thr = ar.take<uint64_t>(1);
+            uint32_t *hist = ar.take<uint32_t>(kPilotBins);
+            fill_u32(hist, kPilotBins, 0u, s);
+            finish(kPilotPart);
+            k_pilot_hist<<<std::min(part_count(nf, kPilotPart) / 16 + 1, 256u), 1024, 0, s>>>(finals, nf, b.mask, b.cscore,
+                                                                                            hist);
+            ASCI_LAUNCH_CHECK();
+            k_pilot_pick<<<1, 1024, 0, s>>>(hist, b.pilot_k, thr);
+            ASCI_LAUNCH_CHECK();
+            fa.thr = thr;
+            finish(kRestPart);
+        } else {
+            finish(kAll);
+        }
     }
     uint32_t *off = ar.take<uint32_t>((size_t)ntile + 1);
     uint32_t *d_v = ar.take<uint32_t>(4);
@@ -1928,12 +2287,14 @@ void bucket_accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
     accumulate<W>(b, ar, s, prof, &hs, false);
     uint32_t *hcnt = (uint32_t *)hs.ptr;
     ASCI_HIP(hipMemcpyAsync(hcnt + 6, b.dn_V, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    if (b.pilot_k > 0) ASCI_HIP(hipMemcpyAsync(hcnt + 7, b.runs, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     b.h_v = hcnt + 6;
     if (b.defer_v) {
         b.V = ~0u;  // unknown until bucket_read_v
     } else {
         ASCI_HIP(hipStreamSynchronize(s));
         b.V = hcnt[6];
+        b.h_runs = hcnt[7];
         finish_bytes(b, W);
     }
 }
@@ -1958,11 +2319,22 @@ int bucket_collect(BucketArgs &b, hipStream_t s, Profiler *prof)
     return ps.tok;
 }
 
+void bucket_diag_bounds(const double *jk, int n, int na, int nb, double E0, double ecore, const double *etab, uint32_t ntab,
+                        double *tmp, double *out, hipStream_t s)
+{
+    const uint32_t nmin = (ntab + kMinRanks - 1) / kMinRanks;
+    k_block_min<<<nmin, kMinRanks, 0, s>>>(etab, ntab, tmp);
+    ASCI_LAUNCH_CHECK();
+    k_diag_bounds<<<1, 1024, 0, s>>>(jk, n, na, nb, E0, ecore, tmp, nmin, out);
+    ASCI_LAUNCH_CHECK();
+}
+
 void bucket_read_v(BucketArgs &b, hipStream_t s)
 {
     if (!b.defer_v) return;
     ASCI_HIP(hipStreamSynchronize(s));
     b.V = *b.h_v;
+    b.h_runs = b.h_v[1];
     b.defer_v = false;
     finish_bytes(b, b.n <= 32 ? 1 : 2);
 }

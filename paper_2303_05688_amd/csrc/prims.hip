@@ -601,14 +601,15 @@ void radix_select_abs(const double *score, size_t n, uint64_t k, SelectState *d_
                       Profiler *prof, const SelectWork *work, const uint32_t *dn, const uint32_t *dk)
 {
     require(k >= 1 && k <= n, ASCI_EINVAL, "radix select: k out of range");
-    // a copy of the entries that match two digits pays where a pass over all of
-    // them costs more than a launch
-    if (n <= ((size_t)1 << 20)) work = nullptr;
+    // Few scores: 32 workgroups a pass, the last of which picks the digit.  More:
+    // a launch of its own picks it, and the entries that match two digits are
+    // copied out.  At 9e5 scores the first took 178 us, the second 90; at 2e5 54 and 75.
+    bool few = n <= ((size_t)1 << 18);
+    if (few) work = nullptr;
     const unsigned nb = (unsigned)((n + kTile - 1) / kTile);
     k_sel_init<<<1, 1024, 0, s>>>(d_state, k, dk, work ? work->d_count : nullptr);
     ASCI_LAUNCH_CHECK();
     const double *x = score;
-    bool few = n <= ((size_t)1 << 20);
     // the 63 bits of |A|, most significant first
     for (int pass = 0, shift = 63; pass < 6; ++pass) {
         const int bits = pass < 3 ? 11 : 10;

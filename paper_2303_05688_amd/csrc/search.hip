@@ -1317,6 +1317,65 @@ static void prepare(asci_ctx *ctx, const SearchArgs &in, uint64_t fit, uint32_t 
     ASCI_HIP(hipStreamSynchronize(s));
 }
 
+// Input determinants whose alpha string lies in the classes [c0, c0 + nc) and
+// that are a target themselves (a single or double of some core determinant):
+// each takes one from *runs.  One wavefront for eight determinants, which share
+// its reads of the core set (one for each was bound by these reads from L2: 220
+// us for 20,000 determinants and a core of 3000, now 55), and 256 rows of it in
+// flight.
+constexpr int kTargetRows = 8;
+__global__ __launch_bounds__(kBlock) void k_psi_targets(const uint64_t *__restrict__ dets, uint32_t nd,
+                                                        const uint64_t *__restrict__ core_a,
+                                                        const uint64_t *__restrict__ core_b, uint32_t nq, ClassMap cmap,
+                                                        uint32_t c0, uint32_t nc, uint32_t *__restrict__ runs)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t i0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6))) * kTargetRows;
+    if (i0 >= nd) return;
+    uint64_t a[kTargetRows], b[kTargetRows];
+    uint32_t open = 0;  // determinants of the batch without a neighbour so far
+#pragma unroll
+    for (int k = 0; k < kTargetRows; ++k) {
+        const uint32_t i = min(i0 + (uint32_t)k, nd - 1u);
+        a[k] = dets[2 * (size_t)i];
+        b[k] = dets[2 * (size_t)i + 1];
+        if (i0 + (uint32_t)k < nd && class_of(a[k], cmap) - c0 < nc) open |= 1u << k;
+    }
+    uint32_t hits = 0;
+    for (uint32_t j0 = 0; j0 < nq && open; j0 += 256) {
+        uint64_t ca[4], cb[4];
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+            const uint32_t j = min(j0 + t * 64 + lane, nq - 1u);
+            ca[t] = core_a[j];
+            cb[t] = core_b[j];
+        }
+#pragma unroll
+        for (int k = 0; k < kTargetRows; ++k) {
+            bool hit = false;
+#pragma unroll
+            for (uint32_t t = 0; t < 4; ++t) {
+                const int d = __popcll(a[k] ^ ca[t]) + __popcll(b[k] ^ cb[t]);
+                hit |= d == 2 || d == 4;
+            }
+            if (__ballot(hit) != 0ull && ((open >> k) & 1u)) {
+                open &= ~(1u << k);
+                ++hits;
+            }
+        }
+    }
+    if (lane == 0 && hits) atomicSub(runs, hits);
+}
+
+// A pilot of the finish bounds the k-th |A| from below before the other
+// segments are finished (its own k-th is about the (16 k)-th of all): it pays
+// where a batch holds far more candidates than that, so that few of them are
+// written, collected and selected from (1.3e8 pairs of 16e20o: 0.58 ms of that
+// became 0.17, the finish went from 1.68 to 1.45 ms with the pilot in it, and
+// the search from 7.06 to 6.44).  At 4.6e7 pairs (8a5b23o) the two came out even,
+// 2.83 and 2.82 ms: the pilot's last wavefronts are alone on the chip.
+constexpr uint64_t kPilotPairs = (uint64_t)1 << 26, kPilotPerK = 256;
+
 // Searches of one class batch of at most this many pairs run without a host
 // round trip until their result is there (12 electrons in 12 orbitals, k =
 // 10 ndets up to 20000, ms against the step-by-step path: 2^15 pairs 0.21 and
@@ -1354,8 +1413,14 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
 
     const SpinTablePlan pl = spin_table_plan(n, in.na, in.nb, search_pairs(in), ctx->spin_tables != 0);
     ctx->tables.reset();
+    // Targets are rejected by bounds where a threshold can arise and both spins
+    // have tables (without, a bound costs what it saves: 22.6 and 21.7 ms for
+    // 1.9e8 pairs of 10 + 10 electrons in 36 orbitals).  Behind the tables: block
+    // minima of E(beta)'s.
+    const bool bounded = topk && !(in.opt.eps > 0.0) && pl.count[0] && pl.count[1];
+    const uint32_t nmin = bounded ? (uint32_t)((pl.count[1] + 255) / 256) : 0u;
     if (pl.bytes) {
-        ctx->tables.reserve(pl.bytes);
+        ctx->tables.reserve(pl.bytes + (bounded ? (size_t)nmin * 8 + 1024 : 0));
         ctx->tables.reset();
     }
     uint32_t *d_binom = take_binom(pl, n, ctx->tables);
@@ -1414,6 +1479,12 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
     double *p_score[2] = {ar.take<double>(pool_cap), ar.take<double>(pool_cap)};
     SelectState *d_sel = ar.take<SelectState>(1);
     uint32_t *d_cnt = ar.take<uint32_t>(16);
+    double *bounds = nullptr;
+    if (bounded && (batches.size() > 1 || (total >= kPilotPairs && total / kPilotPerK >= (uint64_t)out.k))) {
+        bounds = ctx->tables.take<double>(4);
+        bucket_diag_bounds(pp.d_jk, n, in.na, in.nb, in.E0, in.opt.ecore, st.e[1], (uint32_t)pl.count[1],
+                           ctx->tables.take<double>(nmin), bounds, s);
+    }
     const size_t loop_mark = ar.used();
 
     HostStage &hs = ctx->stage;
@@ -1538,6 +1609,7 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
         ba.jk = pp.d_jk;
         ba.st = st;
         ba.thr = topk ? d_thr : nullptr;
+        ba.bounds = bounds;
         ba.ecore = in.opt.ecore;
         ba.E0 = in.E0;
         ba.eps = in.opt.eps;
@@ -1556,6 +1628,17 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
         ba.pool_score = p_score[pcur];
         ba.pool_base = pool_n;
         ba.pool_cap = pool_cap;
+        const bool pilot = topk && !d_thr && !(in.opt.eps > 0.0) && P >= kPilotPairs && P / kPilotPerK >= (uint64_t)out.k;
+        if (pilot) {
+            // the candidates are counted as the distinct targets that are no
+            // input determinant
+            ba.pilot_k = (uint64_t)out.k;
+            ba.runs = d_cnt + 12;
+            fill_u32(ba.runs, 1, 0u, s);
+            k_psi_targets<<<(unsigned)((in.ndets + kTargetRows * (kBlock / 64) - 1) / (kTargetRows * (kBlock / 64))), kBlock, 0, s>>>(
+                in.dets, (uint32_t)in.ndets, pp.q_a, pp.q_b, (uint32_t)nq, pp.cmap(in.na), c0, nc, ba.runs);
+            ASCI_LAUNCH_CHECK();
+        }
         bucket_accumulate<W>(ba, ar, s, prof, hs);
         if (out.pt2) {
             out.pt2_energy = out.pt2_energy + bucket_pt2(ba, ar, s, hs);
@@ -1571,7 +1654,7 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
         const uint32_t V = ba.V;
         ctx->last_finals += ba.nfinal;
         ctx->last_levels = std::max<int64_t>(ctx->last_levels, ba.levels);
-        ctx->last_candidates += V;
+        ctx->last_candidates += pilot ? ba.h_runs : V;
         if (!early) {
             if (topk && pool_n + V > pool_cap) prune((size_t)std::min<uint64_t>(pool_n, (uint64_t)out.k));
             if (pool_n + V > pool_cap)
