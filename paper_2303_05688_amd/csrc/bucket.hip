@@ -2081,6 +2081,8 @@ static void finish_bytes(const BucketArgs &b, int W)
                                             (8.0 * W + 8.0 + (b.cnum ? 8.0 : 0.0)) * (double)b.V);
 }
 
+constexpr size_t kQueuedRecords = (size_t)1 << 28;
+
 // device counters of one batch
 enum { kCtrFinal = 0, kCtrLarge = 1 /* and 2: per level parity */, kCtrOverflow = 3, kCtrSmall = 4 /* and 5: per round */,
        kCtrLevels = 6 };
@@ -2120,13 +2122,15 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
     const size_t mark = ar.used();
     const KeyBufs kb{{b.klo[0], b.klo[1]}, {b.khi[0], b.khi[1]}};
     int lev = 0;
-    // one split level of the (at most nlarge) large segments of list lev & 1
-    auto split_level = [&](uint32_t nlarge) {
+    // One split level of the large segments of list lev & 1: nlarge of them, or
+    // (queued) at most nlarge, their number on the device, on grids of at most
+    // gmax workgroups.
+    auto split_level = [&](uint32_t nlarge, bool queued, uint32_t gmax) {
         ar.reset();
         (void)ar.take<char>(mark);
         require(lev < 64, ASCI_EDEVICE, "bucket split did not converge");
         Seg *segs = lv[lev & 1];
-        const uint32_t *dn_seg = dev ? ctr + kCtrLarge + (lev & 1) : nullptr;
+        const uint32_t *dn_seg = queued ? ctr + kCtrLarge + (lev & 1) : nullptr;
         lists.next = lv[(lev & 1) ^ 1];
         lists.nnext = ctr + kCtrLarge + ((lev & 1) ^ 1);
         const uint32_t ntiles = (uint32_t)level_tiles(P, nlarge);
@@ -2138,11 +2142,11 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         uint32_t *hist = ar.take<uint32_t>(nhist + 1);
         // launch shapes: per-segment kernels stride over the level's segments,
         // tile kernels over its tiles (eight XCD groups of workgroups)
-        const unsigned g_seg = dev ? std::min(nlarge, 2048u) : nlarge;
-        const unsigned g_tiles = 8u * (dev ? std::min((ntiles + 7) / 8, 256u) : (ntiles + 7) / 8);
+        const unsigned g_seg = std::min(nlarge, gmax);
+        const unsigned g_tiles = 8u * std::min((ntiles + 7) / 8, gmax / 8);
         const bool few = ntiles <= 8192;
         k_level_plan<<<1, 1024, 0, s>>>(segs, nlarge, cap, tbase, hbase, skip, lev_tot, lists.nnext, few ? tseg : nullptr,
-                                        dn_seg, dev ? ctr + kCtrLevels : nullptr);
+                                        dn_seg, ctr + kCtrLevels);
         ASCI_LAUNCH_CHECK();
         if (!few) {
             k_tile_seg<<<std::min((ntiles + 255) / 256, 1024u), 256, 0, s>>>(tbase, nlarge, lev_tot, tseg, dn_seg);
@@ -2191,50 +2195,68 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         }
         ++lev;
     };
-    // the segments of one tile at most, each by one workgroup
-    auto small_split = [&](uint32_t nsmall, uint32_t *nsm) {
+    // The segments of one tile at most, each by one workgroup; nsm: their number
+    // on the device (nsmall is then a bound).
+    auto small_split = [&](uint32_t nsmall, uint32_t *nsm, uint32_t gmax) {
         if (nsmall == 0) return;
         ProfScope ps(prof, "small_split", 0.0, s);
-        k_small_split<W><<<dev ? std::min(nsmall, 4096u) : nsmall, kSmallT, 0, s>>>(
-            small, nsmall, dev ? nsm : nullptr, cap, b.klo[0], b.klo[1], b.khi[0], b.khi[1], b.val[0], b.val[1], lists);
+        k_small_split<W><<<std::min(nsmall, gmax), kSmallT, 0, s>>>(
+            small, nsmall, nsm, cap, b.klo[0], b.klo[1], b.khi[0], b.khi[1], b.val[0], b.val[1], lists);
         ASCI_LAUNCH_CHECK();
     };
-    if (dev) {
-        for (int l = 0; l < b.dev_levels; ++l) split_level(level_cap);
-        for (int round = 0; round < b.dev_rounds; ++round) {
+    // levels and a small split, queued, rounds times (one level ahead of each later one)
+    constexpr uint32_t kAnyGrid = 1u << 30;
+    auto queue_rounds = [&](int levels, int rounds, uint32_t bound, uint32_t gmax, uint32_t gsmall) {
+        for (int l = 0; l < levels; ++l) split_level(bound, true, gmax);
+        for (int round = 0; round < rounds; ++round) {
             // the next round takes what the small split of this one left, from list lev & 1
             lists.nsmall = ctr + kCtrSmall + ((round & 1) ^ 1);
-            small_split(level_cap, ctr + kCtrSmall + (round & 1));
-            if (round + 1 < b.dev_rounds) split_level(level_cap);
+            if (round > 0) fill_u32(lists.nsmall, 1, 0u, s);
+            small_split(level_cap, ctr + kCtrSmall + (round & 1), gsmall);
+            if (round + 1 < rounds) split_level(level_cap, true, 2048u);
         }
+    };
+    if (dev) {
+        queue_rounds(b.dev_levels, b.dev_rounds, level_cap, 2048u, 4096u);
         // what is left in list lev & 1 fails the call
         b.dn_nlarge = ctr + kCtrLarge + (lev & 1);
         b.dn_overflow = ctr + kCtrOverflow;
         b.dn_levels = ctr + kCtrLevels;
     } else {
+        // What most batches need is queued at once: a read-back between two
+        // levels leaves the chip idle for about 35 us (8a5b23o, 4.6e7 records: five
+        // read-backs, now two).  Ahead of the first small split a large segment
+        // has more records than a tile.  Above 2^28 records a level takes long
+        // enough, and its grid is better sized by its count.
+        int round = 0;
+        if (P <= kQueuedRecords) {
+            const uint32_t bound = (uint32_t)(P / kTileN + 1);
+            queue_rounds(P <= ((size_t)1 << 19) ? 1 : 2, 2, bound, kAnyGrid, 16384u);
+            round = 2;
+        }
         read_counts();
-        for (int round = 0;; ++round) {
+        for (;; ++round) {
             while (hcnt[kCtrLarge + (lev & 1)] > 0) {
-                split_level(hcnt[kCtrLarge + (lev & 1)]);
+                split_level(hcnt[kCtrLarge + (lev & 1)], false, kAnyGrid);
                 read_counts();
             }
             const uint32_t nsmall = hcnt[kCtrSmall + (round & 1)];
             if (nsmall == 0) break;
             // leftovers go to list lev & 1, whose count is zero here, and the
             // small ones among their children to the other round's count
-            if (round > 0) ASCI_HIP(hipMemsetAsync(ctr + kCtrSmall + ((round & 1) ^ 1), 0, sizeof(uint32_t), s));
+            if (round > 0) fill_u32(ctr + kCtrSmall + ((round & 1) ^ 1), 1, 0u, s);
             lists.nsmall = ctr + kCtrSmall + ((round & 1) ^ 1);
             lists.next = lv[lev & 1];
             lists.nnext = ctr + kCtrLarge + (lev & 1);
-            small_split(nsmall, nullptr);
+            small_split(nsmall, nullptr, kAnyGrid);
             read_counts();
         }
+        b.levels = hcnt[kCtrLevels];
     }
     ar.reset();
     (void)ar.take<char>(mark);
     const uint32_t nf = dev ? finals_cap : hcnt[kCtrFinal];
     b.nfinal = nf;
-    b.levels = (uint32_t)lev;
     // candidate marks: a bit per slot, a count per tile of slots, cleared together
     const uint32_t ntile = (uint32_t)((P + kSlotTile - 1) / kSlotTile);
     const size_t mwords = 2 * (size_t)ntile * (kSlotTile / 64);
