@@ -205,12 +205,15 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t *in, uint
 
 // ---------------------------------------------------------------- merge sort
 // Keys of KW words, the first the most significant, ties by position (a stable
-// sort), a 32-bit payload: chunks sorted in LDS by a bitonic network, then four
+// sort), a 32-bit payload: chunks sorted in LDS by a bitonic network, then eight
 // runs at a time merged, every element finding its place by a binary search in
-// the three other runs.  One launch for the chunks, one more for each factor of
-// four, where a radix sort of 8-bit digits takes three launches a digit (the
-// 2000 scores of a small search took 24 launches, about 110 us, now two).
+// the seven other runs.  One launch for the chunks, one more for each factor of
+// eight, where a radix sort of 8-bit digits takes three launches a digit (the
+// 2000 scores of a small search took 24 launches, about 110 us).  73,000 scores
+// of a bound of 3e5 (8e12o): three merges of 11.7 us, four at a time five of 9.0;
+// with the reads of each search behind its own branch 16 at a time took 22.
 constexpr int kSortT = 512;
+constexpr uint32_t kSortWays = 8;
 constexpr int kSortChunk = 1024;  // one pair a thread and stage: 17 us (a chunk of 4096 took 47)
 
 template <int KW>
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(kSortT) void k_sort_chunks(SortKeys<KW> in, const d
     }
 }
 
-// merges the runs of `width` elements four at a time
+// merges the runs of `width` elements kSortWays at a time
 template <int KW>
 __global__ __launch_bounds__(kThreads) void k_sort_merge(SortKeys<KW> in, const uint32_t *__restrict__ ival,
                                                          SortKeys<KW> out, uint32_t *__restrict__ oval, size_t n,
@@ -303,38 +306,42 @@ __global__ __launch_bounds__(kThreads) void k_sort_merge(SortKeys<KW> in, const 
     n = dev_n(n, dn);
     const size_t g = (size_t)blockIdx.x * kThreads + threadIdx.x;
     if (g >= n) return;
-    const size_t base = g / (4 * width) * (4 * width), off = g - base;
+    const size_t base = g / (kSortWays * width) * (kSortWays * width), off = g - base;
     const uint32_t run = (uint32_t)(off / width);
     uint64_t key[KW];
 #pragma unroll
     for (int k = 0; k < KW; ++k) key[k] = in.w[k][g];
     // elements of the other runs that come first: smaller ones, and in the runs
-    // before this element's equal ones too
-    size_t d = base + (off - run * width);
-    size_t l[4], r[4];
+    // before this element's equal ones too; all searches take a step together,
+    // their reads ahead of the first comparison, so that a step waits once
+    uint32_t l[kSortWays], r[kSortWays];
+    const uint32_t n32 = (uint32_t)n, b32 = (uint32_t)base, w32 = (uint32_t)width;
+    uint32_t d = b32 + ((uint32_t)off - run * w32);
 #pragma unroll
-    for (uint32_t o = 0; o < 4; ++o) {
-        l[o] = min(base + o * width, n);
-        r[o] = o == run ? l[o] : min(base + (o + 1) * width, n);
+    for (uint32_t o = 0; o < kSortWays; ++o) {
+        l[o] = (uint32_t)min(base + o * width, n);
+        r[o] = o == run ? l[o] : (uint32_t)min(base + (o + 1) * width, n);
         d -= l[o];
     }
-    // the searches run in step, so that their reads overlap
-    for (bool more = true; more;) {
-        more = false;
+    for (size_t w = width; w; w >>= 1) {  // uniform: a run of w elements takes bits(w) steps
+        uint64_t y[kSortWays][KW];
 #pragma unroll
-        for (uint32_t o = 0; o < 4; ++o) {
-            if (l[o] >= r[o]) continue;
-            const size_t m = (l[o] + r[o]) >> 1;
-            uint64_t y[KW];
+        for (uint32_t o = 0; o < kSortWays; ++o) {
+            const uint32_t m = min(l[o] + (r[o] - l[o]) / 2u, n32 - 1u);
 #pragma unroll
-            for (int k = 0; k < KW; ++k) y[k] = in.w[k][m];
-            const bool before = o < run ? !words_less<KW>(key, y) : words_less<KW>(y, key);
-            if (before) l[o] = m + 1;
-            else r[o] = m;
-            more = true;
+            for (int k = 0; k < KW; ++k) y[o][k] = in.w[k][m];
+        }
+#pragma unroll
+        for (uint32_t o = 0; o < kSortWays; ++o) {
+            const uint32_t m = l[o] + (r[o] - l[o]) / 2u;
+            const bool open = l[o] < r[o];
+            const bool before = o < run ? !words_less<KW>(key, y[o]) : words_less<KW>(y[o], key);
+            l[o] = open && before ? m + 1u : l[o];
+            r[o] = open && !before ? m : r[o];
         }
     }
-    d += l[0] + l[1] + l[2] + l[3];
+#pragma unroll
+    for (uint32_t o = 0; o < kSortWays; ++o) d += l[o];
 #pragma unroll
     for (int k = 0; k < KW; ++k) out.w[k][d] = key[k];
     oval[d] = ival[g];
@@ -519,7 +526,7 @@ int merge_sort(uint64_t *(*keys)[2], uint32_t *vals[2], const double *score, siz
     k_sort_chunks<KW><<<(unsigned)((n + CH - 1) / CH), kSortT, 0, s>>>(k[0], score, k[1], vals[1], n, dn);
     ASCI_LAUNCH_CHECK();
     int cur = 1;
-    for (size_t width = CH; width < n; width *= 4) {
+    for (size_t width = CH; width < n; width *= kSortWays) {
         k_sort_merge<KW><<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(k[cur], vals[cur], k[cur ^ 1],
                                                                                       vals[cur ^ 1], n, width, dn);
         ASCI_LAUNCH_CHECK();

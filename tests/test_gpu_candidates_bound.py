@@ -25,4 +25,6 @@ def test_one_pass_equals_two(monkeypatch, n, na, nb, ndets, kw):
         monkeypatch.setattr(asci, "_pair_bound", lambda *a: 0)
     for one, two in zip(*got):
         assert one.shape == two.shape and (gu.host(one).view(np.uint64) == gu.host(two).view(np.uint64)).all()
-        assert one.untyped_storage().nbytes() <= max(one.numel(), 1) * one.element_size()
+        # (no candidates: the counting pass allocates one row)
+        row = (2 if one.dim() == 2 else 1) * one.element_size()
+        assert one.untyped_storage().nbytes() <= max(one.numel() * one.element_size(), row)
