@@ -717,18 +717,38 @@ __global__ __launch_bounds__(kBlock) void k_index_keys(const uint32_t *__restric
     if (j < n) key[j] = idx[j];
 }
 
+// Entry j of the core set.  A determinant that fails validation (the call will
+// fail, but a search that reads its flags back at the end still runs) is
+// replaced by the lowest valid one: the generator's orbital lists hold as many
+// entries as the strings have electrons and holes, and what lies behind them
+// would be used as orbitals in reads without a range test.
+__device__ __forceinline__ bool valid_det(uint64_t a, uint64_t b, int n, int na, int nb)
+{
+    const uint64_t full = n == 64 ? ~0ull : ((1ull << n) - 1ull);
+    return !(a & ~full) && !(b & ~full) && popc64(a) == na && popc64(b) == nb;
+}
+__device__ __forceinline__ void put_core(uint64_t a, uint64_t b, double c, int n, int na, int nb, size_t j, uint64_t *qa,
+                                         uint64_t *qb, double *qc)
+{
+    if (!valid_det(a, b, n, na, nb)) {
+        a = na == 64 ? ~0ull : ((1ull << na) - 1ull);
+        b = nb == 64 ? ~0ull : ((1ull << nb) - 1ull);
+    }
+    qa[j] = a;
+    qb[j] = b;
+    qc[j] = c;
+}
+
 __global__ __launch_bounds__(kBlock) void k_gather_core(const uint64_t *__restrict__ dets,
                                                         const double *__restrict__ c,
-                                                        const uint64_t *__restrict__ sel, size_t nq,
-                                                        uint64_t *__restrict__ qa, uint64_t *__restrict__ qb,
+                                                        const uint64_t *__restrict__ sel, size_t nq, int n, int na,
+                                                        int nb, uint64_t *__restrict__ qa, uint64_t *__restrict__ qb,
                                                         double *__restrict__ qc)
 {
     const size_t j = (size_t)blockIdx.x * kBlock + threadIdx.x;
     if (j >= nq) return;
-    const size_t i = sel ? (size_t)sel[j] : j;
-    qa[j] = dets[2 * i];
-    qb[j] = dets[2 * i + 1];
-    qc[j] = c[i];
+    const size_t i = (size_t)sel[j];
+    put_core(dets[2 * i], dets[2 * i + 1], c[i], n, na, nb, j, qa, qb, qc);
 }
 
 // C(p, k), saturated at 2^32 - 1
@@ -829,7 +849,6 @@ __global__ __launch_bounds__(kBlock) void k_prep_tables(PrepArgs g)
 struct InputArgs {
     const double *eri, *packed;
     int n, na, nb;
-    uint64_t full;
     const uint64_t *dets;
     const double *coeffs;
     uint32_t nd;
@@ -856,13 +875,9 @@ __global__ __launch_bounds__(kBlock) void k_prep_inputs(InputArgs g)
     t -= n4;
     if (t >= g.nd) return;
     const uint64_t a = g.dets[2 * (size_t)t], b = g.dets[2 * (size_t)t + 1];
-    if ((a & ~g.full) || (b & ~g.full) || popc64(a) != g.na || popc64(b) != g.nb) atomicOr(g.err, kStatInvalid);
+    if (!valid_det(a, b, g.n, g.na, g.nb)) atomicOr(g.err, kStatInvalid);
     if (g.tlo) psi_insert<W>(a, b, g.n, g.tlo, g.thi, g.state, g.mask, g.filter, g.fmask);
-    if (g.qa) {
-        g.qa[t] = a;
-        g.qb[t] = b;
-        g.qc[t] = g.coeffs[t];
-    }
+    if (g.qa) put_core(a, b, g.coeffs[t], g.n, g.na, g.nb, t, g.qa, g.qb, g.qc);
 }
 
 inline unsigned grid_for(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -1043,22 +1058,19 @@ struct Prepared {
 };
 
 // Core set: the nq inputs of largest |C| (ties: lower index), ascending index.
-static void select_core(const uint64_t *dets, const double *coeffs, size_t nd, size_t nq, uint64_t *q_a, uint64_t *q_b,
-                        double *q_c, Arena &ar, hipStream_t s)
+static void select_core(const SearchArgs &in, size_t nd, size_t nq, uint64_t *q_a, uint64_t *q_b, double *q_c, Arena &ar,
+                        hipStream_t s)
 {
-    const uint64_t *sel = nullptr;
-    if (nq < nd) {
-        uint64_t *ck[1][2] = {{ar.take<uint64_t>(nd), ar.take<uint64_t>(nd)}};
-        uint32_t *ci[2] = {ar.take<uint32_t>(nd), ar.take<uint32_t>(nd)};
-        const int r1 = merge_sort<1>(ck, ci, coeffs, nd, s);
-        // the first nq positions, sorted ascending (payload unused)
-        uint64_t *ik[1][2] = {{ck[0][r1 ^ 1], ar.take<uint64_t>(nq)}};
-        uint32_t *ii[2] = {ci[r1 ^ 1], ar.take<uint32_t>(nq)};
-        k_index_keys<<<grid_for(nq), kBlock, 0, s>>>(ci[r1], nq, ik[0][0]);
-        ASCI_LAUNCH_CHECK();
-        sel = ik[0][merge_sort<1>(ik, ii, nullptr, nq, s)];
-    }
-    k_gather_core<<<grid_for(nq), kBlock, 0, s>>>(dets, coeffs, sel, nq, q_a, q_b, q_c);
+    uint64_t *ck[1][2] = {{ar.take<uint64_t>(nd), ar.take<uint64_t>(nd)}};
+    uint32_t *ci[2] = {ar.take<uint32_t>(nd), ar.take<uint32_t>(nd)};
+    const int r1 = merge_sort<1>(ck, ci, in.coeffs, nd, s);
+    // the first nq positions, sorted ascending (payload unused)
+    uint64_t *ik[1][2] = {{ck[0][r1 ^ 1], ar.take<uint64_t>(nq)}};
+    uint32_t *ii[2] = {ci[r1 ^ 1], ar.take<uint32_t>(nq)};
+    k_index_keys<<<grid_for(nq), kBlock, 0, s>>>(ci[r1], nq, ik[0][0]);
+    ASCI_LAUNCH_CHECK();
+    const uint64_t *sel = ik[0][merge_sort<1>(ik, ii, nullptr, nq, s)];
+    k_gather_core<<<grid_for(nq), kBlock, 0, s>>>(in.dets, in.coeffs, sel, nq, in.n, in.na, in.nb, q_a, q_b, q_c);
     ASCI_LAUNCH_CHECK();
 }
 
@@ -1240,7 +1252,6 @@ static void queue_inputs(const SearchArgs &in, Prepared<W> &pp, uint32_t *binom,
     b.n = n;
     b.na = in.na;
     b.nb = in.nb;
-    b.full = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
     b.dets = in.dets;
     b.coeffs = in.coeffs;
     b.nd = (uint32_t)pp.nd;
@@ -1264,7 +1275,7 @@ static void queue_inputs(const SearchArgs &in, Prepared<W> &pp, uint32_t *binom,
         k_psi_dups<W><<<grid_for(pp.nd), kBlock, 0, s>>>(in.dets, pp.nd, n, pp.psi, pp.d_err);
         ASCI_LAUNCH_CHECK();
     }
-    if (pp.nq < pp.nd) select_core(in.dets, in.coeffs, pp.nd, pp.nq, pp.q_a, pp.q_b, pp.q_c, ar, s);
+    if (pp.nq < pp.nd) select_core(in, pp.nd, pp.nq, pp.q_a, pp.q_b, pp.q_c, ar, s);
 }
 
 // the error of a set of kStat* input bits

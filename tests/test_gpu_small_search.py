@@ -97,3 +97,25 @@ def test_small_search_errors(n, na, nb, fault):
     assert said[0] == said[1]
     d = gu.to_dev(good)
     _compare(d, n, na, nb, -3.5, [100], _expected(d, n, na, nb, -3.5))
+
+
+@pytest.mark.parametrize("n,na,nb", [(12, 6, 6), (9, 3, 2), (34, 3, 3)])
+@pytest.mark.parametrize("alpha,beta", [(0, 0), (1, 1), ("all", "all"), ("more", 0), (0, "more"), ("high", 1), (1, "high")])
+def test_small_search_invalid_strings(n, na, nb, alpha, beta):
+    """Strings with too few, too many or outside orbitals, in the core set: the
+    search reads its flags at the end, so it runs on what takes their place."""
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+
+    mask = {"all": (1 << n) - 1, "more": (1 << (max(na, nb) + 2)) - 1, "high": (1 << 63) | (1 << n)}
+    good = _case(n, na, nb, 24, 11)
+    bad = {k: v.copy() for k, v in good.items()}
+    for i in (0, 5, 23):
+        bad["dets"][i] = (np.uint64(mask.get(alpha, alpha)), np.uint64(mask.get(beta, beta)))
+    d = gu.to_dev(bad)
+    for kw in ({}, {"ncore": 10}):
+        with pytest.raises(asci.AsciError) as e:
+            asci.search(d["h"], d["eri"], n, na, nb, d["dets"], d["coeffs"], -3.5, 100, **kw)
+        assert e.value.code == asci.ASCI_EINVAL
+    d = gu.to_dev(good)
+    _compare(d, n, na, nb, -3.5, [100], _expected(d, n, na, nb, -3.5))
