@@ -1322,7 +1322,8 @@ __device__ __forceinline__ double spin_e_lanes(const Diag<JL> &D, int spin, M s)
 // one final segment of at most 64 * IT records, by one wavefront; its distinct keys
 template <int W, int IT, bool JL>
 __device__ __forceinline__ uint32_t finish_segment(const FinishArgs &f, const Diag<JL> &D, WaveLds<IT> &S, double *acache,
-                                               const Seg &sg, uint64_t thr, bool prune, double &level, Queue<W> &Q)
+                                               const Seg &sg, uint64_t thr, bool prune, double &level, uint32_t &queued,
+                                               Queue<W> &Q)
 {
     using M = std::conditional_t<W == 1, uint32_t, uint64_t>;  // a spin string
     constexpr int CAP = WaveLds<IT>::CAP;
@@ -1619,6 +1620,7 @@ __device__ __forceinline__ uint32_t finish_segment(const FinishArgs &f, const Di
             Q.n += cnt;
             nq += cnt;
         }
+        queued += nq;
         wave_sync();
         return nruns;
     }
@@ -1804,7 +1806,7 @@ __global__ __launch_bounds__(64 * kFinishWaves) __attribute__((amdgpu_waves_per_
     // thr: a lower bound of the final k-th |A|, from a pilot or earlier class batches, if any
     const uint64_t thr = f.thr ? *f.thr : 0ull;
     // the queue takes the place of the alpha cache, which the pruned path has no use for
-    const bool prune = thr != 0ull && !(f.eps > 0.0) && f.bounds;
+    bool prune = thr != 0ull && !(f.eps > 0.0) && f.bounds;
     double level = prune ? f.bounds[2] : 0.0;
     Queue<W> Q;
     Q.lo = reinterpret_cast<uint64_t *>(acache);
@@ -1812,7 +1814,7 @@ __global__ __launch_bounds__(64 * kFinishWaves) __attribute__((amdgpu_waves_per_
     Q.sum = reinterpret_cast<double *>(Q.lo + W * f.qcap);
     Q.slot = reinterpret_cast<uint32_t *>(Q.sum + f.qcap);
     Q.n = 0;
-    uint32_t runs = 0;
+    uint32_t runs = 0, tried = 0, queued = 0;
     const uint32_t step = gridDim.x * kFinishWaves;
     uint32_t i = blockIdx.x + gridDim.x * wv;
     Seg next = i < nf ? f.finals[part_index(i, f.part)] : Seg{0u, 0u, 0u};
@@ -1823,7 +1825,17 @@ __global__ __launch_bounds__(64 * kFinishWaves) __attribute__((amdgpu_waves_per_
             finish_single<W, IT, JL>(f, D, S, sg);
             ++runs;
         } else {
-            runs += finish_segment<W, IT, JL>(f, D, S, acache, sg, thr, prune, level, Q);
+            const uint32_t r = finish_segment<W, IT, JL>(f, D, S, acache, sg, thr, prune, level, queued, Q);
+            runs += r;
+            // An E0 among the diagonal elements leaves no bound.  Where more than a
+            // quarter of the targets are queued, a wavefront goes on without: with
+            // all of them queued a launch of 24e30o takes 28 ms, without bounds
+            // 14.4, and with 2 % of them 10.
+            tried += prune ? r : 0u;
+            if (prune && tried >= 256u && queued > tried / 4u) {
+                while (Q.n) finish_queued<W, JL>(f, D, Q, thr);
+                prune = false;
+            }
         }
     }
     while (Q.n) finish_queued<W, JL>(f, D, Q, thr);

@@ -1385,7 +1385,10 @@ __global__ __launch_bounds__(kBlock) void k_psi_targets(const uint64_t *__restri
 // became 0.17, the finish went from 1.68 to 1.45 ms with the pilot in it, and
 // the search from 7.06 to 6.44).  At 4.6e7 pairs (8a5b23o) the two came out even,
 // 2.83 and 2.82 ms: the pilot's last wavefronts are alone on the chip.
-constexpr uint64_t kPilotPairs = (uint64_t)1 << 26, kPilotPerK = 256;
+// Counting the candidates takes up to ndets * ncore pair tests (3e-13 s each where
+// no determinant has a neighbour) against about 4.6e-12 s saved a pair, so a
+// determinant set far larger than its core set goes without.
+constexpr uint64_t kPilotPairs = (uint64_t)1 << 26, kPilotPerK = 256, kPilotTests = 16;
 
 // Searches of one class batch of at most this many pairs run without a host
 // round trip until their result is there (12 electrons in 12 orbitals, k =
@@ -1491,7 +1494,11 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
     SelectState *d_sel = ar.take<SelectState>(1);
     uint32_t *d_cnt = ar.take<uint32_t>(16);
     double *bounds = nullptr;
-    if (bounded && (batches.size() > 1 || (total >= kPilotPairs && total / kPilotPerK >= (uint64_t)out.k))) {
+    auto pilot_pays = [&](uint64_t pairs) {
+        return !(in.opt.eps > 0.0) && pairs >= kPilotPairs && pairs / kPilotPerK >= (uint64_t)out.k &&
+               (uint64_t)in.ndets <= kPilotTests * pairs / nq;
+    };
+    if (bounded && (batches.size() > 1 || pilot_pays(total))) {
         bounds = ctx->tables.take<double>(4);
         bucket_diag_bounds(pp.d_jk, n, in.na, in.nb, in.E0, in.opt.ecore, st.e[1], (uint32_t)pl.count[1],
                            ctx->tables.take<double>(nmin), bounds, s);
@@ -1639,7 +1646,7 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
         ba.pool_score = p_score[pcur];
         ba.pool_base = pool_n;
         ba.pool_cap = pool_cap;
-        const bool pilot = topk && !d_thr && !(in.opt.eps > 0.0) && P >= kPilotPairs && P / kPilotPerK >= (uint64_t)out.k;
+        const bool pilot = topk && !d_thr && pilot_pays(P);
         if (pilot) {
             // the candidates are counted as the distinct targets that are no
             // input determinant
