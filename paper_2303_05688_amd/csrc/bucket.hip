@@ -32,6 +32,7 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <vector>
 
 namespace asci {
 
@@ -283,11 +284,12 @@ __global__ __launch_bounds__(1024) void k_level_plan(const Seg *__restrict__ seg
                                                      uint32_t *__restrict__ hist_base, uint32_t *__restrict__ skip,
                                                      uint32_t *__restrict__ lev, uint32_t *__restrict__ nnext,
                                                      uint32_t *__restrict__ tile_seg, const uint32_t *dn_seg,
-                                                     uint32_t *__restrict__ nlevels)
+                                                     uint32_t *__restrict__ nlevels, uint32_t *__restrict__ nrec)
 {
-    __shared__ uint32_t s_tmp[16];
+    __shared__ uint32_t s_tmp[16], s_rec;
     const uint32_t ns = dev_count(nseg, dn_seg);
-    uint32_t tiles = 0, entries = 0;
+    uint32_t tiles = 0, entries = 0, rec = 0;
+    if (threadIdx.x == 0) s_rec = 0u;
     for (uint32_t b = 0; b < ns; b += 4096) {
         const uint32_t s0 = b + threadIdx.x * 4u;
         uint32_t t[4], e[4], st = 0, se = 0;
@@ -298,6 +300,7 @@ __global__ __launch_bounds__(1024) void k_level_plan(const Seg *__restrict__ seg
                 const uint32_t size = segs[s0 + k].size;
                 t[k] = seg_tiles(size);
                 e[k] = t[k] * split_ranges(size, cap);
+                rec += size;
             }
             st += t[k];
             se += e[k];
@@ -321,7 +324,13 @@ __global__ __launch_bounds__(1024) void k_level_plan(const Seg *__restrict__ seg
         lev[0] = tiles;
         lev[1] = entries;
         *nnext = 0u;
-        if (nlevels && ns > 0u) ++*nlevels;
+        if (ns > 0u) ++*nlevels;
+    }
+    if (nrec) {  // timing only: the records of the level
+        __syncthreads();
+        atomicAdd(&s_rec, rec);
+        __syncthreads();
+        if (threadIdx.x == 0) *nrec = s_rec;
     }
     if (!tile_seg) return;
     __syncthreads();  // the block's own writes of tile_base
@@ -2131,6 +2140,10 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
     uint64_t *spl_lo = ar.take<uint64_t>(2 * P / cap + 1);
     uint64_t *spl_hi = W == 2 ? ar.take<uint64_t>(2 * P / cap + 1) : nullptr;
     uint32_t *lev_tot = ar.take<uint32_t>(4);
+    // per-kernel timing: the records of each level, for the bytes its passes move
+    const bool timed = prof && prof->on;
+    uint32_t *level_rec = ar.take<uint32_t>(64);
+    std::vector<int> tok_hist, tok_scatter;
     const size_t mark = ar.used();
     const KeyBufs kb{{b.klo[0], b.klo[1]}, {b.khi[0], b.khi[1]}};
     int lev = 0;
@@ -2158,7 +2171,7 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         const unsigned g_tiles = 8u * std::min((ntiles + 7) / 8, gmax / 8);
         const bool few = ntiles <= 8192;
         k_level_plan<<<1, 1024, 0, s>>>(segs, nlarge, cap, tbase, hbase, skip, lev_tot, lists.nnext, few ? tseg : nullptr,
-                                        dn_seg, ctr + kCtrLevels);
+                                        dn_seg, ctr + kCtrLevels, timed ? level_rec + lev : nullptr);
         ASCI_LAUNCH_CHECK();
         if (!few) {
             k_tile_seg<<<std::min((ntiles + 255) / 256, 1024u), 256, 0, s>>>(tbase, nlarge, lev_tot, tseg, dn_seg);
@@ -2192,7 +2205,8 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         sa.spl_hi = spl_hi;
         sa.dig = dig;
         {
-            ProfScope ps(prof, "split_hist", (8.0 * W) * (double)ntiles * kTileN, s);
+            ProfScope ps(prof, "split_hist", 0.0, s);
+            tok_hist.push_back(ps.tok);
             k_split_hist<W><<<g_tiles, kHistT, 0, s>>>(sa);
             ASCI_LAUNCH_CHECK();
         }
@@ -2201,7 +2215,8 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
             segs, nlarge, hbase, hist, cap, spl_lo, spl_hi, skip, lists, dn_seg);
         ASCI_LAUNCH_CHECK();
         {
-            ProfScope ps(prof, "split_scatter", 2.0 * (8.0 * W + 8.0) * (double)ntiles * kTileN, s);
+            ProfScope ps(prof, "split_scatter", 0.0, s);
+            tok_scatter.push_back(ps.tok);
             k_split_scatter<W><<<g_tiles, kTileT, 0, s>>>(sa, skip);
             ASCI_LAUNCH_CHECK();
         }
@@ -2264,6 +2279,15 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
             read_counts();
         }
         b.levels = hcnt[kCtrLevels];
+        if (timed && lev > 0) {
+            std::vector<uint32_t> rec((size_t)lev);
+            ASCI_HIP(hipMemcpyAsync(rec.data(), level_rec, rec.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+            ASCI_HIP(hipStreamSynchronize(s));
+            for (size_t l = 0; l < rec.size(); ++l) {
+                if (tok_hist[l] >= 0) prof->set_bytes(tok_hist[l], 8.0 * W * rec[l]);
+                if (tok_scatter[l] >= 0) prof->set_bytes(tok_scatter[l], 2.0 * (8.0 * W + 8.0) * rec[l]);
+            }
+        }
     }
     ar.reset();
     (void)ar.take<char>(mark);
