@@ -40,8 +40,8 @@ struct PairArgs {
     double *partial;         // energy: one sum per wavefront
 };
 
-// <a|H|i> for two determinants a = (aa, ab) and i = (ia, ib) that differ by a
-// single or a double excitation: the excitation is read from i to a
+// <a|H|i> for two different determinants a = (aa, ab) and i = (ia, ib), a single
+// or a double apart: the excitation is read from i to a
 __device__ __forceinline__ double pair_element(const PairArgs &g, uint64_t aa, uint64_t ab, uint64_t ia, uint64_t ib)
 {
     const int n = g.n;
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs g)
     const uint64_t lt = (1ull << lane) - 1ull;
     const uint32_t row0 = (blockIdx.x * (kPairBlock / 64) + (uint32_t)wv) * kPairRows;
     PairQueue *q0 = &queues[MODE == kPairCount ? 0 : 2 * wv], *q1 = &queues[MODE == kPairCount ? 0 : 2 * wv + 1];
-    uint32_t n0 = 0, n1 = 0;  // entries: doubles and the diagonal, singles
+    uint32_t n0 = 0, n1 = 0;  // entries: doubles and equal determinants, singles
     M ra[kPairRows], rb[kPairRows];
     uint32_t run[kPairRows];
 #pragma unroll
@@ -89,15 +89,16 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs g)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if ((uint32_t)lane < m) {
             const uint32_t j = q->col[lane], i = row0 + q->row[lane];
-            const double v = i == j ? g.hdiag[i]
-                                    : pair_element(g, g.dets[2 * (size_t)i], g.dets[2 * (size_t)i + 1],
-                                                   g.dets[2 * (size_t)j], g.dets[2 * (size_t)j + 1]);
+            const uint64_t ia = g.dets[2 * (size_t)i], ib = g.dets[2 * (size_t)i + 1];
+            const uint64_t ja = g.dets[2 * (size_t)j], jb = g.dets[2 * (size_t)j + 1];
+            // a determinant that the set holds twice couples to its copy by H_ii
+            const double v = ia == ja && ib == jb ? g.hdiag[i] : pair_element(g, ia, ib, ja, jb);
             if (MODE == kPairFill) {
                 const int64_t at = g.start[(size_t)i * g.shares + blockIdx.y] + (int64_t)q->pos[lane];
                 g.cols[at] = (int32_t)j;
                 g.vals[at] = v;
             } else {
-                // both triangles; the diagonal once
+                // both triangles; a row with itself once
                 acc = acc + (i == j ? 1.0 : 2.0) * (g.c[i] * v * g.c[j]);
             }
         }
