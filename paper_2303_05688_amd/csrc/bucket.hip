@@ -1090,10 +1090,11 @@ struct WaveLds {
     uint32_t ck[CAP];
     uint16_t ix[CAP + 8];
     union {
-        double val[CAP];
+        double val[CAP + 2];  // val[CAP] stays 0: what a lane past the end of its run adds
         uint32_t cnt[DIGITS / 2];
     };
-    double zero[2];  // val[CAP]: what a lane past the end of its run adds
+    static_assert(sizeof(cnt) <= sizeof(double) * CAP && sizeof(val) > sizeof(double) * CAP,
+                  "the counters lie below the zero, and the zero inside the values");
 };
 template <int IT>
 constexpr int digit_bits()
@@ -1809,7 +1810,7 @@ __global__ __launch_bounds__(64 * kFinishWaves) __attribute__((amdgpu_waves_per_
     unsigned char *mine = smem_raw + f.tab_bytes + wv * f.wave_bytes;
     WaveLds<IT> &S = *reinterpret_cast<WaveLds<IT> *>(mine);
     double *acache = reinterpret_cast<double *>(mine + ((sizeof(WaveLds<IT>) + 15) & ~size_t(15)));
-    if ((tid & 63) < 2) S.zero[tid & 63] = 0.0;
+    if ((tid & 63) < 2) S.val[WaveLds<IT>::CAP + (tid & 63)] = 0.0;
     __syncthreads();
     const uint32_t nf = part_count(dev_count(f.nfinal, f.dn_final), f.part);
     // thr: a lower bound of the final k-th |A|, from a pilot or earlier class batches, if any
