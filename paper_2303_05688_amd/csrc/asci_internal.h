@@ -426,7 +426,7 @@ struct BucketArgs {
     uint32_t h_runs = 0;                 // its value on the host, once V is there
     const double *bounds = nullptr;      // with thr or a pilot and both tables: k_diag_bounds (optional)
     const uint32_t *dn_levels = nullptr, *dn_nlarge = nullptr, *dn_overflow = nullptr;  // nonzero: not divided / a list overflowed
-    int dev_levels = 0, dev_rounds = 1;  // split levels and small-split rounds queued
+    int dev_levels = 0;  // split levels queued
     // where the candidates lie: a bit per slot, a count and an output offset per tile of slots
     unsigned long long *mask = nullptr;
     uint32_t *tcnt = nullptr, ntile = 0;

@@ -666,16 +666,21 @@ __global__ __launch_bounds__(kTileT) __attribute__((amdgpu_waves_per_eu(8))) voi
 // registers, 16 samples a range are ranked against each other in LDS, and the
 // records are written back range by range, each range in record order.  The
 // separate splitter, histogram, scan and scatter launches of a level would read
-// the records twice more and leave most of every tile empty.  A range that
-// still exceeds cap and holds several keys (the sample misled) goes to the next
-// list; one of a single key is a single-key final.  Of 17,500 cycles a segment
-// of 1000 records, 4900 went into ranking the samples (one thread counted all
-// others for each) and 3500 into grouping the ranges by pointer doubling: 1.3e8
-// records of 16e20o took 1.29 ms, now 1.10 (3.8 TB/s).
+// the records twice more and leave most of every tile empty.  A range of a
+// single key that exceeds cap is a single-key final; one of several keys (the
+// sample misled, as happens where targets have hundreds of contributions each)
+// is split again by the same workgroup, on samples of its own: every split
+// divides a range of several keys, so this ends.  Left to a later launch, such
+// ranges sent small searches of dense spaces back to the step-by-step path (3.9
+// million pairs of 13 + 6 electrons in 14 orbitals 1.16 ms, now 0.52).  Of
+// 17,500 cycles a segment of 1000 records, 4900 went into ranking the samples
+// (one thread counted all others for each) and 3500 into grouping the ranges by
+// pointer doubling: 1.3e8 records of 16e20o took 1.29 ms, now 1.10 (3.8 TB/s).
 constexpr int kSmallT = 512;
 constexpr int kSmallItems = kTileN / kSmallT;
 constexpr int kSmallMax = 64;      // ranges: half of cap each
 constexpr int kSmallSample = 512;  // samples at most
+constexpr int kMinCap = 1024 / kFinishWaves;  // the smallest wave_cap
 template <int W>
 __global__ __launch_bounds__(kSmallT) __attribute__((amdgpu_waves_per_eu(4))) void k_small_split(
     const Seg *__restrict__ segs, uint32_t nseg, const uint32_t *dn_seg, uint32_t cap, uint64_t *__restrict__ klo0,
@@ -690,11 +695,21 @@ __global__ __launch_bounds__(kSmallT) __attribute__((amdgpu_waves_per_eu(4))) vo
     __shared__ uint64_t q_lo[kSmallMax], q_hi[W == 2 ? kSmallMax : 1];
     __shared__ uint16_t s_wcnt[NW][kSmallMax];
     __shared__ uint32_t s_rank[kSmallSample];
+    // ranges to be split again: disjoint, of more than cap of the segment's records
+    __shared__ Seg s_left[kTileN / kMinCap];
+    __shared__ uint32_t s_nleft;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const uint64_t lt = (1ull << lane) - 1ull;
     const uint32_t ns = dev_count(nseg, dn_seg);
-    for (uint32_t s = blockIdx.x; s < ns; s += gridDim.x) {
-        const Seg sg = segs[s];
+    uint32_t left = 0;  // entries of s_left
+    for (uint32_t s = blockIdx.x; left > 0u || s < ns;) {  // uniform
+        Seg sg;
+        if (left > 0u) {
+            sg = s_left[--left];
+        } else {
+            sg = segs[s];
+            s += gridDim.x;
+        }
         const uint32_t size = sg.size, buf = seg_buf(sg);
         uint64_t *klo = (buf ? klo1 : klo0) + sg.start, *khi = W == 2 ? (buf ? khi1 : khi0) + sg.start : nullptr;
         double *val = (buf ? val1 : val0) + sg.start;
@@ -858,7 +873,14 @@ __global__ __launch_bounds__(kSmallT) __attribute__((amdgpu_waves_per_eu(4))) vo
             __syncthreads();
             for (uint32_t i = tid; i < size; i += kSmallT) val[i] = sv[i];
         }
-        if (wv == 0) append_segs(lists, kind, c);
+        if (wv == 0) {
+            const uint64_t again = __ballot(kind == 3u);
+            if (kind == 3u) s_left[left + (uint32_t)__popcll(again & lt)] = c;
+            if (lane == 0) s_nleft = left + (uint32_t)__popcll(again);
+            append_segs(lists, kind == 3u ? 0u : kind, c);
+        }
+        __syncthreads();  // the records, and what is left, are written
+        left = s_nleft;
     }
 }
 
@@ -2106,14 +2128,13 @@ static void finish_bytes(const BucketArgs &b, int W)
 constexpr size_t kQueuedRecords = (size_t)1 << 28;
 
 // device counters of one batch
-enum { kCtrFinal = 0, kCtrLarge = 1 /* and 2: per level parity */, kCtrOverflow = 3, kCtrSmall = 4 /* and 5: per round */,
-       kCtrLevels = 6 };
+enum { kCtrFinal = 0, kCtrLarge = 1 /* and 2: per level parity */, kCtrOverflow = 3, kCtrSmall = 4, kCtrLevels = 6 };
 
 // Split levels, finish, and the scan that places the candidates.  With dev
-// nothing is read back: b.dev_levels levels and b.dev_rounds small splits run
-// on launch shapes sized for bounds (the caller checks b.dn_nlarge and
-// b.dn_overflow); else the host reads the number of large segments once per
-// level and stops when none is left.
+// nothing is read back: b.dev_levels levels and the small split run on launch
+// shapes sized for bounds (the caller checks b.dn_nlarge and b.dn_overflow);
+// else the host reads the number of large segments once per level and stops
+// when none is left.
 template <int W>
 static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, HostStage *hs, bool dev)
 {
@@ -2232,20 +2253,10 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
             small, nsmall, nsm, cap, b.klo[0], b.klo[1], b.khi[0], b.khi[1], b.val[0], b.val[1], lists);
         ASCI_LAUNCH_CHECK();
     };
-    // levels and a small split, queued, rounds times (one level ahead of each later one)
     constexpr uint32_t kAnyGrid = 1u << 30;
-    auto queue_rounds = [&](int levels, int rounds, uint32_t bound, uint32_t gmax, uint32_t gsmall) {
-        for (int l = 0; l < levels; ++l) split_level(bound, true, gmax);
-        for (int round = 0; round < rounds; ++round) {
-            // the next round takes what the small split of this one left, from list lev & 1
-            lists.nsmall = ctr + kCtrSmall + ((round & 1) ^ 1);
-            if (round > 0) fill_u32(lists.nsmall, 1, 0u, s);
-            small_split(level_cap, ctr + kCtrSmall + (round & 1), gsmall);
-            if (round + 1 < rounds) split_level(level_cap, true, 2048u);
-        }
-    };
     if (dev) {
-        queue_rounds(b.dev_levels, b.dev_rounds, level_cap, 2048u, 4096u);
+        for (int l = 0; l < b.dev_levels; ++l) split_level(level_cap, true, 2048u);
+        small_split(level_cap, ctr + kCtrSmall, 4096u);
         // what is left in list lev & 1 fails the call
         b.dn_nlarge = ctr + kCtrLarge + (lev & 1);
         b.dn_overflow = ctr + kCtrOverflow;
@@ -2253,30 +2264,25 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
     } else {
         // What most batches need is queued at once: a read-back between two
         // levels leaves the chip idle for about 35 us (8a5b23o, 4.6e7 records: five
-        // read-backs, now two).  Ahead of the first small split a large segment
-        // has more records than a tile.  Above 2^28 records a level takes long
-        // enough, and its grid is better sized by its count.
-        int round = 0;
-        if (P <= kQueuedRecords) {
-            const uint32_t bound = (uint32_t)(P / kTileN + 1);
-            queue_rounds(P <= ((size_t)1 << 19) ? 1 : 2, 2, bound, kAnyGrid, 16384u);
-            round = 2;
+        // read-backs, now one).  A large segment has more records than a tile.
+        // Above 2^28 records a level takes long enough, and its grid is better
+        // sized by its count.
+        bool small_done = P <= kQueuedRecords;
+        if (small_done) {
+            for (int l = 0; l < (P <= ((size_t)1 << 19) ? 1 : 2); ++l) split_level((uint32_t)(P / kTileN + 1), true, kAnyGrid);
+            small_split(level_cap, ctr + kCtrSmall, 16384u);
         }
         read_counts();
-        for (;; ++round) {
-            while (hcnt[kCtrLarge + (lev & 1)] > 0) {
-                split_level(hcnt[kCtrLarge + (lev & 1)], false, kAnyGrid);
-                read_counts();
-            }
-            const uint32_t nsmall = hcnt[kCtrSmall + (round & 1)];
-            if (nsmall == 0) break;
-            // leftovers go to list lev & 1, whose count is zero here, and the
-            // small ones among their children to the other round's count
-            if (round > 0) fill_u32(ctr + kCtrSmall + ((round & 1) ^ 1), 1, 0u, s);
-            lists.nsmall = ctr + kCtrSmall + ((round & 1) ^ 1);
-            lists.next = lv[lev & 1];
-            lists.nnext = ctr + kCtrLarge + (lev & 1);
-            small_split(nsmall, nullptr, kAnyGrid);
+        if (small_done && hcnt[kCtrLarge + (lev & 1)] > 0) {
+            fill_u32(ctr + kCtrSmall, 1, 0u, s);  // the ones so far are split
+            small_done = false;
+        }
+        while (hcnt[kCtrLarge + (lev & 1)] > 0) {
+            split_level(hcnt[kCtrLarge + (lev & 1)], false, kAnyGrid);
+            read_counts();
+        }
+        if (!small_done && hcnt[kCtrSmall] > 0) {
+            small_split(hcnt[kCtrSmall], nullptr, kAnyGrid);
             read_counts();
         }
         b.levels = hcnt[kCtrLevels];

@@ -1780,11 +1780,11 @@ __global__ __launch_bounds__(64) void k_async_done(DoneArgs g)
 // pairs 0.21 and 0.26, 2^19 0.34 and 0.39, 2^20 0.44 and 0.48, 2^21 0.49 and 0.43).
 constexpr size_t kSortAllPairs = (size_t)1 << 20;
 
-// dev_levels, dev_rounds: split levels and small-split rounds queued (what they
-// leave undivided fails the call with kStatSplit)
+// dev_levels: split levels queued (a segment of more than a tile that they
+// leave fails the call with kStatSplit)
 template <int W>
 static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uint64_t *out_dets, double *out_scores,
-                             asci_async_result *d_result, hipStream_t s, bool plan_only, int dev_levels, int dev_rounds,
+                             asci_async_result *d_result, hipStream_t s, bool plan_only, int dev_levels,
                              uint32_t **stat_out = nullptr)
 {
     const int n = in.n, na = in.na, nb = in.nb;
@@ -1934,7 +1934,6 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     ba.pool_base = 0;
     ba.pool_cap = pool_cap;
     ba.dev_levels = dev_levels;
-    ba.dev_rounds = dev_rounds;
     bucket_accumulate_dev<W>(ba, ar, s);
     bucket_collect_dev<W>(ba, s);
     const uint32_t *d_V = ba.dn_V;
@@ -2007,7 +2006,7 @@ static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out
     ctx->setup.reserve(setup_bytes((size_t)in.ndets, core_count(in), in.n, W));
     ctx->setup.reset();
     uint32_t *d_stat = ctx->setup.take<uint32_t>(16);
-    run_search_async<W>(ctx, in, out.k, out.out_dets, out.out_scores, (asci_async_result *)(d_stat + 8), s, false, levels, 1,
+    run_search_async<W>(ctx, in, out.k, out.out_dets, out.out_scores, (asci_async_result *)(d_stat + 8), s, false, levels,
                         &d_stat);
     const uint32_t *h = (const uint32_t *)hs.ptr;
     ASCI_HIP(hipMemcpyAsync(hs.ptr, d_stat, 16 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
@@ -2024,16 +2023,15 @@ static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out
 }
 
 // Three levels take the largest batch (below 2^31 records) to ranges of one
-// tile, one more isolates single keys, one is spare; another lies between the
-// two rounds of the small split.
-constexpr int kAsyncLevels = 5;
+// tile, one more isolates single keys, two are spare.
+constexpr int kAsyncLevels = 6;
 
 void search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uint64_t *out_dets, double *out_scores,
                   asci_async_result *d_result, hipStream_t s, bool plan_only)
 {
     require(k >= 1, ASCI_EINVAL, "k must be >= 1");
-    if (in.n <= 32) run_search_async<1>(ctx, in, k, out_dets, out_scores, d_result, s, plan_only, kAsyncLevels, 2);
-    else run_search_async<2>(ctx, in, k, out_dets, out_scores, d_result, s, plan_only, kAsyncLevels, 2);
+    if (in.n <= 32) run_search_async<1>(ctx, in, k, out_dets, out_scores, d_result, s, plan_only, kAsyncLevels);
+    else run_search_async<2>(ctx, in, k, out_dets, out_scores, d_result, s, plan_only, kAsyncLevels);
 }
 
 size_t search_async_bytes(const SearchArgs &in, int64_t k, int finish_cap, bool spin_tables)

@@ -119,3 +119,36 @@ def test_small_search_invalid_strings(n, na, nb, alpha, beta):
         assert e.value.code == asci.ASCI_EINVAL
     d = gu.to_dev(good)
     _compare(d, n, na, nb, -3.5, [100], _expected(d, n, na, nb, -3.5))
+
+
+@pytest.mark.parametrize("n,na,nb,ndets", [(14, 13, 6, 948), (10, 8, 5, 3780), (16, 1, 8, 2146), (16, 2, 8, 380),
+                                           (34, 33, 2, 1200)])
+def test_small_search_dense_space(n, na, nb, ndets):
+    """Targets with hundreds of contributions each, so that a small split's
+    ranges of several keys exceed a wavefront's share: they are divided where
+    they arise, for every finish capacity, and no further level is taken."""
+    import asci_synth as syn
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+
+    assert ndets * _pairs(n, na, nb) <= 1 << 22
+    rng = np.random.default_rng(n + ndets)
+    h, eri = syn.integrals(n, rng)
+    dets = np.array(syn.level_dets(n, na, nb, ndets, rng), dtype=np.uint64)
+    d = gu.to_dev({"h": h, "eri": eri, "dets": dets, "coeffs": syn.coefficients(ndets, ndets, rng)})
+    want = None
+    for cap in (4096, 2048, 1024):
+        ctx = asci.Context(0)
+        ctx.set_param("finish_cap", cap)
+        every = _expected(d, n, na, nb, -3.5, ctx=ctx)
+        want = want or every
+        assert (every[0] == want[0]).all() and (every[1].view(np.uint64) == want[1].view(np.uint64)).all()
+        _compare(d, n, na, nb, -3.5, [1, 1025, 4000], want, ctx=ctx)
+        assert ctx.get_param("last_levels") <= 2
+        r = asci.SearchRequest(d["h"], d["eri"], n, na, nb, d["dets"], d["coeffs"], -3.5, 4000)
+        count, status, flags = asci.async_status(asci.search_async(r, ctx=ctx))
+        assert (status, flags) == (0, 0)
+        gk, gs = (gu.host(x) for x in r.result(count))
+        m = min(4000, len(want[1]))
+        assert count == m and (gk == want[0][:m]).all() and (gs.view(np.uint64) == want[1][:m].view(np.uint64)).all()
+        ctx.close()
