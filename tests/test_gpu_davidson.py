@@ -116,3 +116,30 @@ def test_davidson_sign(subspace, seed):
     # two vectors of residual 1e-7 each
     assert np.linalg.norm(gu.host(vec) - u) <= 4e-7 / (w[1] - w[0])
     H.close()
+
+
+@pytest.mark.parametrize("ndets", [300, 5000])
+def test_davidson_products(ndets):
+    """A converged guess takes one product with H and returns that vector; a
+    solve takes at most one more than its iterations."""
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+
+    H = _hmat(16, 6, ndets, 77)
+    e0, v0, _, it0 = asci.davidson(H, max_subspace=12, max_iter=400, tol=1e-9)
+
+    def solve(**kw):
+        H.ctx.set_profiling(True)
+        r = asci.davidson(H, max_subspace=12, max_iter=400, **kw)
+        n = H.ctx.profile()["spmv"][1]
+        H.ctx.set_profiling(False)
+        return r, n
+
+    (e, vec, res, it), n = solve(guess=v0, tol=1e-6)
+    assert (it, n) == (1, 1) and res <= 1e-6
+    assert abs(e - e0) <= 1e-11 * max(abs(e0), 1.0)
+    a, b = gu.host(vec), gu.host(v0)
+    assert min(np.linalg.norm(a - b), np.linalg.norm(a + b)) <= 1e-12
+    (e, vec, res, it), n = solve(tol=1e-9)
+    assert it == it0 > 3 and n <= it + 1 and res <= 1e-9 and e == e0
+    H.close()
