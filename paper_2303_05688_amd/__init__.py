@@ -316,17 +316,23 @@ def candidates(h, eri, norb, nalpha, nbeta, dets, coeffs, E0, ncore=0, eps=0.0, 
             _dev(dets, torch.uint64), _dev(coeffs, torch.float64), dets.shape[0], float(E0), C.byref(o))
     # One pass into buffers for every pair where these are small (4.9 million
     # candidates of 14.6 million pairs: 2.1 ms with a pass that only counts
-    # first, 1.1 so), the used part copied out; else count, then fill.
+    # first, 1.1 so), the used part copied out; else, and where the memory does
+    # not suffice for that, count, then fill.
     bound = _pair_bound(norb, nalpha, nbeta, dets.shape[0], ncore)
-    if 0 < bound <= 1 << 26:
+    if _one_pass(bound, pair_buffer_bytes, h.device):
         try:
             room = [torch.empty(sh, dtype=t, device=h.device) for sh, t in (
                 ((bound, 2), torch.uint64), ((bound,), torch.float64), ((bound,), torch.float64))]
+            rc = _lib.asci_candidates_device(*args, bound, *(t.data_ptr() for t in room), C.byref(cnt), _stream(dev))
+            if rc == ASCI_OK:
+                return tuple(t[:cnt.value].clone() for t in room)
         except torch.cuda.OutOfMemoryError:
-            room = None
-        if room is not None:
-            _check(_lib.asci_candidates_device(*args, bound, *(t.data_ptr() for t in room), C.byref(cnt), _stream(dev)))
-            return tuple(t[:cnt.value].clone() for t in room)
+            rc = ASCI_ENOMEM
+        room = None
+        if rc != ASCI_ENOMEM:
+            _check(rc)
+        torch.cuda.empty_cache()  # back to the device, for the library's workspace
+        cnt.value = 0
     rc = _lib.asci_candidates_device(*args, 0, None, None, None, C.byref(cnt), _stream(dev))
     if rc not in (ASCI_OK, ASCI_ENOMEM) or (rc == ASCI_ENOMEM and cnt.value == 0):
         _check(rc)
@@ -348,6 +354,16 @@ def _pair_bound(norb, nalpha, nbeta, ndets, ncore):
     per = (nalpha * va + nbeta * vb + comb(nalpha, 2) * comb(va, 2) + comb(nbeta, 2) * comb(vb, 2)
            + nalpha * va * nbeta * vb)
     return per * (min(ncore, ndets) if ncore > 0 else ndets)
+
+
+def _one_pass(bound, pair_buffer_bytes, device):
+    """Whether candidates() takes buffers for all `bound` pairs, 32 bytes each: at
+    most 2 GiB, the caller's pair buffer where one is set, and, from 128 MiB on,
+    a sixteenth of the free memory (torch keeps them when they are freed)."""
+    size = 32 * bound
+    if not 0 < size <= 2 << 30 or 0 < pair_buffer_bytes < size:
+        return False
+    return size < 128 << 20 or size <= _torch().cuda.mem_get_info(device)[0] // 16
 
 
 def pt2(h, eri, norb, nalpha, nbeta, dets, coeffs, E0, ncore=0, eps=0.0, ecore=0.0, pair_buffer_bytes=0,
