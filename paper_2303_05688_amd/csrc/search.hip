@@ -1781,11 +1781,12 @@ __global__ __launch_bounds__(64) void k_async_done(DoneArgs g)
 constexpr size_t kSortAllPairs = (size_t)1 << 20;
 
 // dev_levels: split levels queued (a segment of more than a tile that they
-// leave fails the call with kStatSplit)
+// leave fails the call with kStatSplit); tables: the arena of the spin tables
+// (null: in ctx->main)
 template <int W>
 static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uint64_t *out_dets, double *out_scores,
                              asci_async_result *d_result, hipStream_t s, bool plan_only, int dev_levels,
-                             uint32_t **stat_out = nullptr)
+                             Arena *tables = nullptr, uint32_t **stat_out = nullptr)
 {
     const int n = in.n, na = in.na, nb = in.nb;
     const uint64_t full = (n == 64) ? ~0ull : ((1ull << n) - 1ull);
@@ -1818,12 +1819,19 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     Arena &ar = ctx->main;
     ar.reset();
     const SpinTablePlan pl = spin_table_plan(n, na, nb, P, ctx->spin_tables != 0);
-    // the bound of the one-batch search, the tables, and what is sized for its
-    // bound instead of its count
+    // What the step-by-step search takes for these pairs in one batch; with the
+    // tables in here too, room to spare.
     const int fcap = effective_finish_cap(ctx, n, na, P);
-    ar.reserve(main_bytes(E, Pb, pool_cap, (uint32_t)ncls, (size_t)kh, true, W, fcap) + pl.bytes + Pb / 4 +
-               ((size_t)16 << 20));
+    size_t bytes = main_bytes(E, Pb, pool_cap, (uint32_t)ncls, (size_t)kh, true, W, fcap);
+    if (!tables) bytes += pl.bytes + Pb / 4 + ((size_t)16 << 20);
+    ar.reserve(bytes);
     ar.reset();
+    if (tables) {
+        tables->reset();
+        tables->reserve(pl.bytes);
+        tables->reset();
+    }
+    Arena &ta = tables ? *tables : ar;
     if (plan_only) return;  // workspaces sized, nothing queued
 
     // ---- inputs: validation (flags on the device), integral tables, psi set, core set, class masks
@@ -1832,13 +1840,13 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     carve_setup<W>(su, nd, nq, n, pp, d_tree);
     uint32_t *d_stat = pp.d_err;  // [0] status bits, [1] selection size, [2] candidates, [3] final segments
     if (stat_out) *stat_out = d_stat;
-    uint32_t *d_binom = take_binom(pl, n, ar);
+    uint32_t *d_binom = take_binom(pl, n, ta);
     queue_inputs<W>(in, pp, d_binom, pl.kmax, (uint32_t)ncls, L, su, s);
     uint64_t *d_cls = pp.d_cls;
     uint64_t *q_a = pp.q_a, *q_b = pp.q_b;
     double *q_c = pp.q_c, *d_jk = pp.d_jk, *d_eri8 = pp.d_eri8;
     const PsiSet &psi = pp.psi;
-    const SpinTables st = build_spin_tables(pl, d_binom, d_jk, n, na, nb, ar, s);
+    const SpinTables st = build_spin_tables(pl, d_binom, d_jk, n, na, nb, ta, s);
 
     // ---- count matrix, record offsets, generation (one batch: every class)
     uint32_t *counts = ar.take<uint32_t>(E);
@@ -1982,7 +1990,7 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
 // A search of one small class batch through the asynchronous search with as
 // many split levels as it should need, its result and counts read back once.
 // false: outside that scope, or not divided in those levels; the caller then
-// runs the search step by step.
+// runs the search step by step, in the same workspaces.
 template <int W>
 static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipStream_t s)
 {
@@ -2007,7 +2015,7 @@ static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out
     ctx->setup.reset();
     uint32_t *d_stat = ctx->setup.take<uint32_t>(16);
     run_search_async<W>(ctx, in, out.k, out.out_dets, out.out_scores, (asci_async_result *)(d_stat + 8), s, false, levels,
-                        &d_stat);
+                        &ctx->tables, &d_stat);
     const uint32_t *h = (const uint32_t *)hs.ptr;
     ASCI_HIP(hipMemcpyAsync(hs.ptr, d_stat, 16 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     ASCI_HIP(hipStreamSynchronize(s));

@@ -152,3 +152,27 @@ def test_small_search_dense_space(n, na, nb, ndets):
         m = min(4000, len(want[1]))
         assert count == m and (gk == want[0][:m]).all() and (gs.view(np.uint64) == want[1][:m].view(np.uint64)).all()
         ctx.close()
+
+
+@pytest.mark.parametrize("n,na,nb,ndets", [(12, 4, 4, 201), (12, 6, 6, 2300), (16, 8, 2, 1500), (34, 3, 3, 360)])
+def test_small_search_holds_no_more_than_the_steps(n, na, nb, ndets):
+    """Device memory that a context keeps after a small search: no more than
+    after the step-by-step search of the same inputs (profiling takes it)."""
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+    import torch
+
+    assert ndets * _pairs(n, na, nb) <= 1 << 22
+    d = gu.to_dev(_case(n, na, nb, ndets, 5))
+    held = []
+    for steps in (True, False, True, False):  # the first two load the kernels
+        ctx = asci.Context(0)
+        ctx.set_profiling(steps)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info(0)[0]
+        asci.search(d["h"], d["eri"], n, na, nb, d["dets"], d["coeffs"], -3.5, 10 * ndets, ctx=ctx)
+        torch.cuda.synchronize()
+        held.append(before - torch.cuda.mem_get_info(0)[0])
+        ctx.close()
+    print("held", held)
+    assert 0 < held[3] <= held[2]
