@@ -444,14 +444,13 @@ int bucket_collect(BucketArgs &b, hipStream_t s, Profiler *prof);  // profiler t
 void bucket_read_v(BucketArgs &b, hipStream_t s);
 // sum over the batch's candidates of N_a * A_a (deterministic order)
 double bucket_pt2(BucketArgs &b, Arena &ar, hipStream_t s, HostStage &hs);
-// The same sort-and-accumulate with no count read back (asynchronous search):
-// launches sized for host bounds, b.dev_levels split levels, the counts in
-// b.dn_*.
 // out[4]: the bounds that reject targets under a threshold; etab: the table of
 // E(beta), ntab strings, tmp: a double for every 256 of them
 void bucket_diag_bounds(const double *jk, int n, int na, int nb, double E0, double ecore, const double *etab, uint32_t ntab,
                         double *tmp, double *out, hipStream_t s);
-
+// The same sort-and-accumulate with no count read back (asynchronous search):
+// launches sized for host bounds, b.dev_levels split levels, the counts in
+// b.dn_*.
 template <int W>
 void bucket_accumulate_dev(BucketArgs &b, Arena &ar, hipStream_t s);
 template <int W>

@@ -173,7 +173,6 @@ inline size_t level_hist(size_t P, size_t nseg, size_t cap)
 
 struct SplitArgs {
     const Seg *segs;            // large segments of this level
-    uint32_t nseg;
     const uint32_t *tile_base;  // per segment: first tile
     const uint32_t *hist_base;  // per segment: first histogram entry
     const uint32_t *tile_seg;   // per tile: its segment
@@ -2209,7 +2208,6 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         }
         SplitArgs sa;
         sa.segs = segs;
-        sa.nseg = nlarge;
         sa.tile_base = tbase;
         sa.hist_base = hbase;
         sa.tile_seg = tseg;

@@ -501,7 +501,6 @@ void scan_u32(const uint32_t *in, uint32_t *out, size_t n, uint32_t *d_total, Ar
     }
     size_t nb = (n + kTile - 1) / kTile;
     require(nb <= (1u << 26), ASCI_EINVAL, "scan too long");
-    size_t mark = ar.used();
     uint32_t *partial = ar.take<uint32_t>(nb);
     k_scan_reduce<<<(unsigned)nb, kThreads, 0, s>>>(in, n, partial, dn);
     ASCI_LAUNCH_CHECK();
@@ -509,7 +508,6 @@ void scan_u32(const uint32_t *in, uint32_t *out, size_t n, uint32_t *d_total, Ar
     ASCI_LAUNCH_CHECK();
     k_scan_down<<<(unsigned)nb, kThreads, 0, s>>>(in, out, n, partial, dn);
     ASCI_LAUNCH_CHECK();
-    (void)mark;
 }
 
 template <int KW>

@@ -1018,13 +1018,14 @@ static SpinTables build_spin_tables(const SpinTablePlan &pl, const uint32_t *d_b
     return st;
 }
 
-// bytes of the setup arena of a search: inputs keyed, the psi hash set and
-// filter, core set, class masks / totals / split tree, integral tables
-static size_t setup_bytes(size_t nd, size_t nq, int n, int W)
+// bytes of the setup arena of a search: class masks, totals and split tree,
+// integral tables, core set, exclusion set (at most 8 nd slots of 20 bytes, or
+// 1024) and filter (at most 64 nd bits, or 2^16); the keys and positions that
+// the core set is selected with; each rounded up to 256 bytes
+static size_t setup_bytes(size_t nd, size_t nq, int n)
 {
-    const size_t hist_bytes = ((nd + kScanTile - 1) / kScanTile) * 256 * 4 * 2 + (1 << 16);
-    return nd * (8 * 2 * W + 4 * 2) + nd * (8 * 2 + 4 * 2) + nq * 8 * 4 + kMaxClasses * 20 + (size_t)2 * n * n * 8 +
-           2 * hist_bytes + 64 * 256 + (nd * 8 + 1024) * 20 + nd * 8 + eri_packed_count(n) * 8 + 256 + (1 << 14);
+    return kMaxClasses * 20 + (size_t)(2 * n * n + n) * 8 + eri_packed_count(n) * 8 + nq * 24 + (nd * 8 + 1024) * 20 +
+           nd * 8 + (1 << 13) + nd * (2 * 8 + 2 * 4) + nq * (8 + 4) + 64 * 256;
 }
 
 // bytes of the main arena: count matrix and offsets (E entries), the pair
@@ -1304,7 +1305,7 @@ static void prepare(asci_ctx *ctx, const SearchArgs &in, uint64_t fit, uint32_t 
     const BetaFactors bf = beta_factors(n, in.nb);
     Arena &ar = ctx->setup;
     ar.reset();
-    ar.reserve(setup_bytes(nd, nq, n, W));
+    ar.reserve(setup_bytes(nd, nq, n));
     ar.reset();
     uint32_t *d_tree;
     carve_setup<W>(ar, nd, nq, n, pp, d_tree);
@@ -1814,7 +1815,7 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     // ---- workspaces (allocated only when larger than what ctx holds)
     Arena &su = ctx->setup;
     su.reset();
-    su.reserve(setup_bytes(nd, nq, n, W));
+    su.reserve(setup_bytes(nd, nq, n));
     su.reset();
     Arena &ar = ctx->main;
     ar.reset();
@@ -2011,7 +2012,7 @@ static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out
     hs.reserve(256);
     ctx->setup.reset();
     // the result record lies behind the status words, which the setup arena holds first
-    ctx->setup.reserve(setup_bytes((size_t)in.ndets, core_count(in), in.n, W));
+    ctx->setup.reserve(setup_bytes((size_t)in.ndets, core_count(in), in.n));
     ctx->setup.reset();
     uint32_t *d_stat = ctx->setup.take<uint32_t>(16);
     run_search_async<W>(ctx, in, out.k, out.out_dets, out.out_scores, (asci_async_result *)(d_stat + 8), s, false, levels,
@@ -2056,7 +2057,7 @@ size_t search_async_bytes(const SearchArgs &in, int64_t k, int finish_cap, bool 
     if ((size_t)ncls * nq >= (1ull << 31)) return 0;
     const uint64_t kh = std::min<uint64_t>((uint64_t)k, P);
     const SpinTablePlan pl = spin_table_plan(n, na, in.nb, P, spin_tables);
-    return setup_bytes(nd, nq, n, W) + main_bytes((size_t)ncls * nq, (size_t)P, (size_t)P + 1, (uint32_t)ncls,
+    return setup_bytes(nd, nq, n) + main_bytes((size_t)ncls * nq, (size_t)P, (size_t)P + 1, (uint32_t)ncls,
                                                   (size_t)kh, true, W, finish_cap) +
            pl.bytes + (size_t)P / 4 + ((size_t)16 << 20);
 }
@@ -2077,7 +2078,7 @@ size_t search_scratch_bound(const SearchArgs &in, int64_t k, int finish_cap, siz
     const size_t pool_cap = k > 0 ? (size_t)std::min<uint64_t>(P + 1, std::max<uint64_t>(4 * (uint64_t)k, P) + (uint64_t)k)
                                   : (size_t)P + 1;
     const size_t kk = k > 0 ? (size_t)std::min<uint64_t>((uint64_t)k, pool_cap) : 0;
-    setup_part = (setup_bytes(nd, nq, in.n, W) + 255) & ~size_t(255);
+    setup_part = (setup_bytes(nd, nq, in.n) + 255) & ~size_t(255);
     return setup_part + main_bytes(E, (size_t)P, pool_cap, (uint32_t)std::min<uint64_t>(ncls, kMaxBatchClasses), kk,
                                    k > 0, W, finish_cap);
 }
