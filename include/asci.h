@@ -220,8 +220,8 @@ int asci_candidates_device(asci_ctx *ctx, const double *d_h, const double *d_eri
  * Eq. (1); ASCI's final step in Alg. 1):
  *     E_PT2 = sum over candidates a of N_a^2 / (E0 - H_aa) = sum_a N_a * A_a,
  * with N_a, A_a, the core set and eps exactly as in asci_search.  Summation:
- * per bucket of candidates in key order, then a fixed-order tree, so the
- * result is reproducible run to run.  *out_count receives the number of
+ * per tile of 4096 candidate slots (key order), each by a fixed tree, then a
+ * fixed-order tree over the tiles, so the result is reproducible run to run.  *out_count receives the number of
  * candidates.  d_*: device.
  */
 int asci_pt2_device(asci_ctx *ctx, const double *d_h, const double *d_eri, int norb, int nalpha,

@@ -914,7 +914,11 @@ constexpr uint32_t kMinRanks = 256;
 
 constexpr uint32_t kSlotTile = 4096;  // slots per collect tile
 enum { kAll = 0, kPilotPart = 1, kRestPart = 2 };
-constexpr uint32_t kPilot = 16;  // a pilot takes every 16th final segment
+// A pilot takes every 16th final segment: of more, fewer are left to gain from;
+// fewer bound the k-th |A| less tightly (every 8th, 16th and 32nd, ms: 16e20o of
+// 2^27 pairs, k = P / 256 6.64, 6.76, 6.93, k = P / 8192 6.17, 6.08, 6.08; 24e30o
+// of 2^28 pairs, k = P / 1024 20.3, 20.1, 20.2).
+constexpr uint32_t kPilot = 16;
 
 // final segments of a part, and the i-th of them
 __host__ __device__ __forceinline__ uint32_t part_count(uint32_t nf, int part)

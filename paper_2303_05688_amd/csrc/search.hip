@@ -1384,8 +1384,16 @@ __global__ __launch_bounds__(kBlock) void k_psi_targets(const uint64_t *__restri
 // where a batch holds far more candidates than that, so that few of them are
 // written, collected and selected from (1.3e8 pairs of 16e20o: 0.58 ms of that
 // became 0.17, the finish went from 1.68 to 1.45 ms with the pilot in it, and
-// the search from 7.06 to 6.44).  At 4.6e7 pairs (8a5b23o) the two came out even,
-// 2.83 and 2.82 ms: the pilot's last wavefronts are alone on the chip.
+// the search from 7.06 to 6.44).  With few pairs its last wavefronts are alone
+// on the chip, and with a large k it rejects little.  Searches without and with
+// it, ms, of P pairs with k = P / 1024 / with k = P / 256 / with k = P / 128:
+//                 P = 2^25                 2^26                     2^27
+//   16e20o   2.10 2.08 / 2.12 2.21    3.56 3.40 / 3.61 3.60    6.78 6.31 / 6.93 6.76 / 7.09 7.12
+//   24e30o   3.91 4.09 / 3.90 4.13    6.71 6.54 / 6.77 6.68    11.8 11.0 / 12.0 11.3 / 12.2 11.6
+//   12e34o   4.37 4.31 / 4.43 4.46    6.40 6.25 / 6.47 6.39    10.8 10.2 / 11.0 10.6 / 11.1 11.0
+//   20e36o   6.03 6.18 / 6.13 6.21    8.99 9.04 / 9.07 9.16    16.0 15.5 / 16.1 15.6 / 16.2 16.0
+// (12e34o and 20e36o: two-word keys, the last without tables and so without
+// bounds.)  From the lines on it is worth 3 to 10 %, or at worst costs 1 %.
 // Counting the candidates takes up to ndets * ncore pair tests (3e-13 s each where
 // no determinant has a neighbour) against about 4.6e-12 s saved a pair, so a
 // determinant set far larger than its core set goes without.
