@@ -283,6 +283,11 @@ void fill_u32(uint32_t *p, size_t n, uint32_t v, hipStream_t s);
 template <int KW>
 int merge_sort(uint64_t *(*keys)[2], uint32_t *vals[2], const double *score, size_t n, hipStream_t s,
                Profiler *prof = nullptr, const uint32_t *dn = nullptr);
+// The same for keys of one word below 2^bits: long inputs digit by digit, where
+// ar has room for sort_bytes(n) (0: none is needed), else merged.
+int sort_keys(uint64_t *keys[2], uint32_t *vals[2], const double *score, size_t n, int bits, Arena &ar, hipStream_t s,
+              Profiler *prof = nullptr, const uint32_t *dn = nullptr);
+size_t sort_bytes(size_t n);
 
 // radix selection on the IEEE bit pattern of |score[j]|, j < n: finds t, the
 // k-th largest value (1 <= k <= n), and how many entries equal to t must be

@@ -1,5 +1,5 @@
-// Device primitives for the search: exclusive scan, stable merge sort and
-// radix selection.  Written for 64-wide wavefronts (gfx950): ranking inside a
+// Device primitives for the search: exclusive scan, stable merge and radix
+// sorts, and radix selection.  Written for 64-wide wavefronts (gfx950): ranking inside a
 // wave uses ballots, blocks are 256 threads (4 waves).
 #include <algorithm>
 #include "asci_internal.h"
@@ -347,6 +347,115 @@ __global__ __launch_bounds__(kThreads) void k_sort_merge(SortKeys<KW> in, const 
     oval[d] = ival[g];
 }
 
+// ---------------------------------------------------------------- radix sort
+// Long inputs: stable LSD passes of 8 bits, tiles of kTile records.  A merge of
+// eight runs reads each of them at log2(width) scattered places for every
+// element, and its runs outgrow the cache; a digit pass streams.  The sort of
+// the k best of 1.3e8 pairs (16e20o), ms, merged and by digits: k = 3e5 0.09 and
+// 0.25, 1e6 0.30 and 0.35, 3e6 0.80 and 0.47, 2e7 7.3 and 2.4.
+constexpr size_t kRadixFrom = (size_t)3 << 19;
+
+__global__ __launch_bounds__(kThreads) void k_rs_keys(const double *__restrict__ score, uint64_t *__restrict__ key,
+                                                      uint32_t *__restrict__ val, size_t n, const uint32_t *dn)
+{
+    n = dev_n(n, dn);
+    const size_t j = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    if (j >= n) return;
+    if (score) key[j] = ~abs_order(score[j]);
+    val[j] = (uint32_t)j;
+}
+
+// counts of every digit per tile; a tile past a count on the device writes zeros
+__global__ __launch_bounds__(kThreads) void k_rs_hist(const uint64_t *__restrict__ key, size_t n, int shift,
+                                                      uint32_t *__restrict__ hist, uint32_t nblocks, const uint32_t *dn)
+{
+    __shared__ uint32_t h[kWaves][256];
+    n = dev_n(n, dn);
+    const int tid = threadIdx.x, w = tid >> 6;
+    for (int i = tid; i < kWaves * 256; i += kThreads) (&h[0][0])[i] = 0u;
+    __syncthreads();
+    const size_t base = (size_t)blockIdx.x * kTile;
+    for (int i = tid; i < kTile; i += kThreads)
+        if (base + i < n) atomicAdd(&h[w][(uint32_t)(key[base + i] >> shift) & 0xFFu], 1u);
+    __syncthreads();
+    uint32_t c = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) c += h[i][tid];
+    hist[(size_t)tid * nblocks + blockIdx.x] = c;
+}
+
+// Stable scatter of one tile.  Tile order is (wave, row, lane), which is the
+// input order, so equal digits keep their input order.
+__global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint64_t *__restrict__ ikey,
+                                                         const uint32_t *__restrict__ ival, uint64_t *__restrict__ okey,
+                                                         uint32_t *__restrict__ oval, size_t n, int shift,
+                                                         const uint32_t *__restrict__ hist, uint32_t nblocks,
+                                                         const uint32_t *dn)
+{
+    __shared__ uint64_t s_key[kTile];
+    __shared__ uint32_t s_val[kTile];
+    __shared__ uint32_t s_wcnt[kWaves][256];
+    __shared__ uint32_t s_dbase[256], s_gbase[256], s_tmp[kWaves];
+    n = dev_n(n, dn);
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const size_t tile0 = (size_t)blockIdx.x * kTile;
+    if (tile0 >= n) return;  // uniform
+    for (int i = tid; i < kWaves * 256; i += kThreads) (&s_wcnt[0][0])[i] = 0u;
+    __syncthreads();
+    uint64_t rk[kItems];
+    uint32_t rv[kItems], rrank[kItems];
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const size_t wbase = tile0 + (size_t)w * 64 * kItems;
+#pragma unroll
+    for (int s = 0; s < kItems; ++s) {
+        const size_t j = wbase + (size_t)s * 64 + lane;
+        const bool valid = j < n;
+        rk[s] = valid ? ikey[j] : 0ull;
+        rv[s] = valid ? ival[j] : 0u;
+        const uint32_t d = (uint32_t)(rk[s] >> shift) & 0xFFu;
+        const uint64_t peers = wave_match(d, valid, 8);
+        const uint32_t before = s_wcnt[w][d];
+        rrank[s] = before + (uint32_t)__popcll(peers & lt);
+        wave_order();
+        if (valid && (peers & lt) == 0ull) s_wcnt[w][d] = before + (uint32_t)__popcll(peers);
+        wave_order();
+    }
+    __syncthreads();
+    {
+        uint32_t run = 0;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+            const uint32_t c = s_wcnt[i][tid];
+            s_wcnt[i][tid] = run;
+            run += c;
+        }
+        uint32_t tot;
+        s_dbase[tid] = block_excl_scan<kWaves>(run, s_tmp, tot);
+        s_gbase[tid] = hist[(size_t)tid * nblocks + blockIdx.x];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kItems; ++s) {
+        if (wbase + (size_t)s * 64 + lane < n) {
+            const uint32_t d = (uint32_t)(rk[s] >> shift) & 0xFFu;
+            const uint32_t at = min(s_dbase[d] + s_wcnt[w][d] + rrank[s], (uint32_t)kTile - 1u);
+            s_key[at] = rk[s];
+            s_val[at] = rv[s];
+        }
+    }
+    __syncthreads();
+    const uint32_t tn = (uint32_t)min(n - tile0, (size_t)kTile);
+    for (uint32_t i = tid; i < tn; i += kThreads) {
+        const uint64_t k = s_key[i];
+        const uint32_t d = (uint32_t)(k >> shift) & 0xFFu;
+        const size_t g = (size_t)s_gbase[d] + (i - s_dbase[d]);
+        if (g < n) {
+            okey[g] = k;
+            oval[g] = s_val[i];
+        }
+    }
+}
+
 // ---------------------------------------------------------------- radix select
 constexpr int kSelBins = 2048;
 static_assert(sizeof(SelectState::hist) == kSelBins * sizeof(uint32_t), "one counter a bin");
@@ -533,7 +642,40 @@ int merge_sort(uint64_t *(*keys)[2], uint32_t *vals[2], const double *score, siz
     return cur;
 }
 
-template int merge_sort<1>(uint64_t *(*)[2], uint32_t *[2], const double *, size_t, hipStream_t, Profiler *, const uint32_t *);
+size_t sort_bytes(size_t n)
+{
+    const size_t nb = (n + kTile - 1) / kTile;
+    return n > kRadixFrom ? nb * 256 * 4 + (nb * 256 / kTile + 1) * 4 + 512 : 0;
+}
+
+int sort_keys(uint64_t *keys[2], uint32_t *vals[2], const double *score, size_t n, int bits, Arena &ar, hipStream_t s,
+              Profiler *prof, const uint32_t *dn)
+{
+    if (n <= kRadixFrom || ar.capacity() - ar.used() < sort_bytes(n)) {
+        uint64_t *k[1][2] = {{keys[0], keys[1]}};
+        return merge_sort<1>(k, vals, score, n, s, prof, dn);
+    }
+    require(n < (1ull << 32), ASCI_EINVAL, "sort: too many records");
+    ProfScope ps(prof, "sort", (8.0 + 4.0) * 2.0 * n, s);
+    const size_t nb = (n + kTile - 1) / kTile;
+    uint32_t *hist = ar.take<uint32_t>(nb * 256);
+    const size_t mark = ar.used();
+    k_rs_keys<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(score, keys[0], vals[0], n, dn);
+    ASCI_LAUNCH_CHECK();
+    int cur = 0;
+    for (int shift = 0; shift < bits; shift += 8, cur ^= 1) {
+        k_rs_hist<<<(unsigned)nb, kThreads, 0, s>>>(keys[cur], n, shift, hist, (uint32_t)nb, dn);
+        ASCI_LAUNCH_CHECK();
+        scan_u32(hist, hist, nb * 256, nullptr, ar, s);
+        ar.reset();
+        (void)ar.take<char>(mark);
+        k_rs_scatter<<<(unsigned)nb, kThreads, 0, s>>>(keys[cur], vals[cur], keys[cur ^ 1], vals[cur ^ 1], n, shift, hist,
+                                                       (uint32_t)nb, dn);
+        ASCI_LAUNCH_CHECK();
+    }
+    return cur;
+}
+
 template int merge_sort<2>(uint64_t *(*)[2], uint32_t *[2], const double *, size_t, hipStream_t, Profiler *, const uint32_t *);
 template int merge_sort<3>(uint64_t *(*)[2], uint32_t *[2], const double *, size_t, hipStream_t, Profiler *, const uint32_t *);
 

@@ -1020,12 +1020,12 @@ static SpinTables build_spin_tables(const SpinTablePlan &pl, const uint32_t *d_b
 
 // bytes of the setup arena of a search: class masks, totals and split tree,
 // integral tables, core set, exclusion set (at most 8 nd slots of 20 bytes, or
-// 1024) and filter (at most 64 nd bits, or 2^16); the keys and positions that
-// the core set is selected with; each rounded up to 256 bytes
+// 1024) and filter (at most 64 nd bits, or 2^16); the keys, positions and sorts
+// that the core set is selected with; each rounded up to 256 bytes
 static size_t setup_bytes(size_t nd, size_t nq, int n)
 {
     return kMaxClasses * 20 + (size_t)(2 * n * n + n) * 8 + eri_packed_count(n) * 8 + nq * 24 + (nd * 8 + 1024) * 20 +
-           nd * 8 + (1 << 13) + nd * (2 * 8 + 2 * 4) + nq * (8 + 4) + 64 * 256;
+           nd * 8 + (1 << 13) + nd * (2 * 8 + 2 * 4) + nq * (8 + 4) + sort_bytes(nd) + sort_bytes(nq) + 64 * 256;
 }
 
 // bytes of the main arena: count matrix and offsets (E entries), the pair
@@ -1062,15 +1062,15 @@ struct Prepared {
 static void select_core(const SearchArgs &in, size_t nd, size_t nq, uint64_t *q_a, uint64_t *q_b, double *q_c, Arena &ar,
                         hipStream_t s)
 {
-    uint64_t *ck[1][2] = {{ar.take<uint64_t>(nd), ar.take<uint64_t>(nd)}};
+    uint64_t *ck[2] = {ar.take<uint64_t>(nd), ar.take<uint64_t>(nd)};
     uint32_t *ci[2] = {ar.take<uint32_t>(nd), ar.take<uint32_t>(nd)};
-    const int r1 = merge_sort<1>(ck, ci, in.coeffs, nd, s);
+    const int r1 = sort_keys(ck, ci, in.coeffs, nd, 64, ar, s);
     // the first nq positions, sorted ascending (payload unused)
-    uint64_t *ik[1][2] = {{ck[0][r1 ^ 1], ar.take<uint64_t>(nq)}};
+    uint64_t *ik[2] = {ck[r1 ^ 1], ar.take<uint64_t>(nq)};
     uint32_t *ii[2] = {ci[r1 ^ 1], ar.take<uint32_t>(nq)};
-    k_index_keys<<<grid_for(nq), kBlock, 0, s>>>(ci[r1], nq, ik[0][0]);
+    k_index_keys<<<grid_for(nq), kBlock, 0, s>>>(ci[r1], nq, ik[0]);
     ASCI_LAUNCH_CHECK();
-    const uint64_t *sel = ik[0][merge_sort<1>(ik, ii, nullptr, nq, s)];
+    const uint64_t *sel = ik[sort_keys(ik, ii, nullptr, nq, 32, ar, s)];
     k_gather_core<<<grid_for(nq), kBlock, 0, s>>>(in.dets, in.coeffs, sel, nq, in.n, in.na, in.nb, q_a, q_b, q_c);
     ASCI_LAUNCH_CHECK();
 }
@@ -1734,9 +1734,9 @@ static void run_search(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipS
     }
     if (kk < pool_n) prune(kk);
     {
-        uint64_t *fk[1][2] = {{ar.take<uint64_t>(kk), ar.take<uint64_t>(kk)}};
+        uint64_t *fk[2] = {ar.take<uint64_t>(kk), ar.take<uint64_t>(kk)};
         uint32_t *fi[2] = {ar.take<uint32_t>(kk), ar.take<uint32_t>(kk)};
-        const int rr = merge_sort<1>(fk, fi, p_score[pcur], kk, s, prof);
+        const int rr = sort_keys(fk, fi, p_score[pcur], kk, 64, ar, s, prof);
         k_final_gather<W><<<grid_for(kk), kBlock, 0, s>>>(fi[rr], kk, p_lo[pcur], p_hi[pcur], p_score[pcur], n,
                                                           out.out_dets, out.out_scores, nullptr, nullptr);
         ASCI_LAUNCH_CHECK();
@@ -1961,9 +1961,9 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     if (Pb <= kSortAllPairs) {
         // all candidates sorted (the record buffers are free by now): the pool
         // is in key order, so ties keep ascending keys
-        uint64_t *fk[1][2] = {{k_lo[0], k_lo[1]}};
+        uint64_t *fk[2] = {k_lo[0], k_lo[1]};
         uint32_t *fi[2] = {(uint32_t *)v[0], (uint32_t *)v[1]};
-        const int rr = merge_sort<1>(fk, fi, p_score[0], Pb, s, nullptr, d_V);
+        const int rr = sort_keys(fk, fi, p_score[0], Pb, 64, ar, s, nullptr, d_V);
         k_async_done<<<1, 64, 0, s>>>(da);
         ASCI_LAUNCH_CHECK();
         k_final_gather<W><<<grid_for(kh), kBlock, 0, s>>>(fi[rr], kh, p_lo[0], p_hi[0], p_score[0], n, out_dets,
@@ -1986,9 +1986,9 @@ static void run_search_async(asci_ctx *ctx, const SearchArgs &in, int64_t k, uin
     k_keep_scatter<W><<<ntile, kBlock, 0, s>>>(p_lo[0], p_hi[0], p_score[0], Pb, d_sel, eqb, kbs, p_lo[1], p_hi[1],
                                                p_score[1], (size_t)kh, d_V);
     ASCI_LAUNCH_CHECK();
-    uint64_t *fk[1][2] = {{ar.take<uint64_t>(kh), ar.take<uint64_t>(kh)}};
+    uint64_t *fk[2] = {ar.take<uint64_t>(kh), ar.take<uint64_t>(kh)};
     uint32_t *fi[2] = {ar.take<uint32_t>(kh), ar.take<uint32_t>(kh)};
-    const int rr = merge_sort<1>(fk, fi, p_score[1], kh, s, nullptr, d_kk);
+    const int rr = sort_keys(fk, fi, p_score[1], kh, 64, ar, s, nullptr, d_kk);
     k_async_done<<<1, 64, 0, s>>>(da);
     ASCI_LAUNCH_CHECK();
     k_final_gather<W><<<grid_for(kh), kBlock, 0, s>>>(fi[rr], kh, p_lo[1], p_hi[1], p_score[1], n, out_dets, out_scores,
