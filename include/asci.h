@@ -98,7 +98,8 @@ int asci_ctx_destroy(asci_ctx *ctx);
  *   "finish_cap": records a workgroup of the sort-and-accumulate finish holds
  *                 in LDS, 1024, 2048 or 4096 (default 4096, any key width).
  *                 Each of its eight wavefronts takes a final segment of up
- *                 to an eighth of them; smaller segments need more splitting.
+ *                 to an eighth of them, and of up to 256 at least; smaller
+ *                 segments need more splitting.
  *   "batch_slots": concurrent searches of asci_search_batch, 1..8 (default 4).
  *   "spin_tables": 1 (default) tabulates E(s) of every alpha and beta string
  *                 (at most 2^27 strings per spin, and only when the search

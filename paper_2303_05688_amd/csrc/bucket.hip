@@ -44,9 +44,12 @@ constexpr int kHistT = 256;           // threads of the histogram pass
 constexpr int kTileN = kTileT * kTileItems;  // 4096 records per tile
 
 // Records one wavefront finishes: an eighth of the workgroup capacity that
-// finish_cap names (eight wavefronts share a workgroup and its tables).
+// finish_cap names (eight wavefronts share a workgroup and its tables), and 256
+// at least.  Shares of 128, for a finish_cap of 1024, were slower than 256 at
+// every size: ms, 128 and 256, 8e12o 0.30 and 0.27, 16e20o of 1.3e8 pairs 9.4 and
+// 7.3, 24e30o of 2.7e8 30.6 and 24.1, 20e36o of 9.7e7 15.2 and 12.7.
 constexpr int kFinishWaves = 8;
-inline int wave_cap(int finish_cap) { return (finish_cap >= 4096 ? 4096 : (finish_cap >= 2048 ? 2048 : 1024)) / kFinishWaves; }
+inline int wave_cap(int finish_cap) { return (finish_cap >= 4096 ? 4096 : 2048) / kFinishWaves; }
 
 struct Seg {
     uint32_t start, size, meta;  // meta: buf (bit 0) | single key (bit 1)
@@ -679,7 +682,7 @@ constexpr int kSmallT = 512;
 constexpr int kSmallItems = kTileN / kSmallT;
 constexpr int kSmallMax = 64;      // ranges: half of cap each
 constexpr int kSmallSample = 512;  // samples at most
-constexpr int kMinCap = 1024 / kFinishWaves;  // the smallest wave_cap
+constexpr int kMinCap = 2048 / kFinishWaves;  // the smallest wave_cap
 template <int W>
 __global__ __launch_bounds__(kSmallT) __attribute__((amdgpu_waves_per_eu(4))) void k_small_split(
     const Seg *__restrict__ segs, uint32_t nseg, const uint32_t *dn_seg, uint32_t cap, uint64_t *__restrict__ klo0,
@@ -1124,7 +1127,7 @@ struct WaveLds {
 template <int IT>
 constexpr int digit_bits()
 {
-    return IT == 8 ? 11 : (IT == 4 ? 10 : 9);
+    return IT == 8 ? 11 : 10;
 }
 
 // exclusive scan of N counter words per lane, in place: a word's two 16-bit
@@ -1500,7 +1503,7 @@ __device__ __forceinline__ uint32_t finish_segment(const FinishArgs &f, const Di
                 case 64: scan_counters<1>(S.cnt); break;
                 case 128: scan_counters<2>(S.cnt); break;
                 case 256: scan_counters<4>(S.cnt); break;
-                case 512: if (IT >= 4) scan_counters<IT >= 4 ? 8 : 1>(S.cnt); break;
+                case 512: scan_counters<8>(S.cnt); break;
                 default: if (IT >= 8) scan_counters<IT >= 8 ? 16 : 1>(S.cnt); break;
                 }
                 wave_sync();
@@ -2340,8 +2343,7 @@ static void accumulate(BucketArgs &b, Arena &ar, hipStream_t s, Profiler *prof, 
         b.prof = prof;
         auto finish = [&](int part) {
             if (cap == 512) b.finish_tok = launch_finish<W, 8>(fa, b, nf, part, s, prof);
-            else if (cap == 256) b.finish_tok = launch_finish<W, 4>(fa, b, nf, part, s, prof);
-            else b.finish_tok = launch_finish<W, 2>(fa, b, nf, part, s, prof);
+            else b.finish_tok = launch_finish<W, 4>(fa, b, nf, part, s, prof);
         };
         fa.runs = b.pilot_k > 0 ? b.runs : nullptr;
         if (b.pilot_k > 0) {

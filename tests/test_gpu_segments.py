@@ -67,3 +67,26 @@ def test_heavy_target_by_finish_capacity(norb, ndets):
         assert (gu.host(full[0]) == gu.host(part[0])).all()
         assert (gu.host(full[1]) == gu.host(part[1])).all()
         ctx.close()
+
+
+@pytest.mark.parametrize("norb", [12, 34])
+def test_smallest_finish_capacity_takes_the_shares_of_the_next(norb):
+    """A wavefront's share is 256 records at least: finish_cap 1024 divides as
+    2048 does, and finer than 4096."""
+    import asci_synth as syn
+    import gpu_util as gu
+    import paper_2303_05688_amd as asci
+
+    ne = 4 if norb == 12 else 2
+    c = syn.make_case(norb, ne, ne, 300, seed=norb, sampler="level", tau=30.0)
+    d = gu.to_dev(c)
+    finals, out = [], []
+    for cap in (4096, 2048, 1024):
+        ctx = asci.Context(0)
+        ctx.set_param("finish_cap", cap)
+        out.append([gu.host(x) for x in asci.search(d["h"], d["eri"], norb, ne, ne, d["dets"], d["coeffs"], -3.5, 500, ctx=ctx)])
+        finals.append(ctx.get_param("last_finals"))
+        ctx.close()
+    assert finals[0] < finals[1] == finals[2]
+    for k, sc in out[1:]:
+        assert (k == out[0][0]).all() and (sc.view(np.uint64) == out[0][1].view(np.uint64)).all()
