@@ -1402,8 +1402,10 @@ constexpr uint64_t kPilotPairs = (uint64_t)1 << 26, kPilotPerK = 256, kPilotTest
 // Searches of one class batch of at most this many pairs run without a host
 // round trip until their result is there (12 electrons in 12 orbitals, k =
 // 10 ndets up to 20000, ms against the step-by-step path: 2^15 pairs 0.21 and
-// 0.34, 2^18 0.29 and 0.44, 2^22 0.49 and 0.69).  At 2^24 two split levels no
-// longer divide every class, and 1.3 ms leave little to gain.
+// 0.34, 2^18 0.29 and 0.44, 2^22 0.49 and 0.69).  Above, less is left of the
+// gain (two levels divide up to 2^25 pairs of the shapes tried): 2^23 0.65 and
+// 0.72, 2^24 0.99 and 1.08, 2^25 1.73 and 1.78, two-word keys nothing from 2^21
+// on.  The line has not been moved there.
 constexpr uint64_t kSmallPairs = (uint64_t)1 << 22;
 template <int W>
 static bool run_search_small(asci_ctx *ctx, const SearchArgs &in, SearchOut &out, hipStream_t s);
